@@ -18,7 +18,7 @@
 // and per-position argmax partials for the greedy choice (output embedding).
 #include "ngg_internal.h"
 #include <algorithm>
-#include <type_traits>
+#include <cmath>
 
 namespace ngg {
 
@@ -576,267 +576,393 @@ __global__ __launch_bounds__(256) void gemm_wide_kernel(const GemmArgs a, int MT
 }
 
 // ---------------------------------------------------------------------------------------------
-// The wide kernel on the 32x32x16 MFMA, for tiles whose row blocks come in pairs (FM a multiple of 4, an even
-// number of fragments).  Same workgroup, staging and ring as above; what changes is the tile one instruction
-// covers: 32 rows of W (two neighbouring fragments) times 32 block rows over 16 contraction elements.  An
-// operand register then meets twice as many multiply-adds, so the kernel reads half the LDS bytes and issues half
-// the W loads per flop, and the instruction itself runs closer to the matrix cores' rate on this part (a loop of
-// nothing but MFMAs on all CUs: 2.1-2.2 PFLOP/s with 32x32x16 against 1.45-1.55 with 16x16x32).
-// Operand lanes: lane = 32 h + r takes row r of the 32 and contraction elements 8 h .. 8 h + 7 of the 16.  The
-// weights stay in their 16 x 32 blocks: for the q-th half of a step, lane (r, h) reads the 16 bytes that lane
-// (16 (2 q + h) + r % 16) of fragment r / 16 owns in the block (each load still covers whole 128-byte lines: 512
-// contiguous bytes in each of the two blocks).  Accumulator register 4 j + i of lane (r, h) is row
-// 8 j + 4 h + i of the 32 W rows at block row r: fragment j / 2, and inside it what the 16x16 layout keeps
-// in lane group 2 (j % 2) + h, so the epilogues above are called with that group.  Both halves of an output
-// pair now sit in one lane (registers of j and j + 1).  The unembedding stays on gemm_wide_kernel.
+// Tiled GEMM (16-bit operands): prefill pieces and wide blocks, where a weight meets enough block rows that the
+// caches, the LDS and the matrix cores bound the call instead of the stream of W.  A workgroup of WM x WN waves owns
+// TM = 32 WM BM block rows and TN = 32 WN BN rows of W; a wave BM x BN blocks of the 32x32x16 MFMA (a loop of nothing
+// else runs at 2.1-2.2 PFLOP/s here, 16x16x32 at 1.45-1.55).  Both operands go from global memory straight into LDS
+// (16 bytes per lane, no registers in between), in slices of 64 contraction elements, NST slices deep.  Before, W went
+// into registers and the two waves that shared a fragment both fetched it: a 128 x 256 tile asked the L2 for 64 KB per
+// slice, as much as the path between L2 and CU carries in the slice's MFMA time; a 256 x 256 tile fed through LDS asks
+// for half of that per flop.  Measured at the 7B shapes, 2048 rows: gate/up 500 -> 431 us (1.12 PFLOP/s; a library
+// GEMM of the same size reaches 1.11-1.18), down 250 -> 213, output projection 85 -> 74; 777 rows: gate/up 256 -> 210,
+// q/k/v 194 -> 109, down 186 -> 121, projection 67 -> 38; a 768-wide model at 777 rows: 34 -> 15, 27 -> 13, 20 -> 12.5,
+// 22 -> 6.4 (small tiles fill the chip where three 288-row tiles left most CUs idle).  What is left at 2048 rows: the
+// matrix cores are busy 55-63 % of the cycles at the 1.8 GHz the card holds under this load, the LDS about as much.
+//
+// One slice is four multiplication steps of 16 contraction elements.  The fragments of a step are read from LDS under
+// the previous step's MFMAs; the barrier that hands over the buffers sits before the last step, whose operands are in
+// registers by then: behind it the first fragments of the next slice are read and the DMA of slice s + NST goes out
+// between the last step's MFMAs, into the buffer everybody has just finished reading.
+//
+// LDS images.  W: the 1 KB operand blocks as they are stored (16 rows x 32 elements, lane-major), read without bank
+// conflicts.  X: row-major, 128 bytes per row, the 16-byte piece c of row r at position c ^ (r / 2 % 8): a DMA
+// instruction covers whole 128-byte lines of 8 rows, and the 16 rows one quarter of the wave reads meet all banks.
+// Operand lanes: lane 32 h + r takes row r of a 32-row block and contraction elements 8 h .. 8 h + 7 of the 16.
+// Accumulator register 4 j + i of lane (r, h) is W row 8 j + 4 h + i of the 32 at block row r: both halves of an output
+// pair (registers of j and j + 1) sit in one lane.
 // ---------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <typename T, int EPI, int FM, int FN, bool TILED>
-__global__ __launch_bounds__(256) void gemm_wide32_kernel(const GemmArgs a, int MT) {
-  static_assert(sizeof(T) == 2, "16-bit operands only");
-  constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
-  static_assert(FN % 2 == 0 && FM % 4 == 0, "pairs of fragments, pairs of row blocks per wave");
+// 16 bytes per lane from global memory (uniform base + lane offset) to LDS (lane i: lds + 16 i).  The compiler does not
+// see the transfer: the kernel waits for it with its own s_waitcnt before a barrier.  NT: the lines are used once
+// (weights that only one workgroup reads), keep them out of the activations' way in the L2.
+template <bool NT>
+__device__ __forceinline__ void lds_dma16(const void *base, unsigned off, unsigned lds) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void wave_lds_fence() {       // LDS written by other lanes of this wave is readable behind it
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// frag_first, frag_end: 16-row fragments of W this launch covers; MT row tiles, `tiles` tiles in all
+template <int EPI, int WM, int WN, int BM, int BN, int NST, bool NT>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs a, int MT, int tiles, int frag_first, int frag_end) {
+  typedef half_t T;
   static_assert(EPI != EPI_UNEMBED, "the unembedding stays on gemm_wide_kernel");
-  constexpr int FNP = FN / 2;                // pairs of fragments (32 rows of W) per wave
-  constexpr int FMB = FM / 4;                // 32-row blocks of the tile per wave (the waves are laid out 2 x 2)
-  constexpr int KC = KChunk<T>::value;       // chunk of the activation layout (256)
-  constexpr int KW = 64;                     // contraction elements staged per slice: two steps
-  constexpr int SPS = KW / 32;               // steps per slice
-  constexpr int LDX = KW + 8;                // LDS row stride in elements (16 bytes of padding)
-  constexpr int ROWS = 16 * FM;
-  constexpr int PPR = KW / 8;                // 16-byte pieces per row
-  constexpr int PIECES = (ROWS * PPR + 255) / 256;
-  constexpr int RING = 4;                    // W steps in flight per wave (two slices)
-
+  constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
+  constexpr int NW = WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN;
+  constexpr int KC = KChunk<T>::value, KW = 64;
+  constexpr int WI = TN / 8 / NW, XI = TM / 8 / NW;      // DMA instructions (1 KB each) per wave and slice
+  static_assert(WI * NW * 8 == TN && XI * NW * 8 == TM, "whole instructions per wave");
+  constexpr int PER = WI + XI;
+  static_assert((NST - 1) * PER < 64, "vmcnt counts to 63");
+  constexpr int BUF = (TM + TN) * KW * 2;                // bytes of one slice
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  T *xs = reinterpret_cast<T *>(smem);       // [2][ROWS][LDX]
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r32 = lane & 31, h = lane >> 5;
-  const int wn = wave & 1, wm = wave >> 1;   // this wave: fragments wn * FN .. of the workgroup's 2 FN, 32-row blocks wm * FMB ..
+  const int wn = wave % WN, wm = wave / WN;
   const int K = a.K, M = a.M;
-  const int n_frags = a.n_groups;            // 16-row fragments of W, an even number (the launcher checks)
-  const int n_steps = K / 32;
-  const int n_slices = (n_steps + SPS - 1) / SPS;
+  const int n_steps = K / 32, n_slices = (n_steps + 1) / 2;
   const int KS = gridDim.y, ks = blockIdx.y;
-  // workgroup -> (rows of W, row tile) as in gemm_wide_kernel
-  const int nb = TILED ? (blockIdx.x / 8 / MT) * 8 + blockIdx.x % 8 : blockIdx.x;
-  const int m0 = TILED ? (blockIdx.x / 8 % MT) * (16 * FM) : 0;
-  if (TILED && nb * 2 * FN >= n_frags) return;               // padding of the last row of 8
-  const int c0 = (int)(((long)n_slices * ks) / KS), c1 = (int)(((long)n_slices * (ks + 1)) / KS);
+  // Workgroup b runs on XCD b % 8 and takes that XCD's next tile.  Every XCD has a contiguous share of the tiles, row
+  // tiles first: the workgroups that share rows of W run side by side on one L2, which reads them from HBM once.
+  const int per = gridDim.x / 8;
+  const int tile = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (tile >= tiles) return;
+  const int m0 = tile % MT * TM;
+  const int f0 = frag_first + tile / MT * (TN / 16);
+  const int c0 = (int)(((long)n_slices * ks) / KS), c1 = (int)(((long)n_slices * (ks + 1)) / KS);   // c1 > c0: KS <= n_slices
 
-  const T *wptr[FNP];                        // this lane's 16 bytes of the pair's first step, first half
-  int frag0[FNP];                            // first fragment of the pair
-  bool pair_live[FNP];
+  // ---- DMA sources: a wave-uniform base per instruction plus this lane's byte offset ----------------
+  // (fragments past the end repeat the last one, rows past the block's last one repeat that row; neither is stored)
+  const char *wbase[WI];
+  unsigned xoffs[XI];
 #pragma unroll
-  for (int p = 0; p < FNP; ++p) {
-    int f0 = (nb * 2 + wn) * FN + 2 * p;
-    pair_live[p] = f0 < n_frags;
-    if (!pair_live[p]) f0 = n_frags - 2;     // repeats a pair it does not store
-    frag0[p] = f0;
-    wptr[p] = tiled_block((const T *)a.W0, f0 + (r32 >> 4), n_steps, 16 * h + (r32 & 15));
+  for (int i = 0; i < WI; ++i) {                         // instruction wave * WI + i: fragment (.. / 2), step (.. % 2)
+    const int id = wave * WI + i;
+    wbase[i] = (const char *)a.W0 + (size_t)min(f0 + id / 2, frag_end - 1) * n_steps * 1024;
   }
-
-  static_assert(kNormSegs == 4, "one float4 per row");
-  auto row_scale = [&](int m) {
-    float r = 1.0f;
-    if (a.row_ss) {
-      const f32x4 ss = *reinterpret_cast<const f32x4 *>(a.row_ss + (size_t)(m < a.Mcap ? m : a.Mcap - 1) * kNormSegs);
-      r = 1.0f / sqrtf((((ss[0] + ss[1]) + ss[2]) + ss[3]) / (float)K + a.ss_eps);
+#pragma unroll
+  for (int i = 0; i < XI; ++i) {
+    const int row = (wave * XI + i) * 8 + (lane >> 3);
+    const int piece = (lane & 7) ^ ((row >> 1) & 7);
+    xoffs[i] = (unsigned)min(m0 + row, M - 1) * (KC * 2) + piece * 16;
+  }
+  const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  auto dma = [&](int sl, int buf, int i) {               // i-th of the wave's PER instructions for slice sl (clamped to the last)
+    const int s = min(sl, c1 - 1);
+    const unsigned base = lds0 + buf * BUF;
+    if (i < WI) {
+      const int id = wave * WI + i;
+      // K % 64 == 32: the last slice's second step repeats the first; X holds zeros there (the padding of its chunk)
+      const int st = min(2 * s + (id & 1), n_steps - 1);
+      lds_dma16<NT>(wbase[i < WI ? i : 0] + (size_t)st * 1024, lane * 16, base + id * 1024);
+    } else {
+      const int k0 = s * KW;
+      const size_t off = (size_t)(k0 / KC) * a.Mcap * KC + k0 % KC;
+      lds_dma16<false>((const char *)a.X + off * 2, xoffs[i < WI ? 0 : i - WI], base + TN * KW * 2 + (wave * XI + i - WI) * 1024);
     }
-    return r * a.out_scale;
   };
 
-  // X staging as in gemm_wide_kernel
-  const T *xsrc[PIECES];
-  int xdst[PIECES];
+  f32x16 acc[BN][BM];
 #pragma unroll
-  for (int i = 0; i < PIECES; ++i) {
-    const int p = tid + 256 * i;
-    const int row = min(p / PPR, ROWS - 1), col = p % PPR;
-    xsrc[i] = (const T *)a.X + (size_t)min(m0 + row, M - 1) * KC + col * 8;
-    xdst[i] = row * LDX + col * 8;
-  }
-  u32x4 stage[2][PIECES];
-  auto stage_load = [&](u32x4 (&st)[PIECES], int c) {       // slice c of the matrix (clamped into it)
-    const int cl = min(c, n_slices - 1);
-    const int k0 = cl * KW;
-    const size_t off = (size_t)(k0 / KC) * a.Mcap * KC + k0 % KC;
+  for (int p = 0; p < BN; ++p)
 #pragma unroll
-    for (int i = 0; i < PIECES; ++i) st[i] = *reinterpret_cast<const u32x4 *>(xsrc[i] + off);
-  };
-  auto stage_store = [&](const u32x4 (&st)[PIECES], int buf) {
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) *reinterpret_cast<u32x4 *>(xs + (size_t)buf * ROWS * LDX + xdst[i]) = st[i];
-  };
-
-  f32x16 acc[FNP][FMB];
-#pragma unroll
-  for (int p = 0; p < FNP; ++p)
-#pragma unroll
-    for (int b = 0; b < FMB; ++b)
+    for (int b = 0; b < BM; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[p][b][r] = 0.f;
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) stage[c][i] = u32x4{0u, 0u, 0u, 0u};
 
-  Frag<T> ring[RING][FN];                                   // [2 p + q]: pair p, half q of the step
-  auto load_w = [&](Frag<T> (&slot)[FN], int t) {           // wave-step t >= 0 is global step c0 * SPS + t (clamped)
-    const int st = min(c0 * SPS + t, n_steps - 1);
+  // fragments of step q (the q-th 16 of the slice's 64 contraction elements)
+  const int woff = (wn * BN * 2 + (r32 >> 4)) * 2048 + (16 * h + (r32 & 15)) * 16;
+  const int xrow = wm * BM * 32 + r32;
+  const int xsw = (xrow >> 1) & 7;
+  const int xoff = TN * KW * 2 + xrow * 128;
+  half8 wf[2][BN], xf[2][BM];
+  auto read = [&](int set, int buf, int q) {
+    const unsigned char *base = smem + buf * BUF;
 #pragma unroll
-    for (int p = 0; p < FNP; ++p)
+    for (int p = 0; p < BN; ++p)
+      wf[set][p] = *reinterpret_cast<const half8 *>(base + woff + p * 4096 + (q >> 1) * 1024 + (q & 1) * 512);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const T *src = wptr[p] + (size_t)st * 512 + q * 256;
-        slot[2 * p + q] = TILED ? load_frag(src) : load_frag_stream(src);
-      }
+    for (int b = 0; b < BM; ++b)
+      xf[set][b] = *reinterpret_cast<const half8 *>(base + xoff + b * 4096 + ((2 * q + h) ^ xsw) * 16);
+  };
+  constexpr int NMF = BM * BN, NRD = BM + BN;
+  auto mul1 = [&](int set, int k) {
+    acc[k % BN][k / BN] = __builtin_amdgcn_mfma_f32_32x32x16_f16(wf[set][k % BN], xf[set][k / BN], acc[k % BN][k / BN], 0, 0, 0);
   };
 
-  // One slice = two steps = two blocks of MFMAs, and between them the slice's only barrier.  The memory
-  // instructions ride in the shadow of the MFMAs (one wave per SIMD: whatever is issued while no MFMA is in
-  // flight leaves the matrix core idle; with the phases one after the other it was busy 38 % of the time):
-  //   first block (step 0 of slice s):  LDS reads of step 1, global loads of slice s + 2, LDS writes of slice s + 1
-  //                                     into the other buffer (its last readers passed the previous barrier)
-  //   barrier; LDS reads of step 0 of slice s + 1 (they land under the second block)
-  //   second block (step 1 of slice s): the W loads that refill the ring
-  // The groups below ask the scheduler for that order.
-  constexpr int NM = 2 * FMB * FNP;                         // MFMAs per step
-  constexpr int MEM_A = 2 * FMB + 2 * PIECES;               // memory instructions of the first block
-  constexpr int PER_A = (MEM_A + NM - 1) / NM;
-  const int rowoff = (wm * FMB * 32 + r32) * LDX + h * 8;
-  Frag<T> xf[SPS][2 * FMB];                                 // [2 b + q]: 32-row block b, half q of the step
 #pragma unroll
-  for (int i = 0; i < SPS; ++i)
+  for (int i = 0; i < NST; ++i)
 #pragma unroll
-    for (int e = 0; e < 2 * FMB; ++e) xf[i][e].v = half8{0, 0, 0, 0, 0, 0, 0, 0};
-  auto half_trip = [&](auto cc_tag, auto live_tag, int sl, int t0) {
-    constexpr int cc = decltype(cc_tag)::value;
-    constexpr bool live = decltype(live_tag)::value;
-    const T *xcur = xs + (size_t)cc * ROWS * LDX + rowoff, *xnxt = xs + (size_t)(cc ^ 1) * ROWS * LDX + rowoff;
+    for (int j = 0; j < PER; ++j) dma(c0 + i, i, j);
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 1) * PER) : "memory");
+  __builtin_amdgcn_s_barrier();
+  read(0, 0, 0);
+  int buf = 0;
+  for (int s = c0; s < c1; ++s) {
+    const int nbuf = buf + 1 == NST ? 0 : buf + 1;
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int b = 0; b < FMB; ++b)
+    for (int q = 0; q < 3; ++q) {
+      read((q + 1) & 1, buf, q + 1);
 #pragma unroll
-      for (int q = 0; q < 2; ++q) xf[1][2 * b + q] = load_frag(xcur + b * 32 * LDX + 32 + q * 16);
-    stage_load(stage[cc], max(sl + 2, c0));
-    stage_store(stage[cc ^ 1], cc ^ 1);
-    if constexpr (live) {
+      for (int k = 0; k < NMF; ++k) mul1(q & 1, k);
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int b = 0; b < FMB; ++b)
-#pragma unroll
-          for (int p = 0; p < FNP; ++p)
-            acc[p][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[2 * cc][2 * p + q].v, xf[0][2 * b + q].v, acc[p][b], 0, 0, 0);
-#pragma unroll
-      for (int k = 0; k < NM; ++k) {
+      for (int k = 0; k < NMF; ++k) {                    // one MFMA, then its share of the LDS reads
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x320, PER_A, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, (NRD + NMF - 1) / NMF, 0);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NST - 2) * PER) : "memory");   // slice s + 1 has landed
+    __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-#pragma unroll
-    for (int b = 0; b < FMB; ++b)
-#pragma unroll
-      for (int q = 0; q < 2; ++q) xf[0][2 * b + q] = load_frag(xnxt + b * 32 * LDX + q * 16);
+    read(0, nbuf, 0);
     __builtin_amdgcn_sched_barrier(0);
-    load_w(ring[2 * cc], max(t0 + RING, 0));
-    if constexpr (live) {
 #pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int b = 0; b < FMB; ++b)
-#pragma unroll
-          for (int p = 0; p < FNP; ++p)
-            acc[p][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ring[2 * cc + 1][2 * p + q].v, xf[1][2 * b + q].v, acc[p][b], 0, 0, 0);
-#pragma unroll
-      for (int k = 0; k < NM; ++k) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (k < FN) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      }
+    for (int k = 0; k < (NMF > PER ? NMF : PER); ++k) {
+      if (k < NMF) mul1(1, k);
+      if (k < PER) dma(s + NST, buf, k);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    load_w(ring[2 * cc + 1], max(t0 + 1 + RING, 0));
-  };
-
-  // two slices without MFMAs fill the pipeline (the same memory instructions in the same order as the loop's, so
-  // the loop is entered with the loads outstanding that every later trip finds); the loop itself has no branch
-  using Cc0 = std::integral_constant<int, 0>;
-  using Cc1 = std::integral_constant<int, 1>;
-  half_trip(Cc0{}, std::false_type{}, c0 - 2, -2 * SPS);
-  half_trip(Cc1{}, std::false_type{}, c0 - 1, -1 * SPS);
-  int sl = c0;
-  for (; sl + 1 < c1; sl += 2) {
-    half_trip(Cc0{}, std::true_type{}, sl, (sl - c0) * SPS);
-    half_trip(Cc1{}, std::true_type{}, sl + 1, (sl + 1 - c0) * SPS);
+    buf = nbuf;
   }
-  if (sl < c1) half_trip(Cc0{}, std::true_type{}, sl, (sl - c0) * SPS);   // an odd number of slices
-  __syncthreads();                                           // everyone is done with xs
-  float *rs_lds = reinterpret_cast<float *>(smem);           // [ROWS] 1 / rms (times the operand scales) of the tile's rows
-  for (int r = tid; r < ROWS; r += 256) rs_lds[r] = row_scale(m0 + r);
-  __syncthreads();
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __syncthreads();                                       // nothing on its way to LDS any more, everyone is done with it
 
-  const int row0 = wm * FMB * 32 + r32;                      // this lane's row of the tile in 32-row block 0
+  static_assert(kNormSegs == 4, "one float4 per row");
+  float *rs_lds = reinterpret_cast<float *>(smem);       // [TM] 1 / rms times the operand scales
+  if constexpr (PAIRED) {
+    for (int r = tid; r < TM; r += 64 * NW) {
+      float v = 1.0f;
+      if (a.row_ss) {
+        const int m = m0 + r;
+        const f32x4 ss = *reinterpret_cast<const f32x4 *>(a.row_ss + (size_t)(m < a.Mcap ? m : a.Mcap - 1) * kNormSegs);
+        v = 1.0f / sqrtf((((ss[0] + ss[1]) + ss[2]) + ss[3]) / (float)K + a.ss_eps);
+      }
+      rs_lds[r] = v * a.out_scale;
+    }
+    __syncthreads();
+  }
+  const int row0 = wm * BM * 32 + r32;
+  const int fw = f0 + wn * BN * 2;                       // first fragment of this wave
   if constexpr (EPI == EPI_QKV) {
-    // the accumulators leave the registers through LDS (every wave its own region, behind the row scales) and the
-    // rotary epilogue takes them back one fragment at a time, as in gemm_wide_kernel
-    f32x4 *dump = reinterpret_cast<f32x4 *>(smem + (ROWS * sizeof(float) + 15) / 16 * 16) + (size_t)wave * (FN * FMB * 2 * 64);
+    // The scaled accumulators of one 32-row block leave the registers through LDS (every wave its own region) and come
+    // back one fragment at a time: all at once, the fragments' table entries and addresses do not fit the registers.
+    float *dump = reinterpret_cast<float *>(smem + TM * sizeof(float)) + (size_t)wave * (BN * 4 * 256);
+    const int half = a.hd / 2, fph = a.hd / 16;
+    const int P = a.n_dev ? *a.n_dev - 1 : a.P;
 #pragma unroll
-    for (int p = 0; p < FNP; ++p)
+    for (int b = 0; b < BM; ++b) {
+      const int row = row0 + b * 32, m = m0 + row;
+      const float rs = rs_lds[row];
 #pragma unroll
-      for (int b = 0; b < FMB; ++b)
+      for (int p = 0; p < BN; ++p)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          dump[((p * FMB + b) * 4 + j) * 64 + lane] = f32x4{acc[p][b][4 * j], acc[p][b][4 * j + 1], acc[p][b][4 * j + 2], acc[p][b][4 * j + 3]};
-#pragma unroll 2
-    for (int idx = 0; idx < FNP * FMB * 2; ++idx) {          // item: (pair, 32-row block, fragment of the pair)
-      const int pb = idx >> 1, t = idx & 1;
-      const int p = pb / FMB, b = pb - p * FMB;
-      const int frag = (nb * 2 + wn) * FN + 2 * p + t;
-      const int row = row0 + b * 32;
-      if (frag < n_frags) {                                  // uniform per wave
-        const float rs = rs_lds[row];
-        const f32x4 lo = dump[(pb * 4 + 2 * t) * 64 + lane], hi = dump[(pb * 4 + 2 * t + 1) * 64 + lane];
-        const float v[4] = {lo[0] * rs, lo[1] * rs, lo[2] * rs, lo[3] * rs};
-        const float x2[4] = {hi[0] * rs, hi[1] * rs, hi[2] * rs, hi[3] * rs};
-        epi_paired_vals<T, EPI>(a, frag, m0 + row, M, h, v, x2);
-      }
-    }
-  } else {
+          *reinterpret_cast<f32x4 *>(dump + ((p * 4 + j) * 64 + lane) * 4) =
+              f32x4{acc[p][b][4 * j] * rs, acc[p][b][4 * j + 1] * rs, acc[p][b][4 * j + 2] * rs, acc[p][b][4 * j + 3] * rs};
+      wave_lds_fence();
+#pragma unroll 1
+      for (int idx = 0; idx < BN * 2; ++idx) {
+        const int frag = fw + idx;
+        if (frag >= frag_end) break;                     // uniform per wave
+        const int hh = frag / fph, sub = frag - hh * fph;  // head over [q heads | k heads | v heads], 8-dim group of its lower half
+        if (hh < a.H + a.Hkv) {                          // q and k: rotary embedding, then 8 consecutive dims per lane
+          const f32x4 v = *reinterpret_cast<const f32x4 *>(dump + (2 * idx * 64 + lane) * 4);
+          const f32x4 x2 = *reinterpret_cast<const f32x4 *>(dump + ((2 * idx + 1) * 64 + lane) * 4);
+          const int pos = P + block_col(min(m, M - 1), a.C, a.shared0);
+          const f32x4 cs = *reinterpret_cast<const f32x4 *>(a.rope_cos + (size_t)pos * half + sub * 8 + 4 * h);
+          const f32x4 sn = *reinterpret_cast<const f32x4 *>(a.rope_sin + (size_t)pos * half + sub * 8 + 4 * h);
+          union { half4 v; unsigned u[2]; } lo, hi;
 #pragma unroll
-    for (int b = 0; b < FMB; ++b) {
-      const int row = row0 + b * 32;                         // row of the tile
-      const int m = m0 + row;
-      const bool live = m < M;
-      const float rs = PAIRED ? rs_lds[row] : 1.0f;
-#pragma unroll
-      for (int p = 0; p < FNP; ++p) {
-        if (!pair_live[p]) continue;                         // uniform per wave
-        if constexpr (EPI == EPI_GATEUP) {
-#pragma unroll
-          for (int t = 0; t < 2; ++t) {
-            float v[4], x2[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) { v[r] = acc[p][b][8 * t + r] * rs; x2[r] = acc[p][b][8 * t + 4 + r] * rs; }
-            epi_paired_vals<T, EPI>(a, frag0[p] + t, m, M, h, v, x2);
+          for (int r = 0; r < 4; ++r) {
+            lo.v[r] = to_half(v[r] * cs[r] - x2[r] * sn[r]);
+            hi.v[r] = to_half(x2[r] * cs[r] + v[r] * sn[r]);
           }
-        } else {
-          if (live) {
+          // lanes h = 0 collect the 8 lower dims, lanes h = 1 the 8 upper ones
+          const auto w0 = __builtin_amdgcn_permlane32_swap(lo.u[0], hi.u[0], false, false);
+          const auto w1 = __builtin_amdgcn_permlane32_swap(lo.u[1], hi.u[1], false, false);
+          const u32x4 piece = u32x4{w0[0], w1[0], w0[1], w1[1]};
+          const int dim = sub * 8 + (h ? half : 0);
+          T *dst = hh < a.H ? (T *)a.q + ((size_t)hh * a.Mcap + m) * a.hd + dim
+                            : (T *)a.kscr + (size_t)(hh - a.H) * a.kv_rows * a.hd + k_offset(m, dim, a.hd, 2);
+          if (m < M) *reinterpret_cast<u32x4 *>(dst) = piece;
+        } else {                                         // values: 8 consecutive positions of one dim per lane
+          const int dd = lane >> 2, g8 = lane & 3;       // dim of the fragment (0..7 lower, 8..15 upper), group of 8 positions
+          const float *src = dump + ((2 * idx + (dd >> 3)) * 64 + 32 * ((dd >> 2) & 1) + 8 * g8) * 4 + (dd & 3);
+          half8 o;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              epi_residual(a, ks, m, (frag0[p] + (j >> 1)) * 16, 2 * (j & 1) + h,
-                           f32x4{acc[p][b][4 * j], acc[p][b][4 * j + 1], acc[p][b][4 * j + 2], acc[p][b][4 * j + 3]});
-          }
+          for (int e = 0; e < 8; ++e) o[e] = to_half(src[4 * e]);
+          const int mb = m0 + wm * BM * 32 + b * 32 + 8 * g8;
+          const int dim = sub * 8 + (dd & 7) + (dd >> 3) * half;
+          T *dst = (T *)a.vscr + (size_t)(hh - a.H - a.Hkv) * a.kv_rows * a.hd + v_offset(mb, dim, a.hd, 2);
+          if (mb + 8 <= M) *reinterpret_cast<half8 *>(dst) = o;
+          else
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (mb + e < M) dst[e] = o[e];
         }
       }
+      wave_lds_fence();
+    }
+  } else if constexpr (EPI == EPI_GATEUP) {
+    // the tile's activations go through LDS, so that a row's features leave in 16-byte pieces side by side (8-byte
+    // pieces of 32 rows per instruction: 445 instead of 431 us at 2048 rows)
+    constexpr int LDO = TN / 2 + 8;                      // LDS row stride in elements
+    T *ot = reinterpret_cast<T *>(smem + TM * sizeof(float));
+#pragma unroll
+    for (int b = 0; b < BM; ++b) {
+      const int row = row0 + b * 32;
+      const float rs = rs_lds[row];
+#pragma unroll
+      for (int p = 0; p < BN; ++p)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          float o[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o[r] = silu<T>(acc[p][b][8 * t + r] * rs) * (acc[p][b][8 * t + 4 + r] * rs);
+          store4(ot + row * LDO + (wn * BN * 2 + 2 * p + t) * 8 + 4 * h, o[0], o[1], o[2], o[3]);
+        }
+    }
+    __syncthreads();
+    constexpr int PPR = TN / 16;                         // 16-byte pieces per row: one per fragment
+    for (int e = tid; e < TM * PPR; e += 64 * NW) {
+      const int row = e / PPR, fr = e % PPR, m = m0 + row;
+      if (m < M && f0 + fr < frag_end)
+        *reinterpret_cast<u32x4 *>((T *)a.act + act_offset<T>(m, (f0 + fr) * 8, a.Mcap)) = *reinterpret_cast<const u32x4 *>(ot + row * LDO + fr * 8);
+    }
+  } else {
+    // partials: every wave turns its blocks around in LDS of its own and stores whole row segments (stored straight
+    // from the accumulators, 16 bytes per row and instruction: 226 instead of 213 us for down, 92 instead of 74 for O)
+    constexpr int LDO = 32 * BN + 4;
+    float *ot = reinterpret_cast<float *>(smem) + wave * 32 * LDO;
+    constexpr int LPR = 8 * BN;                          // lanes per row segment
+    const int n0 = fw * 16;
+#pragma unroll
+    for (int b = 0; b < BM; ++b) {
+#pragma unroll
+      for (int p = 0; p < BN; ++p)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          *reinterpret_cast<f32x4 *>(ot + r32 * LDO + p * 32 + 8 * j + 4 * h) =
+              f32x4{acc[p][b][4 * j] * a.out_scale, acc[p][b][4 * j + 1] * a.out_scale, acc[p][b][4 * j + 2] * a.out_scale, acc[p][b][4 * j + 3] * a.out_scale};
+      wave_lds_fence();
+#pragma unroll
+      for (int it = 0; it < 32; it += 64 / LPR) {
+        const int row = it + lane / LPR, col = lane % LPR * 4, m = m0 + wm * BM * 32 + b * 32 + row;
+        const f32x4 v = *reinterpret_cast<const f32x4 *>(ot + row * LDO + col);
+        if (m < M && n0 + col < frag_end * 16) *reinterpret_cast<f32x4 *>(a.hpart + ((size_t)ks * a.Mcap + m) * a.N + n0 + col) = v;
+      }
+      wave_lds_fence();
     }
   }
 }
 
+template <int EPI, int WM, int WN, int BM, int BN, int NST>
+static void launch_tile_cfg(const GemmArgs &a, int KS, int frag_first, int frag_end, hipStream_t s) {
+  constexpr int TM = 32 * WM * BM, TN = 32 * WN * BN;
+  size_t lds = (size_t)NST * (TM + TN) * 64 * 2;
+  if (EPI == EPI_QKV) lds = std::max(lds, (size_t)TM * 4 + (size_t)WM * WN * BN * 4096);
+  if (EPI == EPI_GATEUP) lds = std::max(lds, (size_t)TM * 4 + (size_t)TM * (TN / 2 + 8) * 2);
+  if (EPI == EPI_RESIDUAL) lds = std::max(lds, (size_t)WM * WN * 32 * (32 * BN + 4) * 4);
+  static const hipError_t opted = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tile_kernel<EPI, WM, WN, BM, BN, NST, false>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  static const hipError_t opted_nt = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tile_kernel<EPI, WM, WN, BM, BN, NST, true>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  (void)opted; (void)opted_nt;
+  const int MT = (a.M + TM - 1) / TM;
+  const int tiles = MT * ((frag_end - frag_first + TN / 16 - 1) / (TN / 16));
+  const dim3 grid((tiles + 7) / 8 * 8, KS), block(64 * WM * WN);
+  if (MT == 1) hipLaunchKernelGGL((gemm_tile_kernel<EPI, WM, WN, BM, BN, NST, true>), grid, block, lds, s, a, MT, tiles, frag_first, frag_end);
+  else hipLaunchKernelGGL((gemm_tile_kernel<EPI, WM, WN, BM, BN, NST, false>), grid, block, lds, s, a, MT, tiles, frag_first, frag_end);
+}
+
+// Tile shapes of gemm_tile_kernel with what a workgroup costs: microseconds per slice of 64 contraction elements, and
+// for its start and epilogue (fitted to launches at the 7B shapes and at 768-wide ones, 97 to 2048 rows, on MI355X).
+struct TileShape { int tm, tn; float slice_us, fixed_us; };
+constexpr TileShape kTileShapes[] = {{256, 256, 1.60f, 10.0f}, {128, 256, 0.98f, 8.0f}, {128, 128, 0.54f, 6.0f}, {128, 64, 0.36f, 4.5f}, {64, 64, 0.30f, 3.5f}};
+constexpr int kNumTileShapes = 5;
+
+struct TilePlan { int shape, KS, split, shape2; };        // fragments from `split` on run as a second launch in shape2
+
+static float tile_cost(int shape, int epi, int M, int frags, int K, int KS) {
+  const TileShape &t = kTileShapes[shape];
+  const int mt = (M + t.tm - 1) / t.tm;
+  const float rounds = (float)(mt * ((frags * 16 + t.tn - 1) / t.tn) * KS) / 256.0f;
+  // whole rounds of 256 CUs: the last one, partly empty, runs faster than a full one (less traffic, higher clocks)
+  const float eff = rounds <= 1.0f ? 1.0f : 0.5f * (rounds + std::ceil(rounds));
+  const float slices = (float)((K + 63) / 64) / (float)KS;
+  return eff * (slices * t.slice_us + t.fixed_us + (epi == EPI_QKV ? 2.0f : 0.0f));
+}
+
+// The cheapest plan by the costs above.  Splitting the contraction (residual only) fills the chip when there are few
+// tiles; every split costs M x N partials written and read again by the RMSNorm.  When the tiles of a launch fill a
+// number of rounds and a half, the half round is given smaller tiles in a launch of its own.
+static TilePlan tile_plan(int epi, int M, int frags, int K) {
+  const int n_slices = (K + 63) / 64;
+  TilePlan best{0, 1, frags, 0};
+  float cost = 1e30f;
+  for (int c = 0; c < kNumTileShapes; ++c) {
+    const TileShape &t = kTileShapes[c];
+    if (epi == EPI_RESIDUAL) {
+      for (int ks = 1; ks <= kMaxResidualSplits && n_slices >= 2 * ks; ++ks) {
+        const float x = tile_cost(c, epi, M, frags, K, ks) + (float)M * frags * 64.0f * ks / 6.0e6f;
+        if (x < cost) { cost = x; best = {c, ks, frags, c}; }
+      }
+      continue;
+    }
+    const float x = tile_cost(c, epi, M, frags, K, 1);
+    if (x < cost) { cost = x; best = {c, 1, frags, c}; }
+    const int mt = (M + t.tm - 1) / t.tm, cols = (frags * 16 + t.tn - 1) / t.tn;
+    const int whole = mt * cols / 256 * 256 / mt;         // columns that fill whole rounds
+    if (whole < 1 || whole >= cols) continue;
+    const int cut = whole * (t.tn / 16);
+    for (int c2 = 0; c2 < kNumTileShapes; ++c2) {
+      const float y = tile_cost(c, epi, M, cut, K, 1) + tile_cost(c2, epi, M, frags - cut, K, 1) + 3.0f;
+      if (y < cost) { cost = y; best = {c, 1, cut, c2}; }
+    }
+  }
+  return best;
+}
+
+template <int EPI>
+static void launch_tile_shape(int shape, const GemmArgs &a, int KS, int f0, int f1, hipStream_t s) {
+  if (f0 >= f1) return;
+  switch (shape) {
+    case 0: launch_tile_cfg<EPI, 2, 4, 4, 2, 2>(a, KS, f0, f1, s); break;
+    case 1: launch_tile_cfg<EPI, 2, 4, 2, 2, 3>(a, KS, f0, f1, s); break;
+    case 2: launch_tile_cfg<EPI, 2, 4, 2, 1, 4>(a, KS, f0, f1, s); break;
+    case 3: launch_tile_cfg<EPI, 4, 2, 1, 1, 3>(a, KS, f0, f1, s); break;
+    default: launch_tile_cfg<EPI, 2, 2, 1, 1, 4>(a, KS, f0, f1, s);
+  }
+}
+
+template <int EPI>
+static void launch_tile(const GemmArgs &a, hipStream_t s) {
+  const int frags = EPI == EPI_QKV ? (a.H + 2 * a.Hkv) * (a.hd / 16) : (EPI == EPI_GATEUP ? a.N / 8 : a.N / 16);
+  const TilePlan p = tile_plan(EPI, a.M, frags, a.K);
+  launch_tile_shape<EPI>(p.shape, a, p.KS, 0, p.split, s);  // residual: p.KS == a.KS (gemm_residual_splits)
+  launch_tile_shape<EPI>(p.shape2, a, p.KS, p.split, frags, s);
+}
 // FN: fragments per wave; a workgroup owns 2 FN.  MT: row tiles of 16 FM rows (1: the tile holds the whole block).
 template <typename T, int EPI, int FM, int FN>
 static void launch_wide_cfg(const GemmArgs &a, int KS, int MT, hipStream_t s) {
@@ -854,48 +980,11 @@ static void launch_wide_cfg(const GemmArgs &a, int KS, int MT, hipStream_t s) {
   else hipLaunchKernelGGL((gemm_wide_kernel<T, EPI, FM, FN, true>), dim3((blocks + 7) / 8 * 8 * MT, KS), dim3(256), lds, s, a, MT);
 }
 
-template <typename T, int EPI, int FM, int FN>
-static void launch_wide32_cfg(const GemmArgs &a, int KS, int MT, hipStream_t s) {
-  size_t lds = (size_t)2 * 16 * FM * (64 + 8) * sizeof(T);
-  if (EPI == EPI_QKV) lds = std::max(lds, (size_t)(16 * FM * 4 + 15) / 16 * 16 + (size_t)4 * FN * (FM / 2) * 1024);   // accumulator hand-back
-  const int blocks = (a.n_groups + 2 * FN - 1) / (2 * FN);
-  if (lds > 64 * 1024) {
-    static const hipError_t opted = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_wide32_kernel<T, EPI, FM, FN, false>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    static const hipError_t opted_t = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_wide32_kernel<T, EPI, FM, FN, true>),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)opted; (void)opted_t;
-  }
-  if (MT == 1) hipLaunchKernelGGL((gemm_wide32_kernel<T, EPI, FM, FN, false>), dim3(blocks, KS), dim3(256), lds, s, a, 1);
-  else hipLaunchKernelGGL((gemm_wide32_kernel<T, EPI, FM, FN, true>), dim3((blocks + 7) / 8 * 8 * MT, KS), dim3(256), lds, s, a, MT);
-}
-
-template <typename T, int EPI, int FM>
-static void launch_wide_fm(const GemmArgs &a_in, int KS, int MT, hipStream_t s) {
+template <typename T, int FM>
+static void launch_wide_fm(const GemmArgs &a_in, int MT, hipStream_t s) {
   GemmArgs a = a_in;
-  a.n_groups = a.N / 16 * ((EPI == EPI_GATEUP) ? 2 : 1);     // fragments: gate/up interleaves 2 * d_ffn rows
-  if (EPI == EPI_QKV) a.n_groups = (a.H + 2 * a.Hkv) * (a.hd / 16);
-  // 128 rows of W per workgroup (four fragments per wave) where that still gives most CUs a workgroup, 64
-  // otherwise (q/k/v of a 4096-wide model has 768 fragments: 96 workgroups against 192): every workgroup reads
-  // all of X whatever it owns, so the W rows per workgroup only matter once the chip is full.  q/k/v always
-  // takes 64: the unrolled rotary epilogue over more accumulator fragments does not fit the registers.
-  bool narrow = false;
-  if constexpr (EPI == EPI_QKV || EPI == EPI_GATEUP) narrow = (a.n_groups + 7) / 8 * KS * MT < 160;
-  // The 32x32x16 kernel where the tile's row blocks pair up (192 and 256 rows: every prefill piece of 2048 tokens)
-  // and it measured faster on MI355X: q/k/v and gate/up always (7B shapes, 161-192 and 225-256 block rows: q/k/v
-  // 52 -> 48 and 64 -> 57 us, gate/up 70.5 -> 69 and 82 -> 79 us; prefill pieces: 271 -> 230 and 519 -> 464 us), the
-  // residual GEMMs only with several row tiles (prefill: 77 -> 72 and 242 -> 232 us; a single tile streams W from
-  // HBM and was 5 % slower: 18.2 -> 19.2 and 41 -> 42 us).
-  if constexpr (FM % 4 == 0 && EPI != EPI_UNEMBED) {
-    constexpr bool paired = EPI == EPI_QKV || EPI == EPI_GATEUP;
-    if (a.n_groups % 2 == 0 && a.K % 64 == 0 && (paired || MT > 1)) {
-      if (narrow) launch_wide32_cfg<T, EPI, FM, 2>(a, KS, MT, s);
-      else launch_wide32_cfg<T, EPI, FM, 4>(a, KS, MT, s);
-      return;
-    }
-  }
-  if (narrow) launch_wide_cfg<T, EPI, FM, 2>(a, KS, MT, s);
-  else launch_wide_cfg<T, EPI, FM, 4>(a, KS, MT, s);
+  a.n_groups = a.N / 16;
+  launch_wide_cfg<T, EPI_UNEMBED, FM, 4>(a, 1, MT, s);
 }
 
 // Row tiles of the wide kernel: as few as possible (288 rows at most each), then the smallest even
@@ -908,15 +997,15 @@ int gemm_wide_row_blocks(int M) {
   return (fm + 1) / 2 * 2 < 10 ? 10 : (fm + 1) / 2 * 2;
 }
 
-template <typename T, int EPI>
-static void launch_wide(const GemmArgs &a, int KS, hipStream_t s) {
+template <typename T>
+static void launch_wide(const GemmArgs &a, hipStream_t s) {
   const int MT = gemm_wide_row_tiles(a.M);
   switch (gemm_wide_row_blocks(a.M)) {
-    case 10: launch_wide_fm<T, EPI, 10>(a, KS, MT, s); break;
-    case 12: launch_wide_fm<T, EPI, 12>(a, KS, MT, s); break;
-    case 14: launch_wide_fm<T, EPI, 14>(a, KS, MT, s); break;
-    case 16: launch_wide_fm<T, EPI, 16>(a, KS, MT, s); break;
-    default: launch_wide_fm<T, EPI, 18>(a, KS, MT, s);
+    case 10: launch_wide_fm<T, 10>(a, MT, s); break;
+    case 12: launch_wide_fm<T, 12>(a, MT, s); break;
+    case 14: launch_wide_fm<T, 14>(a, MT, s); break;
+    case 16: launch_wide_fm<T, 16>(a, MT, s); break;
+    default: launch_wide_fm<T, 18>(a, MT, s);
   }
 }
 
@@ -1024,16 +1113,26 @@ static void launch_paired(const GemmArgs &a, hipStream_t s) {
 // half the splits of the contraction, so the RMSNorm that follows adds half the partials.
 static bool residual_narrow(int M, int N, int K) { return M <= 16 || K <= N; }
 
+// Which blocks gemm_tile_kernel takes (16-bit operands; the unembedding never).  Above 128 rows: all.  Up to 128 the
+// skinny kernel streams W as fast on wide models (7B shapes, 97 rows: gate/up 49.4 against 47.5-50.6 us, q/k/v 33.8
+// against 35.3; 65 rows: down 26.8 against 29.4) and loses
+//  * where its one or two fragments per workgroup leave CUs idle or too little in flight (768-wide model, 97 rows:
+//    gate/up 9.6 -> 7.1 us, q/k/v 9.9 -> 8.0, down 8.4 -> 5.3; 65 rows: 8.0 -> 7.1, 8.3 -> 8.0, 7.1 -> 5.2; 51 rows:
+//    gate/up 7.0 against 7.4, q/k/v 6.7 against 8.2);
+//  * on the square output projection, whose split contraction it reads X for twice as often (7B: 16.7 -> 12.8 us at 97
+//    rows, 11.0 -> 9.4 at 51, 9.7 -> 9.0 at 33, 8.4 against 8.8 at 17; 768 wide: 9.1 -> 4.0, 6.6 -> 4.2, 5.7 -> 4.1, 4.9 -> 4.0);
+//  * on the down projection from about 80 rows (7B, 97 rows: 32.6 -> 28.4), on narrow models from 33 (6.0 -> 5.4 at 51).
+static bool takes_tile(int epi, int M, int frags, int K) {
+  if (M > 128) return true;
+  if (epi != EPI_RESIDUAL) return M > 64 && frags <= 512;
+  if (K <= frags * 16) return M > 24;
+  return M > (frags < 128 ? 48 : 80);
+}
+
 // Split of the contraction across workgroups for the residual GEMMs: about one workgroup per CU, as
 // long as each split keeps at least 2 chunks.
 int gemm_residual_splits(int dtype, int M, int N, int K) {
-  if (dtype == 1 && M > 128) {              // wide kernel: 128 rows of W per workgroup, slices of 64; at least 8 slices per split
-    const int blocks = (N / 16 + 7) / 8 * ((M + 287) / 288), n_slices = (K + 63) / 64;   // row tiles count as workgroups
-    int ks = (256 + blocks - 1) / blocks;
-    ks = ks > kMaxResidualSplits ? kMaxResidualSplits : ks;
-    while (ks > 1 && n_slices / ks < 8) --ks;
-    return ks < 1 ? 1 : ks;
-  }
+  if (dtype == 1 && takes_tile(EPI_RESIDUAL, M, N / 16, K)) return tile_plan(EPI_RESIDUAL, M, N / 16, K).KS;
   const int kc = dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value;
   const int n_chunks = (K + kc - 1) / kc;
   const int blocks = residual_narrow(M, N, K) ? N / 32 : (N / 32 + 1) / 2;
@@ -1051,12 +1150,13 @@ template <typename T>
 static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   GemmArgs a = a_in;
   if constexpr (sizeof(T) == 2) {
-    if (a.M > 128) {
+    if (epi == EPI_UNEMBED) {
+      if (a.M > 128) { launch_wide<T>(a, s); return; }
+    } else if (takes_tile(epi, a.M, epi == EPI_RESIDUAL ? a.N / 16 : gemm_groups(epi, a), a.K)) {
       switch (epi) {
-        case EPI_QKV: launch_wide<T, EPI_QKV>(a, 1, s); break;
-        case EPI_GATEUP: launch_wide<T, EPI_GATEUP>(a, 1, s); break;
-        case EPI_RESIDUAL: launch_wide<T, EPI_RESIDUAL>(a, a.KS, s); break;
-        default: launch_wide<T, EPI_UNEMBED>(a, 1, s);
+        case EPI_QKV: launch_tile<EPI_QKV>(a, s); break;
+        case EPI_GATEUP: launch_tile<EPI_GATEUP>(a, s); break;
+        default: launch_tile<EPI_RESIDUAL>(a, s);
       }
       return;
     }

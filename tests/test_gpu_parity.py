@@ -738,6 +738,25 @@ def test_row_tiles_of_256_with_an_odd_number_of_contraction_slices_16_bit():
     ctx.close()
 
 
+@pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd", [
+    (5, 5, 32, 224, 257, 16, 8),      # widths 160 and 224: the last 64-element slice is half padding; 257 = one row more than a tile
+    (5, 1, 64, 608, 300, 16, 16),     # grouped heads; 257 block rows; the weights end inside a tile of W rows
+    (6, 2, 128, 96, 130, 20, 6),      # a contraction of 2 slices, heads of 128; 121 block rows: residual GEMMs tiled, q/k/v and gate/up tiled below 129
+    (3, 3, 32, 2080, 1100, 5, 13),    # five row tiles of 256; 66 block rows
+])
+def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd):
+    """gemm_tile_kernel where its tiles end: rows past the block, W rows past the matrix, contractions that are not a
+    multiple of the 64-element slice, K/V rows written into a partly filled tile of 32 positions.  A prompt (prefill
+    pieces) and then one verify block against the oracle; the tolerance is the one of every 16-bit lock-step test."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=heads * hd if heads != 6 else 192,
+                d_ffn=d_ffn, vocab=4096)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=64, k=k, w=wd, k_ctx_max=4)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=2)
+    ctx.close()
+    assert rep.max_rel_logit_err <= 2e-2, rep
+
+
 def test_7b_width_two_layer_twin_bf16_lockstep():
     """7B widths (d 4096, 32 heads of 128, FFN 14336, vocab 32000) with 2 layers so
     the oracle can run it: prompt 2048, k=10, w=5 -- the launch shapes of config 3."""
