@@ -189,9 +189,33 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   if ((size_t)n_splits * Mpart > c->part_rows)
     return fail(c, NGG_ECAPACITY, "attention partials: %d slices of %d rows exceed the %zu rows allocated", n_splits, Mpart, c->part_rows);
   const size_t part_stride = (size_t)c->Mcap * d.d_model;
-  const int ks_o = gemm_residual_splits(dt, M, d.d_model, dq), ks_down = gemm_residual_splits(dt, M, d.d_model, d.d_ffn);
+  int ks_o = gemm_residual_splits(dt, M, d.d_model, dq), ks_down = gemm_residual_splits(dt, M, d.d_model, d.d_ffn);
   const int ss_segs = rmsnorm_segments(d.d_model);
+  // A block of one token: the GEMMs run the RMSNorms and the merge of the attention slices themselves (launch_gemm_row).
+  // Not while the norms' own time is asked for: a profile of that class needs them as launches.
+  const bool one_row = M == 1 && gemm_row_fits(dt, d.d_model, dq) && !((c->prof_mask >> NGG_PROF_NORM) & 1);
+  RowArgs row{};
+  float *h_cur = c->h, *h_next = c->h + d.d_model;   // row 1 of the residual stream is free; 2 n_layers swaps end in row 0
+  if (one_row) {
+    ks_o = gemm_row_splits(d.d_model, dq);
+    ks_down = gemm_row_splits(d.d_model, d.d_ffn);
+    row.hpart = c->hpart; row.part_stride = part_stride;
+  }
   int pending = 0;                                   // residual partials the next RMSNorm has to add
+  // the norm in front of a GEMM: a launch of its own, or (one row) what the GEMM's prologue needs for it
+  auto norm = [&](const void *gain) {
+    if (!one_row) {
+      ProfScope ps(c, NGG_PROF_NORM);
+      launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, gain, c->xn, d.d_model, M, c->Mcap, c->row_ss, s);
+      return;
+    }
+    row.h_in = h_cur; row.h_out = h_next; row.n_part = pending; row.gain = gain; row.part_o = nullptr;
+    if (pending > 0) std::swap(h_cur, h_next);
+  };
+  auto gemm = [&](int epi, const GemmArgs &g) {
+    if (one_row) launch_gemm_row(dt, epi, g, row, s);
+    else launch_gemm(dt, epi, g, s);
+  };
   for (int l = 0; l < d.n_layers; ++l) {
     const ngg_layer_weights &lw = c->layers[l];
     const size_t kv_layer = (size_t)l * d.n_kv_heads;
@@ -203,7 +227,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       vscr_l = (char *)c->vcache + (kv_layer * c->Spad + P) * d.head_dim * c->esize;
       kv_rows = c->Spad;
     }
-    { ProfScope ps(c, NGG_PROF_NORM); launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, lw.attn_norm, c->xn, d.d_model, M, c->Mcap, c->row_ss, s); }
+    norm(lw.attn_norm);
     {
       ProfScope ps(c, NGG_PROF_GEMM_QKV);
       GemmArgs g{};
@@ -215,7 +239,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.rope_cos = c->rope_cos; g.rope_sin = c->rope_sin;
       g.row_ss = c->row_ss; g.ss_segs = ss_segs; g.ss_eps = d.rms_eps;
       g.out_scale = 1.0f / c->lt[l].s_qkv;
-      launch_gemm(dt, EPI_QKV, g, s);
+      gemm(EPI_QKV, g);
     }
     {
       ProfScope ps(c, NGG_PROF_ATTENTION);
@@ -226,7 +250,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       a.kscr = kscr_l; a.vscr = vscr_l; a.kv_rows = kv_rows;
       a.part_o = c->part_o; a.part_ml = c->part_ml; a.out = c->attn;
       a.H = d.n_heads; a.Hkv = d.n_kv_heads; a.Mcap = c->Mcap; a.Spad = c->Spad; a.M = M; a.C = C; a.P = P;
-      a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev;
+      a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0;
       a.scale = 1.0f / std::sqrt((float)d.head_dim);
       launch_attention(dt, d.head_dim, a, s);
     }
@@ -236,9 +260,12 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.X = c->attn; g.W0 = c->lt[l].wo; g.M = M; g.N = d.d_model; g.K = dq;
       g.hpart = c->hpart; g.KS = ks_o; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / c->lt[l].s_o;
-      launch_gemm(dt, EPI_RESIDUAL, g, s);
+      g.hd = d.head_dim;
+      if (one_row) { row.part_o = c->part_o; row.part_ml = c->part_ml; row.n_splits = n_splits; row.attn_out = c->attn; }
+      gemm(EPI_RESIDUAL, g);
     }
-    { ProfScope ps(c, NGG_PROF_NORM); launch_rmsnorm(dt, c->h, c->hpart, ks_o, part_stride, lw.mlp_norm, c->xn, d.d_model, M, c->Mcap, c->row_ss, s); }
+    pending = ks_o;
+    norm(lw.mlp_norm);
     {
       ProfScope ps(c, NGG_PROF_GEMM_GATEUP);
       GemmArgs g{};
@@ -246,7 +273,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.act = c->act; g.Mcap = c->Mcap;
       g.row_ss = c->row_ss; g.ss_segs = ss_segs; g.ss_eps = d.rms_eps;
       g.out_scale = 1.0f / c->lt[l].s_gu;
-      launch_gemm(dt, EPI_GATEUP, g, s);
+      gemm(EPI_GATEUP, g);
     }
     {
       ProfScope ps(c, NGG_PROF_GEMM_DOWN);
@@ -254,12 +281,12 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.X = c->act; g.W0 = c->lt[l].wdown; g.M = M; g.N = d.d_model; g.K = d.d_ffn;
       g.hpart = c->hpart; g.KS = ks_down; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / c->lt[l].s_down;
-      launch_gemm(dt, EPI_RESIDUAL, g, s);
+      gemm(EPI_RESIDUAL, g);
     }
     pending = ks_down;
   }
   if (unembed) {
-    { ProfScope ps(c, NGG_PROF_NORM); launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, c->w.final_norm, c->xn, d.d_model, M, c->Mcap, c->row_ss, s); }
+    norm(c->w.final_norm);
     ProfScope ps(c, NGG_PROF_GEMM_UNEMBED);
     GemmArgs g{};
     g.X = c->xn; g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
@@ -273,7 +300,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.M = 1;
     }
     g.out_scale = 1.0f / c->unemb_scale;
-    launch_gemm(dt, EPI_UNEMBED, g, s);
+    gemm(EPI_UNEMBED, g);
   }
   NGG_HIP(c, hipGetLastError());
   return NGG_OK;

@@ -292,6 +292,15 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(const AttnArgs a, int 
     l = rows_sum(l);                                        // the four lanes of a query each held a share of its sum
     // partial outputs keep the fragment order, [head][slice][16-query group][df][lane][4]: one store
     // instruction of the wave writes 1 KB contiguously
+    if (a.one_row) {                                        // only query 0: its dims side by side
+      const size_t slot = (size_t)h * S + split;
+      if (m == 0) *reinterpret_cast<float4 *>(a.part_o + slot * HD + df * 16 + 4 * g) = float4{o[0], o[1], o[2], o[3]};
+      if (m == 0 && df == 0 && g == 0) {
+        a.part_ml[slot * 2 + 0] = mstar;
+        a.part_ml[slot * 2 + 1] = l;
+      }
+      continue;
+    }
     const size_t blk = ((size_t)h * S + split) * (a.Mpart / 16) + (q0 / 16 + qf);
     *reinterpret_cast<float4 *>(a.part_o + ((blk * DF + df) * 64 + lane) * 4) = float4{o[0], o[1], o[2], o[3]};
     if (m < M && df == 0 && g == 0) {
@@ -536,6 +545,7 @@ static void launch_hd(const AttnArgs &a, hipStream_t s) {
   if (a.M <= 16) launch_stream<T, HD, 1>(a, s);
   else if (a.M <= 64 || attn_shared_qmax<T, HD>() == 1) launch_shared<T, HD, 1>(a, s);
   else launch_shared<T, HD, attn_shared_qmax<T, HD>()>(a, s);
+  if (a.one_row) return;                                    // the output projection merges the slices
   hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);
 }
 

@@ -1176,6 +1176,306 @@ static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// One block token (the single-token decode step, and the blocks of one token a table build leaves over).  Such a step is
+// a chain of short launches: the stream of W takes 5 to 34 us per GEMM at the 7B shapes and 1 us on a 768-wide model,
+// while every launch costs 2 us and a latency chain of its own.  With one row the input of a GEMM is so small that every
+// workgroup can build all of it: the kernel takes over the RMSNorm (residual partials, gain, sum of squares) and the merge
+// of the attention slices, which as launches took 4.7 us (2.5-3.2 on the small model) each.  The row then sits in LDS
+// once and the main loop has no barrier: W fragments stream through a register ring, the four waves split the steps and
+// hand their sums over at the end.  Five launches per layer instead of eight; measured on the whole step: 7B, 2K context
+// 3.55 -> 3.27 ms; 768 wide, 12 layers 510 -> 380 us.  Per launch at the 7B shapes (before: GEMM + norm or merge):
+// q/k/v 18.4 + 4.7 -> 19.1, O 8.2 + 4.6 -> 9.3, gate/up 39.2 + 4.7 -> 39.6, down 19.6 -> 20.2 us.
+//   PRO 0: X is row 0 of an activation buffer.  PRO 1: X = (h + residual partials) * gain, 1 / rms in the epilogue;
+//   workgroup 0 stores the new residual stream to h_out (not over h: others still read it).  PRO 2: X = the merge of the
+//   attention slices; the workgroups with blockIdx.x == 0 store it to attn_out.
+// U: storage type of the gain.
+// ---------------------------------------------------------------------------------------------
+constexpr int kRowThreads = 256;
+
+// q/k/v, gate/up: enough fragments per workgroup that 256 of them cover the matrix; residual: one or two fragments and a
+// split contraction; unembedding: pairs
+static int row_frags_per_wg(int epi, int frags) {
+  if (epi == EPI_RESIDUAL) return frags <= 128 ? 1 : 2;
+  int fn = (frags + 255) / 256;
+  fn = fn > 8 ? 8 : fn;
+  return epi == EPI_UNEMBED ? (fn + 1) / 2 * 2 : fn;
+}
+int gemm_row_splits(int N, int K) {
+  const int wgs = N / 16 / row_frags_per_wg(EPI_RESIDUAL, N / 16);
+  int ks = (256 + wgs - 1) / wgs;
+  ks = ks > kMaxResidualSplits ? kMaxResidualSplits : ks;
+  while (ks > 1 && K / 32 / ks < 8) --ks;                // at least two steps per wave
+  return ks;
+}
+// the normalised row, and the merged attention output's share of a contraction split, have to fit the LDS
+bool gemm_row_fits(int dtype, int d_model, int dq) {
+  const int e = dtype == 1 ? 2 : 4;
+  return (size_t)d_model * e <= 64 * 1024 && ((size_t)dq / gemm_row_splits(d_model, dq) + 64) * e <= 96 * 1024;
+}
+
+// NP: residual partials fetched at once (PRO 1), the number itself is r.n_part <= NP
+template <typename U, typename T, int EPI, int FN, int RING, int PRO, int NP>
+__global__ __launch_bounds__(kRowThreads) void gemm_row_kernel(const GemmArgs a, const RowArgs r) {
+  constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
+  constexpr int KC = KChunk<T>::value, NW = 4;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  T *xs = reinterpret_cast<T *>(smem);                   // [K of this workgroup] (PRO 1, 2)
+  __shared__ float sh[NW];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, g = lane >> 4;
+  const int K = a.K, n_steps = K / 32, n_frags = a.n_groups;
+  const int KS = gridDim.y, ks = blockIdx.y;
+  const int s0 = n_steps * ks / KS, s1 = n_steps * (ks + 1) / KS;
+  const int k0 = s0 * 32, kr = (s1 - s0) * 32;           // contraction elements of this workgroup
+  const int f0 = blockIdx.x * FN;
+  const int nt = s1 - s0 > wave ? (s1 - s0 - wave + NW - 1) / NW : 0;   // steps of this wave: s0 + wave, + 4, ...
+
+  const T *wblk[FN];
+#pragma unroll
+  for (int f = 0; f < FN; ++f) wblk[f] = tiled_block((const T *)a.W0, min(f0 + f, n_frags - 1), n_steps, lane);
+  Frag<T> ring[RING][FN], xring[PRO == 0 ? RING : 1];
+  auto load_w = [&](int slot, int t) {                   // clamped into the matrix: loaded, never multiplied
+    const int st = min(s0 + wave + NW * t, n_steps - 1);
+#pragma unroll
+    for (int f = 0; f < FN; ++f) ring[slot][f] = load_frag_stream(wblk[f] + (size_t)st * 512);
+    // an input that is ready as it stands needs no staging: its 64 bytes of the step travel with the weights
+    if constexpr (PRO == 0) xring[slot] = load_frag((const T *)a.X + (size_t)(st * 32 / KC) * a.Mcap * KC + st * 32 % KC + g * 8);
+  };
+  // The row's loads go out first (they come from the L2), the ring's behind them, so that the row can be waited for
+  // while the weights are on their way; the scheduling barriers keep that order.
+  auto fill_ring = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < RING; ++u) load_w(u, u);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  constexpr int J = NP <= 2 ? 4 : 2;                     // PRO 1: float4 groups per thread and round
+  f32x4 hx[J];
+  const int rounds = (K / 4 + J * kRowThreads - 1) / (J * kRowThreads);
+  if constexpr (PRO == 1) {
+    float ss = 0.0f;
+    for (int rd = 0; rd < rounds; ++rd) {
+      f32x4 p[J][NP], gn[J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int i = min(tid + (rd * J + j) * kRowThreads, K / 4 - 1);
+        hx[j] = *reinterpret_cast<const f32x4 *>(r.h_in + 4 * i);
+#pragma unroll
+        for (int s = 0; s < NP; ++s)                     // surplus slots repeat the last partial (of none: the first) and are not added
+          p[j][s] = *reinterpret_cast<const f32x4 *>(r.hpart + (size_t)max(min(s, r.n_part - 1), 0) * r.part_stride + 4 * i);
+        const U *gp = (const U *)r.gain + 4 * i;
+        gn[j] = f32x4{to_f32(gp[0]), to_f32(gp[1]), to_f32(gp[2]), to_f32(gp[3])};
+      }
+      if (rd == 0) fill_ring();
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int i = tid + (rd * J + j) * kRowThreads;
+#pragma unroll
+        for (int s = 0; s < NP; ++s) {                   // split order
+          const bool add = s < r.n_part;
+          hx[j] += f32x4{add ? p[j][s][0] : 0.f, add ? p[j][s][1] : 0.f, add ? p[j][s][2] : 0.f, add ? p[j][s][3] : 0.f};
+        }
+        const f32x4 x = hx[j];
+        const float q = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+        ss += i < K / 4 ? q : 0.0f;
+        if (i < K / 4) {
+          store4(xs + 4 * i, x[0] * gn[j][0], x[1] * gn[j][1], x[2] * gn[j][2], x[3] * gn[j][3]);
+          if (rd + 1 < rounds && r.n_part > 0 && blockIdx.x == 0) *reinterpret_cast<f32x4 *>(r.h_out + 4 * i) = x;
+        }
+      }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
+    if (lane == 0) sh[wave] = ss;
+    __syncthreads();
+  } else if constexpr (PRO == 2) {
+    // merge of the attention slices: 4 dims per thread and turn, the slices in order, eight at a time
+    const int S = r.n_splits, hd = a.hd;
+    constexpr int G = 2;                                 // turns whose first eight slices are fetched before the weights
+    f32x4 v[G][8];
+    float mm[G][8], ll[G][8];
+    auto fetch = [&](int gi, int i, int t0) {
+      const int k = k0 + 4 * min(i, kr / 4 - 1), h = k / hd, d = k - h * hd;
+      const float *po = r.part_o + (size_t)h * S * hd + d, *ml = r.part_ml + (size_t)h * S * 2;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int sc = min(t0 + t, S - 1);
+        v[gi][t] = *reinterpret_cast<const f32x4 *>(po + (size_t)sc * hd);
+        mm[gi][t] = ml[sc * 2];
+        ll[gi][t] = ml[sc * 2 + 1];
+      }
+    };
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) fetch(gi, tid + gi * kRowThreads, 0);
+    fill_ring();
+    // (the first eight slices apart from the loop over the rest: inside it their loads would be waited for together
+    // with everything issued since, the weights included)
+    auto finish = [&](int gi, int i) {
+      float mrun = kNegBig, l = 0.0f;
+      f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+      auto add8 = [&](int t0) {
+        float mnew = mrun;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) mnew = fmaxf(mnew, t0 + t < S ? mm[gi][t] : kNegBig);
+        const float alpha = part_exp<T>(mrun - mnew);
+        l *= alpha;
+        o *= alpha;
+        mrun = mnew;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const float wgt = t0 + t < S ? part_exp<T>(mm[gi][t] - mrun) : 0.0f;   // surplus slots repeat the last slice: weight 0
+          l += ll[gi][t] * wgt;
+          o += v[gi][t] * wgt;
+        }
+      };
+      add8(0);
+      for (int t0 = 8; t0 < S; t0 += 8) {
+        fetch(gi, i, t0);
+        add8(t0);
+      }
+      if (i < kr / 4) {
+        const float inv = 1.0f / l;
+        store4(xs + 4 * i, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+        if (blockIdx.x == 0) store4((T *)r.attn_out + act_offset<T>(0, k0 + 4 * i, a.Mcap), o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+      }
+    };
+#pragma unroll
+    for (int gi = 0; gi < G; ++gi) finish(gi, tid + gi * kRowThreads);
+    for (int i = tid + G * kRowThreads; i < kr / 4; i += kRowThreads) {
+      fetch(0, i, 0);
+      finish(0, i);
+    }
+    __syncthreads();
+  } else {
+    fill_ring();
+  }
+
+  // ---- the stream of W; every column of the second operand is the row ---------------------------------
+  f32x4 acc[FN];
+#pragma unroll
+  for (int f = 0; f < FN; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t0 = 0; t0 < nt; t0 += RING) {
+#pragma unroll
+    for (int u = 0; u < RING; ++u) {
+      const int t = t0 + u;
+      if (t < nt) {                                      // uniform per wave, no global load inside
+        Frag<T> xf;
+        if constexpr (PRO == 0) xf = xring[u];
+        else xf = load_frag(xs + (wave + NW * t) * 32 + g * 8);
+#pragma unroll
+        for (int f = 0; f < FN; ++f) mma(acc[f], ring[u][f], xf);
+      }
+      load_w(u, t + RING);
+    }
+  }
+  if constexpr (PRO == 1) {                              // the new residual stream (the last round's share of it), behind the stream of W
+    if (r.n_part > 0 && blockIdx.x == 0)
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int i = tid + ((rounds - 1) * J + j) * kRowThreads;
+        if (i < K / 4) *reinterpret_cast<f32x4 *>(r.h_out + 4 * i) = hx[j];
+      }
+  }
+  float rs = a.out_scale;
+  if constexpr (PRO == 1) rs *= 1.0f / sqrtf((((sh[0] + sh[1]) + sh[2]) + sh[3]) / (float)K + a.ss_eps);
+  __syncthreads();                                       // everyone is done with xs
+  f32x4 *red = reinterpret_cast<f32x4 *>(smem);          // [NW][FN][64]
+#pragma unroll
+  for (int f = 0; f < FN; ++f) red[(wave * FN + f) * 64 + lane] = acc[f];
+  __syncthreads();
+  auto total = [&](int f) {
+    f32x4 t = red[f * 64 + lane];
+#pragma unroll
+    for (int o = 1; o < NW; ++o) t += red[(o * FN + f) * 64 + lane];
+    return t;
+  };
+  if constexpr (EPI == EPI_UNEMBED) {
+    for (int f = 2 * wave; f < FN; f += 2 * NW) {
+      if (f0 + f >= n_frags) break;
+      const int nbase[2] = {(f0 + f) * 16, (f0 + f + 1) * 16};
+      const f32x4 sums[2] = {total(f), total(f + 1)};
+      epi_unembed<2>(a, (f0 + f) / 2, li, li == 0, g, rs, nbase, sums);
+    }
+  } else {
+    for (int f = wave; f < FN; f += NW) {
+      if (f0 + f >= n_frags) break;                      // uniform per wave
+      if constexpr (PAIRED) epi_paired<T, EPI>(a, f0 + f, li, 1, g, rs, total(f));
+      else if (li == 0) epi_residual(a, ks, 0, (f0 + f) * 16, g, total(f));
+    }
+  }
+}
+
+template <typename U, int EPI, int FN, int PRO, int NP>
+static void launch_row_np(const GemmArgs &a, const RowArgs &r, int KS, hipStream_t s) {
+  typedef typename Internal<U>::type T;
+  // steps in flight per wave: as many 1 KB fragments as the registers hold without spilling (fp32 fragments are 2 KB)
+  constexpr int RING = (sizeof(T) == 2 ? (FN >= 5 ? 3 : (FN >= 3 ? 5 : 8)) : (FN >= 5 ? 2 : (FN >= 3 ? 3 : 4)));
+  const size_t row = PRO == 0 ? 0 : ((size_t)(a.K / 32 + KS - 1) / KS * 32) * sizeof(T);
+  const size_t lds = std::max(row, (size_t)4 * FN * 1024);
+  static const hipError_t opted = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_row_kernel<U, T, EPI, FN, RING, PRO, NP>),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+  (void)opted;
+  hipLaunchKernelGGL((gemm_row_kernel<U, T, EPI, FN, RING, PRO, NP>), dim3((a.n_groups + FN - 1) / FN, KS), dim3(kRowThreads), lds, s, a, r);
+}
+
+template <typename U, int EPI, int FN, int PRO>
+static void launch_row_cfg(const GemmArgs &a, const RowArgs &r, int KS, hipStream_t s) {
+  if constexpr (PRO == 1) {                              // narrow models split the residual GEMMs further (gemm_row_splits)
+    if (r.n_part > 2) { launch_row_np<U, EPI, FN, PRO, kMaxResidualSplits>(a, r, KS, s); return; }
+  }
+  launch_row_np<U, EPI, FN, PRO, 2>(a, r, KS, s);
+}
+
+template <typename U, int EPI, int PRO>
+static void launch_row_fn(const GemmArgs &a, const RowArgs &r, int KS, hipStream_t s) {
+  const int fn = row_frags_per_wg(EPI, a.n_groups);
+  if constexpr (EPI == EPI_RESIDUAL) {
+    if (fn == 1) launch_row_cfg<U, EPI, 1, PRO>(a, r, KS, s);
+    else launch_row_cfg<U, EPI, 2, PRO>(a, r, KS, s);
+  } else if constexpr (EPI == EPI_UNEMBED) {
+    switch (fn) {
+      case 2: launch_row_cfg<U, EPI, 2, PRO>(a, r, KS, s); break;
+      case 4: launch_row_cfg<U, EPI, 4, PRO>(a, r, KS, s); break;
+      case 6: launch_row_cfg<U, EPI, 6, PRO>(a, r, KS, s); break;
+      default: launch_row_cfg<U, EPI, 8, PRO>(a, r, KS, s);
+    }
+  } else {
+    switch (fn) {
+      case 1: launch_row_cfg<U, EPI, 1, PRO>(a, r, KS, s); break;
+      case 2: launch_row_cfg<U, EPI, 2, PRO>(a, r, KS, s); break;
+      case 3: launch_row_cfg<U, EPI, 3, PRO>(a, r, KS, s); break;
+      case 4: launch_row_cfg<U, EPI, 4, PRO>(a, r, KS, s); break;
+      case 5: launch_row_cfg<U, EPI, 5, PRO>(a, r, KS, s); break;
+      case 6: launch_row_cfg<U, EPI, 6, PRO>(a, r, KS, s); break;
+      case 7: launch_row_cfg<U, EPI, 7, PRO>(a, r, KS, s); break;
+      default: launch_row_cfg<U, EPI, 8, PRO>(a, r, KS, s);
+    }
+  }
+}
+
+template <typename U>
+static void launch_row_t(int epi, const GemmArgs &a_in, const RowArgs &r, hipStream_t s) {
+  GemmArgs a = a_in;
+  a.n_groups = epi == EPI_RESIDUAL || epi == EPI_UNEMBED ? a.N / 16 : gemm_groups(epi, a);
+  switch (epi) {
+    case EPI_QKV: launch_row_fn<U, EPI_QKV, 1>(a, r, 1, s); break;
+    case EPI_GATEUP: launch_row_fn<U, EPI_GATEUP, 1>(a, r, 1, s); break;
+    case EPI_RESIDUAL:
+      if (r.part_o) launch_row_fn<U, EPI_RESIDUAL, 2>(a, r, a.KS, s);
+      else launch_row_fn<U, EPI_RESIDUAL, 0>(a, r, a.KS, s);
+      break;
+    default: launch_row_fn<U, EPI_UNEMBED, 1>(a, r, 1, s);
+  }
+}
+
+void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s) {
+  if (dtype == 1) launch_row_t<bf16_t>(epi, a, r, s);
+  else launch_row_t<float>(epi, a, r, s);
+}
+
 void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
   if (dtype == 1) launch_t<half_t>(epi, a, s);
   else launch_t<float>(epi, a, s);

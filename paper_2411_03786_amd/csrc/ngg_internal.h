@@ -214,6 +214,12 @@ template <> __device__ __forceinline__ float silu<half_t>(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
 }
 
+// exponential of a difference of the attention kernels' reference maxima, which the 16-bit configuration keeps in the
+// base-2 domain
+template <typename T> __device__ __forceinline__ float part_exp(float x);
+template <> __device__ __forceinline__ float part_exp<float>(float x) { return expf(x); }
+template <> __device__ __forceinline__ float part_exp<half_t>(float x) { return __builtin_amdgcn_exp2f(x); }
+
 // ---------------------------------------------------------------------------------------------
 // Block token index.  The model call of Section 3 takes a block of R rows x C columns.  Plain layout
 // (pieces of a prompt, table builds): m = r*C + j.  Shared-first-column layout (a verify block,
@@ -271,6 +277,20 @@ struct GemmArgs {
   int *pmax_idx;          // [N/32][Mcap]
 };
 
+// What the single-row GEMM (launch_gemm_row) builds its input from
+struct RowArgs {
+  const float *h_in;      // residual stream [K], and the partials of the last residual GEMM to add to it
+  float *h_out;           // the sum, stored when n_part > 0 (another buffer than h_in)
+  const float *hpart;
+  int n_part;
+  size_t part_stride;
+  const void *gain;       // [K], the user's storage type
+  const float *part_o;    // attention slices [H][n_splits][hd] and their (maximum, sum); null: X is taken from GemmArgs
+  const float *part_ml;
+  int n_splits;
+  void *attn_out;         // the merged slices, chunk-major like every activation
+};
+
 constexpr int kMaxResidualSplits = 8;
 constexpr int kNormSegs = 4;   // workgroups that may share a row of the RMSNorm; row_ss is [Mcap][kNormSegs]
 
@@ -284,6 +304,7 @@ struct AttnArgs {
   float *part_o;          // [H][n_splits][Mpart/16][hd/16][64 lanes][4]: output fragments as the registers hold them
   float *part_ml;         // [H][n_splits][Mpart][2]
   int Mpart;              // rows per (head, slice) of the two partial buffers: M rounded up to 128
+  int one_row;            // M == 1 and the merge is left to the GEMM that follows: partials are [H][n_splits][hd] and [H][n_splits][2]
   void *out;              // chunk-major [H*hd/KC][Mcap][KC] T
   int H, Hkv, Mcap, Spad, M, C, P, n_splits;   // n_splits: workgroups that share a head's list of key tiles
   const int32_t *n_dev;   // when set, P = *n_dev - 1 (see DraftArgs)
@@ -295,6 +316,11 @@ struct AttnArgs {
 // checks shapes before calling.
 void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s);
 int gemm_residual_splits(int dtype, int M, int N, int K);
+// the GEMMs of a block of one token, with the RMSNorm (q/k/v, gate/up, unembedding) or the merge of the attention slices
+// (output projection, r.part_o set) in front
+void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s);
+int gemm_row_splits(int N, int K);
+bool gemm_row_fits(int dtype, int d_model, int dq);
 void launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
 int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits);
 int attention_workgroups(int dtype, int hd, int H, int M, int n_splits);   // workgroups the main attention kernel is launched with

@@ -757,6 +757,25 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd):
     assert rep.max_rel_logit_err <= 2e-2, rep
 
 
+@pytest.mark.parametrize("dtype,layers,heads,kv,hd,d_model,d_ffn,prompt_len", [
+    ("f32", 2, 3, 3, 32, 96, 160, 70),            # 3 steps of the contraction: waves without one
+    ("f32", 1, 2, 2, 64, 128, 2112, 1500),        # 11 slices of the key list (two rounds of the merge)
+    ("bf16", 3, 5, 1, 64, 320, 608, 333),         # grouped heads; more than two residual partials
+    ("bf16", 2, 2, 2, 128, 256, 96, 1500),        # 11 slices; heads cut by the contraction split
+    ("bf16", 1, 33, 3, 128, 4224, 4160, 40),      # a row of more than 4096 features: two rounds of the norm
+])
+def test_single_token_steps_with_the_norms_and_the_merge_inside_the_gemms(dtype, layers, heads, kv, hd, d_model, d_ffn, prompt_len):
+    """gemm_row_kernel (blocks of one token): plain greedy steps against the oracle, logits at every step, at the edges
+    of its prologues and splits.  The tolerance is the one of every lock-step test of the type."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], layers), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=d_model,
+                d_ffn=d_ffn, vocab=2048, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=12, k=1, w=0, k_ctx_max=0, q_min=1, q_max=1)
+    w_, prompt, model, ctx = _setup(desc, run, random_gains=True)
+    rep = lockstep_run(ctx, model, prompt, 4, run, TOL[dtype], max_steps=3)
+    ctx.close()
+    assert rep.max_rel_logit_err <= TOL[dtype], rep
+
+
 def test_7b_width_two_layer_twin_bf16_lockstep():
     """7B widths (d 4096, 32 heads of 128, FFN 14336, vocab 32000) with 2 layers so
     the oracle can run it: prompt 2048, k=10, w=5 -- the launch shapes of config 3."""
