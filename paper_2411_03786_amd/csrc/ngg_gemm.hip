@@ -372,210 +372,6 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_skinny_kernel(const GemmArg
 
 
 // ---------------------------------------------------------------------------------------------
-// Wide blocks (more than 128 rows; 16-bit types): one pass over W for up to 16*FM = 288 block rows.
-// Section 3's cost model has the call leave the memory-bound regime as k*(w+1) grows; with 128-row
-// tiles the skinny kernel re-streamed all of W for every further 128 rows, which put that transition
-// far below the chip's ops-to-bytes ratio.  Here a workgroup owns 2 FN fragments of W (64 or 128 rows) and
-// all row blocks of the tile; its four waves are laid out 2 x 2: a wave takes FN of the fragments and half
-// of the row blocks (FN * FM / 2 <= 36 accumulator fragments), so a W fragment is loaded once from HBM and
-// meets every block row.  X is staged through LDS in slices of 64 contraction elements (two MFMA steps),
-// double buffered; a wave reads only its half of the rows from LDS (with the four waves side by side along
-// W every wave read all of X, and the LDS reads cost as much as the MFMAs: 10-20 % slower at 130-290 rows).
-// W goes from global memory straight into registers, 4 steps ahead, as in the skinny kernel; the two waves
-// that share a fragment both load it (the second request is served by the L2).  No hand-over between waves:
-// each wave finishes its own accumulators.  gridDim.y splits the contraction (residual only).
-// ---------------------------------------------------------------------------------------------
-template <typename T, int EPI, int FM, int FN, bool TILED>
-__global__ __launch_bounds__(256) void gemm_wide_kernel(const GemmArgs a, int MT) {
-  static_assert(sizeof(T) == 2, "16-bit operands only");
-  constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
-  static_assert(PAIRED || FN % 2 == 0, "unembedding partials are indexed by pairs of fragments");
-  static_assert(FM % 2 == 0, "the waves are laid out 2 x 2 over (row blocks, fragments)");
-  constexpr int FMW = FM / 2;                // row blocks per wave
-  constexpr int KC = KChunk<T>::value;       // chunk of the activation layout (256)
-  constexpr int KW = 64;                     // contraction elements staged per slice: two steps
-  constexpr int SPS = KW / 32;               // steps per slice
-  constexpr int LDX = KW + 8;                // LDS row stride in elements (16 bytes of padding)
-  constexpr int ROWS = 16 * FM;
-  constexpr int PPR = KW / 8;                // 16-byte pieces per row
-  constexpr int PIECES = (ROWS * PPR + 255) / 256;
-  constexpr int RING = 4;                    // W steps in flight per wave (two slices)
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  T *xs = reinterpret_cast<T *>(smem);       // [2][ROWS][LDX]
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int li = lane & 15, g = lane >> 4;
-  const int wn = wave & 1, wm = wave >> 1;   // this wave: fragments wn * FN .. of the workgroup's 2 FN, row blocks wm * FMW ..
-  const int K = a.K, M = a.M;
-  const int n_frags = a.n_groups;            // 16-row fragments of W (the launcher fills it)
-  const int n_steps = K / 32;
-  const int n_slices = (n_steps + SPS - 1) / SPS;
-  const int KS = gridDim.y, ks = blockIdx.y;
-  // Workgroup -> (rows of W, row tile).  With several row tiles (TILED: prefill pieces of more than 288 rows) the
-  // MT workgroups that share rows of W take consecutive slots of one XCD (workgroup b runs on XCD b % 8), so they
-  // run at about the same time on one L2 and the rows come from HBM once; W is then read with ordinary loads
-  // (a non-temporal line may be gone before the next workgroup asks for it).
-  const int nb = TILED ? (blockIdx.x / 8 / MT) * 8 + blockIdx.x % 8 : blockIdx.x;
-  const int m0 = TILED ? (blockIdx.x / 8 % MT) * (16 * FM) : 0;
-  if (TILED && nb * 2 * FN >= n_frags) return;               // padding of the last row of 8
-  const int c0 = (int)(((long)n_slices * ks) / KS), c1 = (int)(((long)n_slices * (ks + 1)) / KS);
-
-  const T *wblk[FN];
-  int fragi[FN];
-  bool frag_live[FN];
-#pragma unroll
-  for (int f = 0; f < FN; ++f) {
-    int frag = (nb * 2 + wn) * FN + f;
-    frag_live[f] = frag < n_frags;
-    if (!frag_live[f]) frag = n_frags - 1;   // repeats a fragment it does not store
-    fragi[f] = frag;
-    wblk[f] = tiled_block((const T *)a.W0, frag, n_steps, lane);
-  }
-
-  static_assert(kNormSegs == 4, "one float4 per row");
-  auto row_scale = [&](int m) {
-    float r = 1.0f;
-    if (a.row_ss) {
-      const f32x4 ss = *reinterpret_cast<const f32x4 *>(a.row_ss + (size_t)(m < a.Mcap ? m : a.Mcap - 1) * kNormSegs);
-      r = 1.0f / sqrtf((((ss[0] + ss[1]) + ss[2]) + ss[3]) / (float)K + a.ss_eps);
-    }
-    return r * a.out_scale;
-  };
-
-  {
-    // X staging: piece p = tid + 256 i is row p / PPR, 16 bytes at column piece p % PPR of the slice; pieces
-    // past the tile repeat its last row, rows past the block's last row repeat that row (the same cache lines
-    // as the threads that stage it: no further traffic from L2; never stored)
-    const T *xsrc[PIECES];
-    int xdst[PIECES];
-#pragma unroll
-    for (int i = 0; i < PIECES; ++i) {
-      const int p = tid + 256 * i;
-      const int row = min(p / PPR, ROWS - 1), col = p % PPR;
-      xsrc[i] = (const T *)a.X + (size_t)min(m0 + row, M - 1) * KC + col * 8;
-      xdst[i] = row * LDX + col * 8;
-    }
-    u32x4 stage[2][PIECES];
-    auto stage_load = [&](u32x4 (&st)[PIECES], int c) {     // slice c of the matrix (clamped into it)
-      const int cl = min(c, n_slices - 1);
-      const int k0 = cl * KW;
-      const size_t off = (size_t)(k0 / KC) * a.Mcap * KC + k0 % KC;
-#pragma unroll
-      for (int i = 0; i < PIECES; ++i) st[i] = *reinterpret_cast<const u32x4 *>(xsrc[i] + off);
-    };
-    auto stage_store = [&](const u32x4 (&st)[PIECES], int buf) {
-#pragma unroll
-      for (int i = 0; i < PIECES; ++i) *reinterpret_cast<u32x4 *>(xs + (size_t)buf * ROWS * LDX + xdst[i]) = st[i];
-    };
-
-    f32x4 acc[FN][FMW];
-#pragma unroll
-    for (int f = 0; f < FN; ++f)
-#pragma unroll
-      for (int fm = 0; fm < FMW; ++fm) acc[f][fm] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    Frag<T> ring[RING][FN];
-    auto load_w = [&](Frag<T> (&slot)[FN], int t) {         // wave-step t >= 0 is global step c0 * SPS + t (clamped)
-      const int st = min(c0 * SPS + t, n_steps - 1);
-#pragma unroll
-      for (int f = 0; f < FN; ++f) slot[f] = TILED ? load_frag(wblk[f] + (size_t)st * 512) : load_frag_stream(wblk[f] + (size_t)st * 512);
-    };
-
-    // As in the skinny kernel the loop starts one unrolled group (two slices) early with the multiplications
-    // off, so that every trip enters with the same loads outstanding in the same order.
-    const int n_iter = (c1 - c0 + 1) / 2 * 2;
-    for (int ci = -2; ci < n_iter; ci += 2) {
-      const bool warm = ci < 0;
-#pragma unroll
-      for (int cc = 0; cc < 2; ++cc) {
-        const int sl = c0 + ci + cc;                         // slice of this half trip
-        if (!warm) stage_store(stage[cc], cc);
-        __syncthreads();
-        const T *xb = xs + (size_t)cc * ROWS * LDX + (wm * FMW * 16 + li) * LDX + g * 8;
-        // All X fragments of a step are read from LDS in one go: those of the slice's first step right behind
-        // the barrier (the global loads of the next slices are issued while they are on their way), those of
-        // the second step before the first step's MFMAs.  The scheduling barriers keep that order (left alone,
-        // the compiler fetched one fragment at a time and waited for each between the MFMAs).
-        const bool live = !warm && sl < c1;                  // uniform per workgroup
-        Frag<T> xf[SPS][FMW];
-#pragma unroll
-        for (int fm = 0; fm < FMW; ++fm) xf[0][fm] = load_frag(xb + fm * 16 * LDX);
-        __builtin_amdgcn_sched_barrier(0);
-        stage_load(stage[cc], max(sl + 2, c0));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < SPS; ++i) {
-          const int slot = cc * SPS + i;
-          if (i + 1 < SPS) {
-#pragma unroll
-            for (int fm = 0; fm < FMW; ++fm) xf[i + 1][fm] = load_frag(xb + fm * 16 * LDX + (i + 1) * 32);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          if (live && sl * SPS + i < n_steps) {
-#pragma unroll
-            for (int fm = 0; fm < FMW; ++fm)
-#pragma unroll
-              for (int f = 0; f < FN; ++f) mma(acc[f][fm], ring[slot][f], xf[i][fm]);
-          }
-          __builtin_amdgcn_sched_barrier(0);
-          load_w(ring[slot], max((ci + cc) * SPS + i + RING, 0));
-        }
-      }
-    }
-    __syncthreads();                                         // everyone is done with xs
-    float *rs_lds = reinterpret_cast<float *>(smem);         // [ROWS] 1 / rms (times the operand scales) of the tile's rows
-    for (int r = tid; r < ROWS; r += 256) rs_lds[r] = row_scale(m0 + r);
-    __syncthreads();
-
-    const int row0 = wm * FMW * 16 + li;
-    if constexpr (EPI == EPI_QKV) {
-      // q/k/v: the accumulators leave the registers through LDS (every wave its own region, behind the row scales)
-      // and the rotary epilogue takes them back one item at a time.  Unrolled over the registers, the FN * FM / 2
-      // items' table entries and addresses were all live at once and the register allocator answered by storing
-      // every accumulator to scratch memory right where the main loop produces it.
-      f32x4 *dump = reinterpret_cast<f32x4 *>(smem + (ROWS * sizeof(float) + 15) / 16 * 16) + (size_t)wave * (FN * FMW * 64);
-#pragma unroll
-      for (int f = 0; f < FN; ++f)
-#pragma unroll
-        for (int fm = 0; fm < FMW; ++fm) dump[(f * FMW + fm) * 64 + lane] = acc[f][fm];
-#pragma unroll 2
-      for (int idx = 0; idx < FN * FMW; ++idx) {
-        const int f = idx / FMW, fm = idx - f * FMW;
-        const int frag = (nb * 2 + wn) * FN + f;
-        const int row = row0 + fm * 16;
-        if (frag < n_frags) epi_paired<T, EPI>(a, frag, m0 + row, M, g, rs_lds[row], dump[idx * 64 + lane]);   // uniform per wave
-      }
-    } else {
-#pragma unroll
-    for (int fm = 0; fm < FMW; ++fm) {
-      const int row = row0 + fm * 16;                        // row of the tile
-      const int m = m0 + row;
-      const bool live = m < M;
-      if constexpr (PAIRED) {
-        const float rs = rs_lds[row];
-#pragma unroll
-        for (int f = 0; f < FN; ++f)
-          if (frag_live[f]) epi_paired<T, EPI>(a, fragi[f], m, M, g, rs, acc[f][fm]);     // uniform per wave
-      } else if constexpr (EPI == EPI_RESIDUAL) {
-#pragma unroll
-        for (int f = 0; f < FN; ++f)
-          if (live && frag_live[f]) epi_residual(a, ks, m, fragi[f] * 16, g, acc[f][fm]);
-      } else {
-#pragma unroll
-        for (int f = 0; f < FN; f += 2)
-          if (frag_live[f]) {                                // a pair of fragments is live or not as a whole (N % 32 == 0)
-            const int nbase[2] = {fragi[f] * 16, fragi[f + 1] * 16};
-            const f32x4 sums[2] = {acc[f][fm], acc[f + 1][fm]};
-            epi_unembed<2>(a, fragi[f] / 2, m, live, g, rs_lds[row], nbase, sums);
-          }
-      }
-    }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------------------
 // Tiled GEMM (16-bit operands): prefill pieces and wide blocks, where a weight meets enough block rows that the
 // caches, the LDS and the matrix cores bound the call instead of the stream of W.  A workgroup of WM x WN waves owns
 // TM = 32 WM BM block rows and TN = 32 WN BN rows of W; a wave BM x BN blocks of the 32x32x16 MFMA (a loop of nothing
@@ -623,8 +419,6 @@ __device__ __forceinline__ void wave_lds_fence() {       // LDS written by other
 template <int EPI, int WM, int WN, int BM, int BN, int NST, bool NT>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs a, int MT, int tiles, int frag_first, int frag_end) {
   typedef half_t T;
-  static_assert(EPI != EPI_UNEMBED, "the unembedding stays on gemm_wide_kernel");
-  constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
   constexpr int NW = WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN;
   constexpr int KC = KChunk<T>::value, KW = 64;
   constexpr int WI = TN / 8 / NW, XI = TM / 8 / NW;      // DMA instructions (1 KB each) per wave and slice
@@ -750,7 +544,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs 
 
   static_assert(kNormSegs == 4, "one float4 per row");
   float *rs_lds = reinterpret_cast<float *>(smem);       // [TM] 1 / rms times the operand scales
-  if constexpr (PAIRED) {
+  if constexpr (EPI != EPI_RESIDUAL) {
     for (int r = tid; r < TM; r += 64 * NW) {
       float v = 1.0f;
       if (a.row_ss) {
@@ -849,6 +643,38 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs 
       const int row = e / PPR, fr = e % PPR, m = m0 + row;
       if (m < M && f0 + fr < frag_end)
         *reinterpret_cast<u32x4 *>((T *)a.act + act_offset<T>(m, (f0 + fr) * 8, a.Mcap)) = *reinterpret_cast<const u32x4 *>(ot + row * LDO + fr * 8);
+    }
+  } else if constexpr (EPI == EPI_UNEMBED) {
+    // optional logits, and the best (value, id) of a block row over every 32 vocabulary rows; ids ascend with (j, i)
+    // inside a lane, the two lanes of a row hold alternate groups of four
+#pragma unroll
+    for (int b = 0; b < BM; ++b) {
+      const int row = row0 + b * 32, m = m0 + row;
+      const float rs = rs_lds[row];
+#pragma unroll
+      for (int p = 0; p < BN; ++p) {
+        if (fw + 2 * p >= frag_end) continue;            // uniform per wave
+        const int n0 = (fw + 2 * p) * 16 + 4 * h;
+        float bv = kNegBig;
+        int bi = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          f32x4 v;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            v[r] = acc[p][b][4 * j + r] * rs;
+            if (v[r] > bv) { bv = v[r]; bi = n0 + 8 * j + r; }
+          }
+          if (a.logits && m < M) *reinterpret_cast<f32x4 *>(a.logits + (size_t)m * a.N + n0 + 8 * j) = v;
+        }
+        const float ov = other_half(bv);
+        const int oi = __float_as_int(other_half(__int_as_float(bi)));
+        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        if (m < M && h == 0) {
+          a.pmax_val[(size_t)(fw / 2 + p) * a.Mcap + m] = bv;
+          a.pmax_idx[(size_t)(fw / 2 + p) * a.Mcap + m] = bi;
+        }
+      }
     }
   } else {
     // partials: every wave turns its blocks around in LDS of its own and stores whole row segments (stored straight
@@ -963,52 +789,6 @@ static void launch_tile(const GemmArgs &a, hipStream_t s) {
   launch_tile_shape<EPI>(p.shape, a, p.KS, 0, p.split, s);  // residual: p.KS == a.KS (gemm_residual_splits)
   launch_tile_shape<EPI>(p.shape2, a, p.KS, p.split, frags, s);
 }
-// FN: fragments per wave; a workgroup owns 2 FN.  MT: row tiles of 16 FM rows (1: the tile holds the whole block).
-template <typename T, int EPI, int FM, int FN>
-static void launch_wide_cfg(const GemmArgs &a, int KS, int MT, hipStream_t s) {
-  size_t lds = (size_t)2 * 16 * FM * (64 + 8) * sizeof(T);
-  if (EPI == EPI_QKV) lds = std::max(lds, (size_t)(16 * FM * 4 + 15) / 16 * 16 + (size_t)4 * FN * (FM / 2) * 1024);   // accumulator hand-back
-  const int blocks = (a.n_groups + 2 * FN - 1) / (2 * FN);
-  if (lds > 64 * 1024) {
-    static const hipError_t opted = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_wide_kernel<T, EPI, FM, FN, false>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    static const hipError_t opted_t = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_wide_kernel<T, EPI, FM, FN, true>),
-                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    (void)opted; (void)opted_t;
-  }
-  if (MT == 1) hipLaunchKernelGGL((gemm_wide_kernel<T, EPI, FM, FN, false>), dim3(blocks, KS), dim3(256), lds, s, a, 1);
-  else hipLaunchKernelGGL((gemm_wide_kernel<T, EPI, FM, FN, true>), dim3((blocks + 7) / 8 * 8 * MT, KS), dim3(256), lds, s, a, MT);
-}
-
-template <typename T, int FM>
-static void launch_wide_fm(const GemmArgs &a_in, int MT, hipStream_t s) {
-  GemmArgs a = a_in;
-  a.n_groups = a.N / 16;
-  launch_wide_cfg<T, EPI_UNEMBED, FM, 4>(a, 1, MT, s);
-}
-
-// Row tiles of the wide kernel: as few as possible (288 rows at most each), then the smallest even
-// number of 16-row blocks that holds a tile's share of the rows.
-static int gemm_wide_row_tiles(int M) { return (M + 287) / 288; }
-int gemm_wide_row_blocks(int M) {
-  const int tiles = gemm_wide_row_tiles(M);
-  const int rows = (M + tiles - 1) / tiles;
-  const int fm = (rows + 15) / 16;
-  return (fm + 1) / 2 * 2 < 10 ? 10 : (fm + 1) / 2 * 2;
-}
-
-template <typename T>
-static void launch_wide(const GemmArgs &a, hipStream_t s) {
-  const int MT = gemm_wide_row_tiles(a.M);
-  switch (gemm_wide_row_blocks(a.M)) {
-    case 10: launch_wide_fm<T, 10>(a, MT, s); break;
-    case 12: launch_wide_fm<T, 12>(a, MT, s); break;
-    case 14: launch_wide_fm<T, 14>(a, MT, s); break;
-    case 16: launch_wide_fm<T, 16>(a, MT, s); break;
-    default: launch_wide_fm<T, 18>(a, MT, s);
-  }
-}
-
 template <typename T, int EPI, int FM, int WN, int WK, int RING, int FN = 2>
 void launch_gemm_cfg(const GemmArgs &a, int KS, hipStream_t s) {
   constexpr int KC = KChunk<T>::value;
@@ -1113,7 +893,7 @@ static void launch_paired(const GemmArgs &a, hipStream_t s) {
 // half the splits of the contraction, so the RMSNorm that follows adds half the partials.
 static bool residual_narrow(int M, int N, int K) { return M <= 16 || K <= N; }
 
-// Which blocks gemm_tile_kernel takes (16-bit operands; the unembedding never).  Above 128 rows: all.  Up to 128 the
+// Which blocks gemm_tile_kernel takes (16-bit operands).  Above 128 rows: all.  Up to 128 the
 // skinny kernel streams W as fast on wide models (7B shapes, 97 rows: gate/up 49.4 against 47.5-50.6 us, q/k/v 33.8
 // against 35.3; 65 rows: down 26.8 against 29.4) and loses
 //  * where its one or two fragments per workgroup leave CUs idle or too little in flight (768-wide model, 97 rows:
@@ -1124,6 +904,7 @@ static bool residual_narrow(int M, int N, int K) { return M <= 16 || K <= N; }
 //  * on the down projection from about 80 rows (7B, 97 rows: 32.6 -> 28.4), on narrow models from 33 (6.0 -> 5.4 at 51).
 static bool takes_tile(int epi, int M, int frags, int K) {
   if (M > 128) return true;
+  if (epi == EPI_UNEMBED) return false;
   if (epi != EPI_RESIDUAL) return M > 64 && frags <= 512;
   if (K <= frags * 16) return M > 24;
   return M > (frags < 128 ? 48 : 80);
@@ -1150,13 +931,12 @@ template <typename T>
 static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   GemmArgs a = a_in;
   if constexpr (sizeof(T) == 2) {
-    if (epi == EPI_UNEMBED) {
-      if (a.M > 128) { launch_wide<T>(a, s); return; }
-    } else if (takes_tile(epi, a.M, epi == EPI_RESIDUAL ? a.N / 16 : gemm_groups(epi, a), a.K)) {
+    if (takes_tile(epi, a.M, epi == EPI_RESIDUAL || epi == EPI_UNEMBED ? a.N / 16 : gemm_groups(epi, a), a.K)) {
       switch (epi) {
         case EPI_QKV: launch_tile<EPI_QKV>(a, s); break;
         case EPI_GATEUP: launch_tile<EPI_GATEUP>(a, s); break;
-        default: launch_tile<EPI_RESIDUAL>(a, s);
+        case EPI_RESIDUAL: launch_tile<EPI_RESIDUAL>(a, s); break;
+        default: launch_tile<EPI_UNEMBED>(a, s);
       }
       return;
     }
