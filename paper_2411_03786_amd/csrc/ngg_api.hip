@@ -182,7 +182,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     launch_embed(dt, c->w.tok_emb, tok_src ? tok_src : c->hist, c->drafts, c->block_tok, c->h, d.d_model, M,
                  tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev);
   }
-  const int n_splits = attention_splits(dt, d.head_dim, d.n_heads, M, P, c->max_splits);
+  const int n_splits = attention_splits(dt, d.head_dim, d.n_heads, M, P, c->max_splits, from_hist && C > 1);
   c->attn_layout[0] = n_splits; c->attn_layout[1] = attention_workgroups(dt, d.head_dim, d.n_heads, M, n_splits);
   c->attn_layout[2] = M; c->attn_layout[3] = P;
   const int Mpart = (M + 127) / 128 * 128;

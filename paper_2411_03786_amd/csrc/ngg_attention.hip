@@ -312,7 +312,10 @@ __global__ __launch_bounds__(256) void attn_stream_kernel(const AttnArgs a, int 
 }
 
 // Workgroup = (head, list slice, group of 64*QF queries); wave w owns queries q0 + 16*QF*w .. and
-// reads every tile of the slice from the LDS copy.  Grid layout as in attn_stream_kernel.
+// reads every tile of the slice from the LDS copy.  Grid layout as in attn_stream_kernel; where a prefill piece gives every
+// CU two workgroups, every other pair of units takes its query groups in reverse, so that the two workgroups a CU holds
+// are a short causal list and a long one (2048-token piece, 32 heads of 128: 106 -> 95 us).  With a single slice the
+// quotient is the result and no merge follows (21 us for that piece).
 template <typename T, int HD, int QF, bool NT>
 __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, int Z, int n_units) {
   constexpr int DS = HD / 32, DF = HD / 16;
@@ -321,7 +324,8 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
   constexpr int PIECES = TILE * (int)sizeof(T) / 16;        // 16-byte pieces of a K (or V) tile
   constexpr int PPT = (PIECES + 255) / 256;                 // pieces per thread
   const int slot_b = blockIdx.x / 8, xcd = blockIdx.x % 8;
-  const int unit = (slot_b / Z) * 8 + xcd;
+  const int unit_x = slot_b / Z;                            // this XCD's unit_x-th unit
+  const int unit = unit_x * 8 + xcd;
   if (unit >= n_units) return;
   const int S = a.n_splits;
   const int split = unit % S, h = unit / S;
@@ -330,7 +334,8 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 15, g = lane >> 4;
   const int M = a.M, C = a.C, P = a.n_dev ? *a.n_dev - 1 : a.P;
-  const int q0 = (slot_b % Z) * GQ;                         // first query of this workgroup (< M)
+  const int z = (unit_x * Z / 32) & 1 ? Z - 1 - slot_b % Z : slot_b % Z;
+  const int q0 = z * GQ;                                    // first query of this workgroup (< M)
   const int qw = q0 + wv * 16 * QF;                         // first query of this wave
   const bool active = qw < M;
 
@@ -449,18 +454,27 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
   if (active) {
 #pragma unroll
     for (int qf = 0; qf < QF; ++qf) {
+      const int m = qw + qf * 16 + li;
+      const float l = rows_sum(lrun[qf]);                   // the four lanes of a query each held a share of its sum
+      if (S == 1) {                                         // the whole list: the quotient is the result, nothing to merge
+        const float inv = 1.0f / l;
+        if (m < M)
+#pragma unroll
+          for (int df = 0; df < DF; ++df)
+            store4((T *)a.out + act_offset<T>(m, h * HD + df * 16 + 4 * g, a.Mcap), O[qf][df][0] * inv, O[qf][df][1] * inv,
+                   O[qf][df][2] * inv, O[qf][df][3] * inv);
+        continue;
+      }
       // partial outputs keep the fragment order, [head][slice][16-query group][df][lane][4]
       const size_t blk = ((size_t)h * S + split) * (a.Mpart / 16) + (qw / 16 + qf);
 #pragma unroll
       for (int df = 0; df < DF; ++df)
         *reinterpret_cast<float4 *>(a.part_o + ((blk * DF + df) * 64 + lane) * 4) =
             float4{O[qf][df][0], O[qf][df][1], O[qf][df][2], O[qf][df][3]};
-      const int m = qw + qf * 16 + li;
-      const float l = rows_sum(lrun[qf]);                   // the four lanes of a query each held a share of its sum
       if (m < M && g == 0) {
-        const size_t slot = ((size_t)h * S + split) * a.Mpart + m;
-        a.part_ml[slot * 2 + 0] = mrun[qf];
-        a.part_ml[slot * 2 + 1] = l;
+        const size_t slot_m = ((size_t)h * S + split) * a.Mpart + m;
+        a.part_ml[slot_m * 2 + 0] = mrun[qf];
+        a.part_ml[slot_m * 2 + 1] = l;
       }
     }
   }
@@ -546,17 +560,20 @@ static void launch_hd(const AttnArgs &a, hipStream_t s) {
   else if (a.M <= 64 || attn_shared_qmax<T, HD>() == 1) launch_shared<T, HD, 1>(a, s);
   else launch_shared<T, HD, attn_shared_qmax<T, HD>()>(a, s);
   if (a.one_row) return;                                    // the output projection merges the slices
+  if (a.M > 16 && a.n_splits == 1) return;                  // attn_shared_kernel wrote the result itself
   hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);
 }
 
 // Number of list slices per head: one workgroup per CU in total; two per CU for blocks of more than
 // 64 tokens once every slice still has 16 tiles (measured at a 16K context: 74 -> 69 us; everywhere
-// else one per CU was as fast or faster); never fewer than 4 tiles per slice.
-int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits) {
+// else one per CU was as fast or faster); never fewer than 4 tiles per slice.  causal: the block is a piece of a prompt,
+// whose own tiles count too, half of them for the average query (777 tokens, 12 heads of 64: 84 workgroups of up to 25
+// tiles took 27 us, three slices take 14.5 + 4.2 for the merge).
+int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, bool causal) {
   const int qmax = dtype == 1 || hd <= 64 ? 2 : 1;
   const int per_wg = M <= 16 ? 16 : (M <= 64 ? 64 : 64 * qmax);
   const int Z = (M + per_wg - 1) / per_wg;
-  const int tiles = (P + 31) / 32 + 1;
+  const int tiles = (P + 31) / 32 + 1 + (causal ? (M + 31) / 64 : 0);
   const int one = 256 / (H * Z), two = M > 64 ? 512 / (H * Z) : one;
   int s = tiles / 16 > one ? tiles / 16 : one;
   s = s < two ? s : two;
