@@ -89,6 +89,9 @@ struct ngg_ctx {
   float unemb_scale = 1.0f;        // the operand-order copy of the output embedding holds the stored values times this
   float emb_scale = 1.0f;          // rows of the input embedding are multiplied by this when they become a 16-bit operand
   int32_t *res_host = nullptr;     // pinned
+  int32_t *drafts_host = nullptr;  // pinned copy of the drafts buffer: drafts, n_ctx (4 words), row_src
+  int drafts_words = 0;            // words of the drafts in front of n_ctx
+  size_t drafts_bytes = 0;
   // host state
   std::vector<int32_t> tokens;     // committed history mirror
   int n = 0;                       // context length (0 = no prefill yet)
@@ -423,14 +426,15 @@ const char *ngg_last_error(const ngg_ctx *ctx) { return ctx ? ctx->err.c_str() :
 ngg_status ngg_destroy(ngg_ctx *c) {
   if (!c) return NGG_EINVAL;
   (void)hipStreamSynchronize(c->stream);
-  void *bufs[] = {c->hist, c->drafts, c->block_tok, c->res, c->next1, c->mlist, c->reps, c->gtab, c->ctx_rows, c->n_ctx,
-                  c->row_src, c->hpart, c->wtiled, c->cand_val, c->cand_idx, c->kcache, c->vcache, c->kscr, c->vscr, c->h, c->part_o, c->part_ml, c->pmax_val, c->z,
+  void *bufs[] = {c->hist, c->drafts, c->block_tok, c->res, c->next1, c->mlist, c->reps, c->gtab, c->ctx_rows,
+                  c->hpart, c->wtiled, c->cand_val, c->cand_idx, c->kcache, c->vcache, c->kscr, c->vscr, c->h, c->part_o, c->part_ml, c->pmax_val, c->z,
                   c->logits, c->rope_cos, c->rope_sin, c->pmax_idx, c->xn, c->q, c->attn, c->act, c->bg_table, c->bg_tok, c->uni_top, c->row_ss, c->n_dev};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   if (c->step_graph) (void)hipGraphExecDestroy(c->step_graph);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
   if (c->res_host) (void)hipHostFree(c->res_host);
+  if (c->drafts_host) (void)hipHostFree(c->drafts_host);
   for (auto &sp : c->spans) { (void)hipEventDestroy(sp.e0); (void)hipEventDestroy(sp.e1); }
   for (auto e : c->free_events) (void)hipEventDestroy(e);
   delete c;
@@ -485,7 +489,11 @@ ngg_status ngg_create(const ngg_model_desc *desc, const ngg_weights *weights, vo
   ngg_status st = NGG_OK;
 #define TRY(x) do { if (st == NGG_OK) st = (x); } while (0)
   TRY(dev_alloc(c, &c->hist, (size_t)c->Spad * 4, true));
-  TRY(dev_alloc(c, &c->drafts, (size_t)d.max_k * std::max(1, d.max_w) * 4, true));
+  // drafts, number of context rows (4 words) and row sources in one buffer: the caller's copies take one transfer
+  c->drafts_words = d.max_k * std::max(1, d.max_w);
+  c->drafts_bytes = (size_t)(c->drafts_words + 4) * 4 + rup((size_t)d.max_k, 4);
+  TRY(dev_alloc(c, &c->drafts, c->drafts_bytes, true));
+  if (st == NGG_OK) { c->n_ctx = c->drafts + c->drafts_words; c->row_src = (int8_t *)(c->n_ctx + 4); }
   TRY(dev_alloc(c, &c->block_tok, (size_t)c->Mcap * 4, true));
   TRY(dev_alloc(c, &c->res, (size_t)(res_greedy_off(d.max_k) + c->Mcap) * 4, true));
   TRY(dev_alloc(c, &c->next1, (size_t)d.vocab * 4, true));
@@ -495,8 +503,6 @@ ngg_status ngg_create(const ngg_model_desc *desc, const ngg_weights *weights, vo
   while (c->gtab_slots < 2 * c->Spad) c->gtab_slots <<= 1;
   TRY(dev_alloc(c, &c->gtab, (size_t)3 * c->gtab_slots * 4, true));
   TRY(dev_alloc(c, &c->ctx_rows, (size_t)d.max_k * std::max(1, d.max_w) * 4, true));
-  TRY(dev_alloc(c, &c->n_ctx, 16, true));
-  TRY(dev_alloc(c, &c->row_src, (size_t)d.max_k, true));
   TRY(dev_alloc(c, &c->kcache, kv_elems * c->Spad * c->esize, true));
   TRY(dev_alloc(c, &c->vcache, kv_elems * c->Spad * c->esize, true));
   TRY(dev_alloc(c, &c->kscr, kv_elems * c->Mcap * c->esize, true));
@@ -524,6 +530,8 @@ ngg_status ngg_create(const ngg_model_desc *desc, const ngg_weights *weights, vo
   TRY(dev_alloc(c, &c->rope_cos, (size_t)c->Spad * half * 4, false));
   TRY(dev_alloc(c, &c->rope_sin, (size_t)c->Spad * half * 4, false));
 #undef TRY
+  if (st == NGG_OK && hipHostMalloc((void **)&c->drafts_host, c->drafts_bytes) != hipSuccess)
+    st = fail(c, NGG_ENOMEM, "ngg_create: hipHostMalloc failed");
   if (st == NGG_OK && hipHostMalloc((void **)&c->res_host, (size_t)(res_greedy_off(d.max_k) + c->Mcap) * 4) != hipSuccess)
     st = fail(c, NGG_ENOMEM, "ngg_create: hipHostMalloc failed");
   if (st == NGG_OK) {
@@ -620,10 +628,12 @@ ngg_status ngg_build_drafts(ngg_ctx *c, const ngg_draft_cfg *cfg, int32_t *draft
   c->drafts_k = cfg->k;
   c->drafts_w = cfg->w;
   if (drafts || row_src || n_ctx_rows) {
-    if (drafts && cfg->w > 0) NGG_HIP(c, hipMemcpyAsync(drafts, c->drafts, (size_t)cfg->k * cfg->w * 4, hipMemcpyDeviceToHost, c->stream));
-    if (row_src) NGG_HIP(c, hipMemcpyAsync(row_src, c->row_src, (size_t)cfg->k, hipMemcpyDeviceToHost, c->stream));
-    if (n_ctx_rows) NGG_HIP(c, hipMemcpyAsync(n_ctx_rows, c->n_ctx, 4, hipMemcpyDeviceToHost, c->stream));
+    // one transfer to pinned memory (three to the caller's pageable buffers, each waited for by the runtime: 25 us more)
+    NGG_HIP(c, hipMemcpyAsync(c->drafts_host, c->drafts, c->drafts_bytes, hipMemcpyDeviceToHost, c->stream));
     NGG_HIP(c, hipStreamSynchronize(c->stream));
+    if (drafts && cfg->w > 0) memcpy(drafts, c->drafts_host, (size_t)cfg->k * cfg->w * 4);
+    if (row_src) memcpy(row_src, c->drafts_host + c->drafts_words + 4, (size_t)cfg->k);
+    if (n_ctx_rows) *n_ctx_rows = c->drafts_host[c->drafts_words];
   }
   return NGG_OK;
 }

@@ -432,10 +432,52 @@ __global__ __launch_bounds__(1024) void ctx_match_kernel(const DraftArgs a) {
 // ---------------------------------------------------------------------------------------------
 constexpr int kGemvBlocks = 256;     // workgroups of the bigram sweep; each keeps its own top-k candidates
 constexpr int kCandStride = 32;      // candidate slots per workgroup (k <= 32)
-constexpr int kGemvRing = 8;
+constexpr int kGemvRing = 16;      // 64 KB per CU on their way (8: 134 us at V = 128256, d = 3072)
 
 __device__ __forceinline__ bool ranks_before(float v, int i, float ov, int oi) {   // (value desc, id asc)
   return v > ov || (v == ov && i < oi);
+}
+
+// Maximum over the 64 lanes, in every lane: four steps inside the rows of 16 lanes on the vector unit's own lane moves
+// (quad permutes and row rotations), two row swaps; a shuffle per step would cost an LDS round trip each.
+__device__ __forceinline__ float wave_max(float x) {
+#define NGG_DPP_MAX(ctrl) x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), ctrl, 0xf, 0xf, true)))
+  NGG_DPP_MAX(0xB1);                                         // quad_perm [1, 0, 3, 2]
+  NGG_DPP_MAX(0x4E);                                         // quad_perm [2, 3, 0, 1]
+  NGG_DPP_MAX(0x124);                                        // row_ror:4
+  NGG_DPP_MAX(0x128);                                        // row_ror:8
+#undef NGG_DPP_MAX
+  return rows_max(x);
+}
+
+// The wave's best `rounds` of the N (value, id) slots every lane holds, by (value desc, id asc), handed to put(rank, value,
+// id) in lane 0; unused slots hold (kNegBig, 0x7fffffff).  A round takes the maximum of the lanes' own best slots; only
+// the lane that owned it looks for its next one.  (Shuffling (value, id) pairs through six steps per round: 18 us for the
+// kernel that picks 10 of 2560 in two levels.)
+template <int N, typename Put>
+__device__ __forceinline__ void wave_best(const float (&v)[N], const int (&id)[N], int rounds, int lane, Put put) {
+  float bv = kNegBig;
+  int bi = 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+    if (ranks_before(v[j], id[j], bv, bi)) { bv = v[j]; bi = id[j]; }
+  for (int r = 0; r < rounds; ++r) {
+    const float m = wave_max(bv);
+    unsigned long long who = __ballot(bv == m);
+    int wid = __builtin_amdgcn_readlane(bi, __builtin_ctzll(who));
+    if (m > kNegBig)                                         // (else every slot is taken)
+      for (who &= who - 1; who; who &= who - 1) wid = min(wid, __builtin_amdgcn_readlane(bi, __builtin_ctzll(who)));   // equal values: lowest id
+    if (lane == 0) put(r, m, wid);
+    if (bv == m && bi == wid) {                              // the owner (ids are unique; exhausted lanes hold no slot) moves on
+      const float lv = bv;
+      const int lid = bi;
+      bv = kNegBig;
+      bi = 0x7fffffff;
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (ranks_before(lv, lid, v[j], id[j]) && ranks_before(v[j], id[j], bv, bi)) { bv = v[j]; bi = id[j]; }
+    }
+  }
 }
 
 template <typename U, typename T>
@@ -445,10 +487,6 @@ __global__ __launch_bounds__(256) void bigram_gemv_kernel(const U *tok_emb, cons
   extern __shared__ __attribute__((aligned(16))) unsigned char gemv_smem[];
   T *es = reinterpret_cast<T *>(gemv_smem);                  // [d] embedding of x_last (times emb_scale, internal type)
   float *zs = reinterpret_cast<float *>(gemv_smem + (size_t)d * sizeof(T));   // this block's scores
-  if (n_dev) n = *n_dev;
-  const int x = hist[n - 1];
-  for (int i = threadIdx.x; i < d; i += 256) es[i] = from_f32<T>(to_f32(tok_emb[(size_t)x * d + i]) * emb_scale);
-  __syncthreads();
   const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_steps = d / 32, n_groups = vocab / 16;
@@ -466,6 +504,11 @@ __global__ __launch_bounds__(256) void bigram_gemv_kernel(const U *tok_emb, cons
   Frag<T> ring[kGemvRing];
 #pragma unroll
   for (int u = 0; u < kGemvRing; ++u) ring[u] = next_frag();
+  // the embedding of the last token, fetched (three dependent loads) while the first scores' weights are on their way
+  if (n_dev) n = *n_dev;
+  const int x = hist[n - 1];
+  for (int i = threadIdx.x; i < d; i += 256) es[i] = from_f32<T>(to_f32(tok_emb[(size_t)x * d + i]) * emb_scale);
+  __syncthreads();
   f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
   int s = 0, gi = 0;                                        // step inside the current group, group counter
   for (int t0 = 0; t0 < total; t0 += kGemvRing) {
@@ -491,33 +534,34 @@ __global__ __launch_bounds__(256) void bigram_gemv_kernel(const U *tok_emb, cons
     }
   }
   __syncthreads();
-  // this workgroup's ksel best scores, by (value desc, id asc): wave 0 pulls them out one by one; an entry
-  // is "still in" when it ranks strictly after the last one taken
+  // This workgroup's ksel best scores, by (value desc, id asc).  Wave 0 takes the scores 512 at a time, eight per lane, and
+  // carries the best of the earlier ones along as one more slot per lane.
   if (wave == 0) {
     const int cnt = max(0, g1 - g0) * 16;
-    float last_v = 0.0f;
-    int last_i = -1;
-    for (int r = 0; r < ksel; ++r) {
-      float bv = kNegBig;
-      int bi = 0x7fffffff;
-      for (int j = lane; j < cnt; j += 64) {
-        const float v = zs[j];
-        const int id = g0 * 16 + j;
-        if (r > 0 && !ranks_before(last_v, last_i, v, id)) continue;      // already taken
-        if (ranks_before(v, id, bv, bi)) { bv = v; bi = id; }
-      }
+    float keep_v = kNegBig;                                  // lane r: the r-th best so far
+    int keep_i = 0x7fffffff;
+    for (int j0 = 0; j0 == 0 || j0 < cnt; j0 += 512) {
+      float v[9];
+      int id[9];
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const float ov = __shfl_xor(bv, off);
-        const int oi = __shfl_xor(bi, off);
-        if (ranks_before(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+      for (int u = 0; u < 8; ++u) {
+        const int j = j0 + u * 64 + lane;
+        v[u] = j < cnt ? zs[j] : kNegBig;
+        id[u] = j < cnt ? g0 * 16 + j : 0x7fffffff;
       }
-      if (lane == 0) {
-        cand_val[blockIdx.x * kCandStride + r] = bv;         // (kNegBig, INT_MAX) once the block ran out
-        cand_idx[blockIdx.x * kCandStride + r] = bi;
-      }
-      last_v = bv;
-      last_i = bi;
+      v[8] = keep_v;
+      id[8] = keep_i;
+      float nv = kNegBig;
+      int ni = 0x7fffffff;
+      wave_best<9>(v, id, ksel, 0, [&](int r, float bv, int bi) {   // (lane 0 for every lane: the pick is uniform)
+        if (lane == r) { nv = bv; ni = bi; }
+      });
+      keep_v = nv;
+      keep_i = ni;
+    }
+    if (lane < ksel) {
+      cand_val[blockIdx.x * kCandStride + lane] = keep_v;    // (kNegBig, INT_MAX) once the block ran out
+      cand_idx[blockIdx.x * kCandStride + lane] = keep_i;
     }
   }
 }
@@ -574,9 +618,8 @@ void launch_tile_weights(int dtype, const void *src, void *dst, int N, int K, in
 
 // Top-(k - n_ctx) of z by (score desc, id asc), chained extension through next1, and assembly of
 // the k x w draft batch (Section 4.3: context rows first, the extended bigram fills the rest).
-// Selection in two levels without a barrier per rank: every wave ranks its own 512 candidate slots
-// (round r takes the best candidate that ranks after the wave's previous pick), then wave 0 ranks
-// the 16 waves' survivors the same way.
+// Selection in two levels without a barrier per rank: every wave ranks its own 512 candidate slots (wave_best), then
+// wave 0 ranks the 16 waves' survivors the same way.
 __global__ __launch_bounds__(1024) void topk_assemble_kernel(const DraftArgs a) {
   constexpr int NWAVE = 16;
   __shared__ float wv[NWAVE * kCandStride];
@@ -587,21 +630,6 @@ __global__ __launch_bounds__(1024) void topk_assemble_kernel(const DraftArgs a) 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_ctx = *a.n_ctx;
   const int k_big = a.w >= 1 ? a.k - n_ctx : 0;
-  // best of n values per lane that rank after (last_v, last_i), over the wave
-  auto wave_pick = [&](const float *v, const int *id, int n, bool first, float last_v, int last_i, float &bv, int &bi) {
-    bv = kNegBig;
-    bi = 0x7fffffff;
-    for (int j = 0; j < n; ++j) {
-      const bool in = first || ranks_before(last_v, last_i, v[j], id[j]);
-      if (in && ranks_before(v[j], id[j], bv, bi)) { bv = v[j]; bi = id[j]; }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const float ov = __shfl_xor(bv, off);
-      const int oi = __shfl_xor(bi, off);
-      if (ranks_before(ov, oi, bv, bi)) { bv = ov; bi = oi; }
-    }
-  };
   if (k_big > 0) {
     // the candidates every workgroup of the sweep kept (its own top-k): the global top-k is among them
     float cv[CPT];
@@ -613,16 +641,10 @@ __global__ __launch_bounds__(1024) void topk_assemble_kernel(const DraftArgs a) 
       cv[j] = used ? a.cand_val[slot] : kNegBig;
       ci[j] = used ? a.cand_idx[slot] : 0x7fffffff;
     }
-    float last_v = 0.0f;
-    int last_i = -1;
-    for (int r = 0; r < k_big; ++r) {
-      float bv;
-      int bi;
-      wave_pick(cv, ci, CPT, r == 0, last_v, last_i, bv, bi);
-      last_v = bv;
-      last_i = bi;
-      if (lane == 0) { wv[wave * kCandStride + r] = bv; wi[wave * kCandStride + r] = bi; }
-    }
+    wave_best<CPT>(cv, ci, k_big, lane, [&](int r, float bv, int bi) {
+      wv[wave * kCandStride + r] = bv;
+      wi[wave * kCandStride + r] = bi;
+    });
   }
   __syncthreads();
   if (wave == 0 && k_big > 0) {
@@ -635,16 +657,7 @@ __global__ __launch_bounds__(1024) void topk_assemble_kernel(const DraftArgs a) 
       sv[j] = used ? wv[e] : kNegBig;
       si[j] = used ? wi[e] : 0x7fffffff;
     }
-    float last_v = 0.0f;
-    int last_i = -1;
-    for (int r = 0; r < k_big; ++r) {
-      float bv;
-      int bi;
-      wave_pick(sv, si, SPL, r == 0, last_v, last_i, bv, bi);
-      last_v = bv;
-      last_i = bi;
-      if (lane == 0) top[r] = bi;
-    }
+    wave_best<SPL>(sv, si, k_big, lane, [&](int r, float, int bi) { top[r] = bi; });
   }
   __syncthreads();
   if (tid < a.k && a.w >= 1) {
