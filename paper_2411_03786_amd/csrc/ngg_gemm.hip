@@ -893,34 +893,43 @@ static void launch_paired(const GemmArgs &a, hipStream_t s) {
 // half the splits of the contraction, so the RMSNorm that follows adds half the partials.
 static bool residual_narrow(int M, int N, int K) { return M <= 16 || K <= N; }
 
-// Which blocks gemm_tile_kernel takes (16-bit operands).  Above 128 rows: all.  Up to 128 the
-// skinny kernel streams W as fast on wide models (7B shapes, 97 rows: gate/up 49.4 against 47.5-50.6 us, q/k/v 33.8
-// against 35.3; 65 rows: down 26.8 against 29.4) and loses
-//  * where its one or two fragments per workgroup leave CUs idle or too little in flight (768-wide model, 97 rows:
-//    gate/up 9.6 -> 7.1 us, q/k/v 9.9 -> 8.0, down 8.4 -> 5.3; 65 rows: 8.0 -> 7.1, 8.3 -> 8.0, 7.1 -> 5.2; 51 rows:
-//    gate/up 7.0 against 7.4, q/k/v 6.7 against 8.2);
-//  * on the square output projection, whose split contraction it reads X for twice as often (7B: 16.7 -> 12.8 us at 97
-//    rows, 11.0 -> 9.4 at 51, 9.7 -> 9.0 at 33, 8.4 against 8.8 at 17; 768 wide: 9.1 -> 4.0, 6.6 -> 4.2, 5.7 -> 4.1, 4.9 -> 4.0);
-//  * on the down projection from about 80 rows (7B, 97 rows: 32.6 -> 28.4), on narrow models from 33 (6.0 -> 5.4 at 51).
-static bool takes_tile(int epi, int M, int frags, int K) {
-  if (M > 128) return true;
-  if (epi == EPI_UNEMBED) return false;
-  if (epi != EPI_RESIDUAL) return M > 64 && frags <= 512;
-  if (K <= frags * 16) return M > 24;
-  return M > (frags < 128 ? 48 : 80);
-}
-
-// Split of the contraction across workgroups for the residual GEMMs: about one workgroup per CU, as
-// long as each split keeps at least 2 chunks.
-int gemm_residual_splits(int dtype, int M, int N, int K) {
-  if (dtype == 1 && takes_tile(EPI_RESIDUAL, M, N / 16, K)) return tile_plan(EPI_RESIDUAL, M, N / 16, K).KS;
-  const int kc = dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value;
+// Workgroups of the skinny kernel for a residual GEMM: about one per CU, as long as each split keeps at least 2 chunks.
+static int skinny_residual_blocks(int M, int N, int K) { return residual_narrow(M, N, K) ? N / 32 : (N / 32 + 1) / 2; }
+static int skinny_residual_splits(int kc, int M, int N, int K) {
   const int n_chunks = (K + kc - 1) / kc;
-  const int blocks = residual_narrow(M, N, K) ? N / 32 : (N / 32 + 1) / 2;
+  const int blocks = skinny_residual_blocks(M, N, K);
   int ks = (256 + blocks - 1) / blocks;
   ks = ks > kMaxResidualSplits ? kMaxResidualSplits : ks;
   while (ks > 1 && n_chunks / ks < 2) --ks;
   return ks < 1 ? 1 : ks;
+}
+
+// Which blocks gemm_tile_kernel takes (16-bit operands).  Above 128 rows: all.  Up to 128, measured on MI355X (skinny ->
+// tiled, us, at 17 / 33 / 51 / 64-65 / 97 rows):
+//  * residual GEMMs.  The tiled kernel reads X once per 64 columns of W instead of 32 and splits the contraction where that
+//    fills the chip: output projection 4096 x 4096 8.4 -> 8.8 / 9.7 -> 9.0 / 11.0 -> 9.4 / 13.6 -> 12.2 / 16.7 -> 12.8, 768 x 768
+//    4.9 -> 4.0 / 5.7 -> 4.1 / 6.6 -> 4.2 / 7.5 -> 3.9 / 9.1 -> 4.0; down 4096 x 14336 20.8 -> 21.6 / 21.8 -> 22.0 / 23.6 -> 22.8 /
+//    26.8 -> 27.4 / 32.6 -> 28.4, 2048 x 5504 7.6 -> 7.7 / 8.5 -> 8.0 / 9.8 -> 8.1 / 9.9 -> 8.4 / 12.8 -> 10.1.  Where the skinny
+//    kernel's workgroups come to more than one per CU the second round costs it most (3072-wide, 288 workgroups: down
+//    16.2 -> 11.7 / 17.7 -> 11.8 / 19.4 -> 12.0 / 20.2 -> 12.3 / 28.3 -> 16.4, projection 8.1 -> 6.9 / 9.8 -> 7.1 / 11.4 -> 7.2).
+//  * gate/up and q/k/v of 65 rows or more on narrow models, where one or two fragments per workgroup leave too little in
+//    flight (768-wide, 97 rows: 9.6 -> 7.1 and 9.9 -> 8.0; 65 rows 8.0 -> 7.1, 8.3 -> 8.0); wide models stream W as fast
+//    either way (4096-wide, 97 rows: 49.4 and 47.5-50.6, 33.8 and 35.3).
+//  * up to 64 rows where 64 x 64 tiles make one full round (14/16 of the CUs at least): 1024 fragments 19.4 -> 18.6 /
+//    20.2 -> 19.2 / 21.6 -> 19.3 / 21.8 -> 20.0; 688 fragments 11.5 against 12.7 at 33 rows, 768 fragments 23.0 against 24.7 at 51.
+static bool takes_tile(int epi, int M, int frags, int K) {
+  if (M > 128) return true;
+  if (epi == EPI_UNEMBED || M <= 16) return false;
+  if (epi != EPI_RESIDUAL) return M > 64 ? frags <= 512 : (frags > 896 && frags <= 1024);
+  const int N = frags * 16;
+  if (skinny_residual_blocks(M, N, K) * skinny_residual_splits(KChunk<half_t>::value, M, N, K) > 256) return true;
+  return M > 24 && !(K > N && frags >= 256 && M > 64 && M <= 80);
+}
+
+// Split of the contraction across workgroups for the residual GEMMs
+int gemm_residual_splits(int dtype, int M, int N, int K) {
+  if (dtype == 1 && takes_tile(EPI_RESIDUAL, M, N / 16, K)) return tile_plan(EPI_RESIDUAL, M, N / 16, K).KS;
+  return skinny_residual_splits(dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value, M, N, K);
 }
 
 // Workgroup shapes measured on MI355X at the 7B shapes (M = 60 and M = 1).  Unembedding: wide tiles
