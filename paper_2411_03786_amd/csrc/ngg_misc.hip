@@ -775,37 +775,29 @@ __global__ __launch_bounds__(256) void argmax_reduce_kernel(const float *__restr
   }
 }
 
-// (the grid and the drafts come to LDS in one round of loads: compared in place, every column of a row and every row of
-// the winner search waited for the memory in turn, 5 us at k = 10 and 7 us at k = 24)
-__global__ __launch_bounds__(256) void accept_kernel(int k, int C, const int32_t *drafts, const int8_t *row_src,
-                                                     const int32_t *n_ctx, int32_t *res, int greedy_off) {
-  constexpr int MAXK = 32, MAXC = 33;                        // ngg_create: max_k <= 32, max_w <= 32
-  __shared__ int32_t gs[MAXK * MAXC], ds[MAXK * MAXC], acc_s[MAXK];
-  const int tid = threadIdx.x, w = C - 1;
+__global__ __launch_bounds__(64) void accept_kernel(int k, int C, const int32_t *drafts, const int8_t *row_src,
+                                                    const int32_t *n_ctx, int32_t *res, int greedy_off) {
+  const int tid = threadIdx.x;
   const int32_t *greedy = res + greedy_off;
-  for (int i = tid; i < k * C; i += 256) gs[i] = greedy[i];
-  for (int i = tid; i < k * w; i += 256) ds[i] = drafts[i];
-  const int src = tid < k ? row_src[tid] : 0;
-  const int nc = *n_ctx;
-  __syncthreads();
-  if (tid < k) {
+  const int w = C - 1;
+  for (int r = tid; r < k; r += 64) {
     int acc = 0;
-    while (acc < w && ds[tid * w + acc] == gs[tid * C + acc]) ++acc;
-    acc_s[tid] = acc;
-    res[RES_ACCEPT + tid] = acc;
+    while (acc < w && drafts[r * w + acc] == greedy[r * C + acc]) ++acc;
+    res[RES_ACCEPT + r] = acc;
   }
   __syncthreads();
-  int win = 0, best = acc_s[0];                              // every thread: the lowest row with the longest prefix
-  for (int r = 1; r < k; ++r)
-    if (acc_s[r] > best) { best = acc_s[r]; win = r; }
-  if (tid < best) res[RES_NEWTOK + tid] = ds[win * w + tid];
-  else if (tid == best) res[RES_NEWTOK + tid] = gs[win * C + tid];
-  if (tid == win) res[RES_WINSRC] = src;
   if (tid == 0) {
+    int win = 0, best = res[RES_ACCEPT];
+    for (int r = 1; r < k; ++r)
+      if (res[RES_ACCEPT + r] > best) { best = res[RES_ACCEPT + r]; win = r; }
     res[RES_WINNER] = win;
     res[RES_NACCEPT] = best;
     res[RES_NNEW] = best + 1;
-    res[RES_NCTX] = nc;                                      // what the draft builder left about these rows travels with the result
+    for (int i = 0; i < best; ++i) res[RES_NEWTOK + i] = drafts[win * w + i];
+    res[RES_NEWTOK + best] = greedy[win * C + best];
+    // what the draft builder left about these rows travels with the result
+    res[RES_NCTX] = *n_ctx;
+    res[RES_WINSRC] = row_src[win];
   }
 }
 
@@ -814,7 +806,7 @@ void launch_argmax_accept(const float *pmax_val, const int *pmax_idx, int tiles,
                           hipStream_t s) {
   hipLaunchKernelGGL(argmax_reduce_kernel, dim3(rows * C), dim3(256), 0, s, pmax_val, pmax_idx, tiles, Mcap, res + greedy_off, C,
                      shared0);
-  if (k > 0) hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(256), 0, s, k, C, drafts, row_src, n_ctx, res, greedy_off);
+  if (k > 0) hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(64), 0, s, k, C, drafts, row_src, n_ctx, res, greedy_off);
 }
 
 void launch_next1_finish(const float *pmax_val, const int *pmax_idx, int tiles, int Mcap, int M, int32_t *next1_out,
