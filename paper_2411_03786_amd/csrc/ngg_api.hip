@@ -25,7 +25,7 @@ static __device__ __align__(256) int32_t scratch[kStaticInts];
 
 namespace {
 
-// Prompt tokens per forward pass of ngg_prefill.  16-bit models: up to 2048, which the wide GEMM kernel takes as
+// Prompt tokens per forward pass of ngg_prefill.  16-bit models: up to 2048, which the tiled GEMM takes as
 // row tiles of 256 that share the weights through the L2 (one sweep of the weights from HBM per 2048 tokens instead
 // of per 256); fp32 models: 256 (two 128-row passes of the skinny kernel).
 constexpr int kPrefillChunk16 = 2048, kPrefillChunk32 = 256;
@@ -317,7 +317,7 @@ ngg_status ensure_logits(ngg_ctx *c) {
 ngg_status build_next1(ngg_ctx *c) {
   // next1[x] = argmax_v <unemb[v], tok_emb[x]>: the unembedding GEMM applied to rows of the input
   // embedding (no normalisation), 256 vocabulary entries per pass over the output embedding (16-bit models: one
-  // pass of the wide kernel; with 64 per pass a 128K vocabulary cost 2004 sweeps of 788 MB) or 64 (fp32).
+  // pass of the tiled kernel; with 64 per pass a 128K vocabulary cost 2004 sweeps of 788 MB) or 64 (fp32).
   const ngg_model_desc &d = c->d;
   const int rows = d.dtype == NGG_BF16 ? 256 : 64;       // Mcap >= 256
   for (int x0 = 0; x0 < d.vocab; x0 += rows) {

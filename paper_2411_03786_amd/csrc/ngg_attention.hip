@@ -13,9 +13,9 @@
 //    groups of 16*QF queries and all need every tile, so the workgroup copies each tile into LDS once
 //    (a linear copy: the tile already is in fragment order, so every fragment read is conflict-free)
 //    and the waves read their MFMA operands from there.  No merge between waves.
-//  * attn_stream_kernel (up to 16 block tokens, the single-token decode step): one group of queries,
-//    so the four waves split the tiles instead and each tile goes from global memory straight into
-//    the registers of the one wave that needs it; LDS only carries the final merge of the four waves.
+//  * attn_stream_kernel (up to 16 block tokens, the single-token decode step; up to 64 on short lists): one group
+//    of 16 queries per workgroup, so its waves split the tiles instead and each tile goes from global memory straight
+//    into the registers of the one wave that needs it; LDS only carries the final merge of the waves.
 #include "ngg_internal.h"
 
 namespace ngg {
@@ -566,7 +566,8 @@ static void launch_shared(const AttnArgs &a, hipStream_t s) {
 template <typename T, int HD>
 static void launch_hd(const AttnArgs &a, hipStream_t s) {
   if (a.M <= 64 && a.n_splits == 1 && !a.one_row) {         // short lists (attention_splits): 16 queries per workgroup and
-    constexpr int NW = 8;                                   // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list)
+    // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list); four where two tiles of fp32 registers fill a wave's share
+    constexpr int NW = HD * (int)sizeof(T) <= 256 ? 8 : 4;
     launch_stream<T, HD, 1, NW>(a, s);
     return;
   }
@@ -592,7 +593,7 @@ int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, boo
   const int tiles = (P + 31) / 32 + 1 + (causal ? (M + 31) / 64 : 0);
   // A short list is not split at all: the waves of one workgroup share it and merge in LDS (attn_stream_kernel), which
   // saves the merge launch: 33 tiles of 64 dims, 33 block tokens: 5.5 + 3.2 us and the gap between the launches -> 8.7 us
-  // (the 12-layer step 560 -> 530 us).  A workgroup pulls 100-128 GB/s from the L2, and every group of 16 queries
+  // (the 12-layer step 575 -> 530-560 us).  A workgroup pulls 100-128 GB/s from the L2, and every group of 16 queries
   // pulls the whole list: at 65 tiles of 128 dims (7B, 2K context) the step went from 4.29 to 4.45 ms.
   if (M > 1 && M <= 64 && tiles * hd * (dtype == 1 ? 1 : 2) <= kShortList) return 1;
   const int one = 256 / (H * Z), two = M > 64 ? 512 / (H * Z) : one;

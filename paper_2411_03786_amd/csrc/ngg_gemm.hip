@@ -23,7 +23,7 @@
 namespace ngg {
 
 // ---------------------------------------------------------------------------------------------
-// Epilogues, shared by the skinny and the wide kernel.  `sum` is one complete 16x16 accumulator
+// Epilogues, shared by the skinny and the single-row kernel.  `sum` is one complete 16x16 accumulator
 // fragment: this lane holds column (block row) m and fragment rows 4g .. 4g+3.
 // ---------------------------------------------------------------------------------------------
 

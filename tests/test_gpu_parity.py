@@ -776,6 +776,26 @@ def test_single_token_steps_with_the_norms_and_the_merge_inside_the_gemms(dtype,
     assert rep.max_rel_logit_err <= TOL[dtype], rep
 
 
+@pytest.mark.parametrize("dtype,heads,hd,prompt_len,k,wd", [
+    ("bf16", 3, 64, 1246, 8, 4),       # 40 key tiles of 64 dims: the longest list that stays whole (the next step may split it)
+    ("bf16", 3, 64, 1280, 8, 4),       # 41: split
+    ("bf16", 2, 128, 606, 21, 3),      # 20 tiles of 128 dims, 64 block tokens
+    ("bf16", 4, 32, 30, 16, 1),        # one tile: most waves have none
+    ("f32", 2, 128, 280, 6, 8),        # fp32: four waves
+    ("f32", 3, 64, 606, 3, 6),
+])
+def test_whole_and_split_key_lists(dtype, heads, hd, prompt_len, k, wd):
+    """Blocks of up to 64 tokens on both sides of the length up to which a head's key list is not split over workgroups
+    (attention_splits), against the oracle, logits at every step; the tolerance of every lock-step test of the type."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=heads, head_dim=hd, d_model=heads * hd,
+                d_ffn=256, vocab=2048, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run)
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL[dtype], max_steps=2)
+    ctx.close()
+    assert rep.max_rel_logit_err <= TOL[dtype], rep
+
+
 def test_7b_width_two_layer_twin_bf16_lockstep():
     """7B widths (d 4096, 32 heads of 128, FFN 14336, vocab 32000) with 2 layers so
     the oracle can run it: prompt 2048, k=10, w=5 -- the launch shapes of config 3."""
