@@ -60,7 +60,7 @@ struct ngg_ctx {
   hipGraphExec_t step_graph = nullptr;
   hipStream_t cap_stream = nullptr;   // the step is recorded on a stream of the library's own (the caller's may be the default
                                       // stream, which cannot be captured) and replayed on the caller's
-  int graph_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // k, w, k_ctx_max, q_min, q_max, attention slices, draft source, 1
+  int graph_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // k, w, k_ctx_max, q_min, q_max, attention slices and route, draft source, 1
   int eager_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // the same of the last step launched on the stream (its kernels are loaded)
   size_t part_rows = 0;            // rows (slices x block rows rounded to 128) the attention partial buffers hold per head
   // device buffers
@@ -186,7 +186,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
                  tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev);
   }
   const int n_splits = attention_splits(dt, d.head_dim, d.n_heads, M, P, c->max_splits, from_hist && C > 1);
-  c->attn_layout[0] = n_splits; c->attn_layout[1] = attention_workgroups(dt, d.head_dim, d.n_heads, M, n_splits);
+  const bool whole = attention_whole(dt, d.head_dim, M, P, from_hist && C > 1);
+  c->attn_layout[0] = n_splits; c->attn_layout[1] = attention_workgroups(dt, d.head_dim, d.n_heads, M, n_splits, whole);
   c->attn_layout[2] = M; c->attn_layout[3] = P;
   const int Mpart = (M + 127) / 128 * 128;
   if ((size_t)n_splits * Mpart > c->part_rows)
@@ -253,7 +254,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       a.kscr = kscr_l; a.vscr = vscr_l; a.kv_rows = kv_rows;
       a.part_o = c->part_o; a.part_ml = c->part_ml; a.out = c->attn;
       a.H = d.n_heads; a.Hkv = d.n_kv_heads; a.Mcap = c->Mcap; a.Spad = c->Spad; a.M = M; a.C = C; a.P = P;
-      a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0;
+      a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0; a.whole = whole ? 1 : 0;
       a.scale = 1.0f / std::sqrt((float)d.head_dim);
       launch_attention(dt, d.head_dim, a, s);
     }
@@ -743,7 +744,8 @@ static void step_key(const ngg_ctx *c, const ngg_draft_cfg &s, int key[8]) {
   const ngg_model_desc &d = c->d;
   const int C = s.w + 1, M = block_tokens(s.k, C, C >= 2 ? 1 : 0);
   key[0] = s.k; key[1] = s.w; key[2] = s.k_ctx_max; key[3] = s.q_min; key[4] = s.q_max;
-  key[5] = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits);
+  key[5] = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) |
+           (attention_whole(d.dtype, d.head_dim, M, c->n - 1) ? 1 << 16 : 0);
   key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0);
   key[7] = 1;
 }

@@ -565,7 +565,7 @@ static void launch_shared(const AttnArgs &a, hipStream_t s) {
 
 template <typename T, int HD>
 static void launch_hd(const AttnArgs &a, hipStream_t s) {
-  if (a.M <= 64 && a.n_splits == 1 && !a.one_row) {         // short lists (attention_splits): 16 queries per workgroup and
+  if (a.whole) {                                            // short lists (attention_whole): 16 queries per workgroup and
     // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list); four where two tiles of fp32 registers fill a wave's share
     constexpr int NW = HD * (int)sizeof(T) <= 256 ? 8 : 4;
     launch_stream<T, HD, 1, NW>(a, s);
@@ -581,6 +581,16 @@ static void launch_hd(const AttnArgs &a, hipStream_t s) {
 
 constexpr int kShortList = 2560;   // key tiles times head dim (doubled for fp32) of a list that stays whole
 
+static int list_tiles(int M, int P, bool causal) { return (P + 31) / 32 + 1 + (causal ? (M + 31) / 64 : 0); }
+
+// A short list is not split at all: the waves of one workgroup share it and merge in LDS (attn_stream_kernel), which
+// saves the merge launch: 33 tiles of 64 dims, 33 block tokens: 5.5 + 3.2 us and the gap between the launches -> 8.7 us
+// (the 12-layer step 575 -> 530-560 us).  A workgroup pulls 100-128 GB/s from the L2, and every group of 16 queries
+// pulls the whole list: at 65 tiles of 128 dims (7B, 2K context) the step went from 4.29 to 4.45 ms.
+bool attention_whole(int dtype, int hd, int M, int P, bool causal) {
+  return M > 1 && M <= 64 && list_tiles(M, P, causal) * hd * (dtype == 1 ? 1 : 2) <= kShortList;
+}
+
 // Number of list slices per head: one workgroup per CU in total; two per CU for blocks of more than
 // 64 tokens once every slice still has 16 tiles (measured at a 16K context: 74 -> 69 us; everywhere
 // else one per CU was as fast or faster); never fewer than 4 tiles per slice.  causal: the block is a piece of a prompt,
@@ -590,12 +600,8 @@ int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, boo
   const int qmax = dtype == 1 || hd <= 64 ? 2 : 1;
   const int per_wg = M <= 16 ? 16 : (M <= 64 ? 64 : 64 * qmax);
   const int Z = (M + per_wg - 1) / per_wg;
-  const int tiles = (P + 31) / 32 + 1 + (causal ? (M + 31) / 64 : 0);
-  // A short list is not split at all: the waves of one workgroup share it and merge in LDS (attn_stream_kernel), which
-  // saves the merge launch: 33 tiles of 64 dims, 33 block tokens: 5.5 + 3.2 us and the gap between the launches -> 8.7 us
-  // (the 12-layer step 575 -> 530-560 us).  A workgroup pulls 100-128 GB/s from the L2, and every group of 16 queries
-  // pulls the whole list: at 65 tiles of 128 dims (7B, 2K context) the step went from 4.29 to 4.45 ms.
-  if (M > 1 && M <= 64 && tiles * hd * (dtype == 1 ? 1 : 2) <= kShortList) return 1;
+  const int tiles = list_tiles(M, P, causal);
+  if (attention_whole(dtype, hd, M, P, causal)) return 1;
   const int one = 256 / (H * Z), two = M > 64 ? 512 / (H * Z) : one;
   int s = tiles / 16 > one ? tiles / 16 : one;
   s = s < two ? s : two;
@@ -604,9 +610,12 @@ int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, boo
   return s < 1 ? 1 : s;
 }
 
-int attention_workgroups(int dtype, int hd, int H, int M, int n_splits) {
+// (a list in one slice is not always a short one: above 128 heads a workgroup per CU leaves no more than one slice per
+// head.  Such a list goes through attn_shared_kernel, which reads it once for 64 queries: 144 heads of 128 on 8 key/value
+// heads, 8K context, 64 block tokens, 4 layers: 1.39 ms on the whole-list kernel, 1.06 ms so)
+int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool whole) {
   const int qmax = dtype == 1 || hd <= 64 ? 2 : 1;
-  const int per_wg = M <= 16 || (M <= 64 && n_splits == 1) ? 16 : (M <= 64 ? 64 : 64 * qmax);
+  const int per_wg = M <= 16 || whole ? 16 : (M <= 64 ? 64 : 64 * qmax);
   return n_splits * H * ((M + per_wg - 1) / per_wg);
 }
 

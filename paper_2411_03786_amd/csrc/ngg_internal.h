@@ -304,6 +304,7 @@ struct AttnArgs {
   float *part_o;          // [H][n_splits][Mpart/16][hd/16][64 lanes][4]: output fragments as the registers hold them
   float *part_ml;         // [H][n_splits][Mpart][2]
   int Mpart;              // rows per (head, slice) of the two partial buffers: M rounded up to 128
+  int whole;              // a short list (attention_whole): one workgroup per head and 16 queries, n_splits == 1
   int one_row;            // M == 1 and the merge is left to the GEMM that follows: partials are [H][n_splits][hd] and [H][n_splits][2]
   void *out;              // chunk-major [H*hd/KC][Mcap][KC] T
   int H, Hkv, Mcap, Spad, M, C, P, n_splits;   // n_splits: workgroups that share a head's list of key tiles
@@ -323,7 +324,8 @@ int gemm_row_splits(int N, int K);
 bool gemm_row_fits(int dtype, int d_model, int dq);
 void launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
 int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, bool causal = false);
-int attention_workgroups(int dtype, int hd, int H, int M, int n_splits);   // workgroups the main attention kernel is launched with
+bool attention_whole(int dtype, int hd, int M, int P, bool causal = false);   // the list is not split (attention_splits returns 1)
+int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool whole);   // workgroups the main attention kernel is launched with
 
 // mode 1: block token m is history token hist_base + m; mode 0: the verify block in the shared-first-column
 // layout (token 0 is hist[hist_base], token m >= 1 is drafts[m - 1]); mode 2: a block of single-column rows (w = 0),

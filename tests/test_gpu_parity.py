@@ -796,6 +796,27 @@ def test_whole_and_split_key_lists(dtype, heads, hd, prompt_len, k, wd):
     assert rep.max_rel_logit_err <= TOL[dtype], rep
 
 
+@pytest.mark.parametrize("k,wd,prompt_len,wgs", [
+    (8, 4, 700, 136),                  # 22 key tiles of 128 dims: a long list in one slice, read once for all 33 tokens
+    (8, 8, 700, 136),                  # 65 tokens: two query groups per wave
+    (8, 1, 700, 136),                  # 9 tokens
+    (8, 4, 300, 3 * 136),              # 10 tiles: a short list, 16 queries per workgroup
+])
+def test_long_key_lists_of_more_than_128_heads_in_one_slice(k, wd, prompt_len, wgs):
+    """Above 128 heads one workgroup per CU leaves one slice per head, whatever the length: the kernel that keeps short
+    lists whole must not take the long ones (it reads the list once per 16 queries).  The launch and the results; the
+    tolerance is the one of every 16-bit lock-step test."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 1), n_heads=136, n_kv_heads=4, head_dim=128, d_model=64, d_ffn=256, vocab=2048)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run)
+    layouts = []
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=1,
+                       on_step=lambda step: layouts.append(ctx.debug_peek("attn_layout", np.int32)[0].tolist()))
+    ctx.close()
+    assert rep.max_rel_logit_err <= TOL["bf16"], rep
+    assert layouts[0][:3] == [1, wgs, 1 + k * wd], layouts
+
+
 def test_7b_width_two_layer_twin_bf16_lockstep():
     """7B widths (d 4096, 32 heads of 128, FFN 14336, vocab 32000) with 2 layers so
     the oracle can run it: prompt 2048, k=10, w=5 -- the launch shapes of config 3."""
