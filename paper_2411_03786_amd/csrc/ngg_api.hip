@@ -186,7 +186,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
                  tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev);
   }
   const int n_splits = attention_splits(dt, d.head_dim, d.n_heads, M, P, c->max_splits, from_hist && C > 1);
-  const bool whole = attention_whole(dt, d.head_dim, M, P, from_hist && C > 1);
+  const bool whole = attention_whole(dt, d.head_dim, d.n_heads, M, P, from_hist && C > 1);
   c->attn_layout[0] = n_splits; c->attn_layout[1] = attention_workgroups(dt, d.head_dim, d.n_heads, M, n_splits, whole);
   c->attn_layout[2] = M; c->attn_layout[3] = P;
   const int Mpart = (M + 127) / 128 * 128;
@@ -745,7 +745,7 @@ static void step_key(const ngg_ctx *c, const ngg_draft_cfg &s, int key[8]) {
   const int C = s.w + 1, M = block_tokens(s.k, C, C >= 2 ? 1 : 0);
   key[0] = s.k; key[1] = s.w; key[2] = s.k_ctx_max; key[3] = s.q_min; key[4] = s.q_max;
   key[5] = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) |
-           (attention_whole(d.dtype, d.head_dim, M, c->n - 1) ? 1 << 16 : 0);
+           (attention_whole(d.dtype, d.head_dim, d.n_heads, M, c->n - 1) ? 1 << 16 : 0);
   key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0);
   key[7] = 1;
 }

@@ -579,16 +579,27 @@ static void launch_hd(const AttnArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);
 }
 
-constexpr int kShortList = 2560;   // key tiles times head dim (doubled for fp32) of a list that stays whole
-
 static int list_tiles(int M, int P, bool causal) { return (P + 31) / 32 + 1 + (causal ? (M + 31) / 64 : 0); }
 
 // A short list is not split at all: the waves of one workgroup share it and merge in LDS (attn_stream_kernel), which
-// saves the merge launch: 33 tiles of 64 dims, 33 block tokens: 5.5 + 3.2 us and the gap between the launches -> 8.7 us
-// (the 12-layer step 575 -> 530-560 us).  A workgroup pulls 100-128 GB/s from the L2, and every group of 16 queries
-// pulls the whole list: at 65 tiles of 128 dims (7B, 2K context) the step went from 4.29 to 4.45 ms.
-bool attention_whole(int dtype, int hd, int M, int P, bool causal) {
-  return M > 1 && M <= 64 && list_tiles(M, P, causal) * hd * (dtype == 1 ? 1 : 2) <= kShortList;
+// saves the merge launch: 33 tiles of 64 dims, 33 block tokens: 5.5 + 3.2 us and the gap between the launches -> 8.7 us.
+// Against it stands that every group of 16 queries pulls the whole list (100-128 GB/s per workgroup from the L2).  Steps of
+// 4 layers with and without it, in turn, at 4 to 136 heads; "length" is key tiles times head dim, doubled for fp32:
+//  * up to 16 tokens the split list is read once too: 64 dims 0.97 of the split list's time at length 1280, 1.00-1.02 at
+//    1536, 1.02-1.07 at 2560; 128 dims 0.98 at 1792, 1.00-1.02 at 2048; fp32 0.99 at 1536, 1.02 at 2048.
+//  * 17-32 tokens 0.98 at 1792, 0.98-1.02 at 2048, 1.00-1.03 at 2560; 33-48 tokens 0.98-1.00 at 2304, 0.99-1.02 at 2560;
+//    49-64 tokens and fp32 above 16 tokens below 1.00 throughout; 65 tiles of 128 dims (length 8320): 4.29 -> 4.45 ms per
+//    32-layer step at 51 tokens.
+//  * one round of workgroups: a CU holds one of them at 256 bytes per head and position or more, two below.  A second
+//    round costs 1.02-1.05 (96 heads of 128, 33 tokens; 136 heads, 17 tokens), a third 1.07.
+bool attention_whole(int dtype, int hd, int H, int M, int P, bool causal) {
+  if (M <= 1 || M > 64) return false;
+  const int groups = (M + 15) / 16, row = hd * (dtype == 1 ? 2 : 4);
+  if (H * groups > (row >= 256 ? 256 : 512)) return false;
+  const int length = list_tiles(M, P, causal) * hd * (dtype == 1 ? 1 : 2);
+  if (groups == 1) return length <= (row >= 256 ? 1792 : 1280);
+  if (dtype != 1) return length <= 2560;
+  return length <= (groups == 2 ? 1920 : (groups == 3 ? 2304 : 2560));
 }
 
 // Number of list slices per head: one workgroup per CU in total; two per CU for blocks of more than
@@ -601,7 +612,7 @@ int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, boo
   const int per_wg = M <= 16 ? 16 : (M <= 64 ? 64 : 64 * qmax);
   const int Z = (M + per_wg - 1) / per_wg;
   const int tiles = list_tiles(M, P, causal);
-  if (attention_whole(dtype, hd, M, P, causal)) return 1;
+  if (attention_whole(dtype, hd, H, M, P, causal)) return 1;
   const int one = 256 / (H * Z), two = M > 64 ? 512 / (H * Z) : one;
   int s = tiles / 16 > one ? tiles / 16 : one;
   s = s < two ? s : two;

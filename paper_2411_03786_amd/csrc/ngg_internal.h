@@ -324,7 +324,7 @@ int gemm_row_splits(int N, int K);
 bool gemm_row_fits(int dtype, int d_model, int dq);
 void launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
 int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, bool causal = false);
-bool attention_whole(int dtype, int hd, int M, int P, bool causal = false);   // the list is not split (attention_splits returns 1)
+bool attention_whole(int dtype, int hd, int H, int M, int P, bool causal = false);   // the list is not split (attention_splits returns 1)
 int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool whole);   // workgroups the main attention kernel is launched with
 
 // mode 1: block token m is history token hist_base + m; mode 0: the verify block in the shared-first-column

@@ -776,31 +776,43 @@ def test_single_token_steps_with_the_norms_and_the_merge_inside_the_gemms(dtype,
     assert rep.max_rel_logit_err <= TOL[dtype], rep
 
 
-@pytest.mark.parametrize("dtype,heads,hd,prompt_len,k,wd", [
-    ("bf16", 3, 64, 1246, 8, 4),       # 40 key tiles of 64 dims: the longest list that stays whole (the next step may split it)
-    ("bf16", 3, 64, 1280, 8, 4),       # 41: split
-    ("bf16", 2, 128, 606, 21, 3),      # 20 tiles of 128 dims, 64 block tokens
-    ("bf16", 4, 32, 30, 16, 1),        # one tile: most waves have none
-    ("f32", 2, 128, 280, 6, 8),        # fp32: four waves
-    ("f32", 3, 64, 606, 3, 6),
+@pytest.mark.parametrize("dtype,heads,hd,prompt_len,k,wd,splits,wgs", [
+    ("bf16", 3, 64, 1120, 8, 4, 1, 9),      # 33 tokens, 36 key tiles of 64 dims: the longest list that stays whole (the next step may split it)
+    ("bf16", 3, 64, 1121, 8, 4, 9, 27),     # 37: split
+    ("bf16", 2, 128, 606, 21, 3, 1, 8),     # 64 tokens, 20 tiles of 128 dims
+    ("bf16", 4, 32, 30, 16, 1, 1, 8),       # 17 tokens, two tiles: most waves have none
+    ("bf16", 3, 64, 928, 31, 1, 1, 6),      # 32 tokens, 30 tiles
+    ("bf16", 3, 64, 929, 31, 1, 7, 21),     # 31: split
+    ("bf16", 3, 64, 608, 8, 1, 1, 3),       # 9 tokens, 20 tiles
+    ("bf16", 3, 64, 609, 8, 1, 5, 15),      # 21: split
+    ("bf16", 2, 128, 416, 5, 3, 1, 2),      # 16 tokens, 14 tiles of 128 dims
+    ("f32", 2, 128, 280, 6, 8, 1, 8),       # fp32: four waves
+    ("f32", 3, 64, 606, 3, 6, 1, 6),
+    ("f32", 3, 64, 416, 8, 1, 1, 3),        # 9 tokens, 14 tiles
+    ("f32", 3, 64, 417, 8, 1, 3, 9),        # 15: split
 ])
-def test_whole_and_split_key_lists(dtype, heads, hd, prompt_len, k, wd):
+def test_whole_and_split_key_lists(dtype, heads, hd, prompt_len, k, wd, splits, wgs):
     """Blocks of up to 64 tokens on both sides of the length up to which a head's key list is not split over workgroups
-    (attention_splits), against the oracle, logits at every step; the tolerance of every lock-step test of the type."""
+    (attention_whole): the launch of the first step, and the results against the oracle, logits at every step; the
+    tolerance of every lock-step test of the type."""
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=heads, head_dim=hd, d_model=heads * hd,
                 d_ffn=256, vocab=2048, dtype=dtype)
     run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
     w_, prompt, model, ctx = _setup(desc, run)
-    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL[dtype], max_steps=2)
+    layouts = []
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL[dtype], max_steps=2,
+                       on_step=lambda step: layouts.append(ctx.debug_peek("attn_layout", np.int32)[0].tolist()))
     ctx.close()
     assert rep.max_rel_logit_err <= TOL[dtype], rep
+    assert layouts[0] == [splits, wgs, 1 + k * wd, prompt_len], layouts
 
 
 @pytest.mark.parametrize("k,wd,prompt_len,wgs", [
     (8, 4, 700, 136),                  # 22 key tiles of 128 dims: a long list in one slice, read once for all 33 tokens
     (8, 8, 700, 136),                  # 65 tokens: two query groups per wave
     (8, 1, 700, 136),                  # 9 tokens
-    (8, 4, 300, 3 * 136),              # 10 tiles: a short list, 16 queries per workgroup
+    (8, 4, 300, 136),                  # 11 tiles: short, but 16 queries per workgroup would make two rounds of workgroups
+    (8, 2, 60, 136),                   # 17 tokens, 3 tiles
 ])
 def test_long_key_lists_of_more_than_128_heads_in_one_slice(k, wd, prompt_len, wgs):
     """Above 128 heads one workgroup per CU leaves one slice per head, whatever the length: the kernel that keeps short
