@@ -289,6 +289,16 @@ ngg_status ngg_profile_read_bandwidth(ngg_ctx *ctx, double *gbps);
  * replay mode, a capture failed, captures so far, replayed steps so far).  Synchronises the stream. */
 ngg_status ngg_debug_peek(ngg_ctx *ctx, const char *name, void *dst, int64_t cap, int64_t *bytes, int32_t *stride);
 
+/* Test aids.  ngg_debug_plan: what a model call on `tokens` block tokens launches for one of its GEMMs (gemm 0 = q, k and
+ * v together, 1 = output projection or down, 2 = gate and up, 3 = unembedding) with n output rows (gate and up: d_ffn) and
+ * a contraction of k.  Host only, no context, no GPU.  plan (HOST, int32[8]): kernel (0 streaming, 1 tiled, 2 single
+ * token), block tokens and weight rows of a tile, splits of the contraction, 16-row weight fragments in the first launch,
+ * tokens and rows of the second launch's tiles, number of tile shapes.
+ * ngg_debug_tiles: every GEMM of this context's 16-bit model calls on two tokens or more takes tile shape `shape`
+ * (0 .. number - 1) of the tiled kernel whatever its size; -1 (default) goes back to the choice by size. */
+ngg_status ngg_debug_plan(int32_t dtype, int32_t gemm, int32_t tokens, int32_t n, int32_t k, int32_t *plan);
+ngg_status ngg_debug_tiles(ngg_ctx *ctx, int32_t shape);
+
 #ifdef __cplusplus
 }
 #endif

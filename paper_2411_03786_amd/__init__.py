@@ -23,7 +23,7 @@ PROF_CLASSES = ("gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down", "gemm_unembed"
 EXPORTS = ("ngg_create", "ngg_destroy", "ngg_prefill", "ngg_build_drafts", "ngg_verify_step", "ngg_commit",
            "ngg_greedy_decode", "ngg_get_tokens", "ngg_last_error", "ngg_profile_enable", "ngg_profile_reset",
            "ngg_profile_read", "ngg_debug_peek", "ngg_bigram_table_build", "ngg_bigram_source", "ngg_profile_bracket_overhead", "ngg_unigram_build", "ngg_decode_more", "ngg_profile_sample",
-           "ngg_context_drafts_static", "ngg_allocation", "ngg_profile_read_bandwidth", "ngg_step_graphs")
+           "ngg_context_drafts_static", "ngg_allocation", "ngg_profile_read_bandwidth", "ngg_step_graphs", "ngg_debug_plan", "ngg_debug_tiles")
 NGG_STATIC_MAX_TOKENS = 32768
 
 
@@ -98,6 +98,8 @@ def load_library():
     lib.ngg_allocation.argtypes = [vp, C.c_int32, C.c_int32, C.c_int32]
     lib.ngg_step_graphs.argtypes = [vp, C.c_int32]
     lib.ngg_profile_read_bandwidth.argtypes = [vp, C.POINTER(C.c_double)]
+    lib.ngg_debug_plan.argtypes = [C.c_int32] * 5 + [i32p]
+    lib.ngg_debug_tiles.argtypes = [vp, C.c_int32]
     lib.ngg_context_drafts_static.argtypes = [vp, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, vp, vp, vp]
     for name in EXPORTS:
         if name != "ngg_last_error":
@@ -110,6 +112,16 @@ class NggError(RuntimeError):
     def __init__(self, status, message):
         super().__init__(f"ngg status {status}: {message}")
         self.status = status
+
+
+def debug_plan(dtype, gemm, tokens, n, k):
+    """What a model call launches for one GEMM (ngg_debug_plan): gemm is "qkv", "residual", "gateup" or "unembed"."""
+    out = (C.c_int32 * 8)()
+    lib = load_library()
+    st = lib.ngg_debug_plan(NGG_BF16 if dtype == "bf16" else NGG_F32, ("qkv", "residual", "gateup", "unembed").index(gemm), tokens, n, k, out)
+    if st != NGG_OK:
+        raise NggError(st, lib.ngg_last_error(None).decode())
+    return dict(zip(("kernel", "tile_tokens", "tile_rows", "splits", "first_frags", "tile2_tokens", "tile2_rows", "shapes"), out))
 
 
 def _i32(a):
@@ -290,6 +302,10 @@ class Context:
         self._check(self.lib.ngg_debug_peek(self.h, name.encode(), out.ctypes.data_as(C.c_void_p), n * item,
                                             C.byref(nbytes), C.byref(stride)))
         return out, stride.value
+
+    def debug_tiles(self, shape):
+        """Every 16-bit GEMM on tile shape `shape`; -1: by size (test aid)."""
+        self._check(self.lib.ngg_debug_tiles(self.h, int(shape)))
 
     def profile_enable(self, class_mask=-1):
         self._check(self.lib.ngg_profile_enable(self.h, int(class_mask)))

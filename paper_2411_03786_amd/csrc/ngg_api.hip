@@ -42,6 +42,7 @@ struct ngg_ctx {
   hipStream_t stream = nullptr;
   int esize = 2;          // bytes per weight / KV element
   int Spad = 0, Mcap = 0, max_splits = 0, unembed_tiles = 0;
+  int tile_only = 0;               // ngg_debug_tiles: see GemmArgs
   int prefill_chunk = 0;           // prompt tokens per forward pass of ngg_prefill
   // One decode step (drafts, block forward, acceptance, commit) captured as a HIP graph: its kernels read the
   // context length from n_dev, so the same graph replays step after step (a replayed launch costs the GPU
@@ -193,7 +194,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   if ((size_t)n_splits * Mpart > c->part_rows)
     return fail(c, NGG_ECAPACITY, "attention partials: %d slices of %d rows exceed the %zu rows allocated", n_splits, Mpart, c->part_rows);
   const size_t part_stride = (size_t)c->Mcap * d.d_model;
-  int ks_o = gemm_residual_splits(dt, M, d.d_model, dq), ks_down = gemm_residual_splits(dt, M, d.d_model, d.d_ffn);
+  int ks_o = gemm_residual_splits(dt, M, d.d_model, dq, c->tile_only);
+  int ks_down = gemm_residual_splits(dt, M, d.d_model, d.d_ffn, c->tile_only);
   const int ss_segs = rmsnorm_segments(d.d_model);
   // A block of one token: the GEMMs run the RMSNorms and the merge of the attention slices themselves (launch_gemm_row).
   // Not while the norms' own time is asked for: a profile of that class needs them as launches.
@@ -216,7 +218,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     row.h_in = h_cur; row.h_out = h_next; row.n_part = pending; row.gain = gain; row.part_o = nullptr;
     if (pending > 0) std::swap(h_cur, h_next);
   };
-  auto gemm = [&](int epi, const GemmArgs &g) {
+  auto gemm = [&](int epi, GemmArgs &g) {
+    g.tile_only = c->tile_only;
     if (one_row) launch_gemm_row(dt, epi, g, row, s);
     else launch_gemm(dt, epi, g, s);
   };
@@ -1181,6 +1184,25 @@ ngg_status ngg_context_drafts_static(const int32_t *tokens, int32_t n, int32_t w
   a.ctx_rows = rows; a.n_ctx = n_rows;
   launch_ctx_match(a, (hipStream_t)hip_stream);      // clears the part of the table it uses itself: nothing to reset here
   NGG_HIP(nullptr, hipGetLastError());
+  return NGG_OK;
+}
+
+ngg_status ngg_debug_plan(int32_t dtype, int32_t gemm, int32_t tokens, int32_t n, int32_t k, int32_t *plan) {
+  if (!plan) return fail(nullptr, NGG_EINVAL, "ngg_debug_plan: null plan");
+  if ((dtype != NGG_F32 && dtype != NGG_BF16) || gemm < 0 || gemm > 3 || tokens < 1 || n < 32 || k < 32 || n % 32 || k % 32)
+    return fail(nullptr, NGG_EINVAL, "ngg_debug_plan: need a dtype, gemm 0..3, tokens >= 1, and n and k multiples of 32");
+  const int epi[4] = {EPI_QKV, EPI_RESIDUAL, EPI_GATEUP, EPI_UNEMBED};
+  const GemmPlan p = gemm_plan(dtype, epi[gemm], tokens, n, k);
+  const int32_t v[8] = {p.kernel, p.tm, p.tn, p.splits, p.split, p.tm2, p.tn2, gemm_tile_shapes()};
+  memcpy(plan, v, sizeof v);
+  return NGG_OK;
+}
+
+ngg_status ngg_debug_tiles(ngg_ctx *c, int32_t shape) {
+  if (!c) return NGG_EINVAL;
+  if (shape < -1 || shape >= gemm_tile_shapes()) return fail(c, NGG_EINVAL, "ngg_debug_tiles: shape must be -1 .. %d", gemm_tile_shapes() - 1);
+  c->tile_only = shape + 1;
+  c->graph_key[7] = 0;                                  // a captured step holds the launches of the earlier choice
   return NGG_OK;
 }
 

@@ -744,11 +744,13 @@ static float tile_cost(int shape, int epi, int M, int frags, int K, int KS) {
 // The cheapest plan by the costs above.  Splitting the contraction (residual only) fills the chip when there are few
 // tiles; every split costs M x N partials written and read again by the RMSNorm.  When the tiles of a launch fill a
 // number of rounds and a half, the half round is given smaller tiles in a launch of its own.
-static TilePlan tile_plan(int epi, int M, int frags, int K) {
+// only: 1 + the shape every launch has to take (0: any).
+static TilePlan tile_plan(int epi, int M, int frags, int K, int only) {
   const int n_slices = (K + 63) / 64;
   TilePlan best{0, 1, frags, 0};
   float cost = 1e30f;
   for (int c = 0; c < kNumTileShapes; ++c) {
+    if (only && c != only - 1) continue;
     const TileShape &t = kTileShapes[c];
     if (epi == EPI_RESIDUAL) {
       for (int ks = 1; ks <= kMaxResidualSplits && n_slices >= 2 * ks; ++ks) {
@@ -764,6 +766,7 @@ static TilePlan tile_plan(int epi, int M, int frags, int K) {
     if (whole < 1 || whole >= cols) continue;
     const int cut = whole * (t.tn / 16);
     for (int c2 = 0; c2 < kNumTileShapes; ++c2) {
+      if (only && c2 != only - 1) continue;
       const float y = tile_cost(c, epi, M, cut, K, 1) + tile_cost(c2, epi, M, frags - cut, K, 1) + 3.0f;
       if (y < cost) { cost = y; best = {c, 1, cut, c2}; }
     }
@@ -786,7 +789,7 @@ static void launch_tile_shape(int shape, const GemmArgs &a, int KS, int f0, int 
 template <int EPI>
 static void launch_tile(const GemmArgs &a, hipStream_t s) {
   const int frags = EPI == EPI_QKV ? (a.H + 2 * a.Hkv) * (a.hd / 16) : (EPI == EPI_GATEUP ? a.N / 8 : a.N / 16);
-  const TilePlan p = tile_plan(EPI, a.M, frags, a.K);
+  const TilePlan p = tile_plan(EPI, a.M, frags, a.K, a.tile_only);
   launch_tile_shape<EPI>(p.shape, a, p.KS, 0, p.split, s);  // residual: p.KS == a.KS (gemm_residual_splits)
   launch_tile_shape<EPI>(p.shape2, a, p.KS, p.split, frags, s);
 }
@@ -918,8 +921,8 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
 //    either way (4096-wide, 97 rows: 49.4 and 47.5-50.6, 33.8 and 35.3).
 //  * up to 64 rows where 64 x 64 tiles make one full round (14/16 of the CUs at least): 1024 fragments 19.4 -> 18.6 /
 //    20.2 -> 19.2 / 21.6 -> 19.3 / 21.8 -> 20.0; 688 fragments 11.5 against 12.7 at 33 rows, 768 fragments 23.0 against 24.7 at 51.
-static bool takes_tile(int epi, int M, int frags, int K) {
-  if (M > 128) return true;
+static bool takes_tile(int epi, int M, int frags, int K, int tile_only) {
+  if (M > 128 || (tile_only && M > 1)) return true;
   if (epi == EPI_UNEMBED || M <= 16) return false;
   if (epi != EPI_RESIDUAL) return M > 64 ? frags <= 512 : (frags > 896 && frags <= 1024);
   const int N = frags * 16;
@@ -928,8 +931,8 @@ static bool takes_tile(int epi, int M, int frags, int K) {
 }
 
 // Split of the contraction across workgroups for the residual GEMMs
-int gemm_residual_splits(int dtype, int M, int N, int K) {
-  if (dtype == 1 && takes_tile(EPI_RESIDUAL, M, N / 16, K)) return tile_plan(EPI_RESIDUAL, M, N / 16, K).KS;
+int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only) {
+  if (dtype == 1 && takes_tile(EPI_RESIDUAL, M, N / 16, K, tile_only)) return tile_plan(EPI_RESIDUAL, M, N / 16, K, tile_only).KS;
   return skinny_residual_splits(dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value, M, N, K);
 }
 
@@ -941,7 +944,7 @@ template <typename T>
 static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   GemmArgs a = a_in;
   if constexpr (sizeof(T) == 2) {
-    if (takes_tile(epi, a.M, epi == EPI_RESIDUAL || epi == EPI_UNEMBED ? a.N / 16 : gemm_groups(epi, a), a.K)) {
+    if (takes_tile(epi, a.M, epi == EPI_RESIDUAL || epi == EPI_UNEMBED ? a.N / 16 : gemm_groups(epi, a), a.K, a.tile_only)) {
       switch (epi) {
         case EPI_QKV: launch_tile<EPI_QKV>(a, s); break;
         case EPI_GATEUP: launch_tile<EPI_GATEUP>(a, s); break;
@@ -1259,6 +1262,21 @@ static void launch_row_t(int epi, const GemmArgs &a_in, const RowArgs &r, hipStr
       break;
     default: launch_row_fn<U, EPI_UNEMBED, 1>(a, r, 1, s);
   }
+}
+
+int gemm_tile_shapes() { return kNumTileShapes; }
+
+GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K) {
+  const int frags = epi == EPI_GATEUP ? N / 8 : N / 16;
+  GemmPlan p{0, 0, 0, 1, frags, 0, 0};
+  if (dtype == 1 && takes_tile(epi, M, frags, K, 0)) {
+    const TilePlan t = tile_plan(epi, M, frags, K, 0);
+    const TileShape &s = kTileShapes[t.shape], &s2 = kTileShapes[t.shape2];
+    return {1, s.tm, s.tn, t.KS, t.split, s2.tm, s2.tn};
+  }
+  if (epi == EPI_RESIDUAL) p.splits = M == 1 ? gemm_row_splits(N, K) : gemm_residual_splits(dtype, M, N, K);
+  if (M == 1) p.kernel = 2;
+  return p;
 }
 
 void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s) {

@@ -256,6 +256,7 @@ struct GemmArgs {
   float ss_eps;
   float out_scale;        // every result is multiplied by this: 1 / (scale of the stored weights * scale of X); 1 for fp32 models
   int n_groups;           // residual, unembedding: pairs of 16-row fragments; q/k/v, gate/up: fragments (filled by the launcher)
+  int tile_only;          // tests: 1 + the tile shape gemm_tile_kernel has to take, and takes any block of two tokens or more; 0: by size
   // EPI_RESIDUAL: split ks of KS stores its fp32 partial at hpart[ks][m][n]; the next RMSNorm adds them
   float *hpart;           // [KS][Mcap][N]
   int KS;
@@ -316,7 +317,13 @@ struct AttnArgs {
 // launchers (host).  dtype: 0 = fp32, 1 = bf16.  Every launcher validates nothing: the API layer
 // checks shapes before calling.
 void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s);
-int gemm_residual_splits(int dtype, int M, int N, int K);
+int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only = 0);
+// What a model call on M block tokens launches for one GEMM of N output rows (q, k and v together; gate/up: d_ffn): kernel 0
+// gemm_skinny_kernel, 1 gemm_tile_kernel (tile rows and columns; fragments from `split` on in a second launch of their own
+// shape), 2 gemm_row_kernel; splits of the contraction.
+struct GemmPlan { int kernel, tm, tn, splits, split, tm2, tn2; };
+GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K);
+int gemm_tile_shapes();   // tile shapes gemm_tile_kernel is built for
 // the GEMMs of a block of one token, with the RMSNorm (q/k/v, gate/up, unembedding) or the merge of the attention slices
 // (output projection, r.part_o set) in front
 void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s);

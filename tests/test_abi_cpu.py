@@ -98,3 +98,18 @@ def test_binding_refuses_to_run_without_a_gpu():
     desc = si.MODELS["tiny"]
     with pytest.raises(RuntimeError, match="no CPU fallback"):
         ngg.Context(desc, si.make_weights(desc), max_seq=64, max_k=2, max_w=2)
+
+
+def test_debug_plan_rejects_bad_arguments_and_names_the_kernels(lib):
+    for bad in (("bf16", "qkv", 0, 128, 128), ("bf16", "qkv", 4, 100, 128), ("bf16", "qkv", 4, 128, 16)):
+        with pytest.raises(ngg.NggError) as e:
+            ngg.debug_plan(*bad)
+        assert e.value.status == ngg.NGG_EINVAL
+    assert lib.ngg_debug_plan(1, 4, 4, 128, 128, (C.c_int32 * 8)()) == ngg.NGG_EINVAL
+    assert lib.ngg_debug_plan(1, 0, 4, 128, 128, None) == ngg.NGG_EINVAL
+    assert lib.ngg_debug_tiles(None, 0) == ngg.NGG_EINVAL
+    assert ngg.debug_plan("bf16", "qkv", 1, 12288, 4096)["kernel"] == 2
+    assert ngg.debug_plan("bf16", "qkv", 51, 12288, 4096)["kernel"] == 0
+    assert ngg.debug_plan("f32", "qkv", 2048, 12288, 4096)["kernel"] == 0
+    big = ngg.debug_plan("bf16", "gateup", 2048, 14336, 4096)
+    assert big["kernel"] == 1 and (big["tile_tokens"], big["tile_rows"]) == (256, 256)

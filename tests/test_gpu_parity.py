@@ -684,10 +684,9 @@ def test_cfg2_small_bf16_lockstep():
 
 @pytest.mark.parametrize("k,w", [(16, 0), (16, 6), (32, 8), (13, 4), (12, 7), (13, 9), (20, 7), (32, 7), (20, 14), (32, 32)])
 def test_bf16_blocks_of_more_than_64_rows(k, w):
-    """Blocks of 112, 288, 65 and 96 rows on the small 16-bit widths (3 layers): GEMM row tiles of 7, 8, 5
-    and 6 column blocks and the attention workgroups with two query groups per wave; then the wide GEMM
-    kernel (more than 128 rows in one pass over the weights): 130, 160, 256 and 288 rows (tiles of 10, 10, 16
-    and 18 row blocks), 300 rows (two row tiles of 160 in one launch) and 1056 rows (four row tiles of 272)."""
+    """Blocks of 16 to 1025 tokens on the small 16-bit widths (3 layers): the streaming GEMMs up to 128 tokens, the tiled
+    ones (which tile shape runs is pinned by test_every_tile_shape_16_bit) and the attention workgroups with two query
+    groups per wave."""
     desc = si.reduced_layers(si.MODELS["small"], 3)
     run = dict(si.RUNS["cfg2"], prompt_len=333, k=k, w=w, k_ctx_max=k, q_min=1, q_max=3, n_gen=30)
     w_, prompt, model, ctx = _setup(desc, run)
@@ -698,9 +697,8 @@ def test_bf16_blocks_of_more_than_64_rows(k, w):
 
 
 def test_prefill_piece_boundaries_16_bit():
-    """Prompt lengths around the row tiles of the prefill (16-bit models take pieces of up to 2048 tokens; the wide
-    GEMM kernel cuts a piece into tiles of up to 288 rows, the skinny kernel takes up to 128 rows) and around the
-    piece boundary itself, on the small 16-bit widths (2 layers).  A context created with a short max_seq has
+    """Prompt lengths around the row tiles of the prefill (16-bit models take pieces of up to 2048 tokens, which the tiled
+    GEMM cuts into tiles of 64 to 384 tokens) and around the piece boundary itself, on the small 16-bit widths (2 layers).  A context created with a short max_seq has
     shorter pieces (max_seq rounded up to 256): the second loop runs the same prompts through 768-token pieces."""
     desc = si.reduced_layers(si.MODELS["small"], 2)
     run = dict(si.RUNS["cfg2"], prompt_len=2400, n_gen=8)
@@ -720,10 +718,8 @@ def test_prefill_piece_boundaries_16_bit():
 
 
 def test_row_tiles_of_256_with_an_odd_number_of_contraction_slices_16_bit():
-    """The 32x32x16 GEMM kernel takes tiles of 192 and 256 rows; its main loop handles two 64-element slices of the
-    contraction per trip and one more after it when their number is odd.  Widths of 192 (3 slices) and 448 (7 slices),
-    2 layers: a 512-token prompt is prefilled as two 256-row tiles (all four GEMMs on that kernel), then verify blocks
-    of 241 and 177 rows (one tile of 256 and of 192 rows: q/k/v and gate/up on it) and a step of the default shape."""
+    """Odd numbers of 64-element contraction slices (widths of 192 and 448), 2 layers: a 512-token prompt and verify blocks
+    of 241 and 177 tokens, as the choice by size runs them (test_every_tile_shape_16_bit: on every tile shape)."""
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=3, n_kv_heads=3, head_dim=64, d_model=192, d_ffn=448,
                 vocab=4096)
     run = dict(si.RUNS["cfg2"], prompt_len=512, n_gen=64)
@@ -736,6 +732,27 @@ def test_row_tiles_of_256_with_an_odd_number_of_contraction_slices_16_bit():
         print("odd slices:", k, wd, rep)
         assert rep.max_rel_logit_err <= 2e-2, (k, wd, rep)
     ctx.close()
+
+
+@pytest.mark.parametrize("shape", range(5))
+@pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd", [
+    (3, 1, 64, 448, 550, 16, 16),     # odd numbers of slices (3 and 7), grouped heads; 257 block tokens, a prompt cut by every tile height
+    (5, 5, 32, 224, 300, 8, 4),       # the last slice is half padding (widths 160 and 224); 33 block tokens in a tile of any height
+])
+def test_every_tile_shape_16_bit(shape, heads, kv, hd, d_ffn, prompt_len, k, wd):
+    """Each tile shape of gemm_tile_kernel under each epilogue, whatever the choice by size would be: row tiles and
+    fragments of W that end inside a tile, contractions of an odd number of slices and of half a slice more.  A prompt
+    (q/k/v straight to the cache, both residual GEMMs, gate/up), then a verify block (the unembedding too) against the
+    oracle; the tolerance is the one of every 16-bit lock-step test."""
+    assert ngg.debug_plan("bf16", "qkv", 300, 512, 512)["shapes"] == 5
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=heads * hd,
+                d_ffn=d_ffn, vocab=2080)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=64, k=k, w=wd, k_ctx_max=4)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
+    ctx.debug_tiles(shape)
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=1)
+    ctx.close()
+    assert rep.max_rel_logit_err <= TOL["bf16"], rep
 
 
 @pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd", [
