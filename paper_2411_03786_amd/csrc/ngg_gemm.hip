@@ -753,7 +753,7 @@ static TilePlan tile_plan(int epi, int M, int frags, int K, int only) {
     if (only && c != only - 1) continue;
     const TileShape &t = kTileShapes[c];
     if (epi == EPI_RESIDUAL) {
-      for (int ks = 1; ks <= kMaxResidualSplits && n_slices >= 2 * ks; ++ks) {
+      for (int ks = 1; ks <= kMaxResidualSplits && (ks == 1 || n_slices >= 2 * ks); ++ks) {
         const float x = tile_cost(c, epi, M, frags, K, ks) + (float)M * frags * 64.0f * ks / 6.0e6f;
         if (x < cost) { cost = x; best = {c, ks, frags, c}; }
       }

@@ -113,3 +113,12 @@ def test_debug_plan_rejects_bad_arguments_and_names_the_kernels(lib):
     assert ngg.debug_plan("f32", "qkv", 2048, 12288, 4096)["kernel"] == 0
     big = ngg.debug_plan("bf16", "gateup", 2048, 14336, 4096)
     assert big["kernel"] == 1 and (big["tile_tokens"], big["tile_rows"]) == (256, 256)
+
+
+@pytest.mark.parametrize("tokens,n,k", [(33, 64, 64), (300, 512, 32), (129, 128, 64), (64, 4096, 32)])
+def test_short_contractions_get_a_tile_that_fits(lib, tokens, n, k):
+    """A residual GEMM with a contraction of one slice (64 or less) is planned like any other: it had no candidate and
+    fell to the largest tile."""
+    p = ngg.debug_plan("bf16", "residual", tokens, n, k)
+    assert p["kernel"] == 1 and p["splits"] == 1
+    assert p["tile_tokens"] * p["tile_rows"] < 256 * 256 and p["tile_rows"] <= 128
