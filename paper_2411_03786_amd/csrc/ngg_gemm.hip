@@ -724,9 +724,19 @@ static void launch_tile_cfg(const GemmArgs &a, int KS, int frag_first, int frag_
 
 // Tile shapes of gemm_tile_kernel with what a workgroup costs: microseconds per slice of 64 contraction elements, and
 // for its start and epilogue (fitted to launches at the 7B shapes and at 768-wide ones, 97 to 2048 rows, on MI355X).
+// The last three are for 257 to 384 rows, which the 256-row tile computes as 512 and the 128-row one as 384 in one and a
+// half rounds (7B shapes, us; before them -> with them): gate/up as one row tile of 288 or 384, 257 rows 118 -> 83, 289-384
+// rows 118-121 -> 97-100; q/k/v as two of 192 x 96, one full round, 67 -> 50-52.  The 288-row tile runs on four waves of
+// nine MFMA blocks: on eight, two of the four SIMDs would have a wave more than the others.
 struct TileShape { int tm, tn; float slice_us, fixed_us; };
-constexpr TileShape kTileShapes[] = {{256, 256, 1.60f, 10.0f}, {128, 256, 0.98f, 8.0f}, {128, 128, 0.54f, 6.0f}, {128, 64, 0.36f, 4.5f}, {64, 64, 0.30f, 3.5f}};
-constexpr int kNumTileShapes = 5;
+constexpr TileShape kTileShapes[] = {{256, 256, 1.60f, 10.0f}, {128, 256, 0.98f, 8.0f}, {128, 128, 0.54f, 6.0f}, {128, 64, 0.36f, 4.5f}, {64, 64, 0.30f, 3.5f},
+                                     {288, 128, 1.13f, 10.0f}, {384, 128, 1.38f, 10.0f}, {192, 96, 0.65f, 7.0f}};
+constexpr int kNumTileShapes = 8;
+
+// Which of them a launch chooses among.  Beyond 384 rows the last three only replace equals (7B: gate/up of 513 rows 163
+// against 162 us, q/k/v of 641 rows 103 and 103); the residual GEMMs do without them (257 rows: 35.2 us on 128 x 256 with
+// five splits, 35.8 on 288 x 128 with eight, and the RMSNorm that adds the splits 7.7 -> 8.9).
+static bool shape_fits(int c, int epi, int M) { return c < 5 || (epi != EPI_RESIDUAL && M > 256 && M <= 384); }
 
 struct TilePlan { int shape, KS, split, shape2; };        // fragments from `split` on run as a second launch in shape2
 
@@ -750,7 +760,7 @@ static TilePlan tile_plan(int epi, int M, int frags, int K, int only) {
   TilePlan best{0, 1, frags, 0};
   float cost = 1e30f;
   for (int c = 0; c < kNumTileShapes; ++c) {
-    if (only && c != only - 1) continue;
+    if (only ? c != only - 1 : !shape_fits(c, epi, M)) continue;
     const TileShape &t = kTileShapes[c];
     if (epi == EPI_RESIDUAL) {
       for (int ks = 1; ks <= kMaxResidualSplits && (ks == 1 || n_slices >= 2 * ks); ++ks) {
@@ -766,7 +776,7 @@ static TilePlan tile_plan(int epi, int M, int frags, int K, int only) {
     if (whole < 1 || whole >= cols) continue;
     const int cut = whole * (t.tn / 16);
     for (int c2 = 0; c2 < kNumTileShapes; ++c2) {
-      if (only && c2 != only - 1) continue;
+      if (only ? c2 != only - 1 : !shape_fits(c2, epi, M)) continue;
       const float y = tile_cost(c, epi, M, cut, K, 1) + tile_cost(c2, epi, M, frags - cut, K, 1) + 3.0f;
       if (y < cost) { cost = y; best = {c, 1, cut, c2}; }
     }
@@ -782,7 +792,10 @@ static void launch_tile_shape(int shape, const GemmArgs &a, int KS, int f0, int 
     case 1: launch_tile_cfg<EPI, 2, 4, 2, 2, 3>(a, KS, f0, f1, s); break;
     case 2: launch_tile_cfg<EPI, 2, 4, 2, 1, 4>(a, KS, f0, f1, s); break;
     case 3: launch_tile_cfg<EPI, 4, 2, 1, 1, 3>(a, KS, f0, f1, s); break;
-    default: launch_tile_cfg<EPI, 2, 2, 1, 1, 4>(a, KS, f0, f1, s);
+    case 4: launch_tile_cfg<EPI, 2, 2, 1, 1, 4>(a, KS, f0, f1, s); break;
+    case 5: launch_tile_cfg<EPI, 1, 4, 9, 1, 3>(a, KS, f0, f1, s); break;
+    case 6: launch_tile_cfg<EPI, 4, 2, 3, 2, 2>(a, KS, f0, f1, s); break;
+    default: launch_tile_cfg<EPI, 2, 3, 3, 1, 4>(a, KS, f0, f1, s);
   }
 }
 
