@@ -61,7 +61,7 @@ struct ngg_ctx {
   hipGraphExec_t step_graph = nullptr;
   hipStream_t cap_stream = nullptr;   // the step is recorded on a stream of the library's own (the caller's may be the default
                                       // stream, which cannot be captured) and replayed on the caller's
-  int graph_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // k, w, k_ctx_max, q_min, q_max, attention slices and route, draft source, 1
+  int graph_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // k, w, k_ctx_max, q_min, q_max, attention slices and route, draft source and single-token route, 1
   int eager_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // the same of the last step launched on the stream (its kernels are loaded)
   size_t part_rows = 0;            // rows (slices x block rows rounded to 128) the attention partial buffers hold per head
   // device buffers
@@ -165,6 +165,13 @@ ngg_status dev_alloc(ngg_ctx *c, P **p, size_t bytes, bool zero) {
   return NGG_OK;
 }
 
+// A block of one token: the GEMMs run the RMSNorms and the merge of the attention slices themselves (launch_gemm_row).
+// Not while the norms' own time is asked for: a profile of that class needs them as launches.
+bool one_row_call(const ngg_ctx *c, int M) {
+  const ngg_model_desc &d = c->d;
+  return M == 1 && gemm_row_fits(d.dtype, d.d_model, d.n_heads * d.head_dim) && !((c->prof_mask >> NGG_PROF_NORM) & 1);
+}
+
 // One forward over a block of R rows x C columns sitting at positions P .. P+C-1 on a cached
 // context of P tokens (Section 3).  Leaves this block's keys/values in the scratch, and, when
 // `unembed` is set, the per-tile argmax partials (and optional logits) of every block position.
@@ -197,9 +204,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   int ks_o = gemm_residual_splits(dt, M, d.d_model, dq, c->tile_only);
   int ks_down = gemm_residual_splits(dt, M, d.d_model, d.d_ffn, c->tile_only);
   const int ss_segs = rmsnorm_segments(d.d_model);
-  // A block of one token: the GEMMs run the RMSNorms and the merge of the attention slices themselves (launch_gemm_row).
-  // Not while the norms' own time is asked for: a profile of that class needs them as launches.
-  const bool one_row = M == 1 && gemm_row_fits(dt, d.d_model, dq) && !((c->prof_mask >> NGG_PROF_NORM) & 1);
+  const bool one_row = one_row_call(c, M);
   RowArgs row{};
   float *h_cur = c->h, *h_next = c->h + d.d_model;   // row 1 of the residual stream is free; 2 n_layers swaps end in row 0
   if (one_row) {
@@ -749,7 +754,7 @@ static void step_key(const ngg_ctx *c, const ngg_draft_cfg &s, int key[8]) {
   key[0] = s.k; key[1] = s.w; key[2] = s.k_ctx_max; key[3] = s.q_min; key[4] = s.q_max;
   key[5] = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) |
            (attention_whole(d.dtype, d.head_dim, d.n_heads, M, c->n - 1) ? 1 << 16 : 0);
-  key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0);
+  key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0) | (one_row_call(c, M) ? 4 : 0);
   key[7] = 1;
 }
 
@@ -1202,7 +1207,7 @@ ngg_status ngg_debug_tiles(ngg_ctx *c, int32_t shape) {
   if (!c) return NGG_EINVAL;
   if (shape < -1 || shape >= gemm_tile_shapes()) return fail(c, NGG_EINVAL, "ngg_debug_tiles: shape must be -1 .. %d", gemm_tile_shapes() - 1);
   c->tile_only = shape + 1;
-  c->graph_key[7] = 0;                                  // a captured step holds the launches of the earlier choice
+  c->graph_key[7] = c->eager_key[7] = 0;                // a captured step holds the launches of the earlier choice
   return NGG_OK;
 }
 

@@ -442,6 +442,28 @@ def test_profile_classes_count_launches_and_sampling(tiny):
         ctx.profile_sample(0)
 
 
+def test_a_step_profiled_with_its_norms_is_not_the_one_captured_afterwards(tiny):
+    """A single-token step runs other kernels while its norms are bracketed.  The first step after that has to run on the
+    stream (its kernels may never have been launched) before one is captured."""
+    desc, run, w, prompt, model, ctx = tiny
+    try:
+        ctx.step_graphs(1)
+        ctx.prefill(prompt)
+        ctx.profile_enable(1 << ngg.PROF_CLASSES.index("norm"))
+        ctx.decode_more(3, 3, None)
+        ctx.profile_enable(0)
+        counts = [ctx.debug_peek("step_graphs", np.int32)[0][2:].tolist()]
+        for _ in range(2):
+            ctx.decode_more(2, 1, None)
+            counts.append(ctx.debug_peek("step_graphs", np.int32)[0][2:].tolist())
+    finally:
+        ctx.profile_enable(0)
+        ctx.profile_reset()
+        ctx.step_graphs(2)
+    assert counts[1] == counts[0], counts                  # on the stream
+    assert counts[2] == [counts[0][0] + 1, counts[0][1] + 1], counts
+
+
 def test_state_and_capacity_errors(tiny):
     desc, run, w, prompt, model, _ = tiny
     ctx = ngg.Context(desc, w, max_seq=140, max_k=4, max_w=3)
