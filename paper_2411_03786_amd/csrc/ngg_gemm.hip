@@ -405,9 +405,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 template <bool NT>
 __device__ __forceinline__ void lds_dma16(const void *base, unsigned off, unsigned lds) {
   if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
   else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
 }
 __device__ __forceinline__ void wave_lds_fence() {       // LDS written by other lanes of this wave is readable behind it
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

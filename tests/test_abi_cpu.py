@@ -132,3 +132,17 @@ def test_blocks_of_257_to_384_tokens_do_not_compute_512_rows(lib, tokens):
         p = ngg.debug_plan("bf16", "gateup", tokens, f, d)
         rows = -(-tokens // p["tile_tokens"]) * p["tile_tokens"]
         assert p["kernel"] == 1 and p["first_frags"] == f // 8 and rows < 1.5 * tokens, p
+
+
+def test_inline_assembly_names_the_registers_it_writes():
+    """Every asm statement of the kernels that writes m0 declares it: the compiler keeps values of its own there."""
+    csrc = os.path.join(ROOT, "paper_2411_03786_amd", "csrc")
+    seen = 0
+    for name in sorted(os.listdir(csrc)):
+        if not name.endswith((".hip", ".h")):
+            continue
+        for stmt in re.findall(r"asm volatile\((.*?)\);", open(os.path.join(csrc, name)).read(), flags=re.S):
+            if re.search(r"s_mov_b32 m0", stmt):
+                seen += 1
+                assert '"m0"' in stmt.rsplit(":", 1)[1], (name, stmt)
+    assert seen >= 2
