@@ -929,6 +929,9 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
 //    26.8 -> 27.4 / 32.6 -> 28.4, 2048 x 5504 7.6 -> 7.7 / 8.5 -> 8.0 / 9.8 -> 8.1 / 9.9 -> 8.4 / 12.8 -> 10.1.  Where the skinny
 //    kernel's workgroups come to more than one per CU the second round costs it most (3072-wide, 288 workgroups: down
 //    16.2 -> 11.7 / 17.7 -> 11.8 / 19.4 -> 12.0 / 20.2 -> 12.3 / 28.3 -> 16.4, projection 8.1 -> 6.9 / 9.8 -> 7.1 / 11.4 -> 7.2).
+//    Left to the skinny kernel: down of 65 to 80 rows on models of 4096 and wider, where it computes 80 rows and a tile 128
+//    (65 / 79 rows: 4096 x 14336 27.3 -> 33.0 / 28.3 -> 34.7, 4096 x 11008 24.1 -> 27.0 / 24.7 -> 28.4,
+//    8192 x 28672 89.1 -> 86.1 / 89.6 -> 96.0; whole steps within 2 % of each other either way).
 //  * gate/up and q/k/v of 65 rows or more on narrow models, where one or two fragments per workgroup leave too little in
 //    flight (768-wide, 97 rows: 9.6 -> 7.1 and 9.9 -> 8.0; 65 rows 8.0 -> 7.1, 8.3 -> 8.0); wide models stream W as fast
 //    either way (4096-wide, 97 rows: 49.4 and 47.5-50.6, 33.8 and 35.3).
@@ -947,6 +950,20 @@ static bool takes_tile(int epi, int M, int frags, int K, int tile_only) {
 int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only) {
   if (dtype == 1 && takes_tile(EPI_RESIDUAL, M, N / 16, K, tile_only)) return tile_plan(EPI_RESIDUAL, M, N / 16, K, tile_only).KS;
   return skinny_residual_splits(dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value, M, N, K);
+}
+
+// fp32: the row tile the block needs.  16-bit: takes_tile leaves this kernel the blocks of up to 24 rows (up to 16 always in the
+// 1 x 4 layout) and, in the 2 x 2 layout, those of 65 to 80.
+template <typename T, int WN, int WK>
+static void launch_residual(const GemmArgs &a, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) launch_fm<T, EPI_RESIDUAL, WN, WK, 4>(a, a.KS, s);
+  else if constexpr (WN == 1) {
+    if (a.M <= 16) launch_gemm_cfg<T, EPI_RESIDUAL, 1, WN, WK, 4>(a, a.KS, s);
+    else launch_gemm_cfg<T, EPI_RESIDUAL, 2, WN, WK, 4>(a, a.KS, s);
+  } else {
+    if (a.M <= 32) launch_gemm_cfg<T, EPI_RESIDUAL, 2, WN, WK, 4>(a, a.KS, s);
+    else launch_gemm_cfg<T, EPI_RESIDUAL, 5, WN, WK, 4>(a, a.KS, s);
+  }
 }
 
 // Workgroup shapes measured on MI355X at the 7B shapes (M = 60 and M = 1).  Unembedding: wide tiles
@@ -973,8 +990,8 @@ static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
     case EPI_QKV: launch_paired<T, EPI_QKV>(a, s); break;
     case EPI_GATEUP: launch_paired<T, EPI_GATEUP>(a, s); break;
     case EPI_RESIDUAL:
-      if (residual_narrow(a.M, a.N, a.K)) launch_fm<T, EPI_RESIDUAL, 1, 4, 4>(a, a.KS, s);
-      else launch_fm<T, EPI_RESIDUAL, 2, 2, 4>(a, a.KS, s);
+      if (residual_narrow(a.M, a.N, a.K)) launch_residual<T, 1, 4>(a, s);
+      else launch_residual<T, 2, 2>(a, s);
       break;
     default:
       if (wide) launch_fm<T, EPI_UNEMBED, 4, 1, 8>(a, 1, s);
