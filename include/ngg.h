@@ -214,9 +214,9 @@ ngg_status ngg_allocation(ngg_ctx *ctx, int32_t mode, int32_t coverage_percent, 
  * step after step and is captured again only when k, w, the draft settings or the number of attention slices change.
  * Steps that the generation budget clamps (the last ones), steps with profiling brackets enabled and the first step
  * of every shape are always launched on the stream.  mode 0: never replay.  mode 1: replay every step that qualifies.
- * mode 2 (default): per step shape, time three steps launched on the stream and, unless those took more than 6 us
- * per kernel launch (a step bound by the device: replay cannot win and the capture is not paid), three replayed; keep the
- * faster way (replay pays where a step is bound by its launches: small models; at the 7B shapes it measured no
+ * mode 2 (default): per step shape, time three steps launched on the stream and, unless those took more than 12 us
+ * per kernel launch of a single-token step or 6 us of a block (a step bound by the device: replay cannot win and the
+ * capture is not paid), three replayed; keep the faster way (replay pays where a step is bound by its launches: small models; at the 7B shapes it measured no
  * gain).  In every
  * mode the same kernels run in the same shapes: the committed tokens and the statistics are identical.
  * ngg_build_drafts, ngg_verify_step and ngg_commit called directly always launch on the stream. */
@@ -286,7 +286,9 @@ ngg_status ngg_profile_read_bandwidth(ngg_ctx *ctx, double *gbps);
  * chunks of 256 (bf16) or 128 (fp32) features: [feature chunk][Mcap rows][chunk]).
  * "attn_layout" (int32[4], host-side record of the last model call: slices of the key list per head,
  * workgroups of the attention kernel, block rows, cached positions).  "step_graphs" (int32[4], host-side record:
- * replay mode, a capture failed, captures so far, replayed steps so far).  Synchronises the stream. */
+ * replay mode, a capture failed, captures so far, replayed steps so far).  "step_launches" (int32[2], host-side record:
+ * kernels the last step of ngg_decode_more launches, nodes of the last captured step: one more).  Synchronises the
+ * stream. */
 ngg_status ngg_debug_peek(ngg_ctx *ctx, const char *name, void *dst, int64_t cap, int64_t *bytes, int32_t *stride);
 
 /* Test aids.  ngg_debug_plan: what a model call on `tokens` block tokens launches for one of its GEMMs (gemm 0 = q, k and

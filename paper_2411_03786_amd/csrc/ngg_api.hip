@@ -58,6 +58,8 @@ struct ngg_ctx {
   double tune_ms[2] = {0.0, 0.0};
   bool graph_broken = false;       // a capture or instantiation failed: stay with stream launches
   int32_t graph_captures = 0, graph_replays = 0;
+  int counted_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // the step shape step_kernels[0] was counted for
+  int32_t step_kernels[2] = {0, 0};   // kernels the last decode step launches (step_launches); nodes of the last captured step
   hipGraphExec_t step_graph = nullptr;
   hipStream_t cap_stream = nullptr;   // the step is recorded on a stream of the library's own (the caller's may be the default
                                       // stream, which cannot be captured) and replayed on the caller's
@@ -744,7 +746,27 @@ static int context_row_cap(const ngg_ctx *c, int configured) {
   return std::min(configured, std::max(1, cap));
 }
 
-constexpr double kGraphLaunchMs = 0.006;   // per kernel launch; steps slower than this are never captured in mode 2
+// Milliseconds per kernel launch above which a step is never captured in mode 2 (stream / replay, us per launch, MI355X).  A
+// single-token step gains 0.2-0.4 us per launch from replay, the 2 % that mode 2 asks for up to about 12 us a launch (12 x 768:
+// 5.1 -> 4.7, 8 x 2048: 8.1 -> 7.8, 8 x 2560: 11.3 -> 11.0, 8 x 4096: 18.2 -> 18.0); the launches of a block step are longer
+// than their queueing, and it gains nothing anywhere (33 tokens, 12 x 768: 5.12 -> 5.11, 8 x 2048: 7.75 -> 7.86).
+constexpr double kGraphLaunchMsRow = 0.012, kGraphLaunchMsBlock = 0.006;
+
+// Kernels a decode step launches (the node that advances n_dev in a captured step not counted)
+static int step_launches(const ngg_ctx *c, const ngg_draft_cfg &s) {
+  const ngg_model_desc &d = c->d;
+  const int C = s.w + 1, M = block_tokens(s.k, C, C >= 2 ? 1 : 0);
+  const int drafts = c->bg_use || c->uni_use || s.w < 1 ? 2 : 3;
+  if (one_row_call(c, M)) return drafts + 1 + 5 * d.n_layers + 1 + 3;     // drafts, embedding, layers, unembedding, argmax + accept + commit
+  auto launches = [&](int epi, int N, int K) {                // a tiled GEMM may cut its matrix in two launches
+    const GemmPlan p = gemm_plan(d.dtype, epi, M, N, K);
+    return p.kernel == 1 && p.split < (epi == EPI_GATEUP ? N / 8 : N / 16) ? 2 : 1;
+  };
+  const int dq = d.n_heads * d.head_dim;
+  const int merge = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) > 1 ? 1 : 0;
+  const int layer = 5 + merge + launches(EPI_QKV, dq + 2 * d.n_kv_heads * d.head_dim, d.d_model) + launches(EPI_GATEUP, d.d_ffn, d.d_model);
+  return drafts + 1 + layer * d.n_layers + 1 + launches(EPI_UNEMBED, d.vocab, d.d_model) + 3;
+}
 
 // What fixes the launch shapes and constant arguments of a decode step: a captured step is replayed only while
 // these stay the same (the number of attention slices moves with the context length)
@@ -790,6 +812,8 @@ static ngg_status graph_step(ngg_ctx *c, const ngg_draft_cfg &step, const int ke
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(c->cap_stream, &g);
     c->stream = callers;
+    size_t nodes = 0;
+    if (st == NGG_OK && e == hipSuccess && hipGraphGetNodes(g, nullptr, &nodes) == hipSuccess) c->step_kernels[1] = (int32_t)nodes;
     if (st == NGG_OK && e == hipSuccess) e = hipGraphInstantiate(&c->step_graph, g, nullptr, nullptr, 0);
     if (g) (void)hipGraphDestroy(g);
     if (st != NGG_OK || e != hipSuccess) {
@@ -844,6 +868,10 @@ static ngg_status decode_loop(ngg_ctx *c, int n0, int n_gen, int64_t max_calls, 
     // needs the stream (profiling brackets) and no clamp on what it may commit, is replayed from a captured graph
     int key[8];
     step_key(c, step, key);
+    if (memcmp(key, c->counted_key, sizeof key) != 0) {
+      memcpy(c->counted_key, key, sizeof key);
+      c->step_kernels[0] = step_launches(c, step);
+    }
     bool replayed = false;
     const bool qualifies = c->graph_mode != 0 && !c->graph_broken && c->prof_mask == 0 && left >= step.w + 1 &&
                            c->n + step.w + 1 <= c->d.max_seq;
@@ -882,10 +910,10 @@ static ngg_status decode_loop(ngg_ctx *c, int n0, int n_gen, int64_t max_calls, 
       else {
         c->tune_ms[which] = std::min(c->tune_ms[which], now_ms() - t0);
         ++c->tune_count;
-        // A step that takes more than kGraphLaunchMs per kernel it launches (ten per layer, a dozen around them) is
-        // bound by the device, not by its launches (the host queues one in about 2.5 us): replay cannot win, so
-        // the capture (milliseconds for a 32-layer step) is not paid either.
-        if (c->tune_count == 3 && c->tune_ms[0] > kGraphLaunchMs * (10 * c->d.n_layers + 12)) c->tune_choice = 0;
+        // a step whose kernels are that long is bound by the device, not by its launches (the host queues one in about
+        // 2.5 us): replay cannot win, so the capture (milliseconds for a 32-layer step) is not paid either
+        const double limit = (key[6] & 4 ? kGraphLaunchMsRow : kGraphLaunchMsBlock) * c->step_kernels[0];
+        if (c->tune_count == 3 && c->tune_ms[0] > limit) c->tune_choice = 0;
         else if (c->tune_count == 6) c->tune_choice = c->tune_ms[1] < 0.98 * c->tune_ms[0] ? 1 : 0;
       }
     }
@@ -1237,6 +1265,11 @@ ngg_status ngg_debug_peek(ngg_ctx *c, const char *name, void *dst, int64_t cap, 
     const int32_t v[4] = {c->graph_mode, c->graph_broken ? 1 : 0, c->graph_captures, c->graph_replays};
     *bytes = (int64_t)sizeof v;
     if (dst && cap > 0) memcpy(dst, v, std::min((size_t)cap, sizeof v));
+    return NGG_OK;
+  }
+  else if (nm == "step_launches") {                     // host-side record: kernels of the last decode step, nodes of the last captured one
+    *bytes = (int64_t)sizeof c->step_kernels;
+    if (dst && cap > 0) memcpy(dst, c->step_kernels, std::min((size_t)cap, sizeof c->step_kernels));
     return NGG_OK;
   }
   else return fail(c, NGG_EINVAL, "ngg_debug_peek: unknown buffer '%s'", name);

@@ -136,6 +136,24 @@ def test_graph_replay_equals_stream_launches(tiny):
         ctx.step_graphs(2)
 
 
+@pytest.mark.parametrize("dtype,k,w,max_k", [
+    ("f32", 1, 0, 4), ("f32", 4, 3, 4), ("bf16", 1, 0, 4), ("bf16", 4, 3, 4), ("bf16", 16, 16, 16),
+])
+def test_the_launches_a_step_is_reckoned_with_are_those_it_captures(dtype, k, w, max_k):
+    """The number of kernels per step decides whether a capture is tried at all: it has to be what the captured step holds
+    (one node more, which advances the context length), for single tokens, short blocks and blocks on the tiled GEMMs."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=4, n_kv_heads=4, head_dim=64, d_model=256, d_ffn=512, vocab=2048, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=700 if k == 4 else 100, n_gen=80, k=k, w=w, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=max_k, max_w=16)
+    ctx.step_graphs(1)
+    ctx.prefill(prompt)
+    ctx.decode_more(60, 3, run)
+    counted, nodes = ctx.debug_peek("step_launches", np.int32)[0].tolist()
+    assert ctx.debug_peek("step_graphs", np.int32)[0][2] >= 1
+    ctx.close()
+    assert nodes == counted + 1
+
+
 def test_injected_drafts_every_accept_length(tiny):
     desc, run, w, prompt, model, ctx = tiny
     V = desc["vocab"]
