@@ -814,23 +814,32 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd):
     assert rep.max_rel_logit_err <= 2e-2, rep
 
 
-@pytest.mark.parametrize("dtype,layers,heads,kv,hd,d_model,d_ffn,prompt_len", [
-    ("f32", 2, 3, 3, 32, 96, 160, 70),            # 3 steps of the contraction: waves without one
-    ("f32", 1, 2, 2, 64, 128, 2112, 1500),        # 11 slices of the key list (two rounds of the merge)
-    ("bf16", 3, 5, 1, 64, 320, 608, 333),         # grouped heads; more than two residual partials
-    ("bf16", 2, 2, 2, 128, 256, 96, 1500),        # 11 slices; heads cut by the contraction split
-    ("bf16", 1, 33, 3, 128, 4224, 4160, 40),      # a row of more than 4096 features: two rounds of the norm
+@pytest.mark.parametrize("dtype,layers,heads,kv,hd,d_model,d_ffn,prompt_len,parts,slices", [
+    ("f32", 2, 3, 3, 32, 96, 160, 70, (1, 1), 1),            # 3 steps of the contraction: waves without one
+    ("f32", 1, 2, 2, 64, 128, 2112, 1500, (1, 8), 12),       # 12 slices of the key list (two rounds of the merge); 8 partials in the unembedding's prologue
+    ("f32", 2, 32, 4, 64, 128, 2112, 333, (8, 8), 3),        # 8 partials in the prologues of q/k/v and gate/up
+    ("bf16", 3, 5, 1, 64, 320, 800, 333, (1, 3), 3),         # grouped heads; 3 partials of the 8 that are fetched
+    ("bf16", 2, 5, 5, 128, 256, 96, 1500, (2, 1), 12),       # the third head is cut by the contraction split; 12 slices
+    ("bf16", 1, 33, 3, 128, 4224, 4160, 40, (2, 2), 1),      # a row of more than 4096 features: two rounds of the norm
+    ("bf16", 2, 8, 2, 128, 2080, 1056, 40, (4, 4), 1),       # 4 partials and more than 2048 features: two rounds of two
 ])
-def test_single_token_steps_with_the_norms_and_the_merge_inside_the_gemms(dtype, layers, heads, kv, hd, d_model, d_ffn, prompt_len):
+def test_single_token_steps_with_the_norms_and_the_merge_inside_the_gemms(dtype, layers, heads, kv, hd, d_model, d_ffn, prompt_len,
+                                                                        parts, slices):
     """gemm_row_kernel (blocks of one token): plain greedy steps against the oracle, logits at every step, at the edges
-    of its prologues and splits.  The tolerance is the one of every lock-step test of the type."""
+    of its prologues and splits: parts = residual partials of the output projection and of down, slices = of the key list.
+    The tolerance is the one of every lock-step test of the type."""
     desc = dict(si.reduced_layers(si.MODELS["small"], layers), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=d_model,
                 d_ffn=d_ffn, vocab=2048, dtype=dtype)
     run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=12, k=1, w=0, k_ctx_max=0, q_min=1, q_max=1)
+    plans = [ngg.debug_plan(dtype, "residual", 1, d_model, width) for width in (heads * hd, d_ffn)]
+    assert all(p["kernel"] == 2 for p in plans) and tuple(p["splits"] for p in plans) == parts
     w_, prompt, model, ctx = _setup(desc, run, random_gains=True)
-    rep = lockstep_run(ctx, model, prompt, 4, run, TOL[dtype], max_steps=3)
+    layouts = []
+    rep = lockstep_run(ctx, model, prompt, 4, run, TOL[dtype], max_steps=3,
+                       on_step=lambda step: layouts.append(ctx.debug_peek("attn_layout", np.int32)[0].tolist()))
     ctx.close()
     assert rep.max_rel_logit_err <= TOL[dtype], rep
+    assert layouts[0][0] == slices and layouts[0][2:] == [1, prompt_len], layouts
 
 
 @pytest.mark.parametrize("dtype,heads,hd,prompt_len,k,wd,splits,wgs", [
