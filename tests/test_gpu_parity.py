@@ -774,6 +774,35 @@ def test_row_tiles_of_256_with_an_odd_number_of_contraction_slices_16_bit():
     ctx.close()
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_bigram_selection_above_512_scores_per_workgroup_with_exact_ties(dtype):
+    """A vocabulary of 163840: every workgroup of the sweep selects from 640 scores in two rounds, the second carrying
+    the first one's picks along.  Rows of the output embedding are repeated so that scores tie exactly inside a lane,
+    between lanes, rounds and workgroups: the picks are the best by (score, lower id) of the scores the sweep left."""
+    V = 163840
+    desc = dict(si.reduced_layers(si.MODELS["small"], 1), n_heads=1, n_kv_heads=1, head_dim=32, d_model=32, d_ffn=32, vocab=V, dtype=dtype)
+    w = si.make_weights(desc, seed=0)
+    u = w["tok_emb"][0]
+    w["tok_emb"][:] = u                                    # the same sweep whatever the last token is
+    wg = 3 * 640                                           # first score of a workgroup
+    high = [wg + 5, wg + 5 + 64, wg + 6, wg + 517, wg + 639, 7, V - 1]            # one value, seven places
+    low = [wg + 4, wg + 512, wg + 600, wg + 640, 11, 12, 13, 640 * 200 + 300]
+    scale = 4.0 * np.max(np.abs(w["unemb"])) / np.max(np.abs(u))                  # far above the other rows' scores
+    scale = np.float32(2.0 ** np.ceil(np.log2(scale)))     # (a power of two keeps the rows representable)
+    w["unemb"][high] = 2 * scale * u
+    w["unemb"][low] = scale * u
+    ctx = ngg.Context(desc, w, max_seq=64, max_k=32, max_w=2)
+    ctx.prefill(np.arange(20, dtype=np.int32))
+    for k in (32, 10, 3):
+        drafts, src, n_ctx = ctx.build_drafts(dict(k=k, w=2, k_ctx_max=0, q_min=1, q_max=1))
+        z, _ = ctx.debug_peek("z", np.float32)
+        order = np.lexsort((np.arange(V), -z))[:k]
+        assert n_ctx == 0 and list(drafts[:, 0]) == list(order)
+        assert list(order[:15]) == (sorted(high) + sorted(low))[:k]
+        assert np.all(drafts[:, 1] == min(high))           # every chain goes to the best row, lowest id first
+    ctx.close()
+
+
 @pytest.mark.parametrize("shape", range(8))
 @pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd", [
     (3, 1, 64, 448, 550, 16, 16),     # odd numbers of slices (3 and 7), grouped heads; 257 block tokens, a prompt cut by every tile height
