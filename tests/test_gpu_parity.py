@@ -824,19 +824,24 @@ def test_every_tile_shape_16_bit(shape, heads, kv, hd, d_ffn, prompt_len, k, wd)
     assert rep.max_rel_logit_err <= TOL["bf16"], rep
 
 
-@pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd", [
-    (5, 5, 32, 224, 257, 16, 8),      # widths 160 and 224: the last 64-element slice is half padding; 257 = one row more than a tile
-    (5, 1, 64, 608, 300, 16, 16),     # grouped heads; 257 block rows; the weights end inside a tile of W rows
-    (6, 2, 128, 96, 130, 20, 6),      # a contraction of 2 slices, heads of 128; 121 block rows: residual GEMMs tiled, q/k/v and gate/up tiled below 129
-    (3, 3, 32, 2080, 1100, 5, 13),    # five row tiles of 256; 66 block rows
+@pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd,tile,parts", [
+    (5, 5, 32, 224, 257, 16, 8, (64, 64), (1, 2)),       # widths 160 and 224: the last 64-element slice is half padding; 257 = one row more than four tiles
+    (5, 1, 64, 608, 300, 16, 16, (64, 64), (2, 5)),      # grouped heads; 257 block rows
+    (6, 2, 128, 96, 130, 20, 6, (64, 64), (6, 1)),       # a contraction of 1.5 slices, heads of 128; 121 block rows, tiled too but for the unembedding
+    (3, 3, 32, 2080, 1100, 5, 13, (128, 256), (1, 7)),   # nine row tiles of 128, the last of 76 rows; W ends inside its last tile; 66 block rows
 ])
-def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd):
-    """gemm_tile_kernel where its tiles end: rows past the block, W rows past the matrix, contractions that are not a
-    multiple of the 64-element slice, K/V rows written into a partly filled tile of 32 positions.  A prompt (prefill
-    pieces) and then one verify block against the oracle; the tolerance is the one of every 16-bit lock-step test."""
+def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd, tile, parts):
+    """gemm_tile_kernel where its tiles end, in the shapes chosen by size (tile: gate/up of the prompt; parts: contraction
+    splits of its residual GEMMs): rows past the block, W rows past the matrix, contractions that are not a multiple of the
+    64-element slice, K/V rows written into a partly filled tile of 32 positions.  A prompt (prefill pieces) and then one
+    verify block against the oracle; the tolerance is the one of every 16-bit lock-step test."""
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=heads * hd if heads != 6 else 192,
                 d_ffn=d_ffn, vocab=4096)
     run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=64, k=k, w=wd, k_ctx_max=4)
+    d = desc["d_model"]
+    plan = ngg.debug_plan("bf16", "gateup", prompt_len, d_ffn, d)
+    assert (plan["tile_tokens"], plan["tile_rows"]) == tile
+    assert tuple(ngg.debug_plan("bf16", "residual", prompt_len, d, width)["splits"] for width in (heads * hd, d_ffn)) == parts
     w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
     rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=2)
     ctx.close()
@@ -937,7 +942,7 @@ def test_7b_width_two_layer_twin_bf16_lockstep():
 
 
 def test_7b_width_one_layer_twin_long_context_shape():
-    """The long-context configuration's draft shape (k=16, w=6: 112 block rows, query back-off q=3..1)
+    """The long-context configuration's draft shape (k=16, w=6: 97 block tokens, query back-off q=3..1)
     at 7B widths, one layer, prompt 1536: the 128-row GEMM tiles at K = 4096 / 14336 and the
     two-query-group attention workgroups at head_dim 128."""
     desc = si.reduced_layers(si.MODELS["7b"], 1)
@@ -950,7 +955,7 @@ def test_7b_width_one_layer_twin_long_context_shape():
 
 
 def test_7b_width_one_layer_twin_at_the_long_context_configurations_own_length():
-    """Config 4 at its own context: prompt 16384 (50 % copied spans), k=16, w=6 (112 block rows), query
+    """Config 4 at its own context: prompt 16384 (50 % copied spans), k=16, w=6 (97 block tokens), query
     back-off q = 3..1, 7B widths, one layer.  The oracle takes the prompt in 512-token pieces through its
     cached block call.  Covers what the shorter twins do not reach: rotary angles, cache tiles and the key
     list at positions up to 16.4K, and the attention launch this shape takes (its slice count and workgroup
@@ -974,13 +979,13 @@ def test_7b_width_one_layer_twin_at_the_long_context_configurations_own_length()
     assert layouts[0][:2] == list(EXPECTED_LONG_CONTEXT_LAYOUT), layouts[0]
 
 
-EXPECTED_LONG_CONTEXT_LAYOUT = (16, 512)      # slices per head, workgroups (two per CU) at M = 112, P = 16384, 32 heads
+EXPECTED_LONG_CONTEXT_LAYOUT = (16, 512)      # slices per head, workgroups (two per CU) at M = 97, P = 16384, 32 heads
 
 
 @pytest.mark.parametrize("k,w", [(10, 5), (32, 8)])
 def test_3b_width_one_layer_twin_at_the_large_vocabulary_configurations_own_length(k, w):
     """Config 5 at its own context: prompt 4096, 3B widths (24 heads of 128, vocabulary 128256), one layer;
-    k=10, w=5 and the largest block of its grid, k=32, w=8 (288 rows)."""
+    k=10, w=5 and the largest block of its grid, k=32, w=8 (257 block tokens)."""
     desc = si.reduced_layers(si.MODELS["3b"], 1)
     run = dict(si.RUNS["cfg5"], k=k, w=w, k_ctx_max=k, n_gen=20)
     assert run["prompt_len"] == 4096
@@ -1001,7 +1006,7 @@ def test_3b_width_one_layer_twin_at_the_large_vocabulary_configurations_own_leng
 def test_3b_width_one_layer_twin_large_vocabulary(k, w):
     """The large-vocabulary configuration's widths (d 3072, 24 heads of 128, FFN 8192, vocab 128256),
     one layer, prompt 512: bigram sweep, next1 table and argmax over 128256 rows; k=32, w=8 is the
-    largest block of its sweep (288 rows: three passes of 128-row tiles)."""
+    largest block of its sweep (257 block tokens)."""
     desc = si.reduced_layers(si.MODELS["3b"], 1)
     run = dict(si.RUNS["cfg5"], prompt_len=512, k=k, w=w, k_ctx_max=k, n_gen=20)
     w_, prompt, model, ctx = _setup(desc, run)
