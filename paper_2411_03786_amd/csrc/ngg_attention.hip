@@ -13,7 +13,7 @@
 //    groups of 16*QF queries and all need every tile, so the workgroup copies each tile into LDS once
 //    (a linear copy: the tile already is in fragment order, so every fragment read is conflict-free)
 //    and the waves read their MFMA operands from there.  No merge between waves.
-//  * attn_stream_kernel (up to 16 block tokens, the single-token decode step; up to 64 on short lists): one group
+//  * attn_stream_kernel (up to 16 block tokens, the single-token decode step; up to 64 on short lists, attention_whole): one group
 //    of 16 queries per workgroup, so its waves split the tiles instead and each tile goes from global memory straight
 //    into the registers of the one wave that needs it; LDS only carries the final merge of the waves.
 #include "ngg_internal.h"
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(64 * NW) void attn_stream_kernel(const AttnArgs a, 
 
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   T *qs = reinterpret_cast<T *>(smem);                      // [QF][DS][64 lanes][8]: the queries as fragments
-  float *red = reinterpret_cast<float *>(smem + (size_t)QF * DS * 512 * sizeof(T));   // [4 waves][DUMP][64]
+  float *red = reinterpret_cast<float *>(smem + (size_t)QF * DS * 512 * sizeof(T));   // [NW waves][DUMP][64]
 
   // ---- the tile list: NP cached tiles, then the NS tiles of the block's own keys that hold the draft
   //      rows of this workgroup's queries; this workgroup takes list entries [t_begin, t_end) -----------

@@ -379,11 +379,11 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_skinny_kernel(const GemmArg
 // (16 bytes per lane, no registers in between), in slices of 64 contraction elements, NST slices deep.  Before, W went
 // into registers and the two waves that shared a fragment both fetched it: a 128 x 256 tile asked the L2 for 64 KB per
 // slice, as much as the path between L2 and CU carries in the slice's MFMA time; a 256 x 256 tile fed through LDS asks
-// for half of that per flop.  Measured at the 7B shapes, 2048 rows: gate/up 500 -> 431 us (1.12 PFLOP/s; a library
-// GEMM of the same size reaches 1.11-1.18), down 250 -> 213, output projection 85 -> 74; 777 rows: gate/up 256 -> 210,
+// for half of that per flop.  Measured at the 7B shapes, 2048 rows: gate/up 500 -> 414 us (1.16 PFLOP/s; a library
+// GEMM of the same size reaches 1.11-1.18), down 250 -> 217, output projection 85 -> 72; 777 rows: gate/up 256 -> 210,
 // q/k/v 194 -> 109, down 186 -> 121, projection 67 -> 38; a 768-wide model at 777 rows: 34 -> 15, 27 -> 13, 20 -> 12.5,
 // 22 -> 6.4 (small tiles fill the chip where three 288-row tiles left most CUs idle).  What is left at 2048 rows: the
-// matrix cores are busy 55-63 % of the cycles at the 1.8 GHz the card holds under this load, the LDS about as much.
+// matrix cores are busy 54-64 % of the cycles at the 1.8 GHz the card holds under this load, the LDS 22-25 %.
 //
 // One slice is four multiplication steps of 16 contraction elements.  The fragments of a step are read from LDS under
 // the previous step's MFMAs; the barrier that hands over the buffers sits before the last step, whose operands are in
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs 
     }
   } else if constexpr (EPI == EPI_GATEUP) {
     // the tile's activations go through LDS, so that a row's features leave in 16-byte pieces side by side (8-byte
-    // pieces of 32 rows per instruction: 445 instead of 431 us at 2048 rows)
+    // pieces of 32 rows per instruction cost 3 % more at 2048 rows)
     constexpr int LDO = TN / 2 + 8;                      // LDS row stride in elements
     T *ot = reinterpret_cast<T *>(smem + TM * sizeof(float));
 #pragma unroll
@@ -723,7 +723,8 @@ static void launch_tile_cfg(const GemmArgs &a, int KS, int frag_first, int frag_
 }
 
 // Tile shapes of gemm_tile_kernel with what a workgroup costs: microseconds per slice of 64 contraction elements, and
-// for its start and epilogue (fitted to launches at the 7B shapes and at 768-wide ones, 97 to 2048 rows, on MI355X).
+// for its start and epilogue (fitted to launches at the 7B shapes above 128 rows and at 768-wide ones from 97, up to 2048, on
+// MI355X; below that it is optimistic for wide models, 29.5 us where q/k/v of 97 rows took 35.3: takes_tile decides there).
 // The last three are for 257 to 384 rows, which the 256-row tile computes as 512 and the 128-row one as 384 in one and a
 // half rounds (7B shapes, us; before them -> with them): gate/up as one row tile of 288 or 384, 257 rows 118 -> 83, 289-384
 // rows 118-121 -> 97-100; q/k/v as two of 192 x 96, one full round, 67 -> 50-52.  The 288-row tile runs on four waves of

@@ -426,7 +426,7 @@ __global__ __launch_bounds__(1024) void ctx_match_kernel(const DraftArgs a) {
 // ---------------------------------------------------------------------------------------------
 // Model bigram scores z[v] = <unemb[v], tok_emb[x_last]> (Section 4.1).  The output embedding is
 // read in operand order: a wave owns groups of 16 vocabulary rows and streams them as one flat
-// sequence of 1 KB fragment loads, a ring of 8 ahead; the contraction runs on MFMA with the
+// sequence of 1 KB fragment loads, a ring of 16 ahead; the contraction runs on MFMA with the
 // embedding of x_last as every column of the other operand (the matrix cores are idle anyway and
 // this keeps the vector ALU out of the way of the loads).  fp32 accumulation.
 // ---------------------------------------------------------------------------------------------
