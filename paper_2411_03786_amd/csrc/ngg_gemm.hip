@@ -930,9 +930,10 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
 //    26.8 -> 27.4 / 32.6 -> 28.4, 2048 x 5504 7.6 -> 7.7 / 8.5 -> 8.0 / 9.8 -> 8.1 / 9.9 -> 8.4 / 12.8 -> 10.1.  Where the skinny
 //    kernel's workgroups come to more than one per CU the second round costs it most (3072-wide, 288 workgroups: down
 //    16.2 -> 11.7 / 17.7 -> 11.8 / 19.4 -> 12.0 / 20.2 -> 12.3 / 28.3 -> 16.4, projection 8.1 -> 6.9 / 9.8 -> 7.1 / 11.4 -> 7.2).
-//    Left to the skinny kernel: down of 65 to 80 rows on models of 4096 and wider, where it computes 80 rows and a tile 128
-//    (65 / 79 rows: 4096 x 14336 27.3 -> 33.0 / 28.3 -> 34.7, 4096 x 11008 24.1 -> 27.0 / 24.7 -> 28.4,
-//    8192 x 28672 89.1 -> 86.1 / 89.6 -> 96.0; whole steps within 2 % of each other either way).
+//    Left to the skinny kernel: down of 65 to 96 rows on models 4096 to 5120 wide, where it computes 80 or 96 rows and a tile
+//    128.  The 128 x 128 tiles take 25-26 us there on some cards and 30-33 on others (4096 x 14336; skinny 27-30), so that
+//    8-layer steps of 81 to 93 rows came to 0.96-0.97 of the skinny kernel's on four cards and 1.00-1.03 on four.  Wider
+//    models run 128 x 256 tiles, faster on all of them (8192 x 28672, 81-93 rows: steps 0.97-0.98).
 //  * gate/up and q/k/v of 65 rows or more on narrow models, where one or two fragments per workgroup leave too little in
 //    flight (768-wide, 97 rows: 9.6 -> 7.1 and 9.9 -> 8.0; 65 rows 8.0 -> 7.1, 8.3 -> 8.0); wide models stream W as fast
 //    either way (4096-wide, 97 rows: 49.4 and 47.5-50.6, 33.8 and 35.3).
@@ -944,7 +945,7 @@ static bool takes_tile(int epi, int M, int frags, int K, int tile_only) {
   if (epi != EPI_RESIDUAL) return M > 64 ? frags <= 512 : (frags > 896 && frags <= 1024);
   const int N = frags * 16;
   if (skinny_residual_blocks(M, N, K) * skinny_residual_splits(KChunk<half_t>::value, M, N, K) > 256) return true;
-  return M > 24 && !(K > N && frags >= 256 && M > 64 && M <= 80);
+  return M > 24 && !(K > N && frags >= 256 && frags <= 320 && M > 64 && M <= 96);
 }
 
 // Split of the contraction across workgroups for the residual GEMMs
@@ -954,7 +955,7 @@ int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only) {
 }
 
 // fp32: the row tile the block needs.  16-bit: takes_tile leaves this kernel the blocks of up to 24 rows (up to 16 always in the
-// 1 x 4 layout) and, in the 2 x 2 layout, those of 65 to 80.
+// 1 x 4 layout) and, in the 2 x 2 layout, those of 65 to 96.
 template <typename T, int WN, int WK>
 static void launch_residual(const GemmArgs &a, hipStream_t s) {
   if constexpr (sizeof(T) == 4) launch_fm<T, EPI_RESIDUAL, WN, WK, 4>(a, a.KS, s);
@@ -963,7 +964,8 @@ static void launch_residual(const GemmArgs &a, hipStream_t s) {
     else launch_gemm_cfg<T, EPI_RESIDUAL, 2, WN, WK, 4>(a, a.KS, s);
   } else {
     if (a.M <= 32) launch_gemm_cfg<T, EPI_RESIDUAL, 2, WN, WK, 4>(a, a.KS, s);
-    else launch_gemm_cfg<T, EPI_RESIDUAL, 5, WN, WK, 4>(a, a.KS, s);
+    else if (a.M <= 80) launch_gemm_cfg<T, EPI_RESIDUAL, 5, WN, WK, 4>(a, a.KS, s);
+    else launch_gemm_cfg<T, EPI_RESIDUAL, 6, WN, WK, 4>(a, a.KS, s);
   }
 }
 

@@ -848,6 +848,19 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd, tile, 
     assert rep.max_rel_logit_err <= 2e-2, rep
 
 
+@pytest.mark.parametrize("k,wd,kernel", [(16, 4, 0), (16, 5, 0), (19, 5, 0), (16, 6, 1)])
+def test_down_of_4096_wide_models_on_both_sides_of_96_tokens(k, wd, kernel):
+    """Blocks of 65, 81 and 96 tokens run down on the streaming kernel (five and six column blocks, 2 x 2 waves, split
+    contraction), one of 97 on the tiled one; the tolerance is the one of every 16-bit lock-step test."""
+    assert ngg.debug_plan("bf16", "residual", 1 + k * wd, 4096, 4160)["kernel"] == kernel
+    desc = dict(si.reduced_layers(si.MODELS["small"], 1), n_heads=4, n_kv_heads=2, head_dim=128, d_model=4096, d_ffn=4160, vocab=2048)
+    run = dict(si.RUNS["cfg2"], prompt_len=150, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run)
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=2)
+    ctx.close()
+    assert rep.max_rel_logit_err <= TOL["bf16"], rep
+
+
 @pytest.mark.parametrize("dtype,layers,heads,kv,hd,d_model,d_ffn,prompt_len,parts,slices", [
     ("f32", 2, 3, 3, 32, 96, 160, 70, (1, 1), 1),            # 3 steps of the contraction: waves without one
     ("f32", 1, 2, 2, 64, 128, 2112, 1500, (1, 8), 12),       # 12 slices of the key list (two rounds of the merge); 8 partials in the unembedding's prologue
