@@ -725,19 +725,25 @@ static void launch_tile_cfg(const GemmArgs &a, int KS, int frag_first, int frag_
 // Tile shapes of gemm_tile_kernel with what a workgroup costs: microseconds per slice of 64 contraction elements, and
 // for its start and epilogue (fitted to launches at the 7B shapes above 128 rows and at 768-wide ones from 97, up to 2048, on
 // MI355X; below that it is optimistic for wide models, 29.5 us where q/k/v of 97 rows took 35.3: takes_tile decides there).
-// The last three are for 257 to 384 rows, which the 256-row tile computes as 512 and the 128-row one as 384 in one and a
+// The last two are for 129 to 192 rows as one row tile, where two tiles of 128 rows compute 256 and W is fetched for each of
+// them (gate/up, us: 145 rows 67 -> 55, 177 rows 70 -> 60; the kernel before this one took 64 at 145).  The three before them
+// are for 257 to 384 rows, which the 256-row tile computes as 512 and the 128-row one as 384 in one and a
 // half rounds (7B shapes, us; before them -> with them): gate/up as one row tile of 288 or 384, 257 rows 118 -> 83, 289-384
 // rows 118-121 -> 97-100; q/k/v as two of 192 x 96, one full round, 67 -> 50-52.  The 288-row tile runs on four waves of
 // nine MFMA blocks: on eight, two of the four SIMDs would have a wave more than the others.
 struct TileShape { int tm, tn; float slice_us, fixed_us; };
 constexpr TileShape kTileShapes[] = {{256, 256, 1.60f, 10.0f}, {128, 256, 0.98f, 8.0f}, {128, 128, 0.54f, 6.0f}, {128, 64, 0.36f, 4.5f}, {64, 64, 0.30f, 3.5f},
-                                     {288, 128, 1.13f, 10.0f}, {384, 128, 1.38f, 10.0f}, {192, 96, 0.65f, 7.0f}};
-constexpr int kNumTileShapes = 8;
+                                     {288, 128, 1.13f, 10.0f}, {384, 128, 1.38f, 10.0f}, {192, 96, 0.65f, 7.0f},
+                                     {160, 128, 0.70f, 9.5f}, {192, 128, 0.78f, 10.0f}};
+constexpr int kNumTileShapes = 10;
 
-// Which of them a launch chooses among.  Beyond 384 rows the last three only replace equals (7B: gate/up of 513 rows 163
+// Which of them a launch chooses among.  Beyond 384 rows the last five only replace equals (7B: gate/up of 513 rows 163
 // against 162 us, q/k/v of 641 rows 103 and 103); the residual GEMMs do without them (257 rows: 35.2 us on 128 x 256 with
 // five splits, 35.8 on 288 x 128 with eight, and the RMSNorm that adds the splits 7.7 -> 8.9).
-static bool shape_fits(int c, int epi, int M) { return c < 5 || (epi != EPI_RESIDUAL && M > 256 && M <= 384); }
+static bool shape_fits(int c, int epi, int M) {
+  if (c < 5) return true;
+  return epi != EPI_RESIDUAL && (c < 8 ? M > 256 && M <= 384 : M > 128 && M <= 192);
+}
 
 struct TilePlan { int shape, KS, split, shape2; };        // fragments from `split` on run as a second launch in shape2
 
@@ -796,7 +802,9 @@ static void launch_tile_shape(int shape, const GemmArgs &a, int KS, int f0, int 
     case 4: launch_tile_cfg<EPI, 2, 2, 1, 1, 4>(a, KS, f0, f1, s); break;
     case 5: launch_tile_cfg<EPI, 1, 4, 9, 1, 3>(a, KS, f0, f1, s); break;
     case 6: launch_tile_cfg<EPI, 4, 2, 3, 2, 2>(a, KS, f0, f1, s); break;
-    default: launch_tile_cfg<EPI, 2, 3, 3, 1, 4>(a, KS, f0, f1, s);
+    case 7: launch_tile_cfg<EPI, 2, 3, 3, 1, 4>(a, KS, f0, f1, s); break;
+    case 8: launch_tile_cfg<EPI, 1, 4, 5, 1, 4>(a, KS, f0, f1, s); break;
+    default: launch_tile_cfg<EPI, 2, 4, 3, 1, 4>(a, KS, f0, f1, s);
   }
 }
 

@@ -124,11 +124,13 @@ def test_short_contractions_get_a_tile_that_fits(lib, tokens, n, k):
     assert p["tile_tokens"] * p["tile_rows"] < 256 * 256 and p["tile_rows"] <= 128
 
 
-@pytest.mark.parametrize("tokens", [257, 273, 288, 289, 320, 353, 384])
-def test_blocks_of_257_to_384_tokens_do_not_compute_512_rows(lib, tokens):
+@pytest.mark.parametrize("tokens", [129, 145, 160, 161, 192, 257, 273, 288, 289, 320, 353, 384])
+def test_blocks_of_129_to_384_tokens_do_not_compute_half_as_many_rows_again(lib, tokens):
     """Gate/up of the widths of the benchmark's larger models: the padded rows of the tiles, over all launches, stay below
-    half of the block's (512 rows for 257 tokens made such a verify call 6 % slower)."""
+    half of the block's (512 rows for 257 tokens made such a verify call 6 % slower, 256 for 145 up to 1.5 %)."""
     for d, f in ((4096, 14336), (3072, 8192), (5120, 13824)):
+        if d == 3072 and tokens <= 192:                    # half a round of such tiles: two of 128 rows each fill one
+            continue
         p = ngg.debug_plan("bf16", "gateup", tokens, f, d)
         rows = -(-tokens // p["tile_tokens"]) * p["tile_tokens"]
         assert p["kernel"] == 1 and p["first_frags"] == f // 8 and rows < 1.5 * tokens, p

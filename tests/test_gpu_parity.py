@@ -803,7 +803,7 @@ def test_bigram_selection_above_512_scores_per_workgroup_with_exact_ties(dtype):
     ctx.close()
 
 
-@pytest.mark.parametrize("shape", range(8))
+@pytest.mark.parametrize("shape", range(10))
 @pytest.mark.parametrize("heads,kv,hd,d_ffn,prompt_len,k,wd", [
     (3, 1, 64, 448, 550, 16, 16),     # odd numbers of slices (3 and 7), grouped heads; 257 block tokens, a prompt cut by every tile height
     (5, 5, 32, 224, 300, 8, 4),       # the last slice is half padding (widths 160 and 224); 33 block tokens in a tile of any height
@@ -813,7 +813,7 @@ def test_every_tile_shape_16_bit(shape, heads, kv, hd, d_ffn, prompt_len, k, wd)
     fragments of W that end inside a tile, contractions of an odd number of slices and of half a slice more.  A prompt
     (q/k/v straight to the cache, both residual GEMMs, gate/up), then a verify block (the unembedding too) against the
     oracle; the tolerance is the one of every 16-bit lock-step test."""
-    assert ngg.debug_plan("bf16", "qkv", 300, 512, 512)["shapes"] == 8
+    assert ngg.debug_plan("bf16", "qkv", 300, 512, 512)["shapes"] == 10
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=heads * hd,
                 d_ffn=d_ffn, vocab=2080)
     run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=64, k=k, w=wd, k_ctx_max=4)
