@@ -294,7 +294,7 @@ ngg_status ngg_debug_peek(ngg_ctx *ctx, const char *name, void *dst, int64_t cap
 /* Test aids.  ngg_debug_plan: what a model call on `tokens` block tokens launches for one of its GEMMs (gemm 0 = q, k and
  * v together, 1 = output projection or down, 2 = gate and up, 3 = unembedding) with n output rows (gate and up: d_ffn) and
  * a contraction of k.  Host only, no context, no GPU.  plan (HOST, int32[8]): kernel (0 streaming, 1 tiled, 2 single
- * token), block tokens and weight rows of a tile, splits of the contraction, 16-row weight fragments in the first launch,
+ * token, 3 a residual GEMM that streams its whole contraction per workgroup and ends with the norm), block tokens and weight rows of a tile, splits of the contraction, 16-row weight fragments in the first launch,
  * tokens and rows of the second launch's tiles, number of tile shapes.
  * ngg_debug_tiles: every GEMM of this context's 16-bit model calls on two tokens or more takes tile shape `shape`
  * (0 .. number - 1) of the tiled kernel whatever its size; -1 (default) goes back to the choice by size. */

@@ -80,10 +80,13 @@ struct ngg_ctx {
   void *kcache = nullptr, *vcache = nullptr, *kscr = nullptr, *vscr = nullptr;
   float *h = nullptr, *hpart = nullptr, *part_o = nullptr, *part_ml = nullptr, *pmax_val = nullptr, *z = nullptr, *logits = nullptr;
   float *rope_cos = nullptr, *rope_sin = nullptr;
-  float *row_ss = nullptr;         // [Mcap][kNormSegs] sums of squares of the rows the last RMSNorm wrote
+  float *row_ss = nullptr;         // sums of squares of the rows the last RMSNorm wrote: kNormSegs or stream_segments per row
   int *pmax_idx = nullptr, *cand_idx = nullptr;
   float *cand_val = nullptr;
   void *xn = nullptr, *q = nullptr, *attn = nullptr, *act = nullptr;
+  // the same in operand order, for gemm_stream_kernel (64 rows).  Buffers of their own: the tiled kernel relies on zeros behind
+  // the last contraction element of the chunk-major ones.
+  void *xn_s = nullptr, *attn_s = nullptr, *act_s = nullptr;
   // the library's own operand-order copies of every matrix it multiplies with
   void *wtiled = nullptr;          // one allocation
   struct LayerT { const void *wqkv, *wo, *wgu, *wdown; float s_qkv, s_o, s_gu, s_down; };   // s_*: power-of-two scale of the stored copy
@@ -167,11 +170,14 @@ ngg_status dev_alloc(ngg_ctx *c, P **p, size_t bytes, bool zero) {
   return NGG_OK;
 }
 
+// Whether the norms may run inside other kernels: not while their own time is asked for, a profile of that class needs them as
+// launches.
+bool norms_inside(const ngg_ctx *c) { return !((c->prof_mask >> NGG_PROF_NORM) & 1); }
+
 // A block of one token: the GEMMs run the RMSNorms and the merge of the attention slices themselves (launch_gemm_row).
-// Not while the norms' own time is asked for: a profile of that class needs them as launches.
 bool one_row_call(const ngg_ctx *c, int M) {
   const ngg_model_desc &d = c->d;
-  return M == 1 && gemm_row_fits(d.dtype, d.d_model, d.n_heads * d.head_dim) && !((c->prof_mask >> NGG_PROF_NORM) & 1);
+  return M == 1 && gemm_row_fits(d.dtype, d.d_model, d.n_heads * d.head_dim) && norms_inside(c);
 }
 
 // One forward over a block of R rows x C columns sitting at positions P .. P+C-1 on a cached
@@ -190,10 +196,20 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   const int dt = d.dtype;
   const int dq = d.n_heads * d.head_dim;
   hipStream_t s = c->stream;
+  // Which kernels the block runs on, and with them the layout of every activation: its consumers' (act_pos)
+  const bool one_row = one_row_call(c, M);
+  const int mb = (M + 15) / 16;
+  auto layout = [&](int epi, int frags, int K) { return !one_row && stream_takes(dt, epi, M, frags, K, c->tile_only) ? mb : 0; };
+  const int xn_mb = layout(EPI_QKV, 0, d.d_model), attn_mb = layout(EPI_RESIDUAL, d.d_model / 16, dq),
+            act_mb = layout(EPI_RESIDUAL, d.d_model / 16, d.d_ffn);
+  void *const xn = xn_mb ? c->xn_s : c->xn, *const attn = attn_mb ? c->attn_s : c->attn, *const act = act_mb ? c->act_s : c->act;
+  const bool inside = !one_row && norms_inside(c);
+  int ss_segs = kNormSegs;                           // sums of squares per row, as the last norm left them
   {
     ProfScope ps(c, NGG_PROF_OTHER);
     launch_embed(dt, c->w.tok_emb, tok_src ? tok_src : c->hist, c->drafts, c->block_tok, c->h, d.d_model, M,
-                 tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev);
+                 tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev, inside ? c->layers[0].attn_norm : nullptr, xn, c->Mcap,
+                 xn_mb, c->row_ss);
   }
   const int n_splits = attention_splits(dt, d.head_dim, d.n_heads, M, P, c->max_splits, from_hist && C > 1);
   const bool whole = attention_whole(dt, d.head_dim, d.n_heads, M, P, from_hist && C > 1);
@@ -203,10 +219,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   if ((size_t)n_splits * Mpart > c->part_rows)
     return fail(c, NGG_ECAPACITY, "attention partials: %d slices of %d rows exceed the %zu rows allocated", n_splits, Mpart, c->part_rows);
   const size_t part_stride = (size_t)c->Mcap * d.d_model;
-  int ks_o = gemm_residual_splits(dt, M, d.d_model, dq, c->tile_only);
-  int ks_down = gemm_residual_splits(dt, M, d.d_model, d.d_ffn, c->tile_only);
-  const int ss_segs = rmsnorm_segments(d.d_model);
-  const bool one_row = one_row_call(c, M);
+  int ks_o = attn_mb ? 1 : gemm_residual_splits(dt, M, d.d_model, dq, c->tile_only);
+  int ks_down = act_mb ? 1 : gemm_residual_splits(dt, M, d.d_model, d.d_ffn, c->tile_only);
   RowArgs row{};
   float *h_cur = c->h, *h_next = c->h + d.d_model;   // row 1 of the residual stream is free; 2 n_layers swaps end in row 0
   if (one_row) {
@@ -215,15 +229,25 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     row.hpart = c->hpart; row.part_stride = part_stride;
   }
   int pending = 0;                                   // residual partials the next RMSNorm has to add
+  bool normed = inside;                              // the kernel before has done the norm
   // the norm in front of a GEMM: a launch of its own, or (one row) what the GEMM's prologue needs for it
   auto norm = [&](const void *gain) {
+    if (normed) { normed = false; return; }
     if (!one_row) {
       ProfScope ps(c, NGG_PROF_NORM);
-      launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, gain, c->xn, d.d_model, M, c->Mcap, c->row_ss, s);
+      launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, gain, xn, d.d_model, M, c->Mcap, xn_mb, c->row_ss, s);
+      ss_segs = kNormSegs;
       return;
     }
     row.h_in = h_cur; row.h_out = h_next; row.n_part = pending; row.gain = gain; row.part_o = nullptr;
     if (pending > 0) std::swap(h_cur, h_next);
+  };
+  // a residual GEMM on gemm_stream_kernel runs the norm behind it
+  auto norm_after = [&](GemmArgs &g, const void *gain) {
+    if (!g.x_mb || !inside) return;
+    g.h = c->h; g.gain = gain; g.xn = xn; g.xn_mb = xn_mb; g.ss_out = c->row_ss;
+    ss_segs = stream_segments(d.d_model);
+    normed = true;
   };
   auto gemm = [&](int epi, GemmArgs &g) {
     g.tile_only = c->tile_only;
@@ -245,7 +269,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     {
       ProfScope ps(c, NGG_PROF_GEMM_QKV);
       GemmArgs g{};
-      g.X = c->xn; g.W0 = c->lt[l].wqkv;
+      g.X = xn; g.x_mb = xn_mb; g.W0 = c->lt[l].wqkv;
       g.M = M; g.N = dq + 2 * d.n_kv_heads * d.head_dim; g.K = d.d_model;
       g.q = c->q; g.kscr = kscr_l; g.vscr = vscr_l; g.kv_rows = kv_rows;
       g.H = d.n_heads; g.Hkv = d.n_kv_heads; g.hd = d.head_dim; g.Mcap = c->Mcap; g.C = C; g.P = P; g.shared0 = shared0;
@@ -262,7 +286,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       a.kcache = (char *)c->kcache + kv_layer * c->Spad * d.head_dim * c->esize;
       a.vcache = (char *)c->vcache + kv_layer * d.head_dim * c->Spad * c->esize;
       a.kscr = kscr_l; a.vscr = vscr_l; a.kv_rows = kv_rows;
-      a.part_o = c->part_o; a.part_ml = c->part_ml; a.out = c->attn;
+      a.part_o = c->part_o; a.part_ml = c->part_ml; a.out = attn; a.out_mb = attn_mb;
       a.H = d.n_heads; a.Hkv = d.n_kv_heads; a.Mcap = c->Mcap; a.Spad = c->Spad; a.M = M; a.C = C; a.P = P;
       a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0; a.whole = whole ? 1 : 0;
       a.scale = 1.0f / std::sqrt((float)d.head_dim);
@@ -271,11 +295,12 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     {
       ProfScope ps(c, NGG_PROF_GEMM_O);
       GemmArgs g{};
-      g.X = c->attn; g.W0 = c->lt[l].wo; g.M = M; g.N = d.d_model; g.K = dq;
+      g.X = attn; g.x_mb = attn_mb; g.W0 = c->lt[l].wo; g.M = M; g.N = d.d_model; g.K = dq;
       g.hpart = c->hpart; g.KS = ks_o; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / c->lt[l].s_o;
       g.hd = d.head_dim;
-      if (one_row) { row.part_o = c->part_o; row.part_ml = c->part_ml; row.n_splits = n_splits; row.attn_out = c->attn; }
+      norm_after(g, lw.mlp_norm);
+      if (one_row) { row.part_o = c->part_o; row.part_ml = c->part_ml; row.n_splits = n_splits; row.attn_out = attn; }
       gemm(EPI_RESIDUAL, g);
     }
     pending = ks_o;
@@ -283,8 +308,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     {
       ProfScope ps(c, NGG_PROF_GEMM_GATEUP);
       GemmArgs g{};
-      g.X = c->xn; g.W0 = c->lt[l].wgu; g.M = M; g.N = d.d_ffn; g.K = d.d_model;
-      g.act = c->act; g.Mcap = c->Mcap;
+      g.X = xn; g.x_mb = xn_mb; g.W0 = c->lt[l].wgu; g.M = M; g.N = d.d_ffn; g.K = d.d_model;
+      g.act = act; g.act_mb = act_mb; g.Mcap = c->Mcap;
       g.row_ss = c->row_ss; g.ss_segs = ss_segs; g.ss_eps = d.rms_eps;
       g.out_scale = 1.0f / c->lt[l].s_gu;
       gemm(EPI_GATEUP, g);
@@ -292,29 +317,34 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     {
       ProfScope ps(c, NGG_PROF_GEMM_DOWN);
       GemmArgs g{};
-      g.X = c->act; g.W0 = c->lt[l].wdown; g.M = M; g.N = d.d_model; g.K = d.d_ffn;
+      g.X = act; g.x_mb = act_mb; g.W0 = c->lt[l].wdown; g.M = M; g.N = d.d_model; g.K = d.d_ffn;
       g.hpart = c->hpart; g.KS = ks_down; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / c->lt[l].s_down;
+      norm_after(g, l + 1 < d.n_layers ? c->layers[l + 1].attn_norm : c->w.final_norm);
       gemm(EPI_RESIDUAL, g);
     }
     pending = ks_down;
   }
   if (unembed) {
-    norm(c->w.final_norm);
+    const bool last_only = last_row_only && M > 1;
+    // the last row alone goes through the single-token kernel, which runs the norm of that row itself (row 0 of the residual
+    // stream, which nobody reads any more, takes the sum)
+    if (!last_only || !norms_inside(c)) norm(c->w.final_norm);
     ProfScope ps(c, NGG_PROF_GEMM_UNEMBED);
     GemmArgs g{};
-    g.X = c->xn; g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
+    g.X = xn; g.x_mb = xn_mb; g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
     g.logits = want_logits ? c->logits : nullptr;
     g.pmax_val = c->pmax_val; g.pmax_idx = c->pmax_idx; g.Mcap = c->Mcap;
     g.row_ss = c->row_ss; g.ss_segs = ss_segs; g.ss_eps = d.rms_eps;
-    if (last_row_only) {                               // rows of the activation layout lie one chunk row apart in every chunk
-      const int kc = dt == 1 ? KChunk<half_t>::value : KChunk<float>::value;
-      g.X = (const char *)c->xn + (size_t)(M - 1) * kc * c->esize;
-      g.row_ss = c->row_ss + (size_t)(M - 1) * kNormSegs;
-      g.M = 1;
-    }
     g.out_scale = 1.0f / c->unemb_scale;
-    gemm(EPI_UNEMBED, g);
+    if (last_only) {
+      const size_t at = (size_t)(M - 1) * d.d_model;
+      g.M = 1;
+      row.h_in = c->h + at; row.h_out = c->h; row.hpart = c->hpart + at; row.part_stride = part_stride;
+      row.n_part = normed || !norms_inside(c) ? 0 : pending;   // (0: the kernel before, or the norm above, has added them)
+      row.gain = c->w.final_norm; row.part_o = nullptr;
+      launch_gemm_row(dt, EPI_UNEMBED, g, row, s);
+    } else gemm(EPI_UNEMBED, g);
   }
   NGG_HIP(c, hipGetLastError());
   return NGG_OK;
@@ -333,10 +363,12 @@ ngg_status build_next1(ngg_ctx *c) {
   const int rows = d.dtype == NGG_BF16 ? 256 : 64;       // Mcap >= 256
   for (int x0 = 0; x0 < d.vocab; x0 += rows) {
     const int M = std::min(rows, d.vocab - x0);
-    launch_pack_rows(d.dtype, (const char *)c->w.tok_emb + (size_t)x0 * d.d_model * c->esize, c->xn, d.d_model, M, c->Mcap,
-                     c->stream, c->emb_scale);
     GemmArgs g{};
-    g.X = c->xn;
+    g.x_mb = stream_takes(d.dtype, EPI_UNEMBED, M, d.vocab / 16, d.d_model, 0) ? (M + 15) / 16 : 0;
+    void *xn = g.x_mb ? c->xn_s : c->xn;
+    g.X = xn;
+    launch_pack_rows(d.dtype, (const char *)c->w.tok_emb + (size_t)x0 * d.d_model * c->esize, xn, d.d_model, M, c->Mcap, g.x_mb,
+                     c->stream, c->emb_scale);
     g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
     g.pmax_val = c->pmax_val; g.pmax_idx = c->pmax_idx; g.Mcap = c->Mcap;
     g.out_scale = 1.0f / (c->unemb_scale * c->emb_scale);
@@ -439,7 +471,7 @@ ngg_status ngg_destroy(ngg_ctx *c) {
   (void)hipStreamSynchronize(c->stream);
   void *bufs[] = {c->hist, c->drafts, c->block_tok, c->res, c->next1, c->mlist, c->reps, c->gtab, c->ctx_rows,
                   c->hpart, c->wtiled, c->cand_val, c->cand_idx, c->kcache, c->vcache, c->kscr, c->vscr, c->h, c->part_o, c->part_ml, c->pmax_val, c->z,
-                  c->logits, c->rope_cos, c->rope_sin, c->pmax_idx, c->xn, c->q, c->attn, c->act, c->bg_table, c->bg_tok, c->uni_top, c->row_ss, c->n_dev};
+                  c->logits, c->rope_cos, c->rope_sin, c->pmax_idx, c->xn, c->q, c->attn, c->act, c->bg_table, c->bg_tok, c->uni_top, c->row_ss, c->n_dev, c->xn_s, c->attn_s, c->act_s};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   if (c->step_graph) (void)hipGraphExecDestroy(c->step_graph);
@@ -519,13 +551,16 @@ ngg_status ngg_create(const ngg_model_desc *desc, const ngg_weights *weights, vo
   TRY(dev_alloc(c, &c->vscr, kv_elems * c->Mcap * c->esize, true));
   TRY(dev_alloc(c, &c->h, (size_t)c->Mcap * d.d_model * 4, true));
   TRY(dev_alloc(c, &c->n_dev, 16, true));
-  // (+ 16 rows: the unembedding of a piece's last token alone starts its row tile at that row)
-  TRY(dev_alloc(c, &c->row_ss, (size_t)(c->Mcap + 16) * kNormSegs * 4, true));
+  // (+ 256: gemm_stream_kernel fetches whole kilobytes)
+  TRY(dev_alloc(c, &c->row_ss, std::max((size_t)c->Mcap * kNormSegs, (size_t)64 * stream_segments(d.d_model)) * 4 + 1024, true));
   TRY(dev_alloc(c, &c->hpart, (size_t)kMaxResidualSplits * c->Mcap * d.d_model * 4, true));
   TRY(dev_alloc(c, &c->xn, act_elems(d.dtype, c->Mcap, d.d_model) * c->esize, true));
   TRY(dev_alloc(c, &c->q, (size_t)c->Mcap * dq * c->esize, true));
   TRY(dev_alloc(c, &c->attn, act_elems(d.dtype, c->Mcap, dq) * c->esize, true));
   TRY(dev_alloc(c, &c->act, act_elems(d.dtype, c->Mcap, d.d_ffn) * c->esize, true));
+  TRY(dev_alloc(c, &c->xn_s, (size_t)64 * d.d_model * c->esize, true));
+  TRY(dev_alloc(c, &c->attn_s, (size_t)64 * dq * c->esize, true));
+  TRY(dev_alloc(c, &c->act_s, (size_t)64 * d.d_ffn * c->esize, true));
   // attention partials, [head][slice][rows]: slices x rows is at most 32 x 128 for blocks of up to 64 tokens, and
   // (two workgroups per CU) x 128 rows per workgroup, shared among the heads, above that (attention_splits)
   c->part_rows = std::max({(size_t)(c->Mcap + 127) / 128 * 128, (size_t)65536 / d.n_heads + 128, (size_t)(c->max_splits + 1) * 128});
@@ -764,8 +799,11 @@ static int step_launches(const ngg_ctx *c, const ngg_draft_cfg &s) {
   };
   const int dq = d.n_heads * d.head_dim;
   const int merge = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) > 1 ? 1 : 0;
-  const int layer = 5 + merge + launches(EPI_QKV, dq + 2 * d.n_kv_heads * d.head_dim, d.d_model) + launches(EPI_GATEUP, d.d_ffn, d.d_model);
-  return drafts + 1 + layer * d.n_layers + 1 + launches(EPI_UNEMBED, d.vocab, d.d_model) + 3;
+  // norms that are launches of their own: all while they are profiled, else those behind a residual GEMM that leaves them
+  const int after_o = !norms_inside(c) || !stream_takes(d.dtype, EPI_RESIDUAL, M, d.d_model / 16, dq, c->tile_only) ? 1 : 0;
+  const int after_down = !norms_inside(c) || !stream_takes(d.dtype, EPI_RESIDUAL, M, d.d_model / 16, d.d_ffn, c->tile_only) ? 1 : 0;
+  const int layer = 3 + merge + after_o + after_down + launches(EPI_QKV, dq + 2 * d.n_kv_heads * d.head_dim, d.d_model) + launches(EPI_GATEUP, d.d_ffn, d.d_model);
+  return drafts + 1 + (norms_inside(c) ? 0 : 1) + layer * d.n_layers + launches(EPI_UNEMBED, d.vocab, d.d_model) + 3;
 }
 
 // What fixes the launch shapes and constant arguments of a decode step: a captured step is replayed only while
@@ -776,7 +814,7 @@ static void step_key(const ngg_ctx *c, const ngg_draft_cfg &s, int key[8]) {
   key[0] = s.k; key[1] = s.w; key[2] = s.k_ctx_max; key[3] = s.q_min; key[4] = s.q_max;
   key[5] = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) |
            (attention_whole(d.dtype, d.head_dim, d.n_heads, M, c->n - 1) ? 1 << 16 : 0);
-  key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0) | (one_row_call(c, M) ? 4 : 0);
+  key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0) | (one_row_call(c, M) ? 4 : 0) | (norms_inside(c) ? 8 : 0);
   key[7] = 1;
 }
 
@@ -1127,10 +1165,12 @@ ngg_status ngg_unigram_build(ngg_ctx *c, int32_t top_k) {
     // embedding, Mcap tokens per pass, then the sum of squares of every output row
     for (int x0 = 0; x0 < d.vocab; x0 += c->Mcap) {
       const int M = std::min(c->Mcap, d.vocab - x0);
-      launch_pack_rows(d.dtype, (const char *)c->w.unemb + (size_t)x0 * d.d_model * c->esize, c->xn, d.d_model, M, c->Mcap,
-                       c->stream, row_scale, mean);
       GemmArgs g{};
-      g.X = c->xn;
+      g.x_mb = stream_takes(d.dtype, EPI_UNEMBED, M, d.vocab / 16, d.d_model, 0) ? (M + 15) / 16 : 0;
+      void *xn = g.x_mb ? c->xn_s : c->xn;
+      g.X = xn;
+      launch_pack_rows(d.dtype, (const char *)c->w.unemb + (size_t)x0 * d.d_model * c->esize, xn, d.d_model, M, c->Mcap, g.x_mb,
+                       c->stream, row_scale, mean);
       g.W0 = emb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
       g.logits = c->logits; g.pmax_val = c->pmax_val; g.pmax_idx = c->pmax_idx; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / (c->emb_scale * row_scale);

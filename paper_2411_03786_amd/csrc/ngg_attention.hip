@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * NW) void attn_stream_kernel(const AttnArgs a, 
     l = rows_sum(l);                                        // the four lanes of a query each held a share of its sum
     if (S == 1 && !a.one_row) {                             // the whole list: the quotient is the result, nothing to merge
       const float inv = 1.0f / l;
-      if (m < M) store4((T *)a.out + act_offset<T>(m, h * HD + df * 16 + 4 * g, a.Mcap), o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+      if (m < M) store4((T *)a.out + act_pos<T>(m, h * HD + df * 16 + 4 * g, a.Mcap, a.out_mb), o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
       continue;
     }
     // partial outputs keep the fragment order, [head][slice][16-query group][df][lane][4]: one store
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
         if (m < M)
 #pragma unroll
           for (int df = 0; df < DF; ++df)
-            store4((T *)a.out + act_offset<T>(m, h * HD + df * 16 + 4 * g, a.Mcap), O[qf][df][0] * inv, O[qf][df][1] * inv,
+            store4((T *)a.out + act_pos<T>(m, h * HD + df * 16 + 4 * g, a.Mcap, a.out_mb), O[qf][df][0] * inv, O[qf][df][1] * inv,
                    O[qf][df][2] * inv, O[qf][df][3] * inv);
         continue;
       }
@@ -528,7 +528,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
       }
     }
     const float inv = 1.0f / l;
-    store4((T *)a.out + act_offset<T>(m, h * HD + d4, a.Mcap), o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+    store4((T *)a.out + act_pos<T>(m, h * HD + d4, a.Mcap, a.out_mb), o.x * inv, o.y * inv, o.z * inv, o.w * inv);
   }
 }
 

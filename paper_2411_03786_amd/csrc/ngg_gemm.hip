@@ -1,6 +1,7 @@
 // Skinny GEMM  Y[M x N] = X[M x K] . W[N x K]^T  for the k*(w+1) block rows of a verify call
 // (Section 3: a model call on a (k, w+1) block is meant to stay memory-bound, so the kernel is
-// built around streaming W exactly once at HBM speed).
+// built around streaming W exactly once at HBM speed): blocks of 65 to 128 rows, every fp32 block above 64, and the residual
+// GEMMs of smaller blocks that gemm_stream_kernel (ngg_stream.hip) leaves.
 //
 // W rows are the MFMA "row" operand.  The library keeps its own copy of every weight matrix in
 // operand order (16 rows x 32 contraction elements per 1 KB block, lane-major), so one load
@@ -16,109 +17,11 @@
 //
 // Epilogues: rotary embedding + KV-scratch write (q, k, v), SwiGLU (gate, up), residual partial,
 // and per-position argmax partials for the greedy choice (output embedding).
-#include "ngg_internal.h"
+#include "ngg_epilogues.h"
 #include <algorithm>
 #include <cmath>
 
 namespace ngg {
-
-// ---------------------------------------------------------------------------------------------
-// Epilogues, shared by the skinny and the single-row kernel.  `sum` is one complete 16x16 accumulator
-// fragment: this lane holds column (block row) m and fragment rows 4g .. 4g+3.
-// ---------------------------------------------------------------------------------------------
-
-// q/k/v and gate/up: the fragment's rows 0..7 are the first members of 8 output pairs, rows 8..15 the
-// second members (rotary pairs (i, i + hd/2) of one head; gate and up of 8 FFN features).  rs: the row's
-// 1 / rms times the operand scales.  The caller has checked frag < n_groups; lanes g >= 2 only lend values.
-// v: the first members (fragment rows 4g .. 4g+3, g < 2), x2: their partners (rows 8 + 4g ..), both already scaled
-template <typename T, int EPI>
-__device__ __forceinline__ void epi_paired_vals(const GemmArgs &a, int frag, int m, int M, int g, const float (&v)[4],
-                                                const float (&x2)[4]) {
-  if (m < M && g < 2) {
-    if constexpr (EPI == EPI_GATEUP) {
-      float o[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) o[r] = silu<T>(v[r]) * x2[r];
-      store4((T *)a.act + act_offset<T>(m, frag * 8 + 4 * g, a.Mcap), o[0], o[1], o[2], o[3]);   // 4 features, one chunk
-    } else {
-      const int half = a.hd / 2, fph = a.hd / 16;    // fragments per head
-      const int hh = frag / fph, sub = frag - hh * fph;                 // head over [q heads | k heads | v heads]
-      const int kind = hh < a.H ? 0 : (hh < a.H + a.Hkv ? 1 : 2);
-      const int head = kind == 0 ? hh : (kind == 1 ? hh - a.H : hh - a.H - a.Hkv);
-      const int i0 = sub * 8 + 4 * g;                // dims i0 .. i0+3 and their partners i0 + half ..
-      if (kind < 2) {                                // rotary embedding on q and k
-        const int pos = (a.n_dev ? *a.n_dev - 1 : a.P) + block_col(m, a.C, a.shared0);
-        const float *cs = a.rope_cos + (size_t)pos * half + i0;
-        const float *sn = a.rope_sin + (size_t)pos * half + i0;
-        float lo[4], hi[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          lo[r] = v[r] * cs[r] - x2[r] * sn[r];
-          hi[r] = x2[r] * cs[r] + v[r] * sn[r];
-        }
-        if (kind == 0) {
-          T *dst = (T *)a.q + ((size_t)head * a.Mcap + m) * a.hd + i0;
-          store4(dst, lo[0], lo[1], lo[2], lo[3]);
-          store4(dst + half, hi[0], hi[1], hi[2], hi[3]);
-        } else {                                     // keys: tiles of 32 block positions in operand order
-          T *kh = (T *)a.kscr + (size_t)head * a.kv_rows * a.hd;
-          store4(kh + k_offset(m, i0, a.hd, (int)sizeof(T)), lo[0], lo[1], lo[2], lo[3]);
-          store4(kh + k_offset(m, i0 + half, a.hd, (int)sizeof(T)), hi[0], hi[1], hi[2], hi[3]);
-        }
-      } else {                                       // values: the transposed tiles
-        T *vh = (T *)a.vscr + (size_t)head * a.kv_rows * a.hd;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          vh[v_offset(m, i0 + r, a.hd, (int)sizeof(T))] = from_f32<T>(v[r]);
-          vh[v_offset(m, i0 + half + r, a.hd, (int)sizeof(T))] = from_f32<T>(x2[r]);
-        }
-      }
-    }
-  }
-}
-
-template <typename T, int EPI>
-__device__ __forceinline__ void epi_paired(const GemmArgs &a, int frag, int m, int M, int g, float rs, const f32x4 &sum) {
-  float v[4], x2[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) { v[r] = sum[r] * rs; x2[r] = other_half(v[r]); }
-  epi_paired_vals<T, EPI>(a, frag, m, M, g, v, x2);
-}
-
-// residual: split ks stores its fp32 partial of output features n0 + 4g .. +4 of block row m
-__device__ __forceinline__ void epi_residual(const GemmArgs &a, int ks, int m, int n0, int g, const f32x4 &sum) {
-  float *dst = a.hpart + ((size_t)ks * a.Mcap + m) * a.N;
-  *reinterpret_cast<float4 *>(dst + n0 + 4 * g) =
-      float4{sum[0] * a.out_scale, sum[1] * a.out_scale, sum[2] * a.out_scale, sum[3] * a.out_scale};
-}
-
-// unembedding: optional logits, and the best (value, id) of block row m over the FN fragments of `group`
-// (vocabulary rows nbase[f] ..): ascending ids, so the first maximum stays
-template <int FN>
-__device__ __forceinline__ void epi_unembed(const GemmArgs &a, int group, int m, bool live, int g, float rs,
-                                            const int (&nbase)[FN], const f32x4 (&sum)[FN]) {
-  float bv = kNegBig;
-  int bi = 0x7fffffff;
-#pragma unroll
-  for (int f = 0; f < FN; ++f)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float v = sum[f][r] * rs;
-      const int n = nbase[f] + 4 * g + r;
-      if (a.logits && live) a.logits[(size_t)m * a.N + n] = v;
-      if (v > bv) { bv = v; bi = n; }
-    }
-#pragma unroll
-  for (int off = 16; off < 64; off <<= 1) {
-    const float ov = __shfl_xor(bv, off);
-    const int oi = __shfl_xor(bi, off);
-    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-  }
-  if (live && g == 0) {
-    a.pmax_val[(size_t)group * a.Mcap + m] = bv;
-    a.pmax_idx[(size_t)group * a.Mcap + m] = bi;
-  }
-}
 
 template <typename T, int EPI, int FM, int WN, int WK, int RING, int FN>
 __global__ __launch_bounds__(64 * WN * WK) void gemm_skinny_kernel(const GemmArgs a) {
@@ -399,16 +302,6 @@ __global__ __launch_bounds__(64 * WN * WK) void gemm_skinny_kernel(const GemmArg
 // ---------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// 16 bytes per lane from global memory (uniform base + lane offset) to LDS (lane i: lds + 16 i).  The compiler does not
-// see the transfer: the kernel waits for it with its own s_waitcnt before a barrier.  NT: the lines are used once
-// (weights that only one workgroup reads), keep them out of the activations' way in the L2.
-template <bool NT>
-__device__ __forceinline__ void lds_dma16(const void *base, unsigned off, unsigned lds) {
-  if constexpr (NT)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0", "memory");
-}
 __device__ __forceinline__ void wave_lds_fence() {       // LDS written by other lanes of this wave is readable behind it
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -642,7 +535,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs 
     for (int e = tid; e < TM * PPR; e += 64 * NW) {
       const int row = e / PPR, fr = e % PPR, m = m0 + row;
       if (m < M && f0 + fr < frag_end)
-        *reinterpret_cast<u32x4 *>((T *)a.act + act_offset<T>(m, (f0 + fr) * 8, a.Mcap)) = *reinterpret_cast<const u32x4 *>(ot + row * LDO + fr * 8);
+        *reinterpret_cast<u32x4 *>((T *)a.act + act_pos<T>(m, (f0 + fr) * 8, a.Mcap, a.act_mb)) = *reinterpret_cast<const u32x4 *>(ot + row * LDO + fr * 8);
     }
   } else if constexpr (EPI == EPI_UNEMBED) {
     // optional logits, and the best (value, id) of a block row over every 32 vocabulary rows; ids ascend with (j, i)
@@ -851,15 +744,21 @@ static int gemm_row_blocks(int M) { return M >= 128 ? 8 : (M + 15) / 16; }
 template <typename T, int EPI, int WN, int WK, int RING>
 static void launch_fm(const GemmArgs &a, int KS, hipStream_t s) {
   switch (gemm_row_blocks(a.M)) {                            // 16-row column blocks of the tile
-    case 1: launch_gemm_cfg<T, EPI, 1, WN, WK, RING>(a, KS, s); break;
-    case 2: launch_gemm_cfg<T, EPI, 2, WN, WK, RING>(a, KS, s); break;
-    case 3: launch_gemm_cfg<T, EPI, 3, WN, WK, RING>(a, KS, s); break;
-    case 4: launch_gemm_cfg<T, EPI, 4, WN, WK, RING>(a, KS, s); break;
-    case 5: launch_gemm_cfg<T, EPI, 5, WN, WK, RING>(a, KS, s); break;
-    case 6: launch_gemm_cfg<T, EPI, 6, WN, WK, RING>(a, KS, s); break;
-    case 7: launch_gemm_cfg<T, EPI, 7, WN, WK, RING>(a, KS, s); break;
-    default: launch_gemm_cfg<T, EPI, 8, WN, WK, RING>(a, KS, s);   // 128-row tiles; more rows loop over W again
+    case 5: launch_gemm_cfg<T, EPI, 5, WN, WK, RING>(a, KS, s); return;
+    case 6: launch_gemm_cfg<T, EPI, 6, WN, WK, RING>(a, KS, s); return;
+    case 7: launch_gemm_cfg<T, EPI, 7, WN, WK, RING>(a, KS, s); return;
+    default: break;
   }
+  if constexpr (EPI == EPI_RESIDUAL) {                       // (the unembedding of up to 64 rows: gemm_stream_kernel)
+    switch (gemm_row_blocks(a.M)) {
+      case 1: launch_gemm_cfg<T, EPI, 1, WN, WK, RING>(a, KS, s); return;
+      case 2: launch_gemm_cfg<T, EPI, 2, WN, WK, RING>(a, KS, s); return;
+      case 3: launch_gemm_cfg<T, EPI, 3, WN, WK, RING>(a, KS, s); return;
+      case 4: launch_gemm_cfg<T, EPI, 4, WN, WK, RING>(a, KS, s); return;
+      default: break;
+    }
+  }
+  launch_gemm_cfg<T, EPI, 8, WN, WK, RING>(a, KS, s);        // 128-row tiles; more rows loop over W again
 }
 
 // q/k/v and gate/up: one workgroup = FN fragments, its four waves split the steps of every chunk
@@ -900,11 +799,7 @@ static void launch_paired_fm(const GemmArgs &a, hipStream_t s) {
 
 template <typename T, int EPI>
 static void launch_paired(const GemmArgs &a, hipStream_t s) {
-  switch (gemm_row_blocks(a.M)) {
-    case 1: launch_paired_fm<T, EPI, 1>(a, s); break;
-    case 2: launch_paired_fm<T, EPI, 2>(a, s); break;
-    case 3: launch_paired_fm<T, EPI, 3>(a, s); break;
-    case 4: launch_paired_fm<T, EPI, 4>(a, s); break;
+  switch (gemm_row_blocks(a.M)) {                            // (up to four: gemm_stream_kernel)
     case 5: launch_paired_fm<T, EPI, 5>(a, s); break;
     case 6: launch_paired_fm<T, EPI, 6>(a, s); break;
     case 7: launch_paired_fm<T, EPI, 7>(a, s); break;
@@ -930,7 +825,7 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
   return ks < 1 ? 1 : ks;
 }
 
-// Which blocks gemm_tile_kernel takes (16-bit operands).  Above 128 rows: all.  Up to 128, measured on MI355X (skinny ->
+// Which blocks gemm_tile_kernel takes of those that gemm_stream_kernel leaves (16-bit operands).  Above 128 rows: all.  Up to 128, measured on MI355X (skinny ->
 // tiled, us, at 17 / 33 / 51 / 64-65 / 97 rows):
 //  * residual GEMMs.  The tiled kernel reads X once per 64 columns of W instead of 32 and splits the contraction where that
 //    fills the chip: output projection 4096 x 4096 8.4 -> 8.8 / 9.7 -> 9.0 / 11.0 -> 9.4 / 13.6 -> 12.2 / 16.7 -> 12.8, 768 x 768
@@ -945,12 +840,10 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
 //  * gate/up and q/k/v of 65 rows or more on narrow models, where one or two fragments per workgroup leave too little in
 //    flight (768-wide, 97 rows: 9.6 -> 7.1 and 9.9 -> 8.0; 65 rows 8.0 -> 7.1, 8.3 -> 8.0); wide models stream W as fast
 //    either way (4096-wide, 97 rows: 49.4 and 47.5-50.6, 33.8 and 35.3).
-//  * up to 64 rows where 64 x 64 tiles make one full round (14/16 of the CUs at least): 1024 fragments 19.4 -> 18.6 /
-//    20.2 -> 19.2 / 21.6 -> 19.3 / 21.8 -> 20.0; 688 fragments 11.5 against 12.7 at 33 rows, 768 fragments 23.0 against 24.7 at 51.
 static bool takes_tile(int epi, int M, int frags, int K, int tile_only) {
   if (M > 128 || (tile_only && M > 1)) return true;
   if (epi == EPI_UNEMBED || M <= 16) return false;
-  if (epi != EPI_RESIDUAL) return M > 64 ? frags <= 512 : (frags > 896 && frags <= 1024);
+  if (epi != EPI_RESIDUAL) return M > 64 && frags <= 512;  // (up to 64 rows: gemm_stream_kernel)
   const int N = frags * 16;
   if (skinny_residual_blocks(M, N, K) * skinny_residual_splits(KChunk<half_t>::value, M, N, K) > 256) return true;
   return M > 24 && !(K > N && frags >= 256 && frags <= 320 && M > 64 && M <= 96);
@@ -1310,6 +1203,10 @@ int gemm_tile_shapes() { return kNumTileShapes; }
 GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K) {
   const int frags = epi == EPI_GATEUP ? N / 8 : N / 16;
   GemmPlan p{0, 0, 0, 1, frags, 0, 0};
+  if (M > 1 && stream_takes(dtype, epi, M, frags, K, 0)) {
+    p.kernel = dtype == 1 && epi == EPI_RESIDUAL ? 3 : 0;
+    return p;
+  }
   if (dtype == 1 && takes_tile(epi, M, frags, K, 0)) {
     const TilePlan t = tile_plan(epi, M, frags, K, 0);
     const TileShape &s = kTileShapes[t.shape], &s2 = kTileShapes[t.shape2];
@@ -1326,7 +1223,8 @@ void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hi
 }
 
 void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
-  if (dtype == 1) launch_t<half_t>(epi, a, s);
+  if (a.x_mb) launch_gemm_stream(dtype, epi, a, s);
+  else if (dtype == 1) launch_t<half_t>(epi, a, s);
   else launch_t<float>(epi, a, s);
 }
 

@@ -120,6 +120,16 @@ __host__ __device__ __forceinline__ size_t act_offset(int m, int k, int Mcap) {
   constexpr int KC = KChunk<T>::value;
   return ((size_t)(k / KC) * Mcap + m) * KC + k % KC;
 }
+// ... or, where gemm_stream_kernel reads them (blocks of up to 64 rows), in operand order like the weights: 1 KB blocks of 16
+// rows x 32 contraction elements, the mb = ceil(M / 16) row blocks of a step side by side, so that a wave fetches its operand
+// with one contiguous load and no LDS in between.  mb = 0 stands for chunk-major.
+template <typename T>
+__host__ __device__ __forceinline__ size_t act_pos(int m, int k, int Mcap, int mb) {
+  if (!mb) return act_offset<T>(m, k, Mcap);
+  const size_t block = ((size_t)(k / 32) * mb + m / 16) * 512;
+  const int l = ((k % 32) / 8) * 16 + m % 16, e = k % 8;
+  return block + (sizeof(T) == 2 ? l * 8 + e : (e / 4) * 256 + l * 4 + e % 4);
+}
 inline size_t act_elems(int dtype, int Mcap, int K) {
   const int kc = dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value;
   return (size_t)((K + kc - 1) / kc) * Mcap * kc;
@@ -251,17 +261,26 @@ struct GemmArgs {
   int M, N, K;            // N = total logical output rows
   // q/k/v, gate/up, unembedding: X is h * gain; the epilogue multiplies row m by
   // 1 / sqrt((row_ss[m][0] + .. + row_ss[m][ss_segs-1]) / K + ss_eps).  Null: X is used as it is.
-  const float *row_ss;
+  const float *row_ss;    // [M][ss_segs]
   int ss_segs;
   float ss_eps;
+  int x_mb;               // layout of X (act_pos)
   float out_scale;        // every result is multiplied by this: 1 / (scale of the stored weights * scale of X); 1 for fp32 models
   int n_groups;           // residual, unembedding: pairs of 16-row fragments; q/k/v, gate/up: fragments (filled by the launcher)
   int tile_only;          // tests: 1 + the tile shape gemm_tile_kernel has to take, and takes any block of two tokens or more; 0: by size
   // EPI_RESIDUAL: split ks of KS stores its fp32 partial at hpart[ks][m][n]; the next RMSNorm adds them
   float *hpart;           // [KS][Mcap][N]
   int KS;
+  // EPI_RESIDUAL, h set (gemm_stream_kernel, KS == 1): the RMSNorm that follows is done here too: h += the result, xn = h * gain
+  // and the sums of squares of every row over 16 features each
+  float *h;               // [Mcap][N]
+  const void *gain;       // [N], the user's storage type
+  void *xn;               // act_pos(.., xn_mb)
+  int xn_mb;
+  float *ss_out;          // [M][stream_segments(N)]
   // EPI_GATEUP
-  void *act;              // chunk-major [N/KC][Mcap][KC] T  (N = d_ffn)
+  void *act;              // [M][N = d_ffn] T, act_pos(.., act_mb)
+  int act_mb;
   // EPI_QKV
   void *q;                // [H][Mcap][hd] T
   void *kscr;             // this layer's block keys, [Hkv][kv_rows/32] tiles (k_offset)
@@ -294,6 +313,8 @@ struct RowArgs {
 
 constexpr int kMaxResidualSplits = 8;
 constexpr int kNormSegs = 4;   // workgroups that may share a row of the RMSNorm; row_ss is [Mcap][kNormSegs]
+// sums of squares per row that gemm_stream_kernel leaves: one per 16 features, in whole groups of four
+inline int stream_segments(int d) { return (d / 16 + 3) / 4 * 4; }
 
 struct AttnArgs {
   const void *q;          // [H][Mcap][hd]
@@ -307,7 +328,8 @@ struct AttnArgs {
   int Mpart;              // rows per (head, slice) of the two partial buffers: M rounded up to 128
   int whole;              // a short list (attention_whole): one workgroup per head and 16 queries, n_splits == 1
   int one_row;            // M == 1 and the merge is left to the GEMM that follows: partials are [H][n_splits][hd] and [H][n_splits][2]
-  void *out;              // chunk-major [H*hd/KC][Mcap][KC] T
+  void *out;              // [M][H*hd] T, act_pos(.., out_mb)
+  int out_mb;
   int H, Hkv, Mcap, Spad, M, C, P, n_splits;   // n_splits: workgroups that share a head's list of key tiles
   const int32_t *n_dev;   // when set, P = *n_dev - 1 (see DraftArgs)
   int shared0;            // block layout (block_index)
@@ -318,9 +340,12 @@ struct AttnArgs {
 // checks shapes before calling.
 void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s);
 int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only = 0);
+// Blocks of up to 64 rows: gemm_stream_kernel.  stream_takes: whether a GEMM runs on it (frags: 16-row fragments of W)
+bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only);
+void launch_gemm_stream(int dtype, int epi, const GemmArgs &a, hipStream_t s);
 // What a model call on M block tokens launches for one GEMM of N output rows (q, k and v together; gate/up: d_ffn): kernel 0
-// gemm_skinny_kernel, 1 gemm_tile_kernel (tile rows and columns; fragments from `split` on in a second launch of their own
-// shape), 2 gemm_row_kernel; splits of the contraction.
+// gemm_skinny_kernel, or gemm_stream_kernel but for the 16-bit residual GEMMs, which are 3 there; 1 gemm_tile_kernel (tile rows
+// and columns; fragments from `split` on in a second launch of their own shape), 2 gemm_row_kernel; splits of the contraction.
 struct GemmPlan { int kernel, tm, tn, splits, split, tm2, tn2; };
 GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K);
 int gemm_tile_shapes();   // tile shapes gemm_tile_kernel is built for
@@ -338,19 +363,19 @@ int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool who
 // layout (token 0 is hist[hist_base], token m >= 1 is drafts[m - 1]); mode 2: a block of single-column rows (w = 0),
 // every token hist[hist_base]
 void launch_embed(int dtype, const void *tok_emb, const int32_t *hist, const int32_t *drafts, int32_t *block_tok,
-                  float *h, int d, int M, int hist_base, int mode, hipStream_t s, const int32_t *n_dev = nullptr);   // n_dev: hist_base = *n_dev - 1
+                  float *h, int d, int M, int hist_base, int mode, hipStream_t s, const int32_t *n_dev = nullptr,   // n_dev: hist_base = *n_dev - 1
+                  const void *gain = nullptr, void *xn = nullptr, int Mcap = 0, int xn_mb = 0, float *row_ss = nullptr);   // gain set: the RMSNorm of the rows too
 // h[m] += sum of n_part partials (hpart[s][m], stride part_stride floats between splits), then
 // xn[m] = rmsnorm(h[m]) * gain, written chunk-major
 // dst = (src - centre) * scale in the internal element type (src: the user's storage type)
-void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int Mcap, hipStream_t s, float scale,
+void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int Mcap, int mb, hipStream_t s, float scale,
                       const float *centre = nullptr);
 // *out_bits = max(*out_bits, bit pattern of max |src[i]|) (fp32 bits; non-negative floats order like unsigned integers)
 void launch_absmax(int dtype, const void *src, size_t n, unsigned *out_bits, hipStream_t s);
 void launch_column_mean(int dtype, const void *src, int N, int d, float *mean, hipStream_t s);
 void launch_neg_row_sumsq(const float *rows, int M, int V, float *out, hipStream_t s);
 void launch_rmsnorm(int dtype, float *h, const float *hpart, int n_part, size_t part_stride, const void *gain, void *xn,
-                    int d, int M, int Mcap, float *row_ss, hipStream_t s);
-int rmsnorm_segments(int d);
+                    int d, int M, int Mcap, int xn_mb, float *row_ss, hipStream_t s);
 
 struct DraftArgs {
   const int32_t *hist; int n;

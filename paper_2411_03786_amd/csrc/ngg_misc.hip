@@ -13,47 +13,6 @@ namespace ngg {
 // token m - 1 of the k x w draft batch (row-major: the same order).  In prefill mode token m is
 // history token hist_base + m.
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T *tok_emb, const int32_t *hist, const int32_t *drafts,
-                                                    int32_t *block_tok, float *h, int d, int hist_base, int mode,
-                                                    const int32_t *n_dev) {
-  const int m = blockIdx.x;
-  if (n_dev) hist_base = *n_dev - 1;
-  // mode 0: a verify block whose rows share token 0 (the last context token), then the drafts row by row;
-  // mode 1: consecutive history tokens; mode 2: single-column rows, every one the last context token
-  const int tok = mode == 1 ? hist[hist_base + m] : (m == 0 || mode == 2 ? hist[hist_base] : drafts[m - 1]);
-  if (threadIdx.x == 0) block_tok[m] = tok;
-  const T *e = tok_emb + (size_t)tok * d;
-  for (int i = 4 * threadIdx.x; i < d; i += 1024) {         // d is a multiple of 32: four elements per load
-    float4 v;
-    if constexpr (sizeof(T) == 2) {
-      const bf16x4 q = *reinterpret_cast<const bf16x4 *>(e + i);
-      v = float4{(float)q[0], (float)q[1], (float)q[2], (float)q[3]};
-    } else {
-      v = *reinterpret_cast<const float4 *>(e + i);
-    }
-    *reinterpret_cast<float4 *>(h + (size_t)m * d + i) = v;
-  }
-}
-
-void launch_embed(int dtype, const void *tok_emb, const int32_t *hist, const int32_t *drafts, int32_t *block_tok,
-                  float *h, int d, int M, int hist_base, int mode, hipStream_t s, const int32_t *n_dev) {
-  if (dtype == 1)
-    hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(M), dim3(256), 0, s, (const bf16_t *)tok_emb, hist, drafts, block_tok,
-                       h, d, hist_base, mode, n_dev);
-  else
-    hipLaunchKernelGGL(embed_kernel<float>, dim3(M), dim3(256), 0, s, (const float *)tok_emb, hist, drafts, block_tok, h,
-                       d, hist_base, mode, n_dev);
-}
-
-// ---------------------------------------------------------------------------------------------
-// RMSNorm, split in two: this kernel adds the residual partials, stores the new residual stream and
-// writes xg = h * gain (not yet divided by the root mean square) as the next GEMM's input, and the
-// sum of squares of its part of the row; the GEMM multiplies its accumulators by
-// 1 / sqrt(sum of squares / d + eps) in the epilogue (the GEMM is linear in its input rows).  That
-// lets `segs` workgroups share a row: a single workgroup per row left one CU to pull the whole row
-// and all its partials, with most CUs idle.
-// ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float block_sum_256(float v, float *sh) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
@@ -64,6 +23,71 @@ __device__ __forceinline__ float block_sum_256(float v, float *sh) {
   return t;
 }
 
+// NORM: the first layer's RMSNorm of the row as well (rmsnorm_kernel below says what it leaves), which saves its launch
+template <typename U, bool NORM>
+__global__ __launch_bounds__(256) void embed_kernel(const U *tok_emb, const int32_t *hist, const int32_t *drafts,
+                                                    int32_t *block_tok, float *h, int d, int hist_base, int mode,
+                                                    const int32_t *n_dev, const U *gain, typename Internal<U>::type *xn, int Mcap,
+                                                    int xn_mb, float *row_ss) {
+  typedef typename Internal<U>::type T;
+  __shared__ float sh[4];
+  const int m = blockIdx.x;
+  if (n_dev) hist_base = *n_dev - 1;
+  // mode 0: a verify block whose rows share token 0 (the last context token), then the drafts row by row;
+  // mode 1: consecutive history tokens; mode 2: single-column rows, every one the last context token
+  const int tok = mode == 1 ? hist[hist_base + m] : (m == 0 || mode == 2 ? hist[hist_base] : drafts[m - 1]);
+  if (threadIdx.x == 0) block_tok[m] = tok;
+  const U *e = tok_emb + (size_t)tok * d;
+  float ss = 0.0f;
+  for (int i = 4 * threadIdx.x; i < d; i += 1024) {         // d is a multiple of 32: four elements per load
+    float4 v;
+    if constexpr (sizeof(U) == 2) {
+      const bf16x4 q = *reinterpret_cast<const bf16x4 *>(e + i);
+      v = float4{(float)q[0], (float)q[1], (float)q[2], (float)q[3]};
+    } else {
+      v = *reinterpret_cast<const float4 *>(e + i);
+    }
+    *reinterpret_cast<float4 *>(h + (size_t)m * d + i) = v;
+    if constexpr (NORM) {
+      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+      store4(xn + act_pos<T>(m, i, Mcap, xn_mb), v.x * to_f32(gain[i]), v.y * to_f32(gain[i + 1]), v.z * to_f32(gain[i + 2]),
+             v.w * to_f32(gain[i + 3]));
+    }
+  }
+  if constexpr (NORM) {
+    ss = block_sum_256(ss, sh);
+    if (threadIdx.x < kNormSegs) row_ss[(size_t)m * kNormSegs + threadIdx.x] = threadIdx.x == 0 ? ss : 0.0f;
+  }
+}
+
+template <typename U>
+static void launch_embed_t(const void *tok_emb, const int32_t *hist, const int32_t *drafts, int32_t *block_tok, float *h, int d, int M,
+                           int hist_base, int mode, hipStream_t s, const int32_t *n_dev, const void *gain, void *xn, int Mcap, int xn_mb,
+                           float *row_ss) {
+  typedef typename Internal<U>::type T;
+  if (gain)
+    hipLaunchKernelGGL((embed_kernel<U, true>), dim3(M), dim3(256), 0, s, (const U *)tok_emb, hist, drafts, block_tok, h, d, hist_base,
+                       mode, n_dev, (const U *)gain, (T *)xn, Mcap, xn_mb, row_ss);
+  else
+    hipLaunchKernelGGL((embed_kernel<U, false>), dim3(M), dim3(256), 0, s, (const U *)tok_emb, hist, drafts, block_tok, h, d, hist_base,
+                       mode, n_dev, (const U *)nullptr, (T *)nullptr, 0, 0, (float *)nullptr);
+}
+
+void launch_embed(int dtype, const void *tok_emb, const int32_t *hist, const int32_t *drafts, int32_t *block_tok,
+                  float *h, int d, int M, int hist_base, int mode, hipStream_t s, const int32_t *n_dev, const void *gain, void *xn,
+                  int Mcap, int xn_mb, float *row_ss) {
+  if (dtype == 1) launch_embed_t<bf16_t>(tok_emb, hist, drafts, block_tok, h, d, M, hist_base, mode, s, n_dev, gain, xn, Mcap, xn_mb, row_ss);
+  else launch_embed_t<float>(tok_emb, hist, drafts, block_tok, h, d, M, hist_base, mode, s, n_dev, gain, xn, Mcap, xn_mb, row_ss);
+}
+
+// ---------------------------------------------------------------------------------------------
+// RMSNorm, split in two: this kernel adds the residual partials, stores the new residual stream and
+// writes xg = h * gain (not yet divided by the root mean square) as the next GEMM's input, and the
+// sum of squares of its part of the row; the GEMM multiplies its accumulators by
+// 1 / sqrt(sum of squares / d + eps) in the epilogue (the GEMM is linear in its input rows).  That
+// lets `segs` workgroups share a row: a single workgroup per row left one CU to pull the whole row
+// and all its partials, with most CUs idle.
+// ---------------------------------------------------------------------------------------------
 // Every thread owns J groups of 4 consecutive features of segment blockIdx.y (group index
 // tid + 256*j): all loads of the row and of its residual partials are issued before anything is
 // used, so the kernel costs one memory round trip instead of one per feature.
@@ -71,7 +95,7 @@ __device__ __forceinline__ float block_sum_256(float v, float *sh) {
 template <typename U, typename T, int J>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, const float *__restrict__ hpart, int n_part,
                                                       size_t part_stride, const U *__restrict__ gain, T *__restrict__ xn,
-                                                      int d, int Mcap, float *__restrict__ row_ss) {
+                                                      int d, int Mcap, int xn_mb, float *__restrict__ row_ss) {
   __shared__ float sh[4];
   const int m = blockIdx.x, segs = gridDim.y;
   const int d4 = d / segs / 4, c4 = blockIdx.y * d4;       // float4 groups of this segment, first group
@@ -126,16 +150,17 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, con
     ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
     if (i4 < d4) {
       if (n_part > 0) *reinterpret_cast<float4 *>(h + (size_t)m * d + 4 * (c4 + i4)) = v[j];
-      T *o = xn + act_offset<T>(m, 4 * (c4 + i4), Mcap);   // 4 features stay inside one chunk
+      T *o = xn + act_pos<T>(m, 4 * (c4 + i4), Mcap, xn_mb);   // 4 features lie side by side in either layout
       store4(o, v[j].x * gn[j].x, v[j].y * gn[j].y, v[j].z * gn[j].z, v[j].w * gn[j].w);
     }
   }
   ss = block_sum_256(ss, sh);
   if (threadIdx.x == 0) row_ss[(size_t)m * kNormSegs + blockIdx.y] = ss;
+  if (blockIdx.y == 0 && threadIdx.x >= segs && threadIdx.x < kNormSegs) row_ss[(size_t)m * kNormSegs + threadIdx.x] = 0.0f;
 }
 
 // segments a row is split into: up to kNormSegs, each at least 1024 features wide
-int rmsnorm_segments(int d) {
+static int rmsnorm_segments(int d) {
   int segs = d / 1024;
   segs = segs < 1 ? 1 : (segs > kNormSegs ? kNormSegs : segs);
   while (d % (segs * 4)) --segs;
@@ -144,13 +169,13 @@ int rmsnorm_segments(int d) {
 
 template <typename U>
 static void launch_rmsnorm_t(float *h, const float *hpart, int n_part, size_t part_stride, const void *gain, void *xn, int d,
-                             int M, int Mcap, float *row_ss, hipStream_t s) {
+                             int M, int Mcap, int xn_mb, float *row_ss, hipStream_t s) {
   typedef typename Internal<U>::type T;
   const int segs = rmsnorm_segments(d);
   const int j = (d / segs / 4 + 255) / 256;
 #define NGG_NORM(J)                                                                                                        \
   hipLaunchKernelGGL((rmsnorm_kernel<U, T, J>), dim3(M, segs), dim3(256), 0, s, h, hpart, n_part, part_stride, (const U *)gain, \
-                     (T *)xn, d, Mcap, row_ss)
+                     (T *)xn, d, Mcap, xn_mb, row_ss)
   if (j <= 1) NGG_NORM(1);
   else if (j <= 2) NGG_NORM(2);
   else if (j <= 4) NGG_NORM(4);
@@ -160,28 +185,28 @@ static void launch_rmsnorm_t(float *h, const float *hpart, int n_part, size_t pa
 }
 
 void launch_rmsnorm(int dtype, float *h, const float *hpart, int n_part, size_t part_stride, const void *gain, void *xn,
-                    int d, int M, int Mcap, float *row_ss, hipStream_t s) {
-  if (dtype == 1) launch_rmsnorm_t<bf16_t>(h, hpart, n_part, part_stride, gain, xn, d, M, Mcap, row_ss, s);
-  else launch_rmsnorm_t<float>(h, hpart, n_part, part_stride, gain, xn, d, M, Mcap, row_ss, s);
+                    int d, int M, int Mcap, int xn_mb, float *row_ss, hipStream_t s) {
+  if (dtype == 1) launch_rmsnorm_t<bf16_t>(h, hpart, n_part, part_stride, gain, xn, d, M, Mcap, xn_mb, row_ss, s);
+  else launch_rmsnorm_t<float>(h, hpart, n_part, part_stride, gain, xn, d, M, Mcap, xn_mb, row_ss, s);
 }
 
 // rows of a row-major matrix of the user's weights -> chunk-major activation layout in the internal type
 // (used to feed embedding rows to the GEMM); `centre` (fp32 [d], may be null) is subtracted first, then the
 // value is multiplied by `scale` (a power of two that the GEMM's out_scale undoes)
 template <typename U, typename T>
-__global__ __launch_bounds__(256) void pack_rows_kernel(const U *src, T *dst, int d, int Mcap, const float *centre, float scale) {
+__global__ __launch_bounds__(256) void pack_rows_kernel(const U *src, T *dst, int d, int Mcap, int mb, const float *centre, float scale) {
   for (int i = threadIdx.x; i < d; i += 256) {
     const float v = to_f32(src[(size_t)blockIdx.x * d + i]);
-    dst[act_offset<T>(blockIdx.x, i, Mcap)] = from_f32<T>((centre ? v - centre[i] : v) * scale);
+    dst[act_pos<T>(blockIdx.x, i, Mcap, mb)] = from_f32<T>((centre ? v - centre[i] : v) * scale);
   }
 }
 
-void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int Mcap, hipStream_t s, float scale,
+void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int Mcap, int mb, hipStream_t s, float scale,
                       const float *centre) {
   if (dtype == 1)
-    hipLaunchKernelGGL((pack_rows_kernel<bf16_t, half_t>), dim3(M), dim3(256), 0, s, (const bf16_t *)src, (half_t *)dst, d, Mcap, centre, scale);
+    hipLaunchKernelGGL((pack_rows_kernel<bf16_t, half_t>), dim3(M), dim3(256), 0, s, (const bf16_t *)src, (half_t *)dst, d, Mcap, mb, centre, scale);
   else
-    hipLaunchKernelGGL((pack_rows_kernel<float, float>), dim3(M), dim3(256), 0, s, (const float *)src, (float *)dst, d, Mcap, centre, scale);
+    hipLaunchKernelGGL((pack_rows_kernel<float, float>), dim3(M), dim3(256), 0, s, (const float *)src, (float *)dst, d, Mcap, mb, centre, scale);
 }
 
 // largest magnitude of a matrix, left as an fp32 bit pattern (magnitudes order like unsigned integers)

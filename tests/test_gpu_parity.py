@@ -848,6 +848,54 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd, tile, 
     assert rep.max_rel_logit_err <= 2e-2, rep
 
 
+@pytest.mark.parametrize("dtype,heads,kv,hd,d_model,d_ffn,vocab,prompt_len,k,wd,down", [
+    ("bf16", 3, 1, 32, 96, 160, 544, 50, 1, 1, 3),        # 2 tokens; contractions of 3 and 5 steps, waves without one; 6 sums of squares per row in 8 places
+    ("bf16", 2, 2, 64, 128, 2080, 2080, 64, 3, 5, 3),     # 16 tokens, one whole column block; a prompt of four; two fragments of gate/up per workgroup
+    ("bf16", 32, 32, 64, 64, 4128, 8224, 33, 4, 4, 3),    # 17 tokens; two fragments of q/k/v, three of gate/up, four of the unembedding
+    ("bf16", 5, 1, 128, 160, 6176, 1056, 80, 31, 1, 1),   # 32 tokens; four, the last workgroup short of three
+    ("bf16", 4, 2, 64, 96, 8224, 1056, 49, 8, 4, 1),      # 33 tokens; five
+    ("bf16", 1, 1, 64, 64, 10272, 1056, 40, 6, 8, 1),     # 49 tokens; six
+    ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 9, 7, 1),     # 64 tokens; seven
+    ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 5, 10, 1),    # 51 tokens; eight
+    ("f32", 3, 1, 32, 96, 160, 544, 50, 1, 1, 0),
+    ("f32", 4, 4, 32, 128, 2080, 16416, 64, 4, 4, 0),     # two fragments per workgroup; the unembedding on eight waves
+    ("f32", 2, 1, 64, 96, 544, 1056, 40, 9, 7, 0),
+])
+def test_streaming_gemm_edges(dtype, heads, kv, hd, d_model, d_ffn, vocab, prompt_len, k, wd, down):
+    """gemm_stream_kernel at the edges of its column blocks and rings: every number of fragments per workgroup, contractions
+    with fewer steps than waves, blocks that end inside a column block, residual GEMMs on both sides of the rule that gives
+    them to it (what follows adds the norm or not), a short prompt and two verify blocks against the oracle; the tolerance is
+    the one of every lock-step test."""
+    assert ngg.debug_plan(dtype, "residual", 1 + k * wd, d_model, d_ffn)["kernel"] == down
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=d_model, d_ffn=d_ffn,
+                vocab=vocab, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=max(1, k // 2))
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL[dtype], max_steps=2)
+    ctx.close()
+    assert rep.max_rel_logit_err <= TOL[dtype], rep
+
+
+@pytest.mark.parametrize("dtype,n,tokens", [("bf16", 96, 33), ("bf16", 64, 17), ("f32", 96, 33)])
+def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
+    """With the norms' own time asked for they are launches of their own, and the streaming residual GEMMs hand over a partial
+    instead: the same hidden states up to the order of the row sums."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=2, n_kv_heads=2, head_dim=32, d_model=n, d_ffn=160, vocab=544, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=40, n_gen=16, k=(tokens - 1) // 4, w=4, k_ctx_max=2)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=run["k"], max_w=4)
+    ctx.prefill(prompt)
+    drafts = np.random.default_rng(5).integers(0, 544, (run["k"], 4)).astype(np.int32)
+    states = []
+    for on in (False, True):
+        if on:
+            ctx.profile_enable(1 << ngg.PROF_CLASSES.index("norm"))
+        ctx.verify_step(drafts)
+        states.append(ctx.debug_peek("h", np.float32, tokens * n)[0].astype(np.float64))
+    assert ctx.profile_read()["norm"][1] == 2 * 2 + 1
+    ctx.close()
+    assert np.linalg.norm(states[0] - states[1]) <= (1e-6 if dtype == "f32" else 1e-3) * np.linalg.norm(states[0])
+
+
 @pytest.mark.parametrize("k,wd,kernel", [(16, 4, 0), (16, 5, 0), (19, 5, 0), (16, 6, 1)])
 def test_down_of_4096_wide_models_on_both_sides_of_96_tokens(k, wd, kernel):
     """Blocks of 65, 81 and 96 tokens run down on the streaming kernel (five and six column blocks, 2 x 2 waves, split
