@@ -8,8 +8,9 @@
 //
 // Keys and values are kept in MFMA operand order (k_offset / v_offset in ngg_internal.h): a tile of
 // 32 positions is 32*hd contiguous elements, cut into 1 KB blocks that are each exactly one
-// wave-wide fragment load.  Two kernels use them:
-//  * attn_shared_kernel (more than 16 block tokens): the four waves of a workgroup own different
+// wave-wide fragment load.  Three kernels use them:
+//  * attn_block_kernel (16-bit, more than 64 block tokens, but for long slices): 32 queries per wave, 64 keys per step.
+//  * attn_shared_kernel (more than 16 block tokens otherwise): the four waves of a workgroup own different
 //    groups of 16*QF queries and all need every tile, so the workgroup copies each tile into LDS once
 //    (a linear copy: the tile already is in fragment order, so every fragment read is conflict-free)
 //    and the waves read their MFMA operands from there.  No merge between waves.
@@ -484,6 +485,215 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// 16-bit blocks of more than 64 tokens (wide verify blocks, prompt pieces): the arithmetic bounds these as much as the
+// stream of tiles.  Workgroup = (head, list slice, 128 queries), a wave owns 32 of them; a step takes two tiles (64 keys)
+// from LDS.  Scores and output run on the 32x32x16 MFMA (a loop of it reaches 2.1-2.2 PFLOP/s here, 16x16x32 1.45-1.55), which
+// the tiles' order serves as it is: row 8 j + 4 h + i of a key tile is key 16 (j % 2) + 8 h + 4 (j / 2) + i, so lane (query, h) ends
+// up with the keys 16 u + 8 h .. + 7 of every 16, its operand of P.V.  Two tiles per barrier, one maximum and one test of the
+// reference for 32 scores of a lane.  Counters on a 16K prompt: matrix cores busy 46 % of the cycles, vector unit 42 %, LDS 35 %.
+// ---------------------------------------------------------------------------------------------
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <int HD>
+__global__ __launch_bounds__(256, 2) void attn_block_kernel(const AttnArgs a, int Z, int n_units) {
+  typedef half_t T;
+  constexpr int DS = HD / 32, KQ = HD / 16, DB = HD / 32;   // 32-dim slices, 16-dim steps of q.k, 32-dim blocks of the output
+  constexpr int TILE = 32 * HD, KT = 2;                     // elements of a tile, tiles per step
+  constexpr int GQ = 128;
+  constexpr int PIECES = TILE * 2 / 16, PPT = (PIECES + 255) / 256;
+  const int slot_b = blockIdx.x / 8, xcd = blockIdx.x % 8;
+  const int unit_x = slot_b / Z;
+  const int unit = unit_x * 8 + xcd;
+  if (unit >= n_units) return;
+  const int S = a.n_splits;
+  const int split = unit % S, head = unit / S;
+  const int hkv = head / (a.H / a.Hkv);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, h = lane >> 5;
+  const int M = a.M, C = a.C, P = a.n_dev ? *a.n_dev - 1 : a.P;
+  const int z = (unit_x * Z / 32) & 1 ? Z - 1 - slot_b % Z : slot_b % Z;
+  const int q0 = z * GQ, qw = q0 + wv * 32;
+  const bool active = qw < M;
+
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  T *kl = reinterpret_cast<T *>(smem);                      // [2][KT][TILE] key tiles
+  T *vl = kl + 2 * KT * TILE;                               // [2][KT][TILE] value tiles
+
+  const int q_hi = min(M, q0 + GQ) - 1;
+  const int NP = (P + 31) / 32;
+  const int sb = block_row_start(q0, C, a.shared0) / 32 * (a.shared0 ? 0 : 1);
+  const int NS = q_hi / 32 + 1 - sb;
+  const int TL = NP + NS;
+  const int t_begin = (int)((long)TL * split / S), t_end = (int)((long)TL * (split + 1) / S);
+  const int n_tiles = t_end - t_begin;
+  // block tiles behind this wave's last query hold nothing it may see
+  const int wave_tiles = min(n_tiles, NP + (min(M, qw + 32) - 1) / 32 + 1 - sb - t_begin);
+  const T *kc = (const T *)a.kcache + (size_t)hkv * a.Spad * HD, *vc = (const T *)a.vcache + (size_t)hkv * a.Spad * HD;
+  const T *ksc = (const T *)a.kscr + (size_t)hkv * a.kv_rows * HD, *vsc = (const T *)a.vscr + (size_t)hkv * a.kv_rows * HD;
+
+  u32x4 kst[KT][PPT], vst[KT][PPT];                         // the next step's tiles, on their way
+  auto stage_load = [&](int t) {
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+      const int ct = max(min(t_begin + t + k, t_end - 1), 0);   // clamped into the list: loads are unconditional
+      const bool own = ct >= NP;
+      const size_t off = (size_t)(own ? sb + ct - NP : ct) * TILE;
+      const T *kp = (own ? ksc : kc) + off, *vp = (own ? vsc : vc) + off;
+#pragma unroll
+      for (int i = 0; i < PPT; ++i) {
+        const int pc = min(tid + 256 * i, PIECES - 1);
+        kst[k][i] = reinterpret_cast<const u32x4 *>(kp)[pc];
+        vst[k][i] = reinterpret_cast<const u32x4 *>(vp)[pc];
+      }
+    }
+  };
+  auto stage_store = [&](int buf) {
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+#pragma unroll
+      for (int i = 0; i < PPT; ++i) {
+        const int pc = min(tid + 256 * i, PIECES - 1);
+        reinterpret_cast<u32x4 *>(kl + (size_t)(buf * KT + k) * TILE)[pc] = kst[k][i];
+        reinterpret_cast<u32x4 *>(vl + (size_t)(buf * KT + k) * TILE)[pc] = vst[k][i];
+      }
+  };
+  stage_load(0);
+
+  // this lane's query: visible block keys are [qlo, qhi]
+  const int mq = min(qw + r32, M - 1);
+  const int qlo = block_row_start(mq, C, a.shared0), qhi = mq;
+  half8 Q[KQ];
+#pragma unroll
+  for (int q = 0; q < KQ; ++q) Q[q] = *reinterpret_cast<const half8 *>((const T *)a.q + ((size_t)head * a.Mcap + mq) * HD + q * 16 + h * 8);
+  float mref = kNegBig, lsum = 0.0f;
+  f32x16 O[DB];
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) O[d][r] = 0.f;
+  const float sfac = Softmax<T>::factor(a.scale);
+  const int loff = (h * 16 + (r32 & 15)) * 8;               // this lane's place in a 1 KB block (elements)
+  const int koff = (r32 >> 4) * DS * 512 + loff, voff = (r32 >> 4) * 512 + loff;
+
+  auto compute = [&](int t, int buf) {
+    if (!active || t >= wave_tiles) return;                 // (uniform per wave)
+    const T *kt = kl + (size_t)buf * KT * TILE + koff, *vt = vl + (size_t)buf * KT * TILE + voff;
+    f32x16 Sc[KT];
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) Sc[k][r] = 0.f;
+#pragma unroll
+    for (int q = 0; q < KQ; ++q)
+#pragma unroll
+      for (int k = 0; k < KT; ++k) {
+        const half8 kf = *reinterpret_cast<const half8 *>(kt + k * TILE + (q >> 1) * 512 + (q & 1) * 256);
+        Sc[k] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, Q[q], Sc[k], 0, 0, 0);
+      }
+    // register 4 j + i of tile k is key 16 (j % 2) + 8 h + 4 (j / 2) + i; a key that this query must not see scores minus
+    // infinity, so that only steps at the end of the list pay for the masks
+    float mx = kNegBig;
+#pragma unroll
+    for (int k = 0; k < KT; ++k) {
+      const int ct = t_begin + t + k;
+      const bool own = ct >= NP, in = t + k < n_tiles;
+      const int tile0 = (own ? sb + ct - NP : ct) * 32;
+      if (own || !in || tile0 + 32 > P) {                   // (uniform)
+        const int lo = own ? qlo : 0, hi = in ? (own ? qhi : P - 1) : -1;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int key = tile0 + 16 * ((r >> 2) & 1) + 8 * h + 4 * (r >> 3) + (r & 3);
+          const bool v = (key >= lo && key <= hi) || (own && in && a.shared0 && key == 0);
+          Sc[k][r] = v ? Sc[k][r] : -__builtin_inff();
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, Sc[k][r]);
+    mx = mx > 0.5f * kNegBig ? mx * sfac : kNegBig;         // sfac > 0: the maximum commutes with the scaling
+    if (__ballot(mx > mref + Softmax<T>::lazy) != 0) {      // uniform; always taken on a query's first visible key
+      const float mnew = fmaxf(mref, fmaxf(mx, other_half(mx)));
+      const float alpha = Softmax<T>::ex(mref - mnew);
+      lsum *= alpha;
+      if (__ballot(mnew != mref && mref > 0.5f * kNegBig) != 0) {
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) O[d][r] *= alpha;
+      }
+      mref = mnew;
+    }
+    const float bias = Softmax<T>::bias(mref);
+    half8 Pf[KT][2];
+    float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int r = 4 * (u + 2 * (e >> 2)) + (e & 3);
+          const float p = Softmax<T>::prob(Sc[k][r], sfac, bias);
+          ps[e & 3] += p;
+          Pf[k][u][e] = (half_t)p;
+        }
+    lsum += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+#pragma unroll
+    for (int k = 0; k < KT; ++k)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int d = 0; d < DB; ++d) {
+          const half8 vf = *reinterpret_cast<const half8 *>(vt + k * TILE + d * 1024 + u * 256);
+          O[d] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, Pf[k][u], O[d], 0, 0, 0);
+        }
+  };
+
+  // (the queries have landed before the loop: see attn_shared_kernel)
+  __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
+  int buf = 0;
+  for (int t = 0; t < n_tiles; t += KT) {                   // barriers are uniform
+    stage_store(buf);
+    __syncthreads();
+    stage_load(t + KT);
+    compute(t, buf);
+    buf ^= 1;
+  }
+
+  if (!active) return;
+  const int m = qw + r32;
+  const float l = lsum + other_half(lsum);                  // the two lanes of a query each held a share of its sum
+  if (S == 1) {                                             // the whole list: the quotient is the result, nothing to merge
+    const float inv = 1.0f / l;
+    if (m < M)
+#pragma unroll
+      for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          store4((T *)a.out + act_pos<T>(m, head * HD + d * 32 + 8 * j + 4 * h, a.Mcap, a.out_mb), O[d][4 * j] * inv, O[d][4 * j + 1] * inv,
+                 O[d][4 * j + 2] * inv, O[d][4 * j + 3] * inv);
+    return;
+  }
+  // partial outputs in the order attn_merge_kernel reads: [head][slice][16-query group][16-dim group][lane][4], lane = 16 (dim / 4 % 4) + query % 16
+  const size_t blk = ((size_t)head * S + split) * (a.Mpart / 16) + (qw / 16 + (r32 >> 4));
+  if (m >= M) return;                                       // (a third of the partials of 97 tokens)
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      *reinterpret_cast<f32x4 *>(a.part_o + ((blk * (HD / 16) + 2 * d + (j >> 1)) * 64 + (2 * (j & 1) + h) * 16 + (r32 & 15)) * 4) =
+          f32x4{O[d][4 * j], O[d][4 * j + 1], O[d][4 * j + 2], O[d][4 * j + 3]};
+  if (h == 0) {
+    const size_t slot_m = ((size_t)head * S + split) * a.Mpart + m;
+    a.part_ml[slot_m * 2 + 0] = mref;
+    a.part_ml[slot_m * 2 + 1] = l;
+  }
+}
+
 // out[m][h*HD + d] = sum_s o_s[d] e^{m_s - m*} / sum_s l_s e^{m_s - m*}, slices taken in index order,
 // 8 at a time with a running maximum (one round of loads when there are at most 8 slices: the kernel
 // is a chain of memory latencies, nothing else).  One workgroup per (16-query group, head); a thread
@@ -545,22 +755,34 @@ static void launch_stream(const AttnArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((attn_stream_kernel<T, HD, QF, NW>), dim3((n_units + 7) / 8 * 8 * Z), dim3(64 * NW), lds, s, a, Z, n_units);
 }
 
-// query groups of 16 per wave in attn_shared_kernel: two once a block has more than 64 tokens,
-// where the registers hold them (fp32 fragments are twice as large)
-template <typename T, int HD> constexpr int attn_shared_qmax() { return sizeof(T) == 2 || HD <= 64 ? 2 : 1; }
+// query groups of 16 per wave in attn_shared_kernel, fp32 blocks of more than 64 tokens: two where the registers hold them
+template <int HD> constexpr int attn_shared_qmax() { return HD <= 64 ? 2 : 1; }
+
+// Slices of a dozen tiles or more that no other workgroup shares are bound by the stream of tiles, which are read with
+// non-temporal loads (measured on MI355X, whole verify step: 7.07 -> 6.86 ms at a 16.4K context with 32 tiles per slice, 3.08 ->
+// 3.06 ms at 13 tiles; 4.18 -> 4.19 ms at 8 tiles, where they stay ordinary loads)
+static bool long_slices(const AttnArgs &a, int Z) { return Z == 1 && ((a.P + 31) / 32 + 1) / a.n_splits >= 12; }
 
 template <typename T, int HD, int QF>
 static void launch_shared(const AttnArgs &a, hipStream_t s) {
   const size_t lds = (size_t)4 * 32 * HD * sizeof(T);
   const int Z = (a.M + 64 * QF - 1) / (64 * QF);
   const int n_units = a.n_splits * a.H;
-  // Slices of a dozen tiles or more that no other workgroup shares are read with non-temporal loads (measured on
-  // MI355X, whole verify step: 7.07 -> 6.86 ms at a 16.4K context with 32 tiles per slice, 3.08 -> 3.06 ms at 13
-  // tiles; 4.18 -> 4.19 ms at 8 tiles, where they stay ordinary loads)
-  const int tiles = ((a.P + 31) / 32 + 1) / a.n_splits;
-  const bool nt = Z == 1 && tiles >= 12;
-  if (nt) hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, true>), dim3((n_units + 7) / 8 * 8 * Z), dim3(256), lds, s, a, Z, n_units);
-  else hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, false>), dim3((n_units + 7) / 8 * 8 * Z), dim3(256), lds, s, a, Z, n_units);
+  const dim3 grid((n_units + 7) / 8 * 8 * Z);
+  if constexpr (sizeof(T) == 4 || QF == 1) {                // (16-bit, two groups: long slices only, see launch_hd)
+    if (!long_slices(a, Z)) { hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, false>), grid, dim3(256), lds, s, a, Z, n_units); return; }
+  }
+  hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, true>), grid, dim3(256), lds, s, a, Z, n_units);
+}
+
+// query groups of 16 per wave in attn_shared_kernel, blocks of more than 64 tokens: two where the registers hold them (fp32
+// fragments are twice as large)
+template <typename T, int HD> constexpr int attn_shared_qmax() { return sizeof(T) == 2 || HD <= 64 ? 2 : 1; }
+
+template <int HD>
+static void launch_block(const AttnArgs &a, hipStream_t s) {
+  const int Z = (a.M + 127) / 128, n_units = a.n_splits * a.H;
+  hipLaunchKernelGGL((attn_block_kernel<HD>), dim3((n_units + 7) / 8 * 8 * Z), dim3(256), (size_t)8 * 32 * HD * 2, s, a, Z, n_units);
 }
 
 template <typename T, int HD>
@@ -572,8 +794,13 @@ static void launch_hd(const AttnArgs &a, hipStream_t s) {
     return;
   }
   if (a.M <= 16) launch_stream<T, HD, 1, 4>(a, s);
-  else if (a.M <= 64 || attn_shared_qmax<T, HD>() == 1) launch_shared<T, HD, 1>(a, s);
-  else launch_shared<T, HD, attn_shared_qmax<T, HD>()>(a, s);
+  else if (a.M <= 64) launch_shared<T, HD, 1>(a, s);
+  else if (sizeof(T) == 2 && !long_slices(a, (a.M + 127) / 128)) {
+    // (32 heads of 128, us, attn_shared_kernel -> this: 97 tokens on 3000 positions 21.5 -> 18.4, 241 on 2048 27.8 -> 23.0, a
+    // 2048-token piece 96 -> 77, behind 13K positions 630 -> 564; 777 tokens, 12 heads of 64: 14.4 -> 12.4.  Long slices, where
+    // the tiles bound the kernel, lose: 97 tokens on 8192 positions 35.8 -> 38.2, on 16384 56.5 -> 61.7)
+    if constexpr (sizeof(T) == 2) launch_block<HD>(a, s);
+  } else launch_shared<T, HD, attn_shared_qmax<T, HD>()>(a, s);
   if (a.one_row) return;                                    // the output projection merges the slices
   if (a.n_splits == 1) return;                              // the kernel wrote the result itself
   hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);

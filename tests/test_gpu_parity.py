@@ -876,6 +876,27 @@ def test_streaming_gemm_edges(dtype, heads, kv, hd, d_model, d_ffn, vocab, promp
     assert rep.max_rel_logit_err <= TOL[dtype], rep
 
 
+@pytest.mark.parametrize("heads,kv,hd,prompt_len,k,wd,slices", [
+    (2, 2, 32, 66, 16, 4, 1),        # 65 tokens: one query in the third wave, none in the fourth; an odd number of tiles, whole list in one slice
+    (4, 1, 64, 129, 16, 8, 1),       # 129 tokens: one query in the second workgroup; a prompt with one query in its second
+    (3, 3, 128, 385, 12, 8, 3),      # 97 tokens, three slices that begin on odd tiles
+    (5, 1, 128, 640, 16, 16, 5),     # 257 tokens, a prompt of whole tiles and whole workgroups
+    (6, 2, 64, 97, 31, 4, 1),        # 125 tokens
+])
+def test_block_attention_edges_16_bit(heads, kv, hd, prompt_len, k, wd, slices):
+    """attn_block_kernel at the edges of its waves, steps of two tiles and slices, causal (the prompt) and with the rows of a
+    block, against the oracle; the tolerance is the one of every lock-step test."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=128, d_ffn=256, vocab=1056)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
+    layouts = []
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=2,
+                       on_step=lambda step: layouts.append(ctx.debug_peek("attn_layout", np.int32)[0].tolist()))
+    ctx.close()
+    assert layouts[0][0] == slices and layouts[0][2] == 1 + k * wd
+    assert rep.max_rel_logit_err <= TOL["bf16"], rep
+
+
 @pytest.mark.parametrize("dtype,n,tokens", [("bf16", 96, 33), ("bf16", 64, 17), ("f32", 96, 33)])
 def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
     """With the norms' own time asked for they are launches of their own, and the streaming residual GEMMs hand over a partial
