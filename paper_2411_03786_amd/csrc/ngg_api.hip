@@ -84,7 +84,7 @@ struct ngg_ctx {
   int *pmax_idx = nullptr, *cand_idx = nullptr;
   float *cand_val = nullptr;
   void *xn = nullptr, *q = nullptr, *attn = nullptr, *act = nullptr;
-  // the same in operand order, for gemm_stream_kernel (64 rows).  Buffers of their own: the tiled kernel relies on zeros behind
+  // the same in operand order, for gemm_stream_kernel (64 rows, xn_s 128).  Buffers of their own: the tiled kernel relies on zeros behind
   // the last contraction element of the chunk-major ones.
   void *xn_s = nullptr, *attn_s = nullptr, *act_s = nullptr;
   // the library's own operand-order copies of every matrix it multiplies with
@@ -200,16 +200,18 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   const bool one_row = one_row_call(c, M);
   const int mb = (M + 15) / 16;
   auto layout = [&](int epi, int frags, int K) { return !one_row && stream_takes(dt, epi, M, frags, K, c->tile_only) ? mb : 0; };
-  const int xn_mb = layout(EPI_QKV, 0, d.d_model), attn_mb = layout(EPI_RESIDUAL, d.d_model / 16, dq),
+  const int qkv_mb = layout(EPI_QKV, (dq + 2 * d.n_kv_heads * d.head_dim) / 16, d.d_model), gu_mb = layout(EPI_GATEUP, d.d_ffn / 8, d.d_model),
+            un_mb = layout(EPI_UNEMBED, d.vocab / 16, d.d_model), attn_mb = layout(EPI_RESIDUAL, d.d_model / 16, dq),
             act_mb = layout(EPI_RESIDUAL, d.d_model / 16, d.d_ffn);
-  void *const xn = xn_mb ? c->xn_s : c->xn, *const attn = attn_mb ? c->attn_s : c->attn, *const act = act_mb ? c->act_s : c->act;
+  auto xn_of = [&](int xn_mb) { return xn_mb ? c->xn_s : c->xn; };   // every norm writes for one GEMM
+  void *const attn = attn_mb ? c->attn_s : c->attn, *const act = act_mb ? c->act_s : c->act;
   const bool inside = !one_row && norms_inside(c);
   int ss_segs = kNormSegs;                           // sums of squares per row, as the last norm left them
   {
     ProfScope ps(c, NGG_PROF_OTHER);
     launch_embed(dt, c->w.tok_emb, tok_src ? tok_src : c->hist, c->drafts, c->block_tok, c->h, d.d_model, M,
-                 tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev, inside ? c->layers[0].attn_norm : nullptr, xn, c->Mcap,
-                 xn_mb, c->row_ss);
+                 tok_src ? 0 : P, from_hist ? 1 : (shared0 ? 0 : 2), s, n_dev, inside ? c->layers[0].attn_norm : nullptr, xn_of(qkv_mb), c->Mcap,
+                 qkv_mb, c->row_ss);
   }
   const int n_splits = attention_splits(dt, d.head_dim, d.n_heads, M, P, c->max_splits, from_hist && C > 1);
   const bool whole = attention_whole(dt, d.head_dim, d.n_heads, M, P, from_hist && C > 1);
@@ -231,11 +233,11 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   int pending = 0;                                   // residual partials the next RMSNorm has to add
   bool normed = inside;                              // the kernel before has done the norm
   // the norm in front of a GEMM: a launch of its own, or (one row) what the GEMM's prologue needs for it
-  auto norm = [&](const void *gain) {
+  auto norm = [&](const void *gain, int xn_mb) {
     if (normed) { normed = false; return; }
     if (!one_row) {
       ProfScope ps(c, NGG_PROF_NORM);
-      launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, gain, xn, d.d_model, M, c->Mcap, xn_mb, c->row_ss, s);
+      launch_rmsnorm(dt, c->h, c->hpart, pending, part_stride, gain, xn_of(xn_mb), d.d_model, M, c->Mcap, xn_mb, c->row_ss, s);
       ss_segs = kNormSegs;
       return;
     }
@@ -243,9 +245,9 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     if (pending > 0) std::swap(h_cur, h_next);
   };
   // a residual GEMM on gemm_stream_kernel runs the norm behind it
-  auto norm_after = [&](GemmArgs &g, const void *gain) {
+  auto norm_after = [&](GemmArgs &g, const void *gain, int xn_mb) {
     if (!g.x_mb || !inside) return;
-    g.h = c->h; g.gain = gain; g.xn = xn; g.xn_mb = xn_mb; g.ss_out = c->row_ss;
+    g.h = c->h; g.gain = gain; g.xn = xn_of(xn_mb); g.xn_mb = xn_mb; g.ss_out = c->row_ss;
     ss_segs = stream_segments(d.d_model);
     normed = true;
   };
@@ -265,11 +267,11 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       vscr_l = (char *)c->vcache + (kv_layer * c->Spad + P) * d.head_dim * c->esize;
       kv_rows = c->Spad;
     }
-    norm(lw.attn_norm);
+    norm(lw.attn_norm, qkv_mb);
     {
       ProfScope ps(c, NGG_PROF_GEMM_QKV);
       GemmArgs g{};
-      g.X = xn; g.x_mb = xn_mb; g.W0 = c->lt[l].wqkv;
+      g.X = xn_of(qkv_mb); g.x_mb = qkv_mb; g.W0 = c->lt[l].wqkv;
       g.M = M; g.N = dq + 2 * d.n_kv_heads * d.head_dim; g.K = d.d_model;
       g.q = c->q; g.kscr = kscr_l; g.vscr = vscr_l; g.kv_rows = kv_rows;
       g.H = d.n_heads; g.Hkv = d.n_kv_heads; g.hd = d.head_dim; g.Mcap = c->Mcap; g.C = C; g.P = P; g.shared0 = shared0;
@@ -299,16 +301,16 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.hpart = c->hpart; g.KS = ks_o; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / c->lt[l].s_o;
       g.hd = d.head_dim;
-      norm_after(g, lw.mlp_norm);
+      norm_after(g, lw.mlp_norm, gu_mb);
       if (one_row) { row.part_o = c->part_o; row.part_ml = c->part_ml; row.n_splits = n_splits; row.attn_out = attn; }
       gemm(EPI_RESIDUAL, g);
     }
     pending = ks_o;
-    norm(lw.mlp_norm);
+    norm(lw.mlp_norm, gu_mb);
     {
       ProfScope ps(c, NGG_PROF_GEMM_GATEUP);
       GemmArgs g{};
-      g.X = xn; g.x_mb = xn_mb; g.W0 = c->lt[l].wgu; g.M = M; g.N = d.d_ffn; g.K = d.d_model;
+      g.X = xn_of(gu_mb); g.x_mb = gu_mb; g.W0 = c->lt[l].wgu; g.M = M; g.N = d.d_ffn; g.K = d.d_model;
       g.act = act; g.act_mb = act_mb; g.Mcap = c->Mcap;
       g.row_ss = c->row_ss; g.ss_segs = ss_segs; g.ss_eps = d.rms_eps;
       g.out_scale = 1.0f / c->lt[l].s_gu;
@@ -320,7 +322,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       g.X = act; g.x_mb = act_mb; g.W0 = c->lt[l].wdown; g.M = M; g.N = d.d_model; g.K = d.d_ffn;
       g.hpart = c->hpart; g.KS = ks_down; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / c->lt[l].s_down;
-      norm_after(g, l + 1 < d.n_layers ? c->layers[l + 1].attn_norm : c->w.final_norm);
+      if (l + 1 < d.n_layers) norm_after(g, c->layers[l + 1].attn_norm, qkv_mb);
+      else norm_after(g, c->w.final_norm, un_mb);
       gemm(EPI_RESIDUAL, g);
     }
     pending = ks_down;
@@ -329,10 +332,10 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     const bool last_only = last_row_only && M > 1;
     // the last row alone goes through the single-token kernel, which runs the norm of that row itself (row 0 of the residual
     // stream, which nobody reads any more, takes the sum)
-    if (!last_only || !norms_inside(c)) norm(c->w.final_norm);
+    if (!last_only || !norms_inside(c)) norm(c->w.final_norm, un_mb);
     ProfScope ps(c, NGG_PROF_GEMM_UNEMBED);
     GemmArgs g{};
-    g.X = xn; g.x_mb = xn_mb; g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
+    g.X = xn_of(un_mb); g.x_mb = un_mb; g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
     g.logits = want_logits ? c->logits : nullptr;
     g.pmax_val = c->pmax_val; g.pmax_idx = c->pmax_idx; g.Mcap = c->Mcap;
     g.row_ss = c->row_ss; g.ss_segs = ss_segs; g.ss_eps = d.rms_eps;
@@ -558,7 +561,7 @@ ngg_status ngg_create(const ngg_model_desc *desc, const ngg_weights *weights, vo
   TRY(dev_alloc(c, &c->q, (size_t)c->Mcap * dq * c->esize, true));
   TRY(dev_alloc(c, &c->attn, act_elems(d.dtype, c->Mcap, dq) * c->esize, true));
   TRY(dev_alloc(c, &c->act, act_elems(d.dtype, c->Mcap, d.d_ffn) * c->esize, true));
-  TRY(dev_alloc(c, &c->xn_s, (size_t)64 * d.d_model * c->esize, true));
+  TRY(dev_alloc(c, &c->xn_s, (size_t)128 * d.d_model * c->esize, true));
   TRY(dev_alloc(c, &c->attn_s, (size_t)64 * dq * c->esize, true));
   TRY(dev_alloc(c, &c->act_s, (size_t)64 * d.d_ffn * c->esize, true));
   // attention partials, [head][slice][rows]: slices x rows is at most 32 x 128 for blocks of up to 64 tokens, and

@@ -761,40 +761,12 @@ static void launch_fm(const GemmArgs &a, int KS, hipStream_t s) {
   launch_gemm_cfg<T, EPI, 8, WN, WK, RING>(a, KS, s);        // 128-row tiles; more rows loop over W again
 }
 
-// q/k/v and gate/up: one workgroup = FN fragments, its four waves split the steps of every chunk
-// (WN = 1, WK = 4).  FN is chosen so that the fragments spread evenly over the 256 CUs (7B shapes:
-// 768 q/k/v fragments = 3 per workgroup, 1792 gate/up fragments = 7 per workgroup, 256 workgroups
-// each); wide fragment sets keep a 2-deep ring (FN KB per slot and wave are in flight anyway).
+// q/k/v and gate/up: one workgroup = FN fragments, its four waves split the steps of every chunk (WN = 1, WK = 4).  fp32
+// only: the 16-bit ones run on gemm_stream_kernel or the tiled one.
 template <typename T, int EPI, int FM>
 static void launch_paired_fm(const GemmArgs &a, hipStream_t s) {
-  constexpr int FMAX = sizeof(T) == 4 ? 2 : (FM == 8 ? 7 : 8);   // accumulators: FN * FM * 4 registers; fp32 fragments: twice the ring
-  int fn = (a.n_groups + 255) / 256;
-  fn = fn < 1 ? 1 : (fn > FMAX ? FMAX : fn);
-  switch (fn) {
-    case 1: launch_gemm_cfg<T, EPI, FM, 1, 4, 4, 1>(a, 1, s); break;
-    case 2: launch_gemm_cfg<T, EPI, FM, 1, 4, 4, 2>(a, 1, s); break;
-    default:
-      if constexpr (FMAX >= 4) {
-        switch (fn) {
-          case 3: launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 3>(a, 1, s); break;
-          case 4: launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 4>(a, 1, s); break;
-          default:
-            if constexpr (FMAX >= 6) {
-              switch (fn) {
-                case 5: launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 5>(a, 1, s); break;
-                case 6: launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 6>(a, 1, s); break;
-                default:
-                  if constexpr (FMAX >= 8) {
-                    if (fn == 7) launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 7>(a, 1, s);
-                    else launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 8>(a, 1, s);
-                  } else {
-                    launch_gemm_cfg<T, EPI, FM, 1, 4, 2, 7>(a, 1, s);   // 128-row tiles: 8 fragments no longer fit the registers
-                  }
-              }
-            }
-        }
-      }
-  }
+  if (a.n_groups <= 256) launch_gemm_cfg<T, EPI, FM, 1, 4, 4, 1>(a, 1, s);
+  else launch_gemm_cfg<T, EPI, FM, 1, 4, 4, 2>(a, 1, s);
 }
 
 template <typename T, int EPI>
@@ -891,8 +863,12 @@ static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   a.n_groups = gemm_groups(epi, a);
   const bool wide = a.n_groups >= 4 * 200;
   switch (epi) {
-    case EPI_QKV: launch_paired<T, EPI_QKV>(a, s); break;
-    case EPI_GATEUP: launch_paired<T, EPI_GATEUP>(a, s); break;
+    case EPI_QKV:
+      if constexpr (sizeof(T) == 4) launch_paired<T, EPI_QKV>(a, s);
+      break;
+    case EPI_GATEUP:
+      if constexpr (sizeof(T) == 4) launch_paired<T, EPI_GATEUP>(a, s);
+      break;
     case EPI_RESIDUAL:
       if (residual_narrow(a.M, a.N, a.K)) launch_residual<T, 1, 4>(a, s);
       else launch_residual<T, 2, 2>(a, s);

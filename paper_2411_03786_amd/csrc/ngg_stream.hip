@@ -1,4 +1,4 @@
-// Streaming GEMM  Y[M x N] = X[M x K] . W[N x K]^T  for blocks of up to 64 rows: a verify call is meant to stay bound by the
+// Streaming GEMM  Y[M x N] = X[M x K] . W[N x K]^T  for blocks of up to 64 rows (q/k/v and gate/up: 128): a verify call is meant to stay bound by the
 // one read of W (Section 3), and what a launch costs beyond that read is its start, its barriers and its finish.
 //
 // A workgroup owns FN fragments (16 rows) of W and all block rows; its NW waves split the steps of 32 contraction elements
@@ -215,6 +215,7 @@ template <typename T, int EPI> constexpr int stream_ring(int fm, int fn) {
   if (EPI == EPI_RESIDUAL) return sizeof(T) == 2 ? 6 : 3;
   if (EPI == EPI_UNEMBED) return sizeof(T) == 2 ? (fn == 8 || fm == 4 ? 2 : 3) : 2;
   if (sizeof(T) == 4) return 2;
+  if (fm > 4) return fn <= 4 ? (fm == 8 ? (fn == 3 ? 2 : 1) : (fn == 3 ? 3 : 2)) : (fn * fm == 64 ? 1 : 2);
   return fn == 1 ? 3 : (fn == 2 ? 2 : (fn <= 4 ? 4 : (fn * fm <= 28 ? 2 : 1)));   // (2 at 8 x 4 fragments spills)
 }
 
@@ -247,6 +248,15 @@ static void launch_stream_fm(const GemmArgs &a, hipStream_t s) {
   } else if constexpr (sizeof(T) == 4) {
     if (fn <= 1) launch_stream_cfg<T, EPI, FM, 1, 4>(a, s);
     else launch_stream_cfg<T, EPI, FM, 2, 4>(a, s);
+  } else if constexpr (FM > 4) {                            // (wide matrices only: stream_takes)
+    switch (fn) {
+      case 3: launch_stream_cfg<T, EPI, FM, 3, 8>(a, s); break;
+      case 4: launch_stream_cfg<T, EPI, FM, 4, 8>(a, s); break;
+      case 5: launch_stream_cfg<T, EPI, FM, 5, 4>(a, s); break;
+      case 6: launch_stream_cfg<T, EPI, FM, 6, 4>(a, s); break;
+      case 7: launch_stream_cfg<T, EPI, FM, 7, 4>(a, s); break;
+      default: launch_stream_cfg<T, EPI, FM, 8, 4>(a, s);
+    }
   } else {
     switch (fn) {
       case 1: launch_stream_cfg<T, EPI, FM, 1, 4>(a, s); break;
@@ -267,7 +277,16 @@ static void launch_stream_epi(const GemmArgs &a, hipStream_t s) {
     case 1: launch_stream_fm<T, EPI, 1>(a, s); break;
     case 2: launch_stream_fm<T, EPI, 2>(a, s); break;
     case 3: launch_stream_fm<T, EPI, 3>(a, s); break;
-    default: launch_stream_fm<T, EPI, 4>(a, s);
+    case 4: launch_stream_fm<T, EPI, 4>(a, s); break;
+    default:
+      if constexpr (sizeof(T) == 2 && (EPI == EPI_QKV || EPI == EPI_GATEUP)) {
+        switch ((a.M + 15) / 16) {
+          case 5: launch_stream_fm<T, EPI, 5>(a, s); break;
+          case 6: launch_stream_fm<T, EPI, 6>(a, s); break;
+          case 7: launch_stream_fm<T, EPI, 7>(a, s); break;
+          default: launch_stream_fm<T, EPI, 8>(a, s);
+        }
+      }
   }
 }
 
@@ -282,13 +301,17 @@ static void launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   }
 }
 
-// Which GEMMs of a block run here (up to 64 rows).  q/k/v, gate/up and the unembedding: all.  Measured against the kernels
+// Which GEMMs of a block run here.  Up to 64 rows, q/k/v, gate/up and the unembedding: all.  Measured against the kernels
 // that stage X through LDS, back to back, us at 2 / 17 / 33 / 51 rows:
 //   q/k/v    768 wide 5.0 -> 3.9 / 5.6 -> 4.1 / 6.1 -> 4.6 / 6.7 -> 5.3, 2048 7.6 -> 7.0 / 8.1 -> 7.8 / 10.0 -> 8.9 / 11.0 -> 10.0,
 //            3072 12.8 -> 11.4 / 13.6 -> 12.7 / 15.5 -> 14.7 / 16.7 -> 16.3, 4096 18.5 -> 17.4 / 19.5 -> 17.9 / 21.4 -> 19.9 / 22.6 -> 21.7
 //   gate/up  768 wide 5.0 -> 4.4 / 5.4 -> 4.7 / 6.4 -> 5.2 / 7.1 -> 5.7, 4096 39.6 -> 37.4 / 39.9 -> 37.9 / 41.3 -> 40.2 / 42.5 -> 40.9;
 //            3072 wide at 51 rows 19.2 (64 x 64 tiles) against 19.9 here, what q/k/v and the norm give back
 //   fp32, 512 wide: q/k/v 5.1 -> 4.1 / 6.5 -> 4.8 / 7.8 -> 5.9 / 9.0 -> 7.0
+// From 65 to 128 rows q/k/v and gate/up of 16-bit models of more than 512 fragments, at 65 / 81 / 97 / 121 rows: 4096 wide q/k/v
+// 27.0 -> 24.9 / 30.1 -> 27.4 / 32.6 -> 30.5 / 34.4 -> 32.9, gate/up 44.4 -> 44.0 / 46.3 and 46.7 / 53.6 -> 50.6 / 61.5 -> 53.5; 3072 wide
+// q/k/v 21.1 -> 18.9 / 23.0 -> 20.7 / 25.6 -> 23.6 / 27.3 -> 25.4.  Narrower ones run 128-row tiles there (768 wide gate/up 7.2 at
+// 97 rows, 7.7 here), and so does nothing for the unembedding (128256 entries, 97 rows: 145 against 161).
 // Residual GEMMs: a workgroup reads all of X here, and the launch of the RMSNorm (4 to 5 us) is saved.  Output projection
 // and norm 768 wide 7.1 -> 3.2 / 8.3 -> 3.8 / 7.4 -> 4.2 / 7.5 -> 4.6, 4096 11.7 -> 8.5 / 11.8 -> 9.2 / 12.6 -> 11.0 / 13.3 -> 12.5; down
 // and norm 768 wide 7.5 -> 5.6 / 8.2 -> 6.6 / 8.6 -> 8.0 / 8.8 and 9.2, 4096 23.4 -> 20.4 / 24.1 and 24.8 / 25.2 and 30.9.  The line:
@@ -297,7 +320,8 @@ static void launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
 // at 460; 3072 x 8192, 50 MB: at 680; 4096 x 14336, 117 MB: at 1100); fp32 a fifth further.  More than one workgroup per CU
 // share its path to the L2.
 bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only) {
-  if (M > 64 || (dtype == 1 && tile_only && M > 1)) return false;
+  if (dtype == 1 && tile_only && M > 1) return false;
+  if (M > 64) return dtype == 1 && M <= 128 && (epi == EPI_QKV || epi == EPI_GATEUP) && frags > 512;
   if (epi != EPI_RESIDUAL) return true;
   if (frags > 512 || K <= 64) return false;               // (the sums of squares of 64 rows fit the LDS of the next GEMM)
   const int e = dtype == 1 ? 2 : 4, fm = (M + 15) / 16;

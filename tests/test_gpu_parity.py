@@ -857,6 +857,13 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd, tile, 
     ("bf16", 1, 1, 64, 64, 10272, 1056, 40, 6, 8, 1),     # 49 tokens; six
     ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 9, 7, 1),     # 64 tokens; seven
     ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 5, 10, 1),    # 51 tokens; eight
+    ("bf16", 1, 1, 32, 64, 4128, 1056, 100, 16, 4, 1),    # 65 tokens, gate/up alone (three fragments); a prompt of seven column blocks
+    ("bf16", 32, 32, 64, 64, 6176, 1056, 66, 8, 10, 1),   # 81 tokens; four
+    ("bf16", 2, 1, 64, 96, 8224, 1056, 128, 19, 5, 1),    # 96 tokens, whole column blocks; five
+    ("bf16", 1, 1, 64, 64, 10272, 1056, 113, 16, 6, 1),   # 97 tokens; six
+    ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 16, 7, 1),    # 113 tokens; seven
+    ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 12, 10, 1),   # 121 tokens; eight
+    ("bf16", 64, 64, 64, 64, 512, 1056, 40, 12, 10, 1),   # 121 tokens, q/k/v alone (three)
     ("f32", 3, 1, 32, 96, 160, 544, 50, 1, 1, 0),
     ("f32", 4, 4, 32, 128, 2080, 16416, 64, 4, 4, 0),     # two fragments per workgroup; the unembedding on eight waves
     ("f32", 2, 1, 64, 96, 544, 1056, 40, 9, 7, 0),
