@@ -184,7 +184,7 @@ def measure(ngg, si, torch, workload, steps, warmup, dev_w, args, full=True):
         bracket_us = ctx.profile_bracket_overhead()
         avg_us = dom_ms * 1e3 / dom_n
         ach = gb / (avg_us * 1e-6) / 1e9
-        roof = {"kernel": "gemm_skinny_kernel<fp16 operands, gate/up + SwiGLU epilogue>", "bound": "hbm", "achieved": ach,
+        roof = {"kernel": "gemm_stream_kernel<fp16 operands, gate/up + SwiGLU epilogue>", "bound": "hbm", "achieved": ach,
                 "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": ach / HBM_PEAK_GBPS,
                 "traffic": measured_traffic(workload),
                 "bytes_per_launch": gb, "avg_launch_us": avg_us, "launches": dom_n,

@@ -311,7 +311,7 @@ static void launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
 // From 65 to 128 rows q/k/v and gate/up of 16-bit models of more than 512 fragments, at 65 / 81 / 97 / 121 rows: 4096 wide q/k/v
 // 27.0 -> 24.9 / 30.1 -> 27.4 / 32.6 -> 30.5 / 34.4 -> 32.9, gate/up 44.4 -> 44.0 / 46.3 and 46.7 / 53.6 -> 50.6 / 61.5 -> 53.5; 3072 wide
 // q/k/v 21.1 -> 18.9 / 23.0 -> 20.7 / 25.6 -> 23.6 / 27.3 -> 25.4.  Narrower ones run 128-row tiles there (768 wide gate/up 7.2 at
-// 97 rows, 7.7 here), and so does nothing for the unembedding (128256 entries, 97 rows: 145 against 161).
+// 97 rows, 7.7 here); the unembedding stays on the skinny kernel too (128256 entries, 97 rows: 145, 161 here).
 // Residual GEMMs: a workgroup reads all of X here, and the launch of the RMSNorm (4 to 5 us) is saved.  Output projection
 // and norm 768 wide 7.1 -> 3.2 / 8.3 -> 3.8 / 7.4 -> 4.2 / 7.5 -> 4.6, 4096 11.7 -> 8.5 / 11.8 -> 9.2 / 12.6 -> 11.0 / 13.3 -> 12.5; down
 // and norm 768 wide 7.5 -> 5.6 / 8.2 -> 6.6 / 8.6 -> 8.0 / 8.8 and 9.2, 4096 23.4 -> 20.4 / 24.1 and 24.8 / 25.2 and 30.9.  The line:
