@@ -274,7 +274,8 @@ ngg_status ngg_context_drafts_static(const int32_t *tokens, int32_t n, int32_t w
 ngg_status ngg_profile_read_bandwidth(ngg_ctx *ctx, double *gbps);
 
 /* Debug aid for parity tests: copies an internal device buffer to dst (HOST), at most cap bytes,
- * and reports its full size in *bytes.  Names: "h" (residual stream, fp32 [M][d_model]), "z"
+ * and reports its full size in *bytes.  Names: "h" (residual stream behind the last layer, fp32
+ * [M][d_model], the rows of the last model call: of a prompt its last piece), "z"
  * (bigram scores of the last ngg_build_drafts, fp32 [vocab]), "next1" (int32 [vocab]), "hist"
  * (int32 token history), "block_tok" (int32 block tokens of the last forward), "kcache" /
  * "vcache" (whole caches, [layer][kv head][*stride / 32 tiles]: a tile holds 32 positions x head_dim

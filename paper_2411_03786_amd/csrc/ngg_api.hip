@@ -103,6 +103,7 @@ struct ngg_ctx {
   int n = 0;                       // context length (0 = no prefill yet)
   bool have_verify = false;
   int last_k = 0, last_w = 0;
+  int h_pending = 0, h_rows = 0;   // residual partials (of how many rows) that the last forward left beside h: a prompt's last piece
   int32_t attn_layout[4] = {0, 0, 0, 0};   // last forward: key-list slices per head, attention workgroups, block rows, cached positions
   bool drafts_on_device = false;
   int drafts_k = 0, drafts_w = 0;
@@ -231,6 +232,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     row.hpart = c->hpart; row.part_stride = part_stride;
   }
   int pending = 0;                                   // residual partials the next RMSNorm has to add
+  c->h_pending = 0; c->h_rows = M;
   bool normed = inside;                              // the kernel before has done the norm
   // the norm in front of a GEMM: a launch of its own, or (one row) what the GEMM's prologue needs for it
   auto norm = [&](const void *gain, int xn_mb) {
@@ -330,8 +332,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   }
   if (unembed) {
     const bool last_only = last_row_only && M > 1;
-    // the last row alone goes through the single-token kernel, which runs the norm of that row itself (row 0 of the residual
-    // stream, which nobody reads any more, takes the sum)
+    // the last row alone goes through the single-token kernel, which runs the norm of that row itself.  It leaves the partials of
+    // all rows where they are (ngg_debug_peek adds them when it is asked for h); the row's sum goes to xn_s, which is free here.
     if (!last_only || !norms_inside(c)) norm(c->w.final_norm, un_mb);
     ProfScope ps(c, NGG_PROF_GEMM_UNEMBED);
     GemmArgs g{};
@@ -343,8 +345,9 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     if (last_only) {
       const size_t at = (size_t)(M - 1) * d.d_model;
       g.M = 1;
-      row.h_in = c->h + at; row.h_out = c->h; row.hpart = c->hpart + at; row.part_stride = part_stride;
+      row.h_in = c->h + at; row.h_out = (float *)c->xn_s; row.hpart = c->hpart + at; row.part_stride = part_stride;
       row.n_part = normed || !norms_inside(c) ? 0 : pending;   // (0: the kernel before, or the norm above, has added them)
+      c->h_pending = row.n_part;
       row.gain = c->w.final_norm; row.part_o = nullptr;
       launch_gemm_row(dt, EPI_UNEMBED, g, row, s);
     } else gemm(EPI_UNEMBED, g);
@@ -873,6 +876,7 @@ static ngg_status graph_step(ngg_ctx *c, const ngg_draft_cfg &step, const int ke
   }
   NGG_HIP(c, hipGraphLaunch(c->step_graph, c->stream));
   c->graph_replays += 1;
+  c->h_pending = 0;
   NGG_HIP(c, hipMemcpyAsync(c->res_host, c->res, (size_t)(goff + M) * 4, hipMemcpyDeviceToHost, c->stream));
   NGG_HIP(c, hipStreamSynchronize(c->stream));
   vo.k = k; vo.w = w;
@@ -1319,6 +1323,12 @@ ngg_status ngg_debug_peek(ngg_ctx *c, const char *name, void *dst, int64_t cap, 
   *bytes = (int64_t)sz;
   if (stride) *stride = c->Spad;
   if (dst && cap > 0) {
+    if (nm == "h" && c->h_pending > 0) {                  // (the norm's own outputs are scratch between calls)
+      launch_rmsnorm(d.dtype, c->h, c->hpart, c->h_pending, (size_t)c->Mcap * d.d_model, c->w.final_norm, c->xn, d.d_model, c->h_rows,
+                     c->Mcap, 0, c->row_ss, c->stream);
+      NGG_HIP(c, hipGetLastError());
+      c->h_pending = 0;
+    }
     NGG_HIP(c, hipMemcpyAsync(dst, src, std::min((size_t)cap, sz), hipMemcpyDeviceToHost, c->stream));
     NGG_HIP(c, hipStreamSynchronize(c->stream));
   }

@@ -904,6 +904,41 @@ def test_block_attention_edges_16_bit(heads, kv, hd, prompt_len, k, wd, slices):
     assert rep.max_rel_logit_err <= TOL["bf16"], rep
 
 
+@pytest.mark.parametrize("dtype,prompt_len", [("f32", 40), ("f32", 100), ("bf16", 40), ("bf16", 100), ("bf16", 300), ("bf16", 1)])
+def test_residual_stream_after_a_prompt(dtype, prompt_len):
+    """The residual stream that a prompt leaves holds every token's own sum of all layers, on short prompts (the norm runs in
+    the last GEMM) and on longer ones (its partials are left to the norm): its logits are the oracle's at every position."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=4, n_kv_heads=2, head_dim=32, d_model=128, d_ffn=256, vocab=544, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=16, k=4, w=3, k_ctx_max=2)
+    w_, prompt, model, ctx = _setup(desc, run, random_gains=True)
+    ctx.prefill(prompt)
+    h = ctx.debug_peek("h", np.float32, prompt_len * 128)[0].astype(np.float64).reshape(prompt_len, 128)
+    again = ctx.debug_peek("h", np.float32, prompt_len * 128)[0].reshape(prompt_len, 128)
+    ctx.close()
+    want = model.forward_full(prompt)
+    got = model.rmsnorm(h, model.final_norm) @ model.unemb.T
+    assert np.array_equal(again, h.astype(np.float32))
+    assert np.abs(got - want).max() <= TOL[dtype] * np.abs(want).max()
+
+
+def test_residual_stream_after_a_replayed_step():
+    """A replayed step right behind a prompt leaves the residual stream that the same step leaves on the stream."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=4, n_kv_heads=2, head_dim=32, d_model=128, d_ffn=256, vocab=544)
+    run = dict(si.RUNS["cfg2"], prompt_len=100, n_gen=40, k=4, w=3, k_ctx_max=2)
+    w_, prompt, model, ctx = _setup(desc, run, random_gains=True)
+    states = []
+    for mode in (0, 1):
+        ctx.step_graphs(mode)
+        for calls in (3, 1):
+            ctx.prefill(prompt)
+            ctx.decode_more(30, calls, run)
+        states.append(ctx.debug_peek("h", np.float32, 13 * 128)[0])
+    replays = ctx.debug_peek("step_graphs", np.int32)[0][3]
+    ctx.close()
+    assert replays >= 3                                   # the second prompt's one step too
+    assert np.array_equal(states[0], states[1])
+
+
 @pytest.mark.parametrize("dtype,n,tokens", [("bf16", 96, 33), ("bf16", 64, 17), ("f32", 96, 33)])
 def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
     """With the norms' own time asked for they are launches of their own, and the streaming residual GEMMs hand over a partial
