@@ -104,6 +104,8 @@ struct ngg_ctx {
   bool have_verify = false;
   int last_k = 0, last_w = 0;
   int h_pending = 0, h_rows = 0;   // residual partials (of how many rows) that the last forward left beside h: a prompt's last piece
+  int attn_mb = 0, attn_rows = 0;  // layout (act_pos) and rows of the attention output that the last forward left: 0 in attn, else in attn_s
+  int graph_attn[2] = {0, 0};      // the same of the captured step
   int32_t attn_layout[4] = {0, 0, 0, 0};   // last forward: key-list slices per head, attention workgroups, block rows, cached positions
   bool drafts_on_device = false;
   int drafts_k = 0, drafts_w = 0;
@@ -205,6 +207,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
             un_mb = layout(EPI_UNEMBED, d.vocab / 16, d.d_model), attn_mb = layout(EPI_RESIDUAL, d.d_model / 16, dq),
             act_mb = layout(EPI_RESIDUAL, d.d_model / 16, d.d_ffn);
   auto xn_of = [&](int xn_mb) { return xn_mb ? c->xn_s : c->xn; };   // every norm writes for one GEMM
+  c->attn_mb = attn_mb; c->attn_rows = M;
   void *const attn = attn_mb ? c->attn_s : c->attn, *const act = act_mb ? c->act_s : c->act;
   const bool inside = !one_row && norms_inside(c);
   int ss_segs = kNormSegs;                           // sums of squares per row, as the last norm left them
@@ -868,6 +871,7 @@ static ngg_status graph_step(ngg_ctx *c, const ngg_draft_cfg &step, const int ke
       return NGG_OK;
     }
     memcpy(c->graph_key, key, sizeof c->graph_key);
+    c->graph_attn[0] = c->attn_mb; c->graph_attn[1] = c->attn_rows;
     c->graph_captures += 1;
   }
   if (c->n_dev_value != c->n) {                          // the device copy follows the steps it runs itself; anything else sets it here
@@ -877,6 +881,7 @@ static ngg_status graph_step(ngg_ctx *c, const ngg_draft_cfg &step, const int ke
   NGG_HIP(c, hipGraphLaunch(c->step_graph, c->stream));
   c->graph_replays += 1;
   c->h_pending = 0;
+  c->attn_mb = c->graph_attn[0]; c->attn_rows = c->graph_attn[1];
   NGG_HIP(c, hipMemcpyAsync(c->res_host, c->res, (size_t)(goff + M) * 4, hipMemcpyDeviceToHost, c->stream));
   NGG_HIP(c, hipStreamSynchronize(c->stream));
   vo.k = k; vo.w = w;
@@ -1328,6 +1333,11 @@ ngg_status ngg_debug_peek(ngg_ctx *c, const char *name, void *dst, int64_t cap, 
                      c->Mcap, 0, c->row_ss, c->stream);
       NGG_HIP(c, hipGetLastError());
       c->h_pending = 0;
+    }
+    if (nm == "attn" && c->attn_mb > 0) {
+      launch_act_chunks(d.dtype, c->attn_s, c->attn, d.n_heads * d.head_dim, c->attn_rows, c->Mcap, c->attn_mb, c->stream);
+      NGG_HIP(c, hipGetLastError());
+      c->attn_mb = 0;
     }
     NGG_HIP(c, hipMemcpyAsync(dst, src, std::min((size_t)cap, sz), hipMemcpyDeviceToHost, c->stream));
     NGG_HIP(c, hipStreamSynchronize(c->stream));

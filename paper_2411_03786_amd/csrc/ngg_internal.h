@@ -370,6 +370,8 @@ void launch_embed(int dtype, const void *tok_emb, const int32_t *hist, const int
 // dst = (src - centre) * scale in the internal element type (src: the user's storage type)
 void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int Mcap, int mb, hipStream_t s, float scale,
                       const float *centre = nullptr);
+// src in operand order (act_pos, mb row blocks) -> dst chunk-major, M rows of d elements
+void launch_act_chunks(int dtype, const void *src, void *dst, int d, int M, int Mcap, int mb, hipStream_t s);
 // *out_bits = max(*out_bits, bit pattern of max |src[i]|) (fp32 bits; non-negative floats order like unsigned integers)
 void launch_absmax(int dtype, const void *src, size_t n, unsigned *out_bits, hipStream_t s);
 void launch_column_mean(int dtype, const void *src, int N, int d, float *mean, hipStream_t s);

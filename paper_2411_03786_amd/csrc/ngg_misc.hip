@@ -209,6 +209,17 @@ void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int M
     hipLaunchKernelGGL((pack_rows_kernel<float, float>), dim3(M), dim3(256), 0, s, (const float *)src, (float *)dst, d, Mcap, mb, centre, scale);
 }
 
+// activations in operand order -> chunk-major (ngg_debug_peek)
+template <typename T>
+__global__ __launch_bounds__(256) void act_chunks_kernel(const T *src, T *dst, int d, int Mcap, int mb) {
+  for (int i = threadIdx.x; i < d; i += 256) dst[act_offset<T>(blockIdx.x, i, Mcap)] = src[act_pos<T>(blockIdx.x, i, Mcap, mb)];
+}
+
+void launch_act_chunks(int dtype, const void *src, void *dst, int d, int M, int Mcap, int mb, hipStream_t s) {
+  if (dtype == 1) hipLaunchKernelGGL(act_chunks_kernel<half_t>, dim3(M), dim3(256), 0, s, (const half_t *)src, (half_t *)dst, d, Mcap, mb);
+  else hipLaunchKernelGGL(act_chunks_kernel<float>, dim3(M), dim3(256), 0, s, (const float *)src, (float *)dst, d, Mcap, mb);
+}
+
 // largest magnitude of a matrix, left as an fp32 bit pattern (magnitudes order like unsigned integers)
 template <typename U>
 __global__ __launch_bounds__(256) void absmax_kernel(const U *src, size_t n, unsigned *out_bits) {

@@ -939,6 +939,32 @@ def test_residual_stream_after_a_replayed_step():
     assert np.array_equal(states[0], states[1])
 
 
+@pytest.mark.parametrize("dtype,k,wd", [("f32", 1, 0), ("f32", 4, 4), ("f32", 32, 3), ("bf16", 1, 0), ("bf16", 1, 1), ("bf16", 8, 4), ("bf16", 9, 7), ("bf16", 16, 4)])
+def test_attention_output_of_the_last_call(dtype, k, wd):
+    """The attention output of the last layer, in the chunks that ngg_debug_peek names, is the last call's: the rest of the
+    (one) layer computed from it gives that call's residual stream.  Blocks of 1, 2, 17, 33, 64, 65 and 97 tokens: the single-token
+    kernels, the ones that keep activations in operand order, and the others; the tolerance is four roundings of the operands."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 1), n_heads=9, n_kv_heads=3, head_dim=32, d_model=128, d_ffn=256, vocab=544, dtype=dtype)
+    run = dict(si.RUNS["cfg2"], prompt_len=40, n_gen=40, k=k, w=wd, k_ctx_max=1, q_min=1, q_max=1)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=32, max_w=8, random_gains=True)
+    ctx.prefill(prompt)
+    M, dq, chunk = (1 if wd == 0 else 1 + k * wd), 9 * 32, 256 if dtype == "bf16" else 128
+    drafts = np.random.default_rng(5).integers(0, 544, (k, wd)).astype(np.int32) if wd else None
+    ctx.verify_step(drafts, k, wd)
+    out = ctx.debug_peek("attn", np.float16 if dtype == "bf16" else np.float32)[0].astype(np.float64)
+    h = ctx.debug_peek("h", np.float32, M * 128)[0].astype(np.float64).reshape(M, 128)
+    tokens = ctx.debug_peek("block_tok", np.int32, M)[0]
+    ctx.close()
+    chunks = out.reshape(-(-dq // chunk), -1, chunk)[:, :M]
+    attn = chunks.transpose(1, 0, 2).reshape(M, -1)[:, :dq]
+    lw = model.layers[0]
+    x = model.tok_emb[tokens] + attn @ lw["wo"].T
+    y = model.rmsnorm(x, lw["mlp_norm"])
+    want = x + (model.silu(y @ lw["w_gate"].T) * (y @ lw["w_up"].T)) @ lw["w_down"].T
+    assert np.abs(attn).max() > 0
+    assert np.linalg.norm(h - want) <= (1e-6 if dtype == "f32" else 2e-3) * np.linalg.norm(want - model.tok_emb[tokens])
+
+
 @pytest.mark.parametrize("dtype,n,tokens", [("bf16", 96, 33), ("bf16", 64, 17), ("f32", 96, 33)])
 def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
     """With the norms' own time asked for they are launches of their own, and the streaming residual GEMMs hand over a partial
