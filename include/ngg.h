@@ -211,7 +211,8 @@ ngg_status ngg_allocation(ngg_ctx *ctx, int32_t mode, int32_t coverage_percent, 
  * model call on the (k, w+1) block, acceptance, commit).  A step whose launch shapes equal the previous step's can be
  * replayed from a HIP graph (recorded on a stream of the library's own, launched on the context's stream); its
  * kernels read the context length from device memory, which the graph's last node advances, so the same graph serves
- * step after step and is captured again only when k, w, the draft settings or the number of attention slices change.
+ * step after step and is captured again only when k, w, the draft settings, the number of attention slices or
+ * the attention kernel change (the last two with the context length).
  * Steps that the generation budget clamps (the last ones), steps with profiling brackets enabled and the first step
  * of every shape are always launched on the stream.  mode 0: never replay.  mode 1: replay every step that qualifies.
  * mode 2 (default): per step shape, time three steps launched on the stream and, unless those took more than 12 us
@@ -286,7 +287,9 @@ ngg_status ngg_profile_read_bandwidth(ngg_ctx *ctx, double *gbps);
  * + k%8 for 2-byte elements), "attn" (attention output of the last layer, model dtype, in
  * chunks of 256 (bf16) or 128 (fp32) features: [feature chunk][Mcap rows][chunk]).
  * "attn_layout" (int32[4], host-side record of the last model call: slices of the key list per head,
- * workgroups of the attention kernel, block rows, cached positions).  "step_graphs" (int32[4], host-side record:
+ * workgroups of the attention kernel, block rows, cached positions).  "attn_kernel" (int32[1], the same call's attention
+ * kernel: 0 whole lists, 1 split lists of up to 16 tokens, 2 tiles shared through LDS, 3 the same with non-temporal loads, 4 the
+ * 32x32 kernel of wide 16-bit blocks).  "step_graphs" (int32[4], host-side record:
  * replay mode, a capture failed, captures so far, replayed steps so far).  "step_launches" (int32[2], host-side record:
  * kernels the last step of ngg_decode_more launches, nodes of the last captured step: one more).  Synchronises the
  * stream. */

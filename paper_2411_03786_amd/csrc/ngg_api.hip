@@ -63,7 +63,7 @@ struct ngg_ctx {
   hipGraphExec_t step_graph = nullptr;
   hipStream_t cap_stream = nullptr;   // the step is recorded on a stream of the library's own (the caller's may be the default
                                       // stream, which cannot be captured) and replayed on the caller's
-  int graph_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // k, w, k_ctx_max, q_min, q_max, attention slices and route, draft source and single-token route, 1
+  int graph_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // k, w, k_ctx_max, q_min, q_max, attention slices and kernel, draft source and routes of the norms, 1
   int eager_key[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // the same of the last step launched on the stream (its kernels are loaded)
   size_t part_rows = 0;            // rows (slices x block rows rounded to 128) the attention partial buffers hold per head
   // device buffers
@@ -107,6 +107,7 @@ struct ngg_ctx {
   int attn_mb = 0, attn_rows = 0;  // layout (act_pos) and rows of the attention output that the last forward left: 0 in attn, else in attn_s
   int graph_attn[2] = {0, 0};      // the same of the captured step
   int32_t attn_layout[4] = {0, 0, 0, 0};   // last forward: key-list slices per head, attention workgroups, block rows, cached positions
+  int32_t attn_kernel = 0;         // last forward: AttnRoute
   bool drafts_on_device = false;
   int drafts_k = 0, drafts_w = 0;
   // row allocation between the strategies inside the library's decode loop (ngg_allocation)
@@ -221,6 +222,8 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   const bool whole = attention_whole(dt, d.head_dim, d.n_heads, M, P, from_hist && C > 1);
   c->attn_layout[0] = n_splits; c->attn_layout[1] = attention_workgroups(dt, d.head_dim, d.n_heads, M, n_splits, whole);
   c->attn_layout[2] = M; c->attn_layout[3] = P;
+  const AttnRoute route = attention_route(dt, d.head_dim, M, P, n_splits, whole);
+  c->attn_kernel = route;
   const int Mpart = (M + 127) / 128 * 128;
   if ((size_t)n_splits * Mpart > c->part_rows)
     return fail(c, NGG_ECAPACITY, "attention partials: %d slices of %d rows exceed the %zu rows allocated", n_splits, Mpart, c->part_rows);
@@ -295,7 +298,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       a.kscr = kscr_l; a.vscr = vscr_l; a.kv_rows = kv_rows;
       a.part_o = c->part_o; a.part_ml = c->part_ml; a.out = attn; a.out_mb = attn_mb;
       a.H = d.n_heads; a.Hkv = d.n_kv_heads; a.Mcap = c->Mcap; a.Spad = c->Spad; a.M = M; a.C = C; a.P = P;
-      a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0; a.whole = whole ? 1 : 0;
+      a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0; a.route = route;
       a.scale = 1.0f / std::sqrt((float)d.head_dim);
       launch_attention(dt, d.head_dim, a, s);
     }
@@ -816,13 +819,14 @@ static int step_launches(const ngg_ctx *c, const ngg_draft_cfg &s) {
 }
 
 // What fixes the launch shapes and constant arguments of a decode step: a captured step is replayed only while
-// these stay the same (the number of attention slices moves with the context length)
+// these stay the same (the number of attention slices and the attention kernel move with the context length)
 static void step_key(const ngg_ctx *c, const ngg_draft_cfg &s, int key[8]) {
   const ngg_model_desc &d = c->d;
   const int C = s.w + 1, M = block_tokens(s.k, C, C >= 2 ? 1 : 0);
   key[0] = s.k; key[1] = s.w; key[2] = s.k_ctx_max; key[3] = s.q_min; key[4] = s.q_max;
-  key[5] = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) |
-           (attention_whole(d.dtype, d.head_dim, d.n_heads, M, c->n - 1) ? 1 << 16 : 0);
+  const int splits = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits);
+  const bool whole = attention_whole(d.dtype, d.head_dim, d.n_heads, M, c->n - 1);
+  key[5] = splits | (int)attention_route(d.dtype, d.head_dim, M, c->n - 1, splits, whole) << 16;
   key[6] = (c->bg_use ? 1 : 0) | (c->uni_use ? 2 : 0) | (one_row_call(c, M) ? 4 : 0) | (norms_inside(c) ? 8 : 0);
   key[7] = 1;
 }
@@ -1311,6 +1315,11 @@ ngg_status ngg_debug_peek(ngg_ctx *c, const char *name, void *dst, int64_t cap, 
   else if (nm == "attn_layout") {                       // host-side record, no device copy
     *bytes = (int64_t)sizeof c->attn_layout;
     if (dst && cap > 0) memcpy(dst, c->attn_layout, std::min((size_t)cap, sizeof c->attn_layout));
+    return NGG_OK;
+  }
+  else if (nm == "attn_kernel") {                       // host-side record
+    *bytes = (int64_t)sizeof c->attn_kernel;
+    if (dst && cap > 0) memcpy(dst, &c->attn_kernel, std::min((size_t)cap, sizeof c->attn_kernel));
     return NGG_OK;
   }
   else if (nm == "step_graphs") {                       // host-side record: on, broken, captures, replays

@@ -755,29 +755,34 @@ static void launch_stream(const AttnArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((attn_stream_kernel<T, HD, QF, NW>), dim3((n_units + 7) / 8 * 8 * Z), dim3(64 * NW), lds, s, a, Z, n_units);
 }
 
-// query groups of 16 per wave in attn_shared_kernel, fp32 blocks of more than 64 tokens: two where the registers hold them
-template <int HD> constexpr int attn_shared_qmax() { return HD <= 64 ? 2 : 1; }
-
 // Slices of a dozen tiles or more that no other workgroup shares are bound by the stream of tiles, which are read with
 // non-temporal loads (measured on MI355X, whole verify step: 7.07 -> 6.86 ms at a 16.4K context with 32 tiles per slice, 3.08 ->
 // 3.06 ms at 13 tiles; 4.18 -> 4.19 ms at 8 tiles, where they stay ordinary loads)
-static bool long_slices(const AttnArgs &a, int Z) { return Z == 1 && ((a.P + 31) / 32 + 1) / a.n_splits >= 12; }
+static bool long_slices(int P, int n_splits, int Z) { return Z == 1 && ((P + 31) / 32 + 1) / n_splits >= 12; }
 
-template <typename T, int HD, int QF>
+// query groups of 16 per wave in attn_shared_kernel, blocks of more than 64 tokens: two where the registers hold them (fp32
+// fragments are twice as large)
+static int shared_groups(int dtype, int hd, int M) { return M > 64 && (dtype == 1 || hd <= 64) ? 2 : 1; }
+
+AttnRoute attention_route(int dtype, int hd, int M, int P, int n_splits, bool whole) {
+  if (whole) return ATTN_WHOLE;
+  if (M <= 16) return ATTN_STREAM;
+  const int per_wg = 64 * shared_groups(dtype, hd, M);
+  const bool longs = long_slices(P, n_splits, (M + per_wg - 1) / per_wg);
+  // (32 heads of 128, us, attn_shared_kernel -> attn_block_kernel: 97 tokens on 3000 positions 21.5 -> 18.4, 241 on 2048 27.8 -> 23.0,
+  // a 2048-token piece 96 -> 77, behind 13K positions 630 -> 564; 777 tokens, 12 heads of 64: 14.4 -> 12.4.  Long slices, where
+  // the tiles bound the kernel, lose: 97 tokens on 8192 positions 35.8 -> 38.2, on 16384 56.5 -> 61.7)
+  if (dtype == 1 && M > 64 && !longs) return ATTN_BLOCK;
+  return longs ? ATTN_SHARED_NT : ATTN_SHARED;
+}
+
+template <typename T, int HD, int QF, bool NT>
 static void launch_shared(const AttnArgs &a, hipStream_t s) {
   const size_t lds = (size_t)4 * 32 * HD * sizeof(T);
   const int Z = (a.M + 64 * QF - 1) / (64 * QF);
   const int n_units = a.n_splits * a.H;
-  const dim3 grid((n_units + 7) / 8 * 8 * Z);
-  if constexpr (sizeof(T) == 4 || QF == 1) {                // (16-bit, two groups: long slices only, see launch_hd)
-    if (!long_slices(a, Z)) { hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, false>), grid, dim3(256), lds, s, a, Z, n_units); return; }
-  }
-  hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, true>), grid, dim3(256), lds, s, a, Z, n_units);
+  hipLaunchKernelGGL((attn_shared_kernel<T, HD, QF, NT>), dim3((n_units + 7) / 8 * 8 * Z), dim3(256), lds, s, a, Z, n_units);
 }
-
-// query groups of 16 per wave in attn_shared_kernel, blocks of more than 64 tokens: two where the registers hold them (fp32
-// fragments are twice as large)
-template <typename T, int HD> constexpr int attn_shared_qmax() { return sizeof(T) == 2 || HD <= 64 ? 2 : 1; }
 
 template <int HD>
 static void launch_block(const AttnArgs &a, hipStream_t s) {
@@ -787,20 +792,31 @@ static void launch_block(const AttnArgs &a, hipStream_t s) {
 
 template <typename T, int HD>
 static void launch_hd(const AttnArgs &a, hipStream_t s) {
-  if (a.whole) {                                            // short lists (attention_whole): 16 queries per workgroup and
-    // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list); four where two tiles of fp32 registers fill a wave's share
-    constexpr int NW = HD * (int)sizeof(T) <= 256 ? 8 : 4;
-    launch_stream<T, HD, 1, NW>(a, s);
-    return;
+  constexpr int DT = sizeof(T) == 2 ? 1 : 0;
+  const bool two = shared_groups(DT, HD, a.M) == 2;
+  switch (a.route) {
+    case ATTN_WHOLE: {                                      // short lists (attention_whole): 16 queries per workgroup and
+      // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list); four where two tiles of fp32 registers fill a wave's share
+      constexpr int NW = HD * (int)sizeof(T) <= 256 ? 8 : 4;
+      launch_stream<T, HD, 1, NW>(a, s);
+      return;
+    }
+    case ATTN_STREAM: launch_stream<T, HD, 1, 4>(a, s); break;
+    case ATTN_BLOCK:
+      if constexpr (DT == 1) launch_block<HD>(a, s);
+      break;
+    case ATTN_SHARED:                                       // (16-bit, two groups: attn_block_kernel)
+      if constexpr (DT == 0 && HD <= 64) {
+        if (two) { launch_shared<T, HD, 2, false>(a, s); break; }
+      }
+      launch_shared<T, HD, 1, false>(a, s);
+      break;
+    default:
+      if constexpr (DT == 1 || HD <= 64) {
+        if (two) { launch_shared<T, HD, 2, true>(a, s); break; }
+      }
+      launch_shared<T, HD, 1, true>(a, s);
   }
-  if (a.M <= 16) launch_stream<T, HD, 1, 4>(a, s);
-  else if (a.M <= 64) launch_shared<T, HD, 1>(a, s);
-  else if (sizeof(T) == 2 && !long_slices(a, (a.M + 127) / 128)) {
-    // (32 heads of 128, us, attn_shared_kernel -> this: 97 tokens on 3000 positions 21.5 -> 18.4, 241 on 2048 27.8 -> 23.0, a
-    // 2048-token piece 96 -> 77, behind 13K positions 630 -> 564; 777 tokens, 12 heads of 64: 14.4 -> 12.4.  Long slices, where
-    // the tiles bound the kernel, lose: 97 tokens on 8192 positions 35.8 -> 38.2, on 16384 56.5 -> 61.7)
-    if constexpr (sizeof(T) == 2) launch_block<HD>(a, s);
-  } else launch_shared<T, HD, attn_shared_qmax<T, HD>()>(a, s);
   if (a.one_row) return;                                    // the output projection merges the slices
   if (a.n_splits == 1) return;                              // the kernel wrote the result itself
   hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);
@@ -835,8 +851,7 @@ bool attention_whole(int dtype, int hd, int H, int M, int P, bool causal) {
 // whose own tiles count too, half of them for the average query (777 tokens, 12 heads of 64: 84 workgroups of up to 25
 // tiles took 27 us, three slices take 14.5 + 4.2 for the merge).
 int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, bool causal) {
-  const int qmax = dtype == 1 || hd <= 64 ? 2 : 1;
-  const int per_wg = M <= 16 ? 16 : (M <= 64 ? 64 : 64 * qmax);
+  const int per_wg = M <= 16 ? 16 : 64 * shared_groups(dtype, hd, M);
   const int Z = (M + per_wg - 1) / per_wg;
   const int tiles = list_tiles(M, P, causal);
   if (attention_whole(dtype, hd, H, M, P, causal)) return 1;
@@ -852,8 +867,7 @@ int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, boo
 // head.  Such a list goes through attn_shared_kernel, which reads it once for 64 queries: 144 heads of 128 on 8 key/value
 // heads, 8K context, 64 block tokens, 4 layers: 1.39 ms on the whole-list kernel, 1.06 ms so)
 int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool whole) {
-  const int qmax = dtype == 1 || hd <= 64 ? 2 : 1;
-  const int per_wg = M <= 16 || whole ? 16 : (M <= 64 ? 64 : 64 * qmax);
+  const int per_wg = M <= 16 || whole ? 16 : 64 * shared_groups(dtype, hd, M);
   return n_splits * H * ((M + per_wg - 1) / per_wg);
 }
 

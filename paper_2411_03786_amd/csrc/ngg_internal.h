@@ -326,7 +326,7 @@ struct AttnArgs {
   float *part_o;          // [H][n_splits][Mpart/16][hd/16][64 lanes][4]: output fragments as the registers hold them
   float *part_ml;         // [H][n_splits][Mpart][2]
   int Mpart;              // rows per (head, slice) of the two partial buffers: M rounded up to 128
-  int whole;              // a short list (attention_whole): one workgroup per head and 16 queries, n_splits == 1
+  int route;              // AttnRoute: which kernel
   int one_row;            // M == 1 and the merge is left to the GEMM that follows: partials are [H][n_splits][hd] and [H][n_splits][2]
   void *out;              // [M][H*hd] T, act_pos(.., out_mb)
   int out_mb;
@@ -357,6 +357,10 @@ bool gemm_row_fits(int dtype, int d_model, int dq);
 void launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
 int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, bool causal = false);
 bool attention_whole(int dtype, int hd, int H, int M, int P, bool causal = false);   // the list is not split (attention_splits returns 1)
+// Which kernel takes a call.  It moves with the context length (P) at a constant number of slices, so a captured step holds for one of
+// them only.  NT: tiles by non-temporal loads.
+enum AttnRoute { ATTN_WHOLE = 0, ATTN_STREAM = 1, ATTN_SHARED = 2, ATTN_SHARED_NT = 3, ATTN_BLOCK = 4 };
+AttnRoute attention_route(int dtype, int hd, int M, int P, int n_splits, bool whole);
 int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool whole);   // workgroups the main attention kernel is launched with
 
 // mode 1: block token m is history token hist_base + m; mode 0: the verify block in the shared-first-column

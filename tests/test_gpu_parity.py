@@ -965,6 +965,38 @@ def test_attention_output_of_the_last_call(dtype, k, wd):
     assert np.linalg.norm(h - want) <= (1e-6 if dtype == "f32" else 2e-3) * np.linalg.norm(want - model.tok_emb[tokens])
 
 
+@pytest.mark.parametrize("k,wd,kernels", [
+    (16, 4, (4, 3)),                   # 65 tokens: the 32x32 kernel below a dozen tiles per slice, the shared one from there on
+    (12, 4, (2, 3)),                   # 49 tokens: the shared kernel with ordinary and with non-temporal loads
+])
+def test_replay_follows_the_attention_kernel_of_the_context_length(k, wd, kernels):
+    """136 heads keep one slice per head at every length here, while the attention kernel changes at twelve tiles (321 cached
+    positions): a captured step must not be replayed across that.  Residual stream and tokens equal to the last bit with and
+    without replay, step by step; two captures, one per kernel."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=136, n_kv_heads=4, head_dim=32, d_model=128, d_ffn=256, vocab=1056)
+    run = dict(si.RUNS["cfg2"], prompt_len=300, n_gen=64, k=k, w=wd, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run, random_gains=True)
+    trace = []
+    for mode in (0, 1):
+        ctx.step_graphs(mode)
+        ctx.prefill(prompt)
+        before = ctx.debug_peek("step_graphs", np.int32)[0][2:].tolist()
+        steps = []
+        while len(ctx.get_tokens()) < 340:
+            ctx.decode_more(12, 1, run)
+            splits, _, M, _ = ctx.debug_peek("attn_layout", np.int32)[0].tolist()
+            assert splits == 1 and M == 1 + k * wd
+            steps.append((int(ctx.debug_peek("attn_kernel", np.int32)[0][0]), list(ctx.get_tokens()), ctx.debug_peek("h", np.float32, M * 128)[0]))
+        trace.append((steps, (np.array(ctx.debug_peek("step_graphs", np.int32)[0][2:]) - before).tolist()))
+    ctx.close()
+    (stream, none), (replay, graphs) = trace
+    assert none == [0, 0] and graphs[0] == 2 and graphs[1] >= len(replay) // 2, graphs
+    assert len(stream) == len(replay)
+    for (kern, toks, h), (rkern, rtoks, rh) in zip(stream, replay):
+        assert kern == rkern and toks == rtoks and np.array_equal(h, rh)
+    assert sorted({s[0] for s in stream}) == sorted(kernels)
+
+
 @pytest.mark.parametrize("dtype,n,tokens", [("bf16", 96, 33), ("bf16", 64, 17), ("f32", 96, 33)])
 def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
     """With the norms' own time asked for they are launches of their own, and the streaming residual GEMMs hand over a partial
