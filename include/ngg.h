@@ -300,9 +300,13 @@ ngg_status ngg_debug_peek(ngg_ctx *ctx, const char *name, void *dst, int64_t cap
  * a contraction of k.  Host only, no context, no GPU.  plan (HOST, int32[8]): kernel (0 streaming, 1 tiled, 2 single
  * token, 3 a residual GEMM that streams its whole contraction per workgroup and ends with the norm), block tokens and weight rows of a tile, splits of the contraction, 16-row weight fragments in the first launch,
  * tokens and rows of the second launch's tiles, number of tile shapes.
+ * ngg_debug_gemm_kernel: the kernel by name that a block's GEMM runs on, arguments as above and the tile shape of ngg_debug_tiles
+ * or -1: 0 X staged through LDS, 1 tiled, 3 both operands streamed (of one token: where the single-token kernel does not take the
+ * call), -1 none (a model call would return NGG_EINVAL).  Host only.
  * ngg_debug_tiles: every GEMM of this context's 16-bit model calls on two tokens or more takes tile shape `shape`
  * (0 .. number - 1) of the tiled kernel whatever its size; -1 (default) goes back to the choice by size. */
 ngg_status ngg_debug_plan(int32_t dtype, int32_t gemm, int32_t tokens, int32_t n, int32_t k, int32_t *plan);
+ngg_status ngg_debug_gemm_kernel(int32_t dtype, int32_t gemm, int32_t tokens, int32_t n, int32_t k, int32_t shape, int32_t *kernel);
 ngg_status ngg_debug_tiles(ngg_ctx *ctx, int32_t shape);
 
 #ifdef __cplusplus

@@ -23,7 +23,8 @@ PROF_CLASSES = ("gemm_qkv", "gemm_o", "gemm_gateup", "gemm_down", "gemm_unembed"
 EXPORTS = ("ngg_create", "ngg_destroy", "ngg_prefill", "ngg_build_drafts", "ngg_verify_step", "ngg_commit",
            "ngg_greedy_decode", "ngg_get_tokens", "ngg_last_error", "ngg_profile_enable", "ngg_profile_reset",
            "ngg_profile_read", "ngg_debug_peek", "ngg_bigram_table_build", "ngg_bigram_source", "ngg_profile_bracket_overhead", "ngg_unigram_build", "ngg_decode_more", "ngg_profile_sample",
-           "ngg_context_drafts_static", "ngg_allocation", "ngg_profile_read_bandwidth", "ngg_step_graphs", "ngg_debug_plan", "ngg_debug_tiles")
+           "ngg_context_drafts_static", "ngg_allocation", "ngg_profile_read_bandwidth", "ngg_step_graphs", "ngg_debug_plan", "ngg_debug_tiles",
+           "ngg_debug_gemm_kernel")
 NGG_STATIC_MAX_TOKENS = 32768
 
 
@@ -99,6 +100,7 @@ def load_library():
     lib.ngg_step_graphs.argtypes = [vp, C.c_int32]
     lib.ngg_profile_read_bandwidth.argtypes = [vp, C.POINTER(C.c_double)]
     lib.ngg_debug_plan.argtypes = [C.c_int32] * 5 + [i32p]
+    lib.ngg_debug_gemm_kernel.argtypes = [C.c_int32] * 6 + [i32p]
     lib.ngg_debug_tiles.argtypes = [vp, C.c_int32]
     lib.ngg_context_drafts_static.argtypes = [vp, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.c_int32, vp, vp, vp]
     for name in EXPORTS:
@@ -122,6 +124,16 @@ def debug_plan(dtype, gemm, tokens, n, k):
     if st != NGG_OK:
         raise NggError(st, lib.ngg_last_error(None).decode())
     return dict(zip(("kernel", "tile_tokens", "tile_rows", "splits", "first_frags", "tile2_tokens", "tile2_rows", "shapes"), out))
+
+
+def debug_gemm_kernel(dtype, gemm, tokens, n, k, shape=-1):
+    """The kernel a block's GEMM runs on (ngg_debug_gemm_kernel): "skinny", "tile", "stream" or, where there is none, None."""
+    out = (C.c_int32 * 1)()
+    lib = load_library()
+    st = lib.ngg_debug_gemm_kernel(NGG_BF16 if dtype == "bf16" else NGG_F32, ("qkv", "residual", "gateup", "unembed").index(gemm), tokens, n, k, shape, out)
+    if st != NGG_OK:
+        raise NggError(st, lib.ngg_last_error(None).decode())
+    return {-1: None, 0: "skinny", 1: "tile", 3: "stream"}[out[0]]
 
 
 def _i32(a):

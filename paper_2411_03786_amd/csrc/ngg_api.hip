@@ -184,6 +184,9 @@ bool one_row_call(const ngg_ctx *c, int M) {
   return M == 1 && gemm_row_fits(d.dtype, d.d_model, d.n_heads * d.head_dim) && norms_inside(c);
 }
 
+// The sizes lead to a kernel that has no instance for them: nothing may go on with what an earlier launch left in the buffers
+ngg_status no_kernel(ngg_ctx *c, int M) { return fail(c, NGG_EINVAL, "no kernel is built for a step of this model's call on %d block tokens", M); }
+
 // One forward over a block of R rows x C columns sitting at positions P .. P+C-1 on a cached
 // context of P tokens (Section 3).  Leaves this block's keys/values in the scratch, and, when
 // `unembed` is set, the per-tile argmax partials (and optional logits) of every block position.
@@ -203,7 +206,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
   // Which kernels the block runs on, and with them the layout of every activation: its consumers' (act_pos)
   const bool one_row = one_row_call(c, M);
   const int mb = (M + 15) / 16;
-  auto layout = [&](int epi, int frags, int K) { return !one_row && stream_takes(dt, epi, M, frags, K, c->tile_only) ? mb : 0; };
+  auto layout = [&](int epi, int frags, int K) { return !one_row && gemm_kernel(dt, epi, M, frags, K, c->tile_only) == GEMM_STREAM ? mb : 0; };
   const int qkv_mb = layout(EPI_QKV, (dq + 2 * d.n_kv_heads * d.head_dim) / 16, d.d_model), gu_mb = layout(EPI_GATEUP, d.d_ffn / 8, d.d_model),
             un_mb = layout(EPI_UNEMBED, d.vocab / 16, d.d_model), attn_mb = layout(EPI_RESIDUAL, d.d_model / 16, dq),
             act_mb = layout(EPI_RESIDUAL, d.d_model / 16, d.d_ffn);
@@ -259,10 +262,11 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
     ss_segs = stream_segments(d.d_model);
     normed = true;
   };
+  bool launched = true;                              // every launch has found its kernel
   auto gemm = [&](int epi, GemmArgs &g) {
     g.tile_only = c->tile_only;
     if (one_row) launch_gemm_row(dt, epi, g, row, s);
-    else launch_gemm(dt, epi, g, s);
+    else launched = launch_gemm(dt, epi, g, s) && launched;
   };
   for (int l = 0; l < d.n_layers; ++l) {
     const ngg_layer_weights &lw = c->layers[l];
@@ -300,7 +304,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       a.H = d.n_heads; a.Hkv = d.n_kv_heads; a.Mcap = c->Mcap; a.Spad = c->Spad; a.M = M; a.C = C; a.P = P;
       a.n_splits = n_splits; a.shared0 = shared0; a.Mpart = Mpart; a.n_dev = n_dev; a.one_row = one_row ? 1 : 0; a.route = route;
       a.scale = 1.0f / std::sqrt((float)d.head_dim);
-      launch_attention(dt, d.head_dim, a, s);
+      launched = launch_attention(dt, d.head_dim, a, s) && launched;
     }
     {
       ProfScope ps(c, NGG_PROF_GEMM_O);
@@ -335,6 +339,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       gemm(EPI_RESIDUAL, g);
     }
     pending = ks_down;
+    if (!launched) return no_kernel(c, M);
   }
   if (unembed) {
     const bool last_only = last_row_only && M > 1;
@@ -358,6 +363,7 @@ ngg_status forward(ngg_ctx *c, int R, int C, int P, bool from_hist, int w, bool 
       launch_gemm_row(dt, EPI_UNEMBED, g, row, s);
     } else gemm(EPI_UNEMBED, g);
   }
+  if (!launched) return no_kernel(c, M);
   NGG_HIP(c, hipGetLastError());
   return NGG_OK;
 }
@@ -376,7 +382,7 @@ ngg_status build_next1(ngg_ctx *c) {
   for (int x0 = 0; x0 < d.vocab; x0 += rows) {
     const int M = std::min(rows, d.vocab - x0);
     GemmArgs g{};
-    g.x_mb = stream_takes(d.dtype, EPI_UNEMBED, M, d.vocab / 16, d.d_model, 0) ? (M + 15) / 16 : 0;
+    g.x_mb = gemm_kernel(d.dtype, EPI_UNEMBED, M, d.vocab / 16, d.d_model, 0) == GEMM_STREAM ? (M + 15) / 16 : 0;
     void *xn = g.x_mb ? c->xn_s : c->xn;
     g.X = xn;
     launch_pack_rows(d.dtype, (const char *)c->w.tok_emb + (size_t)x0 * d.d_model * c->esize, xn, d.d_model, M, c->Mcap, g.x_mb,
@@ -384,7 +390,7 @@ ngg_status build_next1(ngg_ctx *c) {
     g.W0 = c->unemb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
     g.pmax_val = c->pmax_val; g.pmax_idx = c->pmax_idx; g.Mcap = c->Mcap;
     g.out_scale = 1.0f / (c->unemb_scale * c->emb_scale);
-    launch_gemm(d.dtype, EPI_UNEMBED, g, c->stream);
+    if (!launch_gemm(d.dtype, EPI_UNEMBED, g, c->stream)) return no_kernel(c, M);
     launch_next1_finish(c->pmax_val, c->pmax_idx, c->unembed_tiles, c->Mcap, M, c->next1 + x0, c->stream);
   }
   NGG_HIP(c, hipGetLastError());
@@ -812,8 +818,8 @@ static int step_launches(const ngg_ctx *c, const ngg_draft_cfg &s) {
   const int dq = d.n_heads * d.head_dim;
   const int merge = attention_splits(d.dtype, d.head_dim, d.n_heads, M, c->n - 1, c->max_splits) > 1 ? 1 : 0;
   // norms that are launches of their own: all while they are profiled, else those behind a residual GEMM that leaves them
-  const int after_o = !norms_inside(c) || !stream_takes(d.dtype, EPI_RESIDUAL, M, d.d_model / 16, dq, c->tile_only) ? 1 : 0;
-  const int after_down = !norms_inside(c) || !stream_takes(d.dtype, EPI_RESIDUAL, M, d.d_model / 16, d.d_ffn, c->tile_only) ? 1 : 0;
+  auto norm_after = [&](int K) { return norms_inside(c) && gemm_kernel(d.dtype, EPI_RESIDUAL, M, d.d_model / 16, K, c->tile_only) == GEMM_STREAM ? 0 : 1; };
+  const int after_o = norm_after(dq), after_down = norm_after(d.d_ffn);
   const int layer = 3 + merge + after_o + after_down + launches(EPI_QKV, dq + 2 * d.n_kv_heads * d.head_dim, d.d_model) + launches(EPI_GATEUP, d.d_ffn, d.d_model);
   return drafts + 1 + (norms_inside(c) ? 0 : 1) + layer * d.n_layers + launches(EPI_UNEMBED, d.vocab, d.d_model) + 3;
 }
@@ -1182,7 +1188,7 @@ ngg_status ngg_unigram_build(ngg_ctx *c, int32_t top_k) {
     for (int x0 = 0; x0 < d.vocab; x0 += c->Mcap) {
       const int M = std::min(c->Mcap, d.vocab - x0);
       GemmArgs g{};
-      g.x_mb = stream_takes(d.dtype, EPI_UNEMBED, M, d.vocab / 16, d.d_model, 0) ? (M + 15) / 16 : 0;
+      g.x_mb = gemm_kernel(d.dtype, EPI_UNEMBED, M, d.vocab / 16, d.d_model, 0) == GEMM_STREAM ? (M + 15) / 16 : 0;
       void *xn = g.x_mb ? c->xn_s : c->xn;
       g.X = xn;
       launch_pack_rows(d.dtype, (const char *)c->w.unemb + (size_t)x0 * d.d_model * c->esize, xn, d.d_model, M, c->Mcap, g.x_mb,
@@ -1190,13 +1196,13 @@ ngg_status ngg_unigram_build(ngg_ctx *c, int32_t top_k) {
       g.W0 = emb_t; g.M = M; g.N = d.vocab; g.K = d.d_model;
       g.logits = c->logits; g.pmax_val = c->pmax_val; g.pmax_idx = c->pmax_idx; g.Mcap = c->Mcap;
       g.out_scale = 1.0f / (c->emb_scale * row_scale);
-      launch_gemm(d.dtype, EPI_UNEMBED, g, c->stream);
+      if (!launch_gemm(d.dtype, EPI_UNEMBED, g, c->stream)) { st = no_kernel(c, M); break; }
       launch_neg_row_sumsq(c->logits, M, d.vocab, negd2 + x0, c->stream);
     }
     launch_row_topk(negd2, 1, d.vocab, top_k, c->uni_top, c->stream);     // nearest first, ties to the lower id
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) st = fail(c, NGG_EHIP, "ngg_unigram_build: %s", hipGetErrorString(e));
+    if (e != hipSuccess && st == NGG_OK) st = fail(c, NGG_EHIP, "ngg_unigram_build: %s", hipGetErrorString(e));
   }
   if (emb_t) (void)hipFree(emb_t);
   if (mean) (void)hipFree(mean);
@@ -1284,6 +1290,16 @@ ngg_status ngg_debug_plan(int32_t dtype, int32_t gemm, int32_t tokens, int32_t n
   const GemmPlan p = gemm_plan(dtype, epi[gemm], tokens, n, k);
   const int32_t v[8] = {p.kernel, p.tm, p.tn, p.splits, p.split, p.tm2, p.tn2, gemm_tile_shapes()};
   memcpy(plan, v, sizeof v);
+  return NGG_OK;
+}
+
+ngg_status ngg_debug_gemm_kernel(int32_t dtype, int32_t gemm, int32_t tokens, int32_t n, int32_t k, int32_t shape, int32_t *kernel) {
+  if (!kernel) return fail(nullptr, NGG_EINVAL, "ngg_debug_gemm_kernel: null kernel");
+  if ((dtype != NGG_F32 && dtype != NGG_BF16) || gemm < 0 || gemm > 3 || tokens < 1 || n < 32 || k < 32 || n % 32 || k % 32 ||
+      shape < -1 || shape >= gemm_tile_shapes())
+    return fail(nullptr, NGG_EINVAL, "ngg_debug_gemm_kernel: need a dtype, gemm 0..3, tokens >= 1, n and k multiples of 32 and a tile shape or -1");
+  const int epi[4] = {EPI_QKV, EPI_RESIDUAL, EPI_GATEUP, EPI_UNEMBED};
+  *kernel = gemm_kernel(dtype, epi[gemm], tokens, gemm == 2 ? n / 8 : n / 16, k, shape + 1);
   return NGG_OK;
 }
 

@@ -791,7 +791,7 @@ static void launch_block(const AttnArgs &a, hipStream_t s) {
 }
 
 template <typename T, int HD>
-static void launch_hd(const AttnArgs &a, hipStream_t s) {
+static bool launch_hd(const AttnArgs &a, hipStream_t s) {
   constexpr int DT = sizeof(T) == 2 ? 1 : 0;
   const bool two = shared_groups(DT, HD, a.M) == 2;
   switch (a.route) {
@@ -799,27 +799,30 @@ static void launch_hd(const AttnArgs &a, hipStream_t s) {
       // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list); four where two tiles of fp32 registers fill a wave's share
       constexpr int NW = HD * (int)sizeof(T) <= 256 ? 8 : 4;
       launch_stream<T, HD, 1, NW>(a, s);
-      return;
+      return true;
     }
     case ATTN_STREAM: launch_stream<T, HD, 1, 4>(a, s); break;
     case ATTN_BLOCK:
-      if constexpr (DT == 1) launch_block<HD>(a, s);
-      break;
+      if constexpr (DT == 1) { launch_block<HD>(a, s); break; }
+      return false;
     case ATTN_SHARED:                                       // (16-bit, two groups: attn_block_kernel)
       if constexpr (DT == 0 && HD <= 64) {
         if (two) { launch_shared<T, HD, 2, false>(a, s); break; }
       }
       launch_shared<T, HD, 1, false>(a, s);
       break;
-    default:
+    case ATTN_SHARED_NT:
       if constexpr (DT == 1 || HD <= 64) {
         if (two) { launch_shared<T, HD, 2, true>(a, s); break; }
       }
       launch_shared<T, HD, 1, true>(a, s);
+      break;
+    default: return false;
   }
-  if (a.one_row) return;                                    // the output projection merges the slices
-  if (a.n_splits == 1) return;                              // the kernel wrote the result itself
+  if (a.one_row) return true;                               // the output projection merges the slices
+  if (a.n_splits == 1) return true;                         // the kernel wrote the result itself
   hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);
+  return true;
 }
 
 static int list_tiles(int M, int P, bool causal) { return (P + 31) / 32 + 1 + (causal ? (M + 31) / 64 : 0); }
@@ -872,15 +875,14 @@ int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool who
 }
 
 template <typename T>
-static void launch_t(int hd, const AttnArgs &a, hipStream_t s) {
-  if (hd == 32) launch_hd<T, 32>(a, s);
-  else if (hd == 64) launch_hd<T, 64>(a, s);
-  else launch_hd<T, 128>(a, s);
+static bool launch_t(int hd, const AttnArgs &a, hipStream_t s) {
+  if (hd == 32) return launch_hd<T, 32>(a, s);
+  if (hd == 64) return launch_hd<T, 64>(a, s);
+  return launch_hd<T, 128>(a, s);
 }
 
-void launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s) {
-  if (dtype == 1) launch_t<half_t>(hd, a, s);
-  else launch_t<float>(hd, a, s);
+bool launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s) {
+  return dtype == 1 ? launch_t<half_t>(hd, a, s) : launch_t<float>(hd, a, s);
 }
 
 }  // namespace ngg

@@ -828,9 +828,14 @@ int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only) {
 }
 
 // fp32: the row tile the block needs.  16-bit: takes_tile leaves this kernel the blocks of up to 24 rows (up to 16 always in the
-// 1 x 4 layout) and, in the 2 x 2 layout, those of 65 to 96.
+// 1 x 4 layout) and, in the 2 x 2 layout, those of 65 to 96; skinny_built holds what the instances reach.
+static bool skinny_built(int dtype, int epi, int M, int N, int K) {
+  if (epi == EPI_QKV || epi == EPI_GATEUP) return dtype == 0;
+  return dtype == 0 || epi == EPI_UNEMBED || M <= (residual_narrow(M, N, K) ? 32 : 96);
+}
 template <typename T, int WN, int WK>
-static void launch_residual(const GemmArgs &a, hipStream_t s) {
+static bool launch_residual(const GemmArgs &a, hipStream_t s) {
+  if (!skinny_built(sizeof(T) == 2 ? 1 : 0, EPI_RESIDUAL, a.M, a.N, a.K)) return false;
   if constexpr (sizeof(T) == 4) launch_fm<T, EPI_RESIDUAL, WN, WK, 4>(a, a.KS, s);
   else if constexpr (WN == 1) {
     if (a.M <= 16) launch_gemm_cfg<T, EPI_RESIDUAL, 1, WN, WK, 4>(a, a.KS, s);
@@ -840,6 +845,7 @@ static void launch_residual(const GemmArgs &a, hipStream_t s) {
     else if (a.M <= 80) launch_gemm_cfg<T, EPI_RESIDUAL, 5, WN, WK, 4>(a, a.KS, s);
     else launch_gemm_cfg<T, EPI_RESIDUAL, 6, WN, WK, 4>(a, a.KS, s);
   }
+  return true;
 }
 
 // Workgroup shapes measured on MI355X at the 7B shapes (M = 60 and M = 1).  Unembedding: wide tiles
@@ -847,35 +853,24 @@ static void launch_residual(const GemmArgs &a, hipStream_t s) {
 // pair of groups; residual GEMMs: WN x WK = 2 x 2 or 1 x 4 (residual_narrow) with the contraction split
 // across workgroups.
 template <typename T>
-static void launch_t(int epi, const GemmArgs &a_in, hipStream_t s) {
+static bool launch_skinny(int epi, const GemmArgs &a_in, hipStream_t s) {
   GemmArgs a = a_in;
-  if constexpr (sizeof(T) == 2) {
-    if (takes_tile(epi, a.M, epi == EPI_RESIDUAL || epi == EPI_UNEMBED ? a.N / 16 : gemm_groups(epi, a), a.K, a.tile_only)) {
-      switch (epi) {
-        case EPI_QKV: launch_tile<EPI_QKV>(a, s); break;
-        case EPI_GATEUP: launch_tile<EPI_GATEUP>(a, s); break;
-        case EPI_RESIDUAL: launch_tile<EPI_RESIDUAL>(a, s); break;
-        default: launch_tile<EPI_UNEMBED>(a, s);
-      }
-      return;
-    }
-  }
   a.n_groups = gemm_groups(epi, a);
   const bool wide = a.n_groups >= 4 * 200;
   switch (epi) {
     case EPI_QKV:
-      if constexpr (sizeof(T) == 4) launch_paired<T, EPI_QKV>(a, s);
-      break;
+      if constexpr (sizeof(T) == 4) { launch_paired<T, EPI_QKV>(a, s); return true; }
+      return false;
     case EPI_GATEUP:
-      if constexpr (sizeof(T) == 4) launch_paired<T, EPI_GATEUP>(a, s);
-      break;
+      if constexpr (sizeof(T) == 4) { launch_paired<T, EPI_GATEUP>(a, s); return true; }
+      return false;
     case EPI_RESIDUAL:
-      if (residual_narrow(a.M, a.N, a.K)) launch_residual<T, 1, 4>(a, s);
-      else launch_residual<T, 2, 2>(a, s);
-      break;
+      if (residual_narrow(a.M, a.N, a.K)) return launch_residual<T, 1, 4>(a, s);
+      return launch_residual<T, 2, 2>(a, s);
     default:
       if (wide) launch_fm<T, EPI_UNEMBED, 4, 1, 8>(a, 1, s);
       else launch_fm<T, EPI_UNEMBED, 2, 2, 4>(a, 1, s);
+      return true;
   }
 }
 
@@ -1179,17 +1174,18 @@ int gemm_tile_shapes() { return kNumTileShapes; }
 GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K) {
   const int frags = epi == EPI_GATEUP ? N / 8 : N / 16;
   GemmPlan p{0, 0, 0, 1, frags, 0, 0};
-  if (M > 1 && stream_takes(dtype, epi, M, frags, K, 0)) {
+  const GemmKernel kernel = M > 1 ? gemm_kernel(dtype, epi, M, frags, K, 0) : GEMM_ROW;
+  if (kernel == GEMM_STREAM) {
     p.kernel = dtype == 1 && epi == EPI_RESIDUAL ? 3 : 0;
     return p;
   }
-  if (dtype == 1 && takes_tile(epi, M, frags, K, 0)) {
+  if (kernel == GEMM_TILE) {
     const TilePlan t = tile_plan(epi, M, frags, K, 0);
     const TileShape &s = kTileShapes[t.shape], &s2 = kTileShapes[t.shape2];
     return {1, s.tm, s.tn, t.KS, t.split, s2.tm, s2.tn};
   }
   if (epi == EPI_RESIDUAL) p.splits = M == 1 ? gemm_row_splits(N, K) : gemm_residual_splits(dtype, M, N, K);
-  if (M == 1) p.kernel = 2;
+  p.kernel = kernel;
   return p;
 }
 
@@ -1198,10 +1194,28 @@ void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hi
   else launch_row_t<float>(epi, a, r, s);
 }
 
-void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
-  if (a.x_mb) launch_gemm_stream(dtype, epi, a, s);
-  else if (dtype == 1) launch_t<half_t>(epi, a, s);
-  else launch_t<float>(epi, a, s);
+GemmKernel gemm_kernel(int dtype, int epi, int M, int frags, int K, int tile_only) {
+  if (stream_takes(dtype, epi, M, frags, K, tile_only)) return stream_built(dtype, epi, M) ? GEMM_STREAM : GEMM_NONE;
+  if (dtype == 1 && takes_tile(epi, M, frags, K, tile_only)) return GEMM_TILE;
+  return skinny_built(dtype, epi, M, frags * 16, K) ? GEMM_SKINNY : GEMM_NONE;
+}
+
+bool launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
+  const GemmKernel kernel = gemm_kernel(dtype, epi, a.M, epi == EPI_GATEUP ? a.N / 8 : a.N / 16, a.K, a.tile_only);
+  if ((kernel == GEMM_STREAM) != (a.x_mb != 0)) return false;   // X lies in the other kernels' layout
+  switch (kernel) {
+    case GEMM_STREAM: return launch_gemm_stream(dtype, epi, a, s);
+    case GEMM_TILE:
+      switch (epi) {
+        case EPI_QKV: launch_tile<EPI_QKV>(a, s); break;
+        case EPI_GATEUP: launch_tile<EPI_GATEUP>(a, s); break;
+        case EPI_RESIDUAL: launch_tile<EPI_RESIDUAL>(a, s); break;
+        default: launch_tile<EPI_UNEMBED>(a, s);
+      }
+      return true;
+    case GEMM_SKINNY: return dtype == 1 ? launch_skinny<half_t>(epi, a, s) : launch_skinny<float>(epi, a, s);
+    default: return false;
+  }
 }
 
 }  // namespace ngg

@@ -336,13 +336,18 @@ struct AttnArgs {
   float scale;
 };
 
-// launchers (host).  dtype: 0 = fp32, 1 = bf16.  Every launcher validates nothing: the API layer
-// checks shapes before calling.
-void launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s);
+// launchers (host).  dtype: 0 = fp32, 1 = bf16.  Launchers do not validate shapes (the API layer does before calling); those that
+// return false found no kernel for the call and launched nothing.
+// The kernel of a GEMM of a block (frags: 16-row fragments of W): the one rule that the layout of the activations, the launch and the
+// test aids follow.  GEMM_NONE: the rules of the kernels leave it to one that has no instance for it.
+enum GemmKernel { GEMM_NONE = -1, GEMM_SKINNY = 0, GEMM_TILE = 1, GEMM_ROW = 2, GEMM_STREAM = 3 };
+GemmKernel gemm_kernel(int dtype, int epi, int M, int frags, int K, int tile_only);
+bool launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s);
 int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only = 0);
-// Blocks of up to 64 rows: gemm_stream_kernel.  stream_takes: whether a GEMM runs on it (frags: 16-row fragments of W)
+// gemm_stream_kernel: the GEMMs it takes, those it has an instance for, and its launch
 bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only);
-void launch_gemm_stream(int dtype, int epi, const GemmArgs &a, hipStream_t s);
+bool stream_built(int dtype, int epi, int M);
+bool launch_gemm_stream(int dtype, int epi, const GemmArgs &a, hipStream_t s);
 // What a model call on M block tokens launches for one GEMM of N output rows (q, k and v together; gate/up: d_ffn): kernel 0
 // gemm_skinny_kernel, or gemm_stream_kernel but for the 16-bit residual GEMMs, which are 3 there; 1 gemm_tile_kernel (tile rows
 // and columns; fragments from `split` on in a second launch of their own shape), 2 gemm_row_kernel; splits of the contraction.
@@ -354,7 +359,7 @@ int gemm_tile_shapes();   // tile shapes gemm_tile_kernel is built for
 void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s);
 int gemm_row_splits(int N, int K);
 bool gemm_row_fits(int dtype, int d_model, int dq);
-void launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
+bool launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
 int attention_splits(int dtype, int hd, int H, int M, int P, int max_splits, bool causal = false);
 bool attention_whole(int dtype, int hd, int H, int M, int P, bool causal = false);   // the list is not split (attention_splits returns 1)
 // Which kernel takes a call.  It moves with the context length (P) at a constant number of slices, so a captured step holds for one of

@@ -271,33 +271,40 @@ static void launch_stream_fm(const GemmArgs &a, hipStream_t s) {
   }
 }
 
+// column blocks (of 16 rows) an instance is built for
+static constexpr int stream_blocks(int dtype, int epi) { return dtype == 1 && (epi == EPI_QKV || epi == EPI_GATEUP) ? 8 : 4; }
+bool stream_built(int dtype, int epi, int M) { return (M + 15) / 16 <= stream_blocks(dtype, epi); }
+
 template <typename T, int EPI>
-static void launch_stream_epi(const GemmArgs &a, hipStream_t s) {
+static bool launch_stream_epi(const GemmArgs &a, hipStream_t s) {
   switch ((a.M + 15) / 16) {
-    case 1: launch_stream_fm<T, EPI, 1>(a, s); break;
-    case 2: launch_stream_fm<T, EPI, 2>(a, s); break;
-    case 3: launch_stream_fm<T, EPI, 3>(a, s); break;
-    case 4: launch_stream_fm<T, EPI, 4>(a, s); break;
-    default:
-      if constexpr (sizeof(T) == 2 && (EPI == EPI_QKV || EPI == EPI_GATEUP)) {
-        switch ((a.M + 15) / 16) {
-          case 5: launch_stream_fm<T, EPI, 5>(a, s); break;
-          case 6: launch_stream_fm<T, EPI, 6>(a, s); break;
-          case 7: launch_stream_fm<T, EPI, 7>(a, s); break;
-          default: launch_stream_fm<T, EPI, 8>(a, s);
-        }
-      }
+    case 1: launch_stream_fm<T, EPI, 1>(a, s); return true;
+    case 2: launch_stream_fm<T, EPI, 2>(a, s); return true;
+    case 3: launch_stream_fm<T, EPI, 3>(a, s); return true;
+    case 4: launch_stream_fm<T, EPI, 4>(a, s); return true;
+    default: break;
   }
+  if constexpr (stream_blocks(sizeof(T) == 2 ? 1 : 0, EPI) == 8) {
+    switch ((a.M + 15) / 16) {
+      case 5: launch_stream_fm<T, EPI, 5>(a, s); return true;
+      case 6: launch_stream_fm<T, EPI, 6>(a, s); return true;
+      case 7: launch_stream_fm<T, EPI, 7>(a, s); return true;
+      case 8: launch_stream_fm<T, EPI, 8>(a, s); return true;
+      default: break;
+    }
+  }
+  return false;
 }
 
 template <typename T>
-static void launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
+static bool launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
   GemmArgs a = a_in;
+  a.n_groups = epi == EPI_GATEUP ? a.N / 8 : a.N / 16;
   switch (epi) {
-    case EPI_QKV: a.n_groups = (a.H + 2 * a.Hkv) * (a.hd / 16); launch_stream_epi<T, EPI_QKV>(a, s); break;
-    case EPI_GATEUP: a.n_groups = a.N / 8; launch_stream_epi<T, EPI_GATEUP>(a, s); break;
-    case EPI_RESIDUAL: a.n_groups = a.N / 16; launch_stream_epi<T, EPI_RESIDUAL>(a, s); break;
-    default: a.n_groups = a.N / 16; launch_stream_epi<T, EPI_UNEMBED>(a, s);
+    case EPI_QKV: return launch_stream_epi<T, EPI_QKV>(a, s);
+    case EPI_GATEUP: return launch_stream_epi<T, EPI_GATEUP>(a, s);
+    case EPI_RESIDUAL: return launch_stream_epi<T, EPI_RESIDUAL>(a, s);
+    default: return launch_stream_epi<T, EPI_UNEMBED>(a, s);
   }
 }
 
@@ -330,9 +337,8 @@ bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only) {
   return kb <= (dtype == 1 ? limit : 1.2f * limit);
 }
 
-void launch_gemm_stream(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
-  if (dtype == 1) launch_stream_t<half_t>(epi, a, s);
-  else launch_stream_t<float>(epi, a, s);
+bool launch_gemm_stream(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
+  return dtype == 1 ? launch_stream_t<half_t>(epi, a, s) : launch_stream_t<float>(epi, a, s);
 }
 
 }  // namespace ngg

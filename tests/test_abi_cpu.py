@@ -161,3 +161,28 @@ def test_16_bit_residual_gemms_reach_the_streaming_kernel_where_it_is_built(lib)
                     assert m <= 24 or (65 <= m <= 96 and k > n and 4096 <= n <= 5120), (m, n, k)
                     reached.add((m + 15) // 16)
     assert reached == {1, 2, 5, 6}
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_every_gemm_of_every_block_has_a_kernel(lib, dtype):
+    """The rules that give the GEMMs to the kernels and the instances that are built stand in different places: no size may fall
+    between them, by its own size or in a tile shape that is asked for (a model call would be refused)."""
+    tokens = [*range(1, 131), 160, 192, 193, 256, 257, 384, 385, 1057, 2048]
+    seen = set()
+    for gemm in ("qkv", "residual", "gateup", "unembed"):
+        for n in (32, 64, 768, 2048, 3072, 4096, 5120, 8192, 8224, 12288, 14336, 16384, 28672, 128256):
+            if gemm == "residual" and n > 16384:
+                continue
+            for k in (32, 64, 96, 768, 4096, 5120, 8192, 14336, 16384, 65536):
+                if gemm != "residual" and k > 16384:
+                    continue
+                for m in tokens:
+                    for shape in (-1, 0, 9):
+                        kernel = ngg.debug_gemm_kernel(dtype, gemm, m, n, k, shape)
+                        assert kernel is not None, (gemm, m, n, k, shape)
+                        if shape < 0:
+                            seen.add((gemm, kernel))
+    assert len(seen) == (8 if dtype == "f32" else 10), seen
+    for bad in ((0, 4, 4, 128, 128, -1), (1, 0, 4, 128, 128, 10), (1, 0, 0, 128, 128, -1), (1, 0, 4, 100, 128, -1)):
+        assert lib.ngg_debug_gemm_kernel(*bad, (C.c_int32 * 1)()) == ngg.NGG_EINVAL
+    assert lib.ngg_debug_gemm_kernel(1, 0, 4, 128, 128, -1, None) == ngg.NGG_EINVAL
