@@ -154,14 +154,19 @@ def measure(ngg, si, torch, workload, steps, warmup, dev_w, args, full=True):
 
     breakdown = None
     if full:
-        # per-class device time of a few more steps (all classes; perturbs timing, so outside the timed region)
-        ctx.profile_reset()
-        ctx.profile_enable(-1)
-        for _ in range(5):
-            step()
-        prof = ctx.profile_read()
-        ctx.profile_enable(0)
-        breakdown = {name: {"ms_per_step": ms / 5, "launches_per_step": cnt / 5} for name, (ms, cnt) in prof.items() if cnt}
+        # per-class device time of a few more steps (perturbs timing, so outside the timed region).  While the norms' own time is
+        # asked for they are launches of their own, all of them, so they get a pass apart: the other classes are the timed step's
+        # kernels, with the norms inside that have no launch there
+        breakdown = {}
+        norm = 1 << ngg.PROF_CLASSES.index("norm")
+        for mask, suffix in ((-1 & ~norm, ""), (norm, "_all_as_launches")):
+            ctx.profile_reset()
+            ctx.profile_enable(mask)
+            for _ in range(5):
+                step()
+            prof = ctx.profile_read()
+            ctx.profile_enable(0)
+            breakdown.update({name + suffix: {"ms_per_step": ms / 5, "launches_per_step": cnt / 5} for name, (ms, cnt) in prof.items() if cnt})
 
     # single-token decode step (k=1, w=0: one model call, no drafting) at the same context length
     if warmup:

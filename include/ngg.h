@@ -235,8 +235,10 @@ const char *ngg_last_error(const ngg_ctx *ctx);
  * (bit i = class i, -1 = all, 0 = off).  Events between launches cost a little
  * time: enable few classes while timing whole steps.  ngg_profile_read sums the
  * milliseconds and launch counts per class since the last ngg_profile_reset.  A model call on one token runs its
- * norms and the merge of its attention slices inside the GEMMs that follow them; while NGG_PROF_NORM is enabled
- * they are launches of their own, so that they can be bracketed. */
+ * norms and the merge of its attention slices inside the GEMMs that follow them, and a block its first norm with the
+ * embedding and others inside the residual GEMMs in front of them; while NGG_PROF_NORM is enabled they are launches of their
+ * own, so that they can be bracketed: other kernels, whose results may differ in the last bits.  The other classes leave the
+ * kernels as they are. */
 enum {
   NGG_PROF_GEMM_QKV = 0, NGG_PROF_GEMM_O, NGG_PROF_GEMM_GATEUP, NGG_PROF_GEMM_DOWN, NGG_PROF_GEMM_UNEMBED,
   NGG_PROF_ATTENTION, NGG_PROF_NORM, NGG_PROF_DRAFTS, NGG_PROF_ACCEPT_COMMIT, NGG_PROF_OTHER, NGG_PROF_COUNT

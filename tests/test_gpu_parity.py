@@ -1000,20 +1000,22 @@ def test_replay_follows_the_attention_kernel_of_the_context_length(k, wd, kernel
 @pytest.mark.parametrize("dtype,n,tokens", [("bf16", 96, 33), ("bf16", 64, 17), ("f32", 96, 33)])
 def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
     """With the norms' own time asked for they are launches of their own, and the streaming residual GEMMs hand over a partial
-    instead: the same hidden states up to the order of the row sums."""
+    instead: the same hidden states up to the order of the row sums.  With every other class bracketed nothing changes."""
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=2, n_kv_heads=2, head_dim=32, d_model=n, d_ffn=160, vocab=544, dtype=dtype)
     run = dict(si.RUNS["cfg2"], prompt_len=40, n_gen=16, k=(tokens - 1) // 4, w=4, k_ctx_max=2)
     w_, prompt, model, ctx = _setup(desc, run, max_k=run["k"], max_w=4)
     ctx.prefill(prompt)
     drafts = np.random.default_rng(5).integers(0, 544, (run["k"], 4)).astype(np.int32)
     states = []
-    for on in (False, True):
-        if on:
-            ctx.profile_enable(1 << ngg.PROF_CLASSES.index("norm"))
+    norm = 1 << ngg.PROF_CLASSES.index("norm")
+    for mask in (0, -1 & ~norm, norm):
+        ctx.profile_reset()
+        ctx.profile_enable(mask)
         ctx.verify_step(drafts)
         states.append(ctx.debug_peek("h", np.float32, tokens * n)[0].astype(np.float64))
     assert ctx.profile_read()["norm"][1] == 2 * 2 + 1
     ctx.close()
+    assert np.array_equal(states[0], states.pop(1))
     assert np.linalg.norm(states[0] - states[1]) <= (1e-6 if dtype == "f32" else 1e-3) * np.linalg.norm(states[0])
 
 
