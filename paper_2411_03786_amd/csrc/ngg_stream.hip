@@ -117,18 +117,26 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(const GemmArgs a) 
   }
 
   // ---- the stream: groups of RING steps; the last two refill only what is still there ---------------
+  // Every refill stays behind its own slot's products: left alone the compiler moves the group's products together, which
+  // waits for the whole ring before the first refill.  (us so -> pinned: fp32 4096 wide at 33 rows q/k/v 80.5 -> 65.3, gate/up 124 ->
+  // 98; 16-bit 5120 wide at 49 rows 34.6 -> 33.4 and 51.4 -> 50.5, 4096 wide at 51 24.8 -> 24.4 and 43.1 -> 43.0.)  Not where one step
+  // is in flight (gate/up of 113 rows, 6144 wide 166.9 -> 168.7; fp32 unembedding 117 -> 144), and not in the unembedding, whose
+  // two workgroups per CU fill each other's gaps (4096 wide at 51 rows 49.6 -> 51.0).
+  constexpr bool PIN = RING > 1 && EPI != EPI_UNEMBED;
   int t0 = 0;
   for (; t0 + 2 * RING <= nt; t0 += RING) {
 #pragma unroll
     for (int u = 0; u < RING; ++u) {
       mul(u);
       load(u, t0 + u + RING);
+      if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
     }
   }
 #pragma unroll
   for (int u = 0; u < RING; ++u) {
     if (t0 + u < nt) mul(u);                             // (uniform)
     if (t0 + u + RING < nt) load(u, t0 + u + RING);
+    if constexpr (PIN) __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int u = 0; u < RING; ++u)
