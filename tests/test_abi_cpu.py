@@ -3,6 +3,8 @@ symbol include/ngg.h declares, and rejects bad arguments before touching the dev
 import ctypes as C
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -186,3 +188,38 @@ def test_every_gemm_of_every_block_has_a_kernel(lib, dtype):
     for bad in ((0, 4, 4, 128, 128, -1), (1, 0, 4, 128, 128, 10), (1, 0, 0, 128, 128, -1), (1, 0, 4, 100, 128, -1)):
         assert lib.ngg_debug_gemm_kernel(*bad, (C.c_int32 * 1)()) == ngg.NGG_EINVAL
     assert lib.ngg_debug_gemm_kernel(1, 0, 4, 128, 128, -1, None) == ngg.NGG_EINVAL
+
+
+@pytest.mark.parametrize("elem,epi,fm,fn,waves,ring", [
+    ("DF16_", 0, 4, 3, 8, 4), ("DF16_", 0, 2, 3, 8, 4), ("DF16_", 2, 4, 7, 8, 2), ("DF16_", 1, 4, 1, 4, 6), ("DF16_", 0, 7, 3, 8, 3),
+    ("f", 0, 3, 2, 4, 2), ("f", 2, 3, 2, 4, 2), ("f", 1, 3, 1, 4, 3),
+])
+def test_the_streaming_gemm_refills_its_ring_step_by_step(lib, tmp_path, elem, epi, fm, fn, waves, ring):
+    """The steady loop of gemm_stream_kernel, as it was compiled: between two refills lie no more products than one step of the
+    ring holds (the compiler moves a whole group's products in front of the first refill if it may, which drains the ring)."""
+    objdump = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    name = f"_ZN3ngg18gemm_stream_kernelI{elem}Li{epi}ELi{fm}ELi{fn}ELi{waves}ELi{ring}EEEvNS_8GemmArgsE"
+    shutil.copy(ngg.LIB_PATH, tmp_path / "lib.so")
+    subprocess.run([objdump, "--offloading", "lib.so"], cwd=tmp_path, check=True, capture_output=True)
+    text = ""
+    for part in sorted(tmp_path.glob("*gfx950")):
+        out = subprocess.run([objdump, "-d", f"--disassemble-symbols={name}", str(part)], capture_output=True, text=True).stdout
+        text = out if "v_mfma" in out else text
+    ops = [(int(m.group(3), 16), m.group(1), m.group(2)) for m in re.finditer(r"^\s+(\S+)(.*?)// ([0-9A-F]+):", text, flags=re.M)]
+    assert ops, name
+    base = ops[0][0]
+    loops = []
+    for at, op, rest in ops:
+        target = re.search(r"\+0x([0-9a-f]+)>", text[text.find(f"{at:012X}:"):].split("\n", 1)[0]) if op.startswith("s_cbranch") else None
+        if target and base + int(target.group(1), 16) <= at:
+            body = [o for a, o, _ in ops if base + int(target.group(1), 16) <= a <= at]
+            loops.append(body)
+    per_step = fm * fn * (1 if elem == "DF16_" else 8)
+    body = min((b for b in loops if sum("mfma" in o for o in b) == ring * per_step), key=len)
+    run = longest = 0
+    for op in body + body:                                # the loop closes on itself
+        run = run + 1 if "mfma" in op else 0 if op.startswith("global_load") else run
+        longest = max(longest, run)
+    assert longest <= per_step, (longest, per_step)
