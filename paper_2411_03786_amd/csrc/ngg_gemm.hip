@@ -1177,6 +1177,7 @@ GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K) {
   const GemmKernel kernel = M > 1 ? gemm_kernel(dtype, epi, M, frags, K, 0) : GEMM_ROW;
   if (kernel == GEMM_STREAM) {
     p.kernel = dtype == 1 && epi == EPI_RESIDUAL ? 3 : 0;
+    if (dtype == 1 && (epi == EPI_QKV || epi == EPI_GATEUP)) p.tn = 16 * stream_paired_frags(frags);
     return p;
   }
   if (kernel == GEMM_TILE) {

@@ -348,6 +348,7 @@ int gemm_residual_splits(int dtype, int M, int N, int K, int tile_only = 0);
 bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only);
 bool stream_built(int dtype, int epi, int M);
 bool launch_gemm_stream(int dtype, int epi, const GemmArgs &a, hipStream_t s);
+int stream_paired_frags(int frags);   // fragments per workgroup of its 16-bit q/k/v and gate/up
 // What a model call on M block tokens launches for one GEMM of N output rows (q, k and v together; gate/up: d_ffn): kernel 0
 // gemm_skinny_kernel, or gemm_stream_kernel but for the 16-bit residual GEMMs, which are 3 there; 1 gemm_tile_kernel (tile rows
 // and columns; fragments from `split` on in a second launch of their own shape), 2 gemm_row_kernel; splits of the contraction.

@@ -237,10 +237,19 @@ static void launch_stream_cfg(const GemmArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((gemm_stream_kernel<T, EPI, FM, FN, NW, RING>), dim3((a.n_groups + FN - 1) / FN), dim3(64 * NW), lds, s, a);
 }
 
-// Fragments per workgroup: as many as spread the matrix over the 256 CUs
+// Fragments per workgroup of the 16-bit q/k/v and gate/up: as many as spread the matrix over the 256 CUs in one round, or, above the
+// 2048 fragments that eight per workgroup hold, in equal rounds (one workgroup is on a CU: its LDS).  Eight whatever the number left
+// the last round partly filled: gate/up 7168 x 20480 (2560 fragments, five instead of eight) at 49 / 121 rows 127 -> 102 / 193 -> 142 us,
+// 8192 x 22016 (2752, six) 149 -> 130 / 217 -> 170, 8192 x 28672 (3584, seven) 163 -> 155 / 231 -> 196, 12288 x 36864 (4608, six) 337 -> 296 / 482 -> 383
+int stream_paired_frags(int frags) {
+  const int rounds = (frags + 2047) / 2048;
+  return (frags + 256 * rounds - 1) / (256 * rounds);
+}
+
 template <typename T, int EPI, int FM>
 static void launch_stream_fm(const GemmArgs &a, hipStream_t s) {
-  const int fn = (a.n_groups + 255) / 256;
+  const bool paired = sizeof(T) == 2 && (EPI == EPI_QKV || EPI == EPI_GATEUP);
+  const int fn = paired ? stream_paired_frags(a.n_groups) : (a.n_groups + 255) / 256;
   if constexpr (EPI == EPI_RESIDUAL) launch_stream_cfg<T, EPI, FM, 1, 4>(a, s);
   else if constexpr (EPI == EPI_UNEMBED) {
     if constexpr (sizeof(T) == 2) {

@@ -190,6 +190,20 @@ def test_every_gemm_of_every_block_has_a_kernel(lib, dtype):
     assert lib.ngg_debug_gemm_kernel(1, 0, 4, 128, 128, -1, None) == ngg.NGG_EINVAL
 
 
+def test_streamed_wide_matrices_are_dealt_out_in_equal_rounds(lib):
+    """16-bit q/k/v and gate/up that stream both operands: one workgroup of up to eight fragments is on each of the 256 CUs at a
+    time, and a workgroup takes no more than the fewest rounds need (eight of 2560 left the second round three quarters empty:
+    gate/up of 121 rows 193 us instead of 142)."""
+    rounds = lambda frags, fn: -(-(-(-frags // fn)) // 256)
+    for gemm, unit in (("gateup", 8), ("qkv", 16)):
+        for frags in [*range(516, 2049, 68), 2048, 2052, 2304, 2560, 2752, 3072, 3584, 4096, 4100, 4608, 6144, 8192]:
+            for tokens in (2, 17, 51, 64, 65, 97, 128):
+                p = ngg.debug_plan("bf16", gemm, tokens, frags * unit, 8192)
+                assert p["kernel"] == 0
+                fn = p["tile_rows"] // 16
+                assert 1 <= fn <= 8 and rounds(frags, fn) == rounds(frags, 8) < rounds(frags, fn - 1), (gemm, frags, tokens, fn)
+
+
 @pytest.mark.parametrize("elem,epi,fm,fn,waves,ring", [
     ("DF16_", 0, 4, 3, 8, 4), ("DF16_", 0, 2, 3, 8, 4), ("DF16_", 2, 4, 7, 8, 2), ("DF16_", 1, 4, 1, 4, 6), ("DF16_", 0, 7, 3, 8, 3),
     ("f", 0, 3, 2, 4, 2), ("f", 2, 3, 2, 4, 2), ("f", 1, 3, 1, 4, 3),

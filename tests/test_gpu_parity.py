@@ -864,6 +864,8 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd, tile, 
     ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 16, 7, 1),    # 113 tokens; seven
     ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 12, 10, 1),   # 121 tokens; eight
     ("bf16", 64, 64, 64, 64, 512, 1056, 40, 12, 10, 1),   # 121 tokens, q/k/v alone (three)
+    ("bf16", 1, 1, 32, 64, 16416, 1056, 40, 5, 10, 1),    # 51 tokens; two rounds of five fragments, the last workgroup short of three
+    ("bf16", 1, 1, 32, 64, 16416, 1056, 40, 12, 10, 1),   # 121 tokens
     ("f32", 3, 1, 32, 96, 160, 544, 50, 1, 1, 0),
     ("f32", 4, 4, 32, 128, 2080, 16416, 64, 4, 4, 0),     # two fragments per workgroup; the unembedding on eight waves
     ("f32", 2, 1, 64, 96, 544, 1056, 40, 9, 7, 0),
