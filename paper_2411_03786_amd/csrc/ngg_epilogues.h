@@ -13,16 +13,17 @@ namespace ngg {
 // q/k/v and gate/up: the fragment's rows 0..7 are the first members of 8 output pairs, rows 8..15 the
 // second members (rotary pairs (i, i + hd/2) of one head; gate and up of 8 FFN features).  rs: the row's
 // 1 / rms times the operand scales.  The caller has checked frag < n_groups; lanes g >= 2 only lend values.
-// v: the first members (fragment rows 4g .. 4g+3, g < 2), x2: their partners (rows 8 + 4g ..), both already scaled
+// v: the first members (fragment rows 4g .. 4g+3, g < 2), x2: their partners (rows 8 + 4g ..), both already scaled.
+// act_mb: layout of the SwiGLU output; a constant 0 in the kernels whose output gemm_stream_kernel never reads (launch_gemm checks it)
 template <typename T, int EPI>
 __device__ __forceinline__ void epi_paired_vals(const GemmArgs &a, int frag, int m, int M, int g, const float (&v)[4],
-                                                const float (&x2)[4]) {
+                                                const float (&x2)[4], int act_mb) {
   if (m < M && g < 2) {
     if constexpr (EPI == EPI_GATEUP) {
       float o[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) o[r] = silu<T>(v[r]) * x2[r];
-      store4((T *)a.act + act_pos<T>(m, frag * 8 + 4 * g, a.Mcap, a.act_mb), o[0], o[1], o[2], o[3]);   
+      store4((T *)a.act + act_pos<T>(m, frag * 8 + 4 * g, a.Mcap, act_mb), o[0], o[1], o[2], o[3]);   // 4 features lie side by side in either layout
     } else {
       const int half = a.hd / 2, fph = a.hd / 16;    // fragments per head
       const int hh = frag / fph, sub = frag - hh * fph;                 // head over [q heads | k heads | v heads]
@@ -61,11 +62,11 @@ __device__ __forceinline__ void epi_paired_vals(const GemmArgs &a, int frag, int
 }
 
 template <typename T, int EPI>
-__device__ __forceinline__ void epi_paired(const GemmArgs &a, int frag, int m, int M, int g, float rs, const f32x4 &sum) {
+__device__ __forceinline__ void epi_paired(const GemmArgs &a, int frag, int m, int M, int g, float rs, const f32x4 &sum, int act_mb = 0) {
   float v[4], x2[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) { v[r] = sum[r] * rs; x2[r] = other_half(v[r]); }
-  epi_paired_vals<T, EPI>(a, frag, m, M, g, v, x2);
+  epi_paired_vals<T, EPI>(a, frag, m, M, g, v, x2, act_mb);
 }
 
 // residual: split ks stores its fp32 partial of output features n0 + 4g .. +4 of block row m

@@ -535,7 +535,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs 
     for (int e = tid; e < TM * PPR; e += 64 * NW) {
       const int row = e / PPR, fr = e % PPR, m = m0 + row;
       if (m < M && f0 + fr < frag_end)
-        *reinterpret_cast<u32x4 *>((T *)a.act + act_pos<T>(m, (f0 + fr) * 8, a.Mcap, a.act_mb)) = *reinterpret_cast<const u32x4 *>(ot + row * LDO + fr * 8);
+        *reinterpret_cast<u32x4 *>((T *)a.act + act_offset<T>(m, (f0 + fr) * 8, a.Mcap)) = *reinterpret_cast<const u32x4 *>(ot + row * LDO + fr * 8);
     }
   } else if constexpr (EPI == EPI_UNEMBED) {
     // optional logits, and the best (value, id) of a block row over every 32 vocabulary rows; ids ascend with (j, i)
@@ -1203,7 +1203,8 @@ GemmKernel gemm_kernel(int dtype, int epi, int M, int frags, int K, int tile_onl
 
 bool launch_gemm(int dtype, int epi, const GemmArgs &a, hipStream_t s) {
   const GemmKernel kernel = gemm_kernel(dtype, epi, a.M, epi == EPI_GATEUP ? a.N / 8 : a.N / 16, a.K, a.tile_only);
-  if ((kernel == GEMM_STREAM) != (a.x_mb != 0)) return false;   // X lies in the other kernels' layout
+  // X lies in the other kernels' layout, or the output is asked for in one that only gemm_stream_kernel writes
+  if ((kernel == GEMM_STREAM) != (a.x_mb != 0) || (kernel != GEMM_STREAM && a.act_mb)) return false;
   switch (kernel) {
     case GEMM_STREAM: return launch_gemm_stream(dtype, epi, a, s);
     case GEMM_TILE:

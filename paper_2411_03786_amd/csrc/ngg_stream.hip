@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(const GemmArgs a) 
         const int idx = wave + NW * j;
         if (idx >= items) break;
         const int f = idx / cnt, fm = rd * FMR + idx - f * cnt;
-        if (f0 + f < n_frags) epi_paired<T, EPI>(a, f0 + f, fm * 16 + li, M, g, rs[fm * 16 + li], total(idx));   // (uniform)
+        if (f0 + f < n_frags) epi_paired<T, EPI>(a, f0 + f, fm * 16 + li, M, g, rs[fm * 16 + li], total(idx), a.act_mb);   // (uniform)
       }
     } else if constexpr (EPI == EPI_UNEMBED) {
       for (int it = wave; it < items / 2; it += NW) {    // pairs of fragments

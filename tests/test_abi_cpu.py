@@ -190,6 +190,18 @@ def test_every_gemm_of_every_block_has_a_kernel(lib, dtype):
     assert lib.ngg_debug_gemm_kernel(1, 0, 4, 128, 128, -1, None) == ngg.NGG_EINVAL
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_only_streaming_gate_up_feeds_a_streaming_down(lib, dtype):
+    """The other kernels write the SwiGLU output in one layout, without looking at the one that is asked for (a look at run time made
+    fp32 gate/up of 65 to 97 tokens 1 % slower): wherever down streams, gate/up must too (a model call would be refused)."""
+    for m in [*range(1, 131), 192, 256, 2048]:
+        for d in (32, 512, 768, 4096, 8192):
+            for f in (32, 1408, 3072, 14336, 28672):
+                for shape in (-1, 0):
+                    down, gate = (ngg.debug_gemm_kernel(dtype, g, m, n, k, shape) for g, n, k in (("residual", d, f), ("gateup", f, d)))
+                    assert down != "stream" or gate == "stream", (m, d, f, shape)
+
+
 def test_streamed_wide_matrices_are_dealt_out_in_equal_rounds(lib):
     """16-bit q/k/v and gate/up that stream both operands: one workgroup of up to eight fragments is on each of the 256 CUs at a
     time, and a workgroup takes no more than the fewest rounds need (eight of 2560 left the second round three quarters empty:
