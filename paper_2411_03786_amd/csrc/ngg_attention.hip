@@ -466,7 +466,7 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
         if (m < M)
 #pragma unroll
           for (int df = 0; df < DF; ++df)
-            store4((T *)a.out + act_pos<T>(m, h * HD + df * 16 + 4 * g, a.Mcap, a.out_mb), O[qf][df][0] * inv, O[qf][df][1] * inv,
+            store4((T *)a.out + act_pos<T>(m, h * HD + df * 16 + 4 * g, a.Mcap, QF == 1 ? a.out_mb : 0), O[qf][df][0] * inv, O[qf][df][1] * inv,
                    O[qf][df][2] * inv, O[qf][df][3] * inv);
         continue;
       }
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(256, 2) void attn_block_kernel(const AttnArgs a, in
       for (int d = 0; d < DB; ++d)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          store4((T *)a.out + act_pos<T>(m, head * HD + d * 32 + 8 * j + 4 * h, a.Mcap, a.out_mb), O[d][4 * j] * inv, O[d][4 * j + 1] * inv,
+          store4((T *)a.out + act_offset<T>(m, head * HD + d * 32 + 8 * j + 4 * h, a.Mcap), O[d][4 * j] * inv, O[d][4 * j + 1] * inv,
                  O[d][4 * j + 2] * inv, O[d][4 * j + 3] * inv);
     return;
   }
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256, 2) void attn_block_kernel(const AttnArgs a, in
 // 8 at a time with a running maximum (one round of loads when there are at most 8 slices: the kernel
 // is a chain of memory latencies, nothing else).  One workgroup per (16-query group, head); a thread
 // owns one lane's 4 values of an output fragment (dims 16 df + 4 (lane/16) .. +4 of query lane%16).
-template <typename T, int HD>
+template <typename T, int HD, bool ORD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
   constexpr int DF = HD / 16;
   const int qb = blockIdx.x, h = blockIdx.y;
@@ -738,7 +738,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const AttnArgs a) {
       }
     }
     const float inv = 1.0f / l;
-    store4((T *)a.out + act_pos<T>(m, h * HD + d4, a.Mcap, a.out_mb), o.x * inv, o.y * inv, o.z * inv, o.w * inv);
+    store4((T *)a.out + act_at<T, ORD>(m, h * HD + d4, a.Mcap, a.out_mb), o.x * inv, o.y * inv, o.z * inv, o.w * inv);
   }
 }
 
@@ -794,6 +794,7 @@ template <typename T, int HD>
 static bool launch_hd(const AttnArgs &a, hipStream_t s) {
   constexpr int DT = sizeof(T) == 2 ? 1 : 0;
   const bool two = shared_groups(DT, HD, a.M) == 2;
+  if (a.M > 64 && a.out_mb) return false;                   // (kernels of wide blocks write the chunks only)
   switch (a.route) {
     case ATTN_WHOLE: {                                      // short lists (attention_whole): 16 queries per workgroup and
       // eight waves (16: 9.6 instead of 8.7 us on the 33-tile list); four where two tiles of fp32 registers fill a wave's share
@@ -821,7 +822,9 @@ static bool launch_hd(const AttnArgs &a, hipStream_t s) {
   }
   if (a.one_row) return true;                               // the output projection merges the slices
   if (a.n_splits == 1) return true;                         // the kernel wrote the result itself
-  hipLaunchKernelGGL((attn_merge_kernel<T, HD>), dim3((a.M + 15) / 16, a.H, 2), dim3(256), 0, s, a);
+  const dim3 grid((a.M + 15) / 16, a.H, 2);
+  if (a.out_mb) hipLaunchKernelGGL((attn_merge_kernel<T, HD, true>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((attn_merge_kernel<T, HD, false>), grid, dim3(256), 0, s, a);
   return true;
 }
 

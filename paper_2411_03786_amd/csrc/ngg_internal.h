@@ -130,6 +130,12 @@ __host__ __device__ __forceinline__ size_t act_pos(int m, int k, int Mcap, int m
   const int l = ((k % 32) / 8) * 16 + m % 16, e = k % 8;
   return block + (sizeof(T) == 2 ? l * 8 + e : (e / 4) * 256 + l * 4 + e % 4);
 }
+// ... in kernels built for either layout (ORD: operand order): both in one kernel cost the short ones up to half a microsecond
+template <typename T, bool ORD>
+__host__ __device__ __forceinline__ size_t act_at(int m, int k, int Mcap, int mb) {
+  if constexpr (ORD) { if (mb < 1) __builtin_unreachable(); }
+  return act_pos<T>(m, k, Mcap, ORD ? mb : 0);
+}
 inline size_t act_elems(int dtype, int Mcap, int K) {
   const int kc = dtype == 1 ? KChunk<half_t>::value : KChunk<float>::value;
   return (size_t)((K + kc - 1) / kc) * Mcap * kc;

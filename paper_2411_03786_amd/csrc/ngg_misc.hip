@@ -92,7 +92,7 @@ void launch_embed(int dtype, const void *tok_emb, const int32_t *hist, const int
 // tid + 256*j): all loads of the row and of its residual partials are issued before anything is
 // used, so the kernel costs one memory round trip instead of one per feature.
 // U: storage type of the gain (the user's weights); T: internal element type of xn.
-template <typename U, typename T, int J>
+template <typename U, typename T, int J, bool ORD>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, const float *__restrict__ hpart, int n_part,
                                                       size_t part_stride, const U *__restrict__ gain, T *__restrict__ xn,
                                                       int d, int Mcap, int xn_mb, float *__restrict__ row_ss) {
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(float *__restrict__ h, con
     ss += v[j].x * v[j].x + v[j].y * v[j].y + v[j].z * v[j].z + v[j].w * v[j].w;
     if (i4 < d4) {
       if (n_part > 0) *reinterpret_cast<float4 *>(h + (size_t)m * d + 4 * (c4 + i4)) = v[j];
-      T *o = xn + act_pos<T>(m, 4 * (c4 + i4), Mcap, xn_mb);   // 4 features lie side by side in either layout
+      T *o = xn + act_at<T, ORD>(m, 4 * (c4 + i4), Mcap, xn_mb);   // 4 features lie side by side in either layout
       store4(o, v[j].x * gn[j].x, v[j].y * gn[j].y, v[j].z * gn[j].z, v[j].w * gn[j].w);
     }
   }
@@ -173,15 +173,17 @@ static void launch_rmsnorm_t(float *h, const float *hpart, int n_part, size_t pa
   typedef typename Internal<U>::type T;
   const int segs = rmsnorm_segments(d);
   const int j = (d / segs / 4 + 255) / 256;
-#define NGG_NORM(J)                                                                                                        \
-  hipLaunchKernelGGL((rmsnorm_kernel<U, T, J>), dim3(M, segs), dim3(256), 0, s, h, hpart, n_part, part_stride, (const U *)gain, \
+#define NGG_NORM_IN(J, ORD)                                                                                                \
+  hipLaunchKernelGGL((rmsnorm_kernel<U, T, J, ORD>), dim3(M, segs), dim3(256), 0, s, h, hpart, n_part, part_stride, (const U *)gain, \
                      (T *)xn, d, Mcap, xn_mb, row_ss)
+#define NGG_NORM(J) do { if (xn_mb) NGG_NORM_IN(J, true); else NGG_NORM_IN(J, false); } while (0)
   if (j <= 1) NGG_NORM(1);
   else if (j <= 2) NGG_NORM(2);
   else if (j <= 4) NGG_NORM(4);
   else if (j <= 8) NGG_NORM(8);
   else NGG_NORM(16);
 #undef NGG_NORM
+#undef NGG_NORM_IN
 }
 
 void launch_rmsnorm(int dtype, float *h, const float *hpart, int n_part, size_t part_stride, const void *gain, void *xn,
