@@ -724,9 +724,8 @@ def test_cfg2_small_bf16_lockstep():
 
 @pytest.mark.parametrize("k,w", [(16, 0), (16, 6), (32, 8), (13, 4), (12, 7), (13, 9), (20, 7), (32, 7), (20, 14), (32, 32)])
 def test_bf16_blocks_of_more_than_64_rows(k, w):
-    """Blocks of 16 to 1025 tokens on the small 16-bit widths (3 layers): the streaming GEMMs up to 128 tokens, the tiled
-    ones (which tile shape runs is pinned by test_every_tile_shape_16_bit) and the attention workgroups with two query
-    groups per wave."""
+    """Blocks of 16 to 1025 tokens on the small 16-bit widths (3 layers): the streaming GEMMs up to 64 tokens, above them the
+    tiled ones and the unembedding's LDS-staged kernel (which tile shape runs is pinned by test_every_tile_shape_16_bit) and the attention kernel of wide blocks."""
     desc = si.reduced_layers(si.MODELS["small"], 3)
     run = dict(si.RUNS["cfg2"], prompt_len=333, k=k, w=w, k_ctx_max=k, q_min=1, q_max=3, n_gen=30)
     w_, prompt, model, ctx = _setup(desc, run)
@@ -848,38 +847,47 @@ def test_tiled_gemm_edges_16_bit(heads, kv, hd, d_ffn, prompt_len, k, wd, tile, 
     assert rep.max_rel_logit_err <= 2e-2, rep
 
 
-@pytest.mark.parametrize("dtype,heads,kv,hd,d_model,d_ffn,vocab,prompt_len,k,wd,down", [
-    ("bf16", 3, 1, 32, 96, 160, 544, 50, 1, 1, 3),        # 2 tokens; contractions of 3 and 5 steps, waves without one; 6 sums of squares per row in 8 places
-    ("bf16", 2, 2, 64, 128, 2080, 2080, 64, 3, 5, 3),     # 16 tokens, one whole column block; a prompt of four; two fragments of gate/up per workgroup
-    ("bf16", 32, 32, 64, 64, 4128, 8224, 33, 4, 4, 3),    # 17 tokens; two fragments of q/k/v, three of gate/up, four of the unembedding
-    ("bf16", 5, 1, 128, 160, 6176, 1056, 80, 31, 1, 1),   # 32 tokens; four, the last workgroup short of three
-    ("bf16", 4, 2, 64, 96, 8224, 1056, 49, 8, 4, 1),      # 33 tokens; five
-    ("bf16", 1, 1, 64, 64, 10272, 1056, 40, 6, 8, 1),     # 49 tokens; six
-    ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 9, 7, 1),     # 64 tokens; seven
-    ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 5, 10, 1),    # 51 tokens; eight
-    ("bf16", 1, 1, 32, 64, 4128, 1056, 100, 16, 4, 1),    # 65 tokens, gate/up alone (three fragments); a prompt of seven column blocks
-    ("bf16", 32, 32, 64, 64, 6176, 1056, 66, 8, 10, 1),   # 81 tokens; four
-    ("bf16", 2, 1, 64, 96, 8224, 1056, 128, 19, 5, 1),    # 96 tokens, whole column blocks; five
-    ("bf16", 1, 1, 64, 64, 10272, 1056, 113, 16, 6, 1),   # 97 tokens; six
-    ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 16, 7, 1),    # 113 tokens; seven
-    ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 12, 10, 1),   # 121 tokens; eight
-    ("bf16", 64, 64, 64, 64, 512, 1056, 40, 12, 10, 1),   # 121 tokens, q/k/v alone (three)
-    ("bf16", 1, 1, 32, 64, 16416, 1056, 40, 5, 10, 1),    # 51 tokens; two rounds of five fragments, the last workgroup short of three
-    ("bf16", 1, 1, 32, 64, 16416, 1056, 40, 12, 10, 1),   # 121 tokens
-    ("f32", 3, 1, 32, 96, 160, 544, 50, 1, 1, 0),
-    ("f32", 4, 4, 32, 128, 2080, 16416, 64, 4, 4, 0),     # two fragments per workgroup; the unembedding on eight waves
-    ("f32", 2, 1, 64, 96, 544, 1056, 40, 9, 7, 0),
+@pytest.mark.parametrize("dtype,heads,kv,hd,d_model,d_ffn,vocab,prompt_len,k,wd,routes,frags", [
+    ("bf16", 3, 1, 32, 96, 160, 544, 50, 1, 1, "SSSSS", (1, 1)),        # 2 tokens; contractions of 3 and 5 steps, waves without one; 6 sums of squares per row in 8 places
+    ("bf16", 2, 2, 64, 128, 2080, 2080, 64, 3, 5, "SSSSS", (1, 2)),     # 16 tokens, one whole column block; a prompt of four; two fragments of gate/up per workgroup
+    ("bf16", 32, 32, 64, 64, 4128, 8224, 33, 4, 4, "SSSSS", (2, 3)),    # 17 tokens; two fragments of q/k/v, three of gate/up, four of the unembedding
+    ("bf16", 5, 1, 128, 160, 6176, 1056, 80, 31, 1, "SSSTS", (1, 4)),   # 32 tokens; four, the last workgroup short of three
+    ("bf16", 4, 2, 64, 96, 8224, 1056, 49, 8, 4, "SSSTS", (1, 5)),      # 33 tokens; five
+    ("bf16", 1, 1, 64, 64, 10272, 1056, 40, 6, 8, "STSTS", (1, 6)),     # 49 tokens; six
+    ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 9, 7, "STSTS", (1, 7)),     # 64 tokens; seven
+    ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 5, 10, "STSTS", (1, 8)),    # 51 tokens; eight
+    ("bf16", 1, 1, 32, 64, 4128, 1056, 100, 16, 4, "TTSTL", (0, 3)),    # 65 tokens, gate/up alone (three fragments); a prompt of seven column blocks
+    ("bf16", 32, 32, 64, 64, 6176, 1056, 66, 8, 10, "TTSTL", (0, 4)),   # 81 tokens; four
+    ("bf16", 2, 1, 64, 96, 8224, 1056, 128, 19, 5, "TTSTL", (0, 5)),    # 96 tokens, whole column blocks; five
+    ("bf16", 1, 1, 64, 64, 10272, 1056, 113, 16, 6, "TTSTL", (0, 6)),   # 97 tokens; six
+    ("bf16", 1, 1, 32, 64, 12320, 1056, 40, 16, 7, "TTSTL", (0, 7)),    # 113 tokens; seven
+    ("bf16", 1, 1, 32, 64, 14368, 1056, 40, 12, 10, "TTSTL", (0, 8)),   # 121 tokens; eight
+    ("bf16", 64, 64, 64, 64, 512, 1056, 40, 12, 10, "STTTL", (3, 0)),   # 121 tokens, q/k/v alone (three)
+    ("bf16", 1, 1, 32, 64, 16416, 1056, 40, 5, 10, "STSTS", (1, 5)),    # 51 tokens; two rounds of five fragments, the last workgroup short of three
+    ("bf16", 1, 1, 32, 64, 16416, 1056, 40, 12, 10, "TTSTL", (0, 5)),   # 121 tokens
+    ("f32", 3, 1, 32, 96, 160, 544, 50, 1, 1, "SSSSS", (0, 0)),
+    ("f32", 4, 4, 32, 128, 2080, 16416, 64, 4, 4, "SSSSS", (0, 0)),     # two fragments per workgroup; the unembedding on eight waves
+    ("f32", 2, 1, 64, 96, 544, 1056, 40, 9, 7, "SSSSS", (0, 0)),
+    ("f32", 2, 1, 64, 96, 2080, 1056, 40, 8, 4, "SSSSS", (0, 0)),     # 33 tokens: the longest contraction of down that stays whole ..
+    ("f32", 2, 1, 64, 96, 2080, 1056, 40, 12, 4, "SSSLS", (0, 0)),    # 49: .. and the first that is split
 ])
-def test_streaming_gemm_edges(dtype, heads, kv, hd, d_model, d_ffn, vocab, prompt_len, k, wd, down):
+def test_streaming_gemm_edges(dtype, heads, kv, hd, d_model, d_ffn, vocab, prompt_len, k, wd, routes, frags):
     """gemm_stream_kernel at the edges of its column blocks and rings: every number of fragments per workgroup, contractions
     with fewer steps than waves, blocks that end inside a column block, residual GEMMs on both sides of the rule that gives
-    them to it (what follows adds the norm or not), a short prompt and two verify blocks against the oracle; the tolerance is
-    the one of every lock-step test."""
-    assert ngg.debug_plan(dtype, "residual", 1 + k * wd, d_model, d_ffn)["kernel"] == down
+    them to it (what follows adds the norm or not), a short prompt and two verify blocks against the oracle, with gains that differ
+    from feature to feature; the tolerance is the one of every lock-step test.  routes: kernel of q/k/v, output projection, gate/up,
+    down and unembedding (S streams both operands, T tiled, L stages X through LDS); frags: fragments per workgroup where 16-bit q/k/v
+    and gate/up stream."""
+    M, widths = 1 + k * wd, (("qkv", (heads + 2 * kv) * hd, d_model), ("residual", d_model, heads * hd), ("gateup", d_ffn, d_model),
+                             ("residual", d_model, d_ffn), ("unembed", vocab, d_model))
+    assert "".join({"stream": "S", "tile": "T", "skinny": "L"}[ngg.debug_gemm_kernel(dtype, g, M, n, c)] for g, n, c in widths) == routes
+    for (g, n, c), route, fn in ((widths[0], routes[0], frags[0]), (widths[2], routes[2], frags[1])):
+        if dtype == "bf16" and route == "S":
+            assert ngg.debug_plan(dtype, g, M, n, c)["tile_rows"] == 16 * fn
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=d_model, d_ffn=d_ffn,
                 vocab=vocab, dtype=dtype)
     run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=max(1, k // 2))
-    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd, random_gains=True)
     rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL[dtype], max_steps=2)
     ctx.close()
     assert rep.max_rel_logit_err <= TOL[dtype], rep
@@ -893,16 +901,36 @@ def test_streaming_gemm_edges(dtype, heads, kv, hd, d_model, d_ffn, vocab, promp
     (6, 2, 64, 97, 31, 4, 1),        # 125 tokens
 ])
 def test_block_attention_edges_16_bit(heads, kv, hd, prompt_len, k, wd, slices):
-    """attn_block_kernel at the edges of its waves, steps of two tiles and slices, causal (the prompt) and with the rows of a
-    block, against the oracle; the tolerance is the one of every lock-step test."""
+    """attn_block_kernel (attn_kernel 4) at the edges of its waves, steps of two tiles and slices, causal (the prompt) and with the rows
+    of a block, against the oracle; the tolerance is the one of every lock-step test."""
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=heads, n_kv_heads=kv, head_dim=hd, d_model=128, d_ffn=256, vocab=1056)
     run = dict(si.RUNS["cfg2"], prompt_len=prompt_len, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
-    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd, random_gains=True)
     layouts = []
     rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=2,
-                       on_step=lambda step: layouts.append(ctx.debug_peek("attn_layout", np.int32)[0].tolist()))
+                       on_step=lambda step: layouts.append(ctx.debug_peek("attn_layout", np.int32)[0].tolist() + ctx.debug_peek("attn_kernel", np.int32)[0].tolist()))
     ctx.close()
-    assert layouts[0][0] == slices and layouts[0][2] == 1 + k * wd
+    assert layouts[0][0] == slices and all(l[2] == 1 + k * wd and l[4] == 4 for l in layouts), layouts
+    assert rep.max_rel_logit_err <= TOL["bf16"], rep
+
+
+@pytest.mark.parametrize("hd", [32, 64, 128])
+@pytest.mark.parametrize("k,wd,kernels", [
+    (16, 4, (4, 3)),       # 65 tokens: attn_block_kernel below a dozen tiles per slice, attn_shared_kernel with two query groups from there on
+    (16, 8, (4, 4)),       # 129: two workgroups share a slice, the block kernel takes both
+    (12, 4, (2, 3)),       # 49: attn_shared_kernel, ordinary and non-temporal loads
+])
+def test_attention_on_both_sides_of_a_dozen_tiles_per_slice(hd, k, wd, kernels):
+    """136 heads keep one slice per head: 320 cached positions are eleven tiles, one more makes twelve, and the kernel changes.  Steps
+    on both sides against the oracle; the tolerance is the one of every 16-bit lock-step test."""
+    desc = dict(si.reduced_layers(si.MODELS["small"], 1), n_heads=136, n_kv_heads=4, head_dim=hd, d_model=128, d_ffn=256, vocab=1056)
+    run = dict(si.RUNS["cfg2"], prompt_len=320, n_gen=3 * (wd + 1), k=k, w=wd, k_ctx_max=k // 2)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=k, max_w=wd, random_gains=True)
+    seen = []
+    rep = lockstep_run(ctx, model, prompt, 2 * (wd + 1), run, TOL["bf16"], max_steps=2,
+                       on_step=lambda step: seen.append((ctx.debug_peek("attn_layout", np.int32)[0].tolist(), int(ctx.debug_peek("attn_kernel", np.int32)[0][0]))))
+    ctx.close()
+    assert [(l[0], l[2], kern) for l, kern in seen] == [(1, 1 + k * wd, kern) for kern in kernels] and seen[0][0][3] == 320, seen
     assert rep.max_rel_logit_err <= TOL["bf16"], rep
 
 
@@ -1005,7 +1033,7 @@ def test_profiled_norms_leave_the_streaming_gemms(dtype, n, tokens):
     instead: the same hidden states up to the order of the row sums.  With every other class bracketed nothing changes."""
     desc = dict(si.reduced_layers(si.MODELS["small"], 2), n_heads=2, n_kv_heads=2, head_dim=32, d_model=n, d_ffn=160, vocab=544, dtype=dtype)
     run = dict(si.RUNS["cfg2"], prompt_len=40, n_gen=16, k=(tokens - 1) // 4, w=4, k_ctx_max=2)
-    w_, prompt, model, ctx = _setup(desc, run, max_k=run["k"], max_w=4)
+    w_, prompt, model, ctx = _setup(desc, run, max_k=run["k"], max_w=4, random_gains=True)
     ctx.prefill(prompt)
     drafts = np.random.default_rng(5).integers(0, 544, (run["k"], 4)).astype(np.int32)
     states = []
@@ -1095,7 +1123,7 @@ def test_whole_and_split_key_lists(dtype, heads, hd, prompt_len, k, wd, splits, 
 
 @pytest.mark.parametrize("k,wd,prompt_len,wgs", [
     (8, 4, 700, 136),                  # 22 key tiles of 128 dims: a long list in one slice, read once for all 33 tokens
-    (8, 8, 700, 136),                  # 65 tokens: two query groups per wave
+    (8, 8, 700, 136),                  # 65 tokens: two query groups per wave (23 tiles in a slice)
     (8, 1, 700, 136),                  # 9 tokens
     (8, 4, 300, 136),                  # 11 tiles: short, but 16 queries per workgroup would make two rounds of workgroups
     (8, 2, 60, 136),                   # 17 tokens, 3 tiles
@@ -1129,8 +1157,8 @@ def test_7b_width_two_layer_twin_bf16_lockstep():
 
 def test_7b_width_one_layer_twin_long_context_shape():
     """The long-context configuration's draft shape (k=16, w=6: 97 block tokens, query back-off q=3..1)
-    at 7B widths, one layer, prompt 1536: the 128-row GEMM tiles at K = 4096 / 14336 and the
-    two-query-group attention workgroups at head_dim 128."""
+    at 7B widths, one layer, prompt 1536: q/k/v and gate/up streamed in seven column blocks, the tiled residual GEMMs at
+    K = 4096 / 14336 and the 32x32 attention kernel of short slices at head_dim 128."""
     desc = si.reduced_layers(si.MODELS["7b"], 1)
     run = dict(si.RUNS["cfg4"], prompt_len=1536, n_gen=20)
     w, prompt, model, ctx = _setup(desc, run)
