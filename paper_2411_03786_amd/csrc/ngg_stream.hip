@@ -326,12 +326,18 @@ static bool launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
 }
 
 // Which GEMMs of a block run here.  Up to 64 rows, q/k/v, gate/up and the unembedding: all.  Measured against the kernels
-// that stage X through LDS, back to back, us at 2 / 17 / 33 / 51 rows:
+// that stage X through LDS, back to back (from 5120 wide and fp32 from 1024: in the call), us at 2 / 17 / 33 / 51 rows:
 //   q/k/v    768 wide 5.0 -> 3.9 / 5.6 -> 4.1 / 6.1 -> 4.6 / 6.7 -> 5.3, 2048 7.6 -> 7.0 / 8.1 -> 7.8 / 10.0 -> 8.9 / 11.0 -> 10.0,
 //            3072 12.8 -> 11.4 / 13.6 -> 12.7 / 15.5 -> 14.7 / 16.7 -> 16.3, 4096 18.5 -> 17.4 / 19.5 -> 17.9 / 21.4 -> 19.9 / 22.6 -> 21.7
 //   gate/up  768 wide 5.0 -> 4.4 / 5.4 -> 4.7 / 6.4 -> 5.2 / 7.1 -> 5.7, 4096 39.6 -> 37.4 / 39.9 -> 37.9 / 41.3 -> 40.2 / 42.5 -> 40.9;
 //            3072 wide at 51 rows 19.2 (64 x 64 tiles) against 19.9 here, what q/k/v and the norm give back
-//   fp32, 512 wide: q/k/v 5.1 -> 4.1 / 6.5 -> 4.8 / 7.8 -> 5.9 / 9.0 -> 7.0
+//   5120     q/k/v 30.8 -> 29.8 / 31.6 -> 28.6 / 32.3 -> 31.1 / 33.5 -> 33.3, gate/up 49.3 -> 48.3 / 49.3 -> 46.3 / 50.3 -> 48.3 / 51.3 -> 50.5
+//   6144     42.4 -> 41.0 / 43.1 -> 41.2 / 43.5 -> 42.0 / 46.5 -> 44.6, 68.5 -> 66.1 / 69.3 -> 66.7 / 68.7 -> 65.6 / 70.1 -> 68.4
+//   8192     gate/up of 28672 features 153 -> 146 / 152 -> 143 / 154 -> 147 / 161 -> 154
+//   fp32     512 wide q/k/v 5.1 -> 4.1 / 6.5 -> 4.8 / 7.8 -> 5.9 / 9.0 -> 7.0, 1024 10.7 -> 8.9 / 12.1 -> 8.9 / 14.2 -> 10.1 / 16.4 -> 11.3, 4096 44 -> 41 /
+//            57 -> 49 / 83 -> 66 / 104 -> 85, its gate/up 67 -> 60 / 83 -> 72 / 112 -> 98 / 154 -> 124
+// It loses where long contractions leave CUs idle at 33 rows or more: q/k/v of 576 fragments (192 workgroups), 7168 wide, 30.0 -> 26.5 /
+// 28.6 -> 27.9 / 31.5 -> 32.4 / 34.8 -> 36.8, 35.2 -> 38.7 at 64 rows (whole calls 0.94 / 0.97 / 0.99 / 1.00 and 1.01 of their time).
 // From 65 to 128 rows q/k/v and gate/up of 16-bit models of more than 512 fragments, at 65 / 81 / 97 / 121 rows: 4096 wide q/k/v
 // 27.0 -> 24.9 / 30.1 -> 27.4 / 32.6 -> 30.5 / 34.4 -> 32.9, gate/up 44.4 -> 44.0 / 46.3 and 46.7 / 53.6 -> 50.6 / 61.5 -> 53.5; 3072 wide
 // q/k/v 21.1 -> 18.9 / 23.0 -> 20.7 / 25.6 -> 23.6 / 27.3 -> 25.4.  Narrower ones run 128-row tiles there (768 wide gate/up 7.2 at
@@ -341,8 +347,11 @@ static bool launch_stream_t(int epi, const GemmArgs &a_in, hipStream_t s) {
 // and norm 768 wide 7.5 -> 5.6 / 8.2 -> 6.6 / 8.6 -> 8.0 / 8.8 and 9.2, 4096 23.4 -> 20.4 / 24.1 and 24.8 / 25.2 and 30.9.  The line:
 // the kilobytes a workgroup pulls (its 16 rows of W, and X as if a partly filled column block counted half) against the
 // bytes of W, which the splitting kernels stream in that time too (768 x 3072, 4.7 MB: equal at 400 KB; 2048 x 5504, 22 MB:
-// at 460; 3072 x 8192, 50 MB: at 680; 4096 x 14336, 117 MB: at 1100); fp32 a fifth further.  More than one workgroup per CU
-// share its path to the L2.
+// at 460; 3072 x 8192, 50 MB: at 680; 4096 x 14336, 117 MB: at 1100; from there on the splitting kernels stream faster: 8192 x 14336,
+// 235 MB: at 1600; 7168 x 16384 loses 5 of 47 us at 1820; 8192 x 28672, 470 MB: 4 us faster at 2800, 6 slower at 3190).  More than one
+// workgroup per CU share its path to the L2.  fp32 a fifth further: with its norm (4.4) down 512 x 1408 at 17 / 33 / 64 rows 14.7 -> 9.1 /
+// 16.9 -> 10.6 / 19.4 -> 12.6, 768 x 3072 at 25 15.8 -> 13.9, 1024 x 4096 at 9 14.5 and 14.4, 4096 x 11008 at 9 and 17 41.4 -> 35.6 and 40.2 -> 39.8,
+// the projection 4096 wide at 17 / 41 rows 26.8 -> 18.4 / 31.8 -> 27.5.
 bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only) {
   if (dtype == 1 && tile_only && M > 1) return false;
   if (M > 64) return dtype == 1 && M <= 128 && (epi == EPI_QKV || epi == EPI_GATEUP) && frags > 512;
@@ -350,7 +359,8 @@ bool stream_takes(int dtype, int epi, int M, int frags, int K, int tile_only) {
   if (frags > 512 || K <= 64) return false;               // (the sums of squares of 64 rows fit the LDS of the next GEMM)
   const int e = dtype == 1 ? 2 : 4, fm = (M + 15) / 16;
   const float kb = (0.5f * ((float)fm + (float)M / 16.0f) + 1.0f) * (float)(K / 32) * (float)(e / 2) * (float)((frags + 255) / 256);
-  const float limit = 390.0f + 6.2f * ((float)frags * 16.0f * (float)K * (float)e / 1.0e6f);
+  const float mb_w = (float)frags * 16.0f * (float)K * (float)e / 1.0e6f;
+  const float limit = std::min(390.0f + 6.2f * mb_w, 600.0f + 5.0f * mb_w);
   return kb <= (dtype == 1 ? limit : 1.2f * limit);
 }
 

@@ -202,6 +202,14 @@ def test_only_streaming_gate_up_feeds_a_streaming_down(lib, dtype):
                     assert down != "stream" or gate == "stream", (m, d, f, shape)
 
 
+def test_whole_contractions_of_wide_residual_gemms_end_where_they_were_measured(lib):
+    """16-bit residual GEMMs on both sides of the line up to which a workgroup takes the whole contraction: 9 rows of 7168 x 16384 and
+    8192 x 28672 took 52 and 87 us with the norm inside, 47 and 81 with it behind."""
+    for d, f, tokens, kernel in ((4096, 14336, 9, "stream"), (4096, 14336, 33, "tile"), (8192, 14336, 9, "stream"), (7168, 16384, 2, "stream"),
+                                 (7168, 16384, 9, "skinny"), (8192, 28672, 2, "stream"), (8192, 28672, 9, "skinny"), (6144, 16384, 2, "stream")):
+        assert ngg.debug_gemm_kernel("bf16", "residual", tokens, d, f) == kernel, (d, f, tokens)
+
+
 def test_streamed_wide_matrices_are_dealt_out_in_equal_rounds(lib):
     """16-bit q/k/v and gate/up that stream both operands: one workgroup of up to eight fragments is on each of the 256 CUs at a
     time, and a workgroup takes no more than the fewest rounds need (eight of 2560 left the second round three quarters empty:
