@@ -42,7 +42,7 @@ struct ngg_ctx {
   hipStream_t stream = nullptr;
   int esize = 2;          // bytes per weight / KV element
   int Spad = 0, Mcap = 0, max_splits = 0, unembed_tiles = 0;
-  int tile_only = 0;               // ngg_debug_tiles: see GemmArgs
+  int tile_only = 0;               // ngg_debug_tiles: see GemmCore
   int prefill_chunk = 0;           // prompt tokens per forward pass of ngg_prefill
   // One decode step (drafts, block forward, acceptance, commit) captured as a HIP graph: its kernels read the
   // context length from n_dev, so the same graph replays step after step (a replayed launch costs the GPU

@@ -16,7 +16,7 @@ namespace ngg {
 // v: the first members (fragment rows 4g .. 4g+3, g < 2), x2: their partners (rows 8 + 4g ..), both already scaled.
 // act_mb: layout of the SwiGLU output; a constant 0 in the kernels whose output gemm_stream_kernel never reads (launch_gemm checks it)
 template <typename T, int EPI>
-__device__ __forceinline__ void epi_paired_vals(const GemmArgs &a, int frag, int m, int M, int g, const float (&v)[4],
+__device__ __forceinline__ void epi_paired_vals(const GemmCore &a, int frag, int m, int M, int g, const float (&v)[4],
                                                 const float (&x2)[4], int act_mb) {
   if (m < M && g < 2) {
     if constexpr (EPI == EPI_GATEUP) {
@@ -62,7 +62,7 @@ __device__ __forceinline__ void epi_paired_vals(const GemmArgs &a, int frag, int
 }
 
 template <typename T, int EPI>
-__device__ __forceinline__ void epi_paired(const GemmArgs &a, int frag, int m, int M, int g, float rs, const f32x4 &sum, int act_mb = 0) {
+__device__ __forceinline__ void epi_paired(const GemmCore &a, int frag, int m, int M, int g, float rs, const f32x4 &sum, int act_mb = 0) {
   float v[4], x2[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) { v[r] = sum[r] * rs; x2[r] = other_half(v[r]); }
@@ -70,7 +70,7 @@ __device__ __forceinline__ void epi_paired(const GemmArgs &a, int frag, int m, i
 }
 
 // residual: split ks stores its fp32 partial of output features n0 + 4g .. +4 of block row m
-__device__ __forceinline__ void epi_residual(const GemmArgs &a, int ks, int m, int n0, int g, const f32x4 &sum) {
+__device__ __forceinline__ void epi_residual(const GemmCore &a, int ks, int m, int n0, int g, const f32x4 &sum) {
   float *dst = a.hpart + ((size_t)ks * a.Mcap + m) * a.N;
   *reinterpret_cast<float4 *>(dst + n0 + 4 * g) =
       float4{sum[0] * a.out_scale, sum[1] * a.out_scale, sum[2] * a.out_scale, sum[3] * a.out_scale};
@@ -79,7 +79,7 @@ __device__ __forceinline__ void epi_residual(const GemmArgs &a, int ks, int m, i
 // unembedding: optional logits, and the best (value, id) of block row m over the FN fragments of `group`
 // (vocabulary rows nbase[f] ..): ascending ids, so the first maximum stays
 template <int FN>
-__device__ __forceinline__ void epi_unembed(const GemmArgs &a, int group, int m, bool live, int g, float rs,
+__device__ __forceinline__ void epi_unembed(const GemmCore &a, int group, int m, bool live, int g, float rs,
                                             const int (&nbase)[FN], const f32x4 (&sum)[FN]) {
   float bv = kNegBig;
   int bi = 0x7fffffff;

@@ -1,7 +1,7 @@
 // Skinny GEMM  Y[M x N] = X[M x K] . W[N x K]^T  for the k*(w+1) block rows of a verify call
 // (Section 3: a model call on a (k, w+1) block is meant to stay memory-bound, so the kernel is
-// built around streaming W exactly once at HBM speed): blocks of 65 to 128 rows, every fp32 block above 64, and the residual
-// GEMMs of smaller blocks that gemm_stream_kernel (ngg_stream.hip) leaves.
+// built around streaming W exactly once at HBM speed): every fp32 block above 64 rows, the 16-bit unembedding of 65 to 128, and the
+// residual GEMMs of smaller blocks that gemm_stream_kernel (ngg_stream.hip) and gemm_tile_kernel leave.
 //
 // W rows are the MFMA "row" operand.  The library keeps its own copy of every weight matrix in
 // operand order (16 rows x 32 contraction elements per 1 KB block, lane-major), so one load
@@ -24,7 +24,7 @@
 namespace ngg {
 
 template <typename T, int EPI, int FM, int WN, int WK, int RING, int FN>
-__global__ __launch_bounds__(64 * WN * WK) void gemm_skinny_kernel(const GemmArgs a) {
+__global__ __launch_bounds__(64 * WN * WK) void gemm_skinny_kernel(const GemmCore a) {
   constexpr int XD = FM > 4 ? 1 : 2;         // X register stages (chunks fetched ahead); one when the tile is 128 rows
   static_assert(WN * WK == 4 || WN * WK == 8, "four or eight waves per workgroup");
   constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;   // fragments that hold both halves of 8 output pairs
@@ -310,7 +310,7 @@ __device__ __forceinline__ void wave_lds_fence() {       // LDS written by other
 
 // frag_first, frag_end: 16-row fragments of W this launch covers; MT row tiles, `tiles` tiles in all
 template <int EPI, int WM, int WN, int BM, int BN, int NST, bool NT>
-__global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs a, int MT, int tiles, int frag_first, int frag_end) {
+__global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmCore a, int MT, int tiles, int frag_first, int frag_end) {
   typedef half_t T;
   constexpr int NW = WM * WN, TM = 32 * WM * BM, TN = 32 * WN * BN;
   constexpr int KC = KChunk<T>::value, KW = 64;
@@ -597,7 +597,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(const GemmArgs 
 }
 
 template <int EPI, int WM, int WN, int BM, int BN, int NST>
-static void launch_tile_cfg(const GemmArgs &a, int KS, int frag_first, int frag_end, hipStream_t s) {
+static void launch_tile_cfg(const GemmCore &a, int KS, int frag_first, int frag_end, hipStream_t s) {
   constexpr int TM = 32 * WM * BM, TN = 32 * WN * BN;
   size_t lds = (size_t)NST * (TM + TN) * 64 * 2;
   if (EPI == EPI_QKV) lds = std::max(lds, (size_t)TM * 4 + (size_t)WM * WN * BN * 4096);
@@ -685,7 +685,7 @@ static TilePlan tile_plan(int epi, int M, int frags, int K, int only) {
 }
 
 template <int EPI>
-static void launch_tile_shape(int shape, const GemmArgs &a, int KS, int f0, int f1, hipStream_t s) {
+static void launch_tile_shape(int shape, const GemmCore &a, int KS, int f0, int f1, hipStream_t s) {
   if (f0 >= f1) return;
   switch (shape) {
     case 0: launch_tile_cfg<EPI, 2, 4, 4, 2, 2>(a, KS, f0, f1, s); break;
@@ -702,14 +702,14 @@ static void launch_tile_shape(int shape, const GemmArgs &a, int KS, int f0, int 
 }
 
 template <int EPI>
-static void launch_tile(const GemmArgs &a, hipStream_t s) {
+static void launch_tile(const GemmCore &a, hipStream_t s) {
   const int frags = EPI == EPI_QKV ? (a.H + 2 * a.Hkv) * (a.hd / 16) : (EPI == EPI_GATEUP ? a.N / 8 : a.N / 16);
   const TilePlan p = tile_plan(EPI, a.M, frags, a.K, a.tile_only);
   launch_tile_shape<EPI>(p.shape, a, p.KS, 0, p.split, s);  // residual: p.KS == a.KS (gemm_residual_splits)
   launch_tile_shape<EPI>(p.shape2, a, p.KS, p.split, frags, s);
 }
 template <typename T, int EPI, int FM, int WN, int WK, int RING, int FN = 2>
-void launch_gemm_cfg(const GemmArgs &a, int KS, hipStream_t s) {
+void launch_gemm_cfg(const GemmCore &a, int KS, hipStream_t s) {
   constexpr int KC = KChunk<T>::value;
   constexpr int PAD = 16 / (int)sizeof(T);
   constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
@@ -728,7 +728,7 @@ void launch_gemm_cfg(const GemmArgs &a, int KS, hipStream_t s) {
 }
 
 // residual, unembedding: pairs of 16-row fragments; q/k/v and gate/up: 16-row fragments of 8 output pairs
-int gemm_groups(int epi, const GemmArgs &a) {
+int gemm_groups(int epi, const GemmCore &a) {
   switch (epi) {
     case EPI_QKV: return (a.H + 2 * a.Hkv) * (a.hd / 16);
     case EPI_GATEUP: return a.N / 8;
@@ -742,7 +742,7 @@ int gemm_groups(int epi, const GemmArgs &a) {
 static int gemm_row_blocks(int M) { return M >= 128 ? 8 : (M + 15) / 16; }
 
 template <typename T, int EPI, int WN, int WK, int RING>
-static void launch_fm(const GemmArgs &a, int KS, hipStream_t s) {
+static void launch_fm(const GemmCore &a, int KS, hipStream_t s) {
   switch (gemm_row_blocks(a.M)) {                            // 16-row column blocks of the tile
     case 5: launch_gemm_cfg<T, EPI, 5, WN, WK, RING>(a, KS, s); return;
     case 6: launch_gemm_cfg<T, EPI, 6, WN, WK, RING>(a, KS, s); return;
@@ -764,13 +764,13 @@ static void launch_fm(const GemmArgs &a, int KS, hipStream_t s) {
 // q/k/v and gate/up: one workgroup = FN fragments, its four waves split the steps of every chunk (WN = 1, WK = 4).  fp32
 // only: the 16-bit ones run on gemm_stream_kernel or the tiled one.
 template <typename T, int EPI, int FM>
-static void launch_paired_fm(const GemmArgs &a, hipStream_t s) {
+static void launch_paired_fm(const GemmCore &a, hipStream_t s) {
   if (a.n_groups <= 256) launch_gemm_cfg<T, EPI, FM, 1, 4, 4, 1>(a, 1, s);
   else launch_gemm_cfg<T, EPI, FM, 1, 4, 4, 2>(a, 1, s);
 }
 
 template <typename T, int EPI>
-static void launch_paired(const GemmArgs &a, hipStream_t s) {
+static void launch_paired(const GemmCore &a, hipStream_t s) {
   switch (gemm_row_blocks(a.M)) {                            // (up to four: gemm_stream_kernel)
     case 5: launch_paired_fm<T, EPI, 5>(a, s); break;
     case 6: launch_paired_fm<T, EPI, 6>(a, s); break;
@@ -797,8 +797,8 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
   return ks < 1 ? 1 : ks;
 }
 
-// Which blocks gemm_tile_kernel takes of those that gemm_stream_kernel leaves (16-bit operands).  Above 128 rows: all.  Up to 128, measured on MI355X (skinny ->
-// tiled, us, at 17 / 33 / 51 / 64-65 / 97 rows):
+// Which blocks gemm_tile_kernel takes of those that gemm_stream_kernel leaves (16-bit operands).  Above 128 rows: all.  Up to 128,
+// measured on MI355X (skinny -> tiled, us, at 17 / 33 / 51 / 64-65 / 97 rows):
 //  * residual GEMMs.  The tiled kernel reads X once per 64 columns of W instead of 32 and splits the contraction where that
 //    fills the chip: output projection 4096 x 4096 8.4 -> 8.8 / 9.7 -> 9.0 / 11.0 -> 9.4 / 13.6 -> 12.2 / 16.7 -> 12.8, 768 x 768
 //    4.9 -> 4.0 / 5.7 -> 4.1 / 6.6 -> 4.2 / 7.5 -> 3.9 / 9.1 -> 4.0; down 4096 x 14336 20.8 -> 21.6 / 21.8 -> 22.0 / 23.6 -> 22.8 /
@@ -810,8 +810,8 @@ static int skinny_residual_splits(int kc, int M, int N, int K) {
 //    8-layer steps of 81 to 93 rows came to 0.96-0.97 of the skinny kernel's on four cards and 1.00-1.03 on four.  Wider
 //    models run 128 x 256 tiles, faster on all of them (8192 x 28672, 81-93 rows: steps 0.97-0.98).
 //  * gate/up and q/k/v of 65 rows or more on narrow models, where one or two fragments per workgroup leave too little in
-//    flight (768-wide, 97 rows: 9.6 -> 7.1 and 9.9 -> 8.0; 65 rows 8.0 -> 7.1, 8.3 -> 8.0); wide models stream W as fast
-//    either way (4096-wide, 97 rows: 49.4 and 47.5-50.6, 33.8 and 35.3).
+//    flight (768-wide, 97 rows, against kernels that staged X through LDS: 9.6 -> 7.1 and 9.9 -> 8.0; 65 rows 8.0 -> 7.1, 8.3 -> 8.0); wide
+//    ones run gemm_stream_kernel (stream_takes has the figures).
 static bool takes_tile(int epi, int M, int frags, int K, int tile_only) {
   if (M > 128 || (tile_only && M > 1)) return true;
   if (epi == EPI_UNEMBED || M <= 16) return false;
@@ -834,7 +834,7 @@ static bool skinny_built(int dtype, int epi, int M, int N, int K) {
   return dtype == 0 || epi == EPI_UNEMBED || M <= (residual_narrow(M, N, K) ? 32 : 96);
 }
 template <typename T, int WN, int WK>
-static bool launch_residual(const GemmArgs &a, hipStream_t s) {
+static bool launch_residual(const GemmCore &a, hipStream_t s) {
   if (!skinny_built(sizeof(T) == 2 ? 1 : 0, EPI_RESIDUAL, a.M, a.N, a.K)) return false;
   if constexpr (sizeof(T) == 4) launch_fm<T, EPI_RESIDUAL, WN, WK, 4>(a, a.KS, s);
   else if constexpr (WN == 1) {
@@ -848,13 +848,13 @@ static bool launch_residual(const GemmArgs &a, hipStream_t s) {
   return true;
 }
 
-// Workgroup shapes measured on MI355X at the 7B shapes (M = 60 and M = 1).  Unembedding: wide tiles
+// Workgroup shapes measured on MI355X at the 7B shapes (60 rows).  Unembedding: wide tiles
 // (WN = 4) where there are enough row groups to give every CU a workgroup, otherwise two waves per
 // pair of groups; residual GEMMs: WN x WK = 2 x 2 or 1 x 4 (residual_narrow) with the contraction split
 // across workgroups.
 template <typename T>
-static bool launch_skinny(int epi, const GemmArgs &a_in, hipStream_t s) {
-  GemmArgs a = a_in;
+static bool launch_skinny(int epi, const GemmCore &a_in, hipStream_t s) {
+  GemmCore a = a_in;
   a.n_groups = gemm_groups(epi, a);
   const bool wide = a.n_groups >= 4 * 200;
   switch (epi) {
@@ -914,7 +914,7 @@ bool gemm_row_fits(int dtype, int d_model, int dq) {
 
 // NP: residual partials fetched at once (PRO 1), the number itself is r.n_part <= NP
 template <typename U, typename T, int EPI, int FN, int RING, int PRO, int NP>
-__global__ __launch_bounds__(kRowThreads) void gemm_row_kernel(const GemmArgs a, const RowArgs r) {
+__global__ __launch_bounds__(kRowThreads) void gemm_row_kernel(const GemmCore a, const RowArgs r) {
   constexpr bool PAIRED = EPI == EPI_QKV || EPI == EPI_GATEUP;
   constexpr int KC = KChunk<T>::value, NW = 4;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(kRowThreads) void gemm_row_kernel(const GemmArgs a,
 }
 
 template <typename U, int EPI, int FN, int PRO, int NP>
-static void launch_row_np(const GemmArgs &a, const RowArgs &r, int KS, hipStream_t s) {
+static void launch_row_np(const GemmCore &a, const RowArgs &r, int KS, hipStream_t s) {
   typedef typename Internal<U>::type T;
   // steps in flight per wave: as many 1 KB fragments as the registers hold without spilling (fp32 fragments are 2 KB)
   constexpr int RING = (sizeof(T) == 2 ? (FN >= 5 ? 3 : (FN >= 3 ? 5 : 8)) : (FN >= 5 ? 2 : (FN >= 3 ? 3 : 4)));
@@ -1120,7 +1120,7 @@ static void launch_row_np(const GemmArgs &a, const RowArgs &r, int KS, hipStream
 }
 
 template <typename U, int EPI, int FN, int PRO>
-static void launch_row_cfg(const GemmArgs &a, const RowArgs &r, int KS, hipStream_t s) {
+static void launch_row_cfg(const GemmCore &a, const RowArgs &r, int KS, hipStream_t s) {
   if constexpr (PRO == 1) {                              // narrow models split the residual GEMMs further (gemm_row_splits)
     if (r.n_part > 2) { launch_row_np<U, EPI, FN, PRO, kMaxResidualSplits>(a, r, KS, s); return; }
   }
@@ -1128,7 +1128,7 @@ static void launch_row_cfg(const GemmArgs &a, const RowArgs &r, int KS, hipStrea
 }
 
 template <typename U, int EPI, int PRO>
-static void launch_row_fn(const GemmArgs &a, const RowArgs &r, int KS, hipStream_t s) {
+static void launch_row_fn(const GemmCore &a, const RowArgs &r, int KS, hipStream_t s) {
   const int fn = row_frags_per_wg(EPI, a.n_groups);
   if constexpr (EPI == EPI_RESIDUAL) {
     if (fn == 1) launch_row_cfg<U, EPI, 1, PRO>(a, r, KS, s);
@@ -1155,8 +1155,8 @@ static void launch_row_fn(const GemmArgs &a, const RowArgs &r, int KS, hipStream
 }
 
 template <typename U>
-static void launch_row_t(int epi, const GemmArgs &a_in, const RowArgs &r, hipStream_t s) {
-  GemmArgs a = a_in;
+static void launch_row_t(int epi, const GemmCore &a_in, const RowArgs &r, hipStream_t s) {
+  GemmCore a = a_in;
   a.n_groups = epi == EPI_RESIDUAL || epi == EPI_UNEMBED ? a.N / 16 : gemm_groups(epi, a);
   switch (epi) {
     case EPI_QKV: launch_row_fn<U, EPI_QKV, 1>(a, r, 1, s); break;
@@ -1190,7 +1190,7 @@ GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K) {
   return p;
 }
 
-void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s) {
+void launch_gemm_row(int dtype, int epi, const GemmCore &a, const RowArgs &r, hipStream_t s) {
   if (dtype == 1) launch_row_t<bf16_t>(epi, a, r, s);
   else launch_row_t<float>(epi, a, r, s);
 }

@@ -120,7 +120,7 @@ __host__ __device__ __forceinline__ size_t act_offset(int m, int k, int Mcap) {
   constexpr int KC = KChunk<T>::value;
   return ((size_t)(k / KC) * Mcap + m) * KC + k % KC;
 }
-// ... or, where gemm_stream_kernel reads them (blocks of up to 64 rows), in operand order like the weights: 1 KB blocks of 16
+// ... or, where gemm_stream_kernel reads them (blocks of up to 64 rows; q/k/v and gate/up of wide 16-bit models: 128), in operand order like the weights: 1 KB blocks of 16
 // rows x 32 contraction elements, the mb = ceil(M / 16) row blocks of a step side by side, so that a wave fetches its operand
 // with one contiguous load and no LDS in between.  mb = 0 stands for chunk-major.
 template <typename T>
@@ -261,8 +261,10 @@ __host__ __device__ __forceinline__ int block_tokens(int R, int C, int shared0) 
 // ---------------------------------------------------------------------------------------------
 enum GemmEpilogue { EPI_QKV = 0, EPI_RESIDUAL = 1, EPI_GATEUP = 2, EPI_UNEMBED = 3 };
 
-struct GemmArgs {
-  const void *X;          // activations, chunk-major [K/KC][Mcap][KC], element type T
+// What every GEMM kernel takes.  gemm_stream_kernel's own arguments are in a type of their own behind it, so that the other kernels'
+// argument block is no longer for them.
+struct GemmCore {
+  const void *X;          // activations, element type T: chunk-major [K/KC][Mcap][KC], or what GemmArgs::x_mb says
   const void *W0;         // weight matrix in operand order (QKV: rows [q | k | v]; gate/up: rows [gate | up])
   int M, N, K;            // N = total logical output rows
   // q/k/v, gate/up, unembedding: X is h * gain; the epilogue multiplies row m by
@@ -270,23 +272,14 @@ struct GemmArgs {
   const float *row_ss;    // [M][ss_segs]
   int ss_segs;
   float ss_eps;
-  int x_mb;               // layout of X (act_pos)
   float out_scale;        // every result is multiplied by this: 1 / (scale of the stored weights * scale of X); 1 for fp32 models
-  int n_groups;           // residual, unembedding: pairs of 16-row fragments; q/k/v, gate/up: fragments (filled by the launcher)
+  int n_groups;           // 16-row fragments of W; of gemm_skinny_kernel's residual and unembedding: pairs of them (filled by the launcher)
   int tile_only;          // tests: 1 + the tile shape gemm_tile_kernel has to take, and takes any block of two tokens or more; 0: by size
-  // EPI_RESIDUAL: split ks of KS stores its fp32 partial at hpart[ks][m][n]; the next RMSNorm adds them
+  // EPI_RESIDUAL: split ks of KS stores its fp32 partial at hpart[ks][m][n]; the RMSNorm that follows adds them
   float *hpart;           // [KS][Mcap][N]
   int KS;
-  // EPI_RESIDUAL, h set (gemm_stream_kernel, KS == 1): the RMSNorm that follows is done here too: h += the result, xn = h * gain
-  // and the sums of squares of every row over 16 features each
-  float *h;               // [Mcap][N]
-  const void *gain;       // [N], the user's storage type
-  void *xn;               // act_pos(.., xn_mb)
-  int xn_mb;
-  float *ss_out;          // [M][stream_segments(N)]
   // EPI_GATEUP
-  void *act;              // [M][N = d_ffn] T, act_pos(.., act_mb)
-  int act_mb;
+  void *act;              // [M][N = d_ffn] T, chunk-major, or what GemmArgs::act_mb says
   // EPI_QKV
   void *q;                // [H][Mcap][hd] T
   void *kscr;             // this layer's block keys, [Hkv][kv_rows/32] tiles (k_offset)
@@ -303,6 +296,19 @@ struct GemmArgs {
   int *pmax_idx;          // [N/32][Mcap]
 };
 
+// ... and what gemm_stream_kernel takes beyond it; x_mb says whether it is the kernel at all
+struct GemmArgs : GemmCore {
+  int x_mb;               // layout of X (act_pos)
+  int act_mb;             // EPI_GATEUP: layout of act
+  // EPI_RESIDUAL, h set (KS == 1): the RMSNorm that follows is done here too: h += the result, xn = h * gain and the sums of
+  // squares of every row over 16 features each
+  float *h;               // [Mcap][N]
+  const void *gain;       // [N], the user's storage type
+  void *xn;               // act_pos(.., xn_mb)
+  int xn_mb;
+  float *ss_out;          // [M][stream_segments(N)]
+};
+
 // What the single-row GEMM (launch_gemm_row) builds its input from
 struct RowArgs {
   const float *h_in;      // residual stream [K], and the partials of the last residual GEMM to add to it
@@ -311,14 +317,14 @@ struct RowArgs {
   int n_part;
   size_t part_stride;
   const void *gain;       // [K], the user's storage type
-  const float *part_o;    // attention slices [H][n_splits][hd] and their (maximum, sum); null: X is taken from GemmArgs
+  const float *part_o;    // attention slices [H][n_splits][hd] and their (maximum, sum); null: X is taken from GemmCore
   const float *part_ml;
   int n_splits;
-  void *attn_out;         // the merged slices, chunk-major like every activation
+  void *attn_out;         // the merged slices, chunk-major
 };
 
 constexpr int kMaxResidualSplits = 8;
-constexpr int kNormSegs = 4;   // workgroups that may share a row of the RMSNorm; row_ss is [Mcap][kNormSegs]
+constexpr int kNormSegs = 4;   // workgroups that may share a row of the RMSNorm, and sums of squares per row that it leaves
 // sums of squares per row that gemm_stream_kernel leaves: one per 16 features, in whole groups of four
 inline int stream_segments(int d) { return (d / 16 + 3) / 4 * 4; }
 
@@ -328,7 +334,7 @@ struct AttnArgs {
   const void *vcache;     // this layer's cached values, same tiling (v_offset)
   const void *kscr;       // this layer's block keys, [Hkv][kv_rows/32] tiles
   const void *vscr;       // this layer's block values, [Hkv][kv_rows/32] tiles
-  int kv_rows;            // positions per kv head of kscr/vscr (Mcap, or the cache's padded length: see GemmArgs)
+  int kv_rows;            // positions per kv head of kscr/vscr (Mcap, or the cache's padded length: see GemmCore)
   float *part_o;          // [H][n_splits][Mpart/16][hd/16][64 lanes][4]: output fragments as the registers hold them
   float *part_ml;         // [H][n_splits][Mpart][2]
   int Mpart;              // rows per (head, slice) of the two partial buffers: M rounded up to 128
@@ -363,7 +369,7 @@ GemmPlan gemm_plan(int dtype, int epi, int M, int N, int K);
 int gemm_tile_shapes();   // tile shapes gemm_tile_kernel is built for
 // the GEMMs of a block of one token, with the RMSNorm (q/k/v, gate/up, unembedding) or the merge of the attention slices
 // (output projection, r.part_o set) in front
-void launch_gemm_row(int dtype, int epi, const GemmArgs &a, const RowArgs &r, hipStream_t s);
+void launch_gemm_row(int dtype, int epi, const GemmCore &a, const RowArgs &r, hipStream_t s);
 int gemm_row_splits(int N, int K);
 bool gemm_row_fits(int dtype, int d_model, int dq);
 bool launch_attention(int dtype, int hd, const AttnArgs &a, hipStream_t s);
@@ -381,9 +387,7 @@ int attention_workgroups(int dtype, int hd, int H, int M, int n_splits, bool who
 void launch_embed(int dtype, const void *tok_emb, const int32_t *hist, const int32_t *drafts, int32_t *block_tok,
                   float *h, int d, int M, int hist_base, int mode, hipStream_t s, const int32_t *n_dev = nullptr,   // n_dev: hist_base = *n_dev - 1
                   const void *gain = nullptr, void *xn = nullptr, int Mcap = 0, int xn_mb = 0, float *row_ss = nullptr);   // gain set: the RMSNorm of the rows too
-// h[m] += sum of n_part partials (hpart[s][m], stride part_stride floats between splits), then
-// xn[m] = rmsnorm(h[m]) * gain, written chunk-major
-// dst = (src - centre) * scale in the internal element type (src: the user's storage type)
+// dst = (src - centre) * scale in the internal element type (src: the user's storage type) and the layout mb (act_pos)
 void launch_pack_rows(int dtype, const void *src, void *dst, int d, int M, int Mcap, int mb, hipStream_t s, float scale,
                       const float *centre = nullptr);
 // src in operand order (act_pos, mb row blocks) -> dst chunk-major, M rows of d elements
@@ -392,6 +396,8 @@ void launch_act_chunks(int dtype, const void *src, void *dst, int d, int M, int 
 void launch_absmax(int dtype, const void *src, size_t n, unsigned *out_bits, hipStream_t s);
 void launch_column_mean(int dtype, const void *src, int N, int d, float *mean, hipStream_t s);
 void launch_neg_row_sumsq(const float *rows, int M, int V, float *out, hipStream_t s);
+// h[m] += sum of n_part partials (hpart[s][m], stride part_stride floats between splits), then xn[m] = h[m] * gain in the layout
+// xn_mb (act_pos) and kNormSegs sums of squares per row, from which the GEMM that follows takes 1 / rms
 void launch_rmsnorm(int dtype, float *h, const float *hpart, int n_part, size_t part_stride, const void *gain, void *xn,
                     int d, int M, int Mcap, int xn_mb, float *row_ss, hipStream_t s);
 
