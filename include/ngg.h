@@ -299,9 +299,10 @@ ngg_status ngg_debug_peek(ngg_ctx *ctx, const char *name, void *dst, int64_t cap
 
 /* Test aids.  ngg_debug_plan: what a model call on `tokens` block tokens launches for one of its GEMMs (gemm 0 = q, k and
  * v together, 1 = output projection or down, 2 = gate and up, 3 = unembedding) with n output rows (gate and up: d_ffn) and
- * a contraction of k.  Host only, no context, no GPU.  plan (HOST, int32[8]): kernel (0 streaming, 1 tiled, 2 single
- * token, 3 a residual GEMM that streams its whole contraction per workgroup and ends with the norm), block tokens and weight rows of a tile, splits of the contraction, 16-row weight fragments in the first launch,
- * tokens and rows of the second launch's tiles, number of tile shapes.  Streamed 16-bit q/k/v, gate and up: weight rows of a
+ * a contraction of k.  Host only, no context, no GPU.  plan (HOST, int32[8]): kernel (0 one of the two that stream the weights
+ * past whole blocks, ngg_debug_gemm_kernel says which; 1 tiled; 2 single token; 3 a 16-bit residual GEMM that streams its whole
+ * contraction per workgroup and ends with the norm), block tokens and weight rows of a tile, splits of the contraction, 16-row
+ * weight fragments in the first launch, tokens and rows of the second launch's tiles, number of tile shapes.  Streamed 16-bit q/k/v, gate and up: weight rows of a
  * workgroup in the place of a tile's.
  * ngg_debug_gemm_kernel: the kernel by name that a block's GEMM runs on, arguments as above and the tile shape of ngg_debug_tiles
  * or -1: 0 X staged through LDS, 1 tiled, 3 both operands streamed (of one token: where the single-token kernel does not take the

@@ -317,10 +317,8 @@ __global__ __launch_bounds__(64 * NW) void attn_stream_kernel(const AttnArgs a, 
 }
 
 // Workgroup = (head, list slice, group of 64*QF queries); wave w owns queries q0 + 16*QF*w .. and
-// reads every tile of the slice from the LDS copy.  Grid layout as in attn_stream_kernel; where a prefill piece gives every
-// CU two workgroups, every other pair of units takes its query groups in reverse, so that the two workgroups a CU holds
-// are a short causal list and a long one (2048-token piece, 32 heads of 128: 106 -> 95 us).  With a single slice the
-// quotient is the result and no merge follows (21 us for that piece).
+// reads every tile of the slice from the LDS copy.  Grid layout as in attn_stream_kernel; the order of the query groups as in
+// attn_block_kernel.  With a single slice the quotient is the result and no merge follows.
 template <typename T, int HD, int QF, bool NT>
 __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, int Z, int n_units) {
   constexpr int DS = HD / 32, DF = HD / 16;
@@ -492,6 +490,9 @@ __global__ __launch_bounds__(256, 2) void attn_shared_kernel(const AttnArgs a, i
 // the tiles' order serves as it is: row 8 j + 4 h + i of a key tile is key 16 (j % 2) + 8 h + 4 (j / 2) + i, so lane (query, h) ends
 // up with the keys 16 u + 8 h .. + 7 of every 16, its operand of P.V.  Two tiles per barrier, one maximum and one test of the
 // reference for 32 scores of a lane.  Counters on a 16K prompt: matrix cores busy 46 % of the cycles, vector unit 42 %, LDS 35 %.
+// Where a prompt piece gives every CU two workgroups, every other pair of units takes its query groups in reverse, so that the two a
+// CU holds are a short causal list and a long one (2048-token piece, 32 heads of 128, with 16 x 16 tiles: 106 -> 95 us).  With a single
+// slice the quotient is the result and no merge follows (21 us for that piece).
 // ---------------------------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -755,9 +756,9 @@ static void launch_stream(const AttnArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((attn_stream_kernel<T, HD, QF, NW>), dim3((n_units + 7) / 8 * 8 * Z), dim3(64 * NW), lds, s, a, Z, n_units);
 }
 
-// Slices of a dozen tiles or more that no other workgroup shares are bound by the stream of tiles, which are read with
-// non-temporal loads (measured on MI355X, whole verify step: 7.07 -> 6.86 ms at a 16.4K context with 32 tiles per slice, 3.08 ->
-// 3.06 ms at 13 tiles; 4.18 -> 4.19 ms at 8 tiles, where they stay ordinary loads)
+// Slices of a dozen tiles or more that no other workgroup shares are read with non-temporal loads (measured with
+// attn_shared_kernel on MI355X, whole verify step: 7.07 -> 6.86 ms at a 16.4K context with 32 tiles per slice, 3.08 -> 3.06 ms at 13
+// tiles; 4.18 -> 4.19 ms at 8 tiles, where they stay ordinary loads)
 static bool long_slices(int P, int n_splits, int Z) { return Z == 1 && ((P + 31) / 32 + 1) / n_splits >= 12; }
 
 // query groups of 16 per wave in attn_shared_kernel, blocks of more than 64 tokens: two where the registers hold them (fp32
@@ -770,8 +771,9 @@ AttnRoute attention_route(int dtype, int hd, int M, int P, int n_splits, bool wh
   const int per_wg = 64 * shared_groups(dtype, hd, M);
   const bool longs = long_slices(P, n_splits, (M + per_wg - 1) / per_wg);
   // (32 heads of 128, us, attn_shared_kernel -> attn_block_kernel: 97 tokens on 3000 positions 21.5 -> 18.4, 241 on 2048 27.8 -> 23.0,
-  // a 2048-token piece 96 -> 77, behind 13K positions 630 -> 564; 777 tokens, 12 heads of 64: 14.4 -> 12.4.  Long slices, where
-  // the tiles bound the kernel, lose: 97 tokens on 8192 positions 35.8 -> 38.2, on 16384 56.5 -> 61.7)
+  // a 2048-token piece 96 -> 77, behind 13K positions 630 -> 564; 777 tokens, 12 heads of 64: 14.4 -> 12.4.  Long slices stay with
+  // the non-temporal loads, which attn_block_kernel has not: 97 tokens on 8192 positions 35.8 against 38.2 there with ordinary
+  // ones, on 16384 56.5 against 61.7.  How much of that the loads make and how much the kernel has not been measured.)
   if (dtype == 1 && M > 64 && !longs) return ATTN_BLOCK;
   return longs ? ATTN_SHARED_NT : ATTN_SHARED;
 }

@@ -1,5 +1,5 @@
-// Streaming GEMM  Y[M x N] = X[M x K] . W[N x K]^T  for blocks of up to 64 rows (q/k/v and gate/up: 128): a verify call is meant to stay bound by the
-// one read of W (Section 3), and what a launch costs beyond that read is its start, its barriers and its finish.
+// Streaming GEMM  Y[M x N] = X[M x K] . W[N x K]^T  for blocks of up to 64 rows (q/k/v and gate/up: 128): a verify call is meant to
+// stay bound by the one read of W (Section 3), and what a launch costs beyond that read is its start, its barriers and its finish.
 //
 // A workgroup owns FN fragments (16 rows) of W and all block rows; its NW waves split the steps of 32 contraction elements
 // among them, so every element of W and of X is needed by exactly one wave.  Both operands lie in memory in the order the
